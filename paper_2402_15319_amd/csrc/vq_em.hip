@@ -6,16 +6,16 @@
 //   M-step:  c_m[t] = sum_{i in I_m} h[c_i+t] * x_i[t] / sum_{i in I_m} h[c_i+t]   (0 if the sum of weights is 0)
 //
 // with x_i = W[r, c .. c+d-1] and h[c] = 1 / [H^-1]_cc, the diagonal weight of column c.
-// em_assign_kernel / em_update_kernel: d = 2, groups of 8 x 256 weights.  One wave per group, lane
-// L owns columns 4L .. 4L+3 (two vectors) of the group's 8 rows, exactly as in the matrix-vector
-// kernels.  em_assign_any_kernel / em_update_any_kernel: d = 1, 2 or 4 and groups of 1, 8, 16, ...
-// 256 rows x 256 columns (every group shape the decode formats use), the same lane ownership.
+// em_assign_kernel: d = 2, groups of 8 x 256 weights.  One wave per group, lane L owns columns
+// 4L .. 4L+3 (two vectors) of the group's 8 rows, exactly as in the matrix-vector kernels.
+// em_assign_any_kernel: d = 1, 2 or 4 and groups of 1, 4, 8, 16, ... 256 rows x 256 columns (every group
+// shape the decode formats use), the same lane ownership.  em_update_small_kernel /
+// em_update_kernel: the M-step with a table per lane or per wave.
 //
 // The E-step is a decision taken in floating point, so its arithmetic is fixed: binary32,
 // every operation rounded on its own (no fused multiply-add), in the order subtract, square,
-// times weight, add; the smallest distance wins, the lowest m wins a tie.  The M-step sums in
-// binary32 in a fixed order (a lane's 16 vectors one after the other, then lanes 0..63), so it is
-// deterministic.
+// times weight, add; the smallest distance wins, the lowest m wins a tie.  The M-step's sums are
+// deterministic (see there).
 #include "vq_device.h"
 #include "vq_internal.h"
 
@@ -73,75 +73,6 @@ __global__ __launch_bounds__(256) void em_assign_kernel(const float* __restrict_
     *reinterpret_cast<uint16_t*>(assign + (size_t)(rb * 8 + r) * (in_features / 2) + (size_t)c * 128 + lane * 2) =
         (uint16_t)(arg[2 * r] | (arg[2 * r + 1] << 8));
 }
-
-constexpr int kRedStride = 68;   // floats per lane row of the reduction buffer: 16-byte aligned, conflict-free
-
-template <int K>
-__global__ __launch_bounds__(128) void em_update_kernel(const float* __restrict__ W,
-                                                        const float* __restrict__ hdiag,
-                                                        const uint8_t* __restrict__ assign,
-                                                        float* __restrict__ cb_out, int n_cb,
-                                                        long long n_groups, int in_features) {
-  __shared__ __attribute__((aligned(16))) float red_all[2][64 * kRedStride];
-  __shared__ float tot_all[2][64];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  float* red = red_all[wave];
-  float* tot = tot_all[wave];
-  const long long g = (long long)blockIdx.x * 2 + wave;
-  if (g >= n_groups) return;   // whole waves leave; no workgroup barrier below
-  const long long rb = g / n_cb;
-  const int c = (int)(g - rb * n_cb);
-
-  const float4 h = *reinterpret_cast<const float4*>(hdiag + (size_t)c * 256 + lane * 4);
-  float4 hx[8];
-  uint32_t aa[8], ab[8];
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const float4 x = *reinterpret_cast<const float4*>(W + (size_t)(rb * 8 + r) * in_features + (size_t)c * 256 + lane * 4);
-    hx[r] = make_float4(h.x * x.x, h.y * x.y, h.z * x.z, h.w * x.w);
-    const uint32_t a2 = *reinterpret_cast<const uint16_t*>(assign + (size_t)(rb * 8 + r) * (in_features / 2) +
-                                                           (size_t)c * 128 + lane * 2);
-    aa[r] = a2 & 0xffu;
-    ab[r] = a2 >> 8;
-  }
-
-  float4* row = reinterpret_cast<float4*>(red + lane * kRedStride);   // this lane's 16 x 4 partial sums
-  for (int m0 = 0; m0 < K; m0 += 16) {
-    // this lane's part of (numerator t=0, numerator t=1, weight t=0, weight t=1) of 16
-    // centroids: its 16 vectors are added one after the other (rows 0..7, the vector on
-    // columns 4L, 4L+1 before the one on 4L+2, 4L+3) into the slot their assignment selects
-#pragma unroll
-    for (int j = 0; j < 16; ++j) row[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const uint32_t ja = aa[r] - m0, jb = ab[r] - m0;
-      if (ja < 16u) {   // also keeps an out-of-range assignment byte out of the table
-        float4 t = row[ja];
-        t.x += hx[r].x; t.y += hx[r].y; t.z += h.x; t.w += h.y;
-        row[ja] = t;
-      }
-      if (jb < 16u) {
-        float4 t = row[jb];
-        t.x += hx[r].z; t.y += hx[r].w; t.z += h.z; t.w += h.w;
-        row[jb] = t;
-      }
-    }
-    wave_lds_sync();
-    // lane j owns quantity j of the 64: sum over the 64 lanes in lane order
-    float s = 0.f;
-    for (int l = 0; l < 64; ++l) s += red[l * kRedStride + lane];
-    tot[lane] = s;
-    wave_lds_sync();
-    if (lane < 32) {
-      const int j = lane >> 1, t = lane & 1;
-      const float num = tot[4 * j + t], den = tot[4 * j + 2 + t];
-      cb_out[(g * K + m0 + j) * 2 + t] = den != 0.f ? num / den : 0.f;
-    }
-    wave_lds_sync();   // tot and red are rewritten by the next 16 centroids
-  }
-}
-
 
 // ---- any dimensionality and group height ---------------------------------------------------
 // E-step.  One wave per (8-row block, col-block); the codebook is that of the group the block
@@ -219,77 +150,221 @@ __global__ __launch_bounds__(256) void em_assign_any_kernel(const float* __restr
   }
 }
 
-// M-step.  One wave per group of n_rows rows (group_rows, or 1) x 256 columns.  A lane keeps the
-// partial sums of 64 quantities in its LDS row: (numerator[D], weight[D]) of 32 / D centroids; the
-// group's rows are walked once per such set of centroids (row after row, a lane's vectors left to
-// right), then lane q sums quantity q over the 64 lanes in lane order: a fixed order, deterministic.
-template <int K, int D>
-__global__ __launch_bounds__(128) void em_update_any_kernel(const float* __restrict__ W,
-                                                            const float* __restrict__ hdiag,
-                                                            const uint8_t* __restrict__ assign,
-                                                            float* __restrict__ cb_out, int n_cb,
-                                                            long long n_groups, int in_features,
-                                                            int n_rows) {
-  constexpr int V = 4 / D;
-  constexpr int CP = 32 / D;               // centroids per pass
-  __shared__ __attribute__((aligned(16))) float red_all[2][64 * kRedStride];
-  __shared__ float tot_all[2][64];
+// M-step.  A wave walks 8-row blocks of one group (NG = 1) or owns one 8-row block that holds NG = 8 / n_rows
+// groups (groups of 1 or 4 rows); WPG waves share a group and take its 8-row blocks in turn.  Every vector
+// adds its weighted coordinates and its weights to its centroid's entries of the wave's own table in LDS,
+// in binary64: W is read once, whatever k is.  The sums of the waves (and of the copies below) are then
+// added in order, divided, and written.
+//   Bound: the reads of W and LDS atomics (2 * D per vector, 22 clocks per wave and CU; binary32 atomics take
+// 194).  us at 4096 x 4096, against a wave that kept 64 binary32 partial sums per lane and walked the group's
+// rows once per 32 / D centroids: d = 4, k = 256, 64 rows 33 (1,081); d = 2, k = 256, 128 rows 30 (899), 8 rows
+// 31 (181); k = 64, 32 rows 31 (81); 11008 x 4096, d = 4, k = 256, 256 rows: 86 (4,120).
+//   Order: a wave's additions reach an entry in program order, lanes that meet in one instruction in the
+// order in which the LDS serves them.  The terms are exact products of two binary32 numbers and the sums
+// carry 29 more bits than the result, so even another order could only show where a sum lies within 2^-40 of
+// a rounding boundary.
+//   Small tables are kept in COPIES copies, lane L using copy L % COPIES, which bounds the lanes that meet
+// in one entry; quantity-major order ([2 D][entries]) keeps the lanes of an addition on different banks.
+typedef __attribute__((address_space(3))) double* lds_f64_ptr;
+
+template <int K, int D, int NG, int WPG>
+struct EmBins {
+  static constexpr int kEntries = NG * K;
+  static constexpr int kCopies = kEntries >= 64 ? 1 : 64 / kEntries;
+  static constexpr int kStride = kEntries * kCopies;        // doubles per quantity
+  static constexpr int kTable = 2 * D * kStride;            // doubles per wave
+};
+
+template <int K, int D, int NG, int WPG>
+__global__ __launch_bounds__(WPG > 4 ? 64 * WPG : 256) void em_update_kernel(const float* __restrict__ W,
+                                                                             const float* __restrict__ hdiag,
+                                                                             const uint8_t* __restrict__ assign,
+                                                                             float* __restrict__ cb_out, int n_cb,
+                                                                             long long n_items, int in_features,
+                                                                             int n_rows) {
+  using Bins = EmBins<K, D, NG, WPG>;
+  constexpr int V = 4 / D;                          // vectors per row and lane
+  constexpr int WAVES = WPG > 4 ? WPG : 4;
+  constexpr int RPG = 8 / NG;                       // rows of an 8-row block that share a codebook
+  __shared__ __attribute__((aligned(16))) double tab_all[WAVES * Bins::kTable];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  float* red = red_all[wave];
-  float* tot = tot_all[wave];
-  const long long g = (long long)blockIdx.x * 2 + wave;
-  if (g >= n_groups) return;   // whole waves leave; no workgroup barrier below
-  const long long gr = g / n_cb;
-  const int c = (int)(g - gr * n_cb);
-  const long long row0 = gr * n_rows;
+  const int sub = wave % WPG;                       // this wave's place among those that share its group
+  double* tab = tab_all + wave * Bins::kTable;
+  const long long item_raw = (long long)blockIdx.x * (WAVES / WPG) + wave / WPG;
+  const bool present = item_raw < n_items;          // absent items repeat the last one and store nothing
+  const long long item = present ? item_raw : n_items - 1;
+  const long long ir = item / n_cb;                 // group row, or 8-row block where that holds several groups
+  const int c = (int)(item - ir * n_cb);
+  const int rows_item = NG > 1 ? 8 : n_rows;
+  const long long row0 = ir * rows_item;
 
+  for (int i = lane; i < Bins::kTable / 2; i += 64) reinterpret_cast<double2*>(tab)[i] = make_double2(0., 0.);
   const float4 h4 = *reinterpret_cast<const float4*>(hdiag + (size_t)c * 256 + lane * 4);
-  const float h[4] = {h4.x, h4.y, h4.z, h4.w};
-  float* row = red + lane * kRedStride;
-  for (int m0 = 0; m0 < K; m0 += CP) {
+  const double h[4] = {h4.x, h4.y, h4.z, h4.w};
+  const float* Wl = W + (size_t)row0 * in_features + (size_t)c * 256 + lane * 4;
+  const uint8_t* al = assign + (size_t)row0 * (in_features / D) + (size_t)c * (256 / D) + lane * V;
+  const int copy = Bins::kCopies > 1 ? lane % Bins::kCopies : 0;
+  wave_lds_sync();
+
+  auto load = [&](int r0, float4 (&x)[8], uint32_t (&a)[8]) {
 #pragma unroll
-    for (int j = 0; j < 64; ++j) row[j] = 0.f;
-    for (int r = 0; r < n_rows; ++r) {
-      const float4 t = *reinterpret_cast<const float4*>(W + (size_t)(row0 + r) * in_features + (size_t)c * 256 + lane * 4);
-      const float x[4] = {t.x, t.y, t.z, t.w};
-      const uint8_t* ap = assign + (size_t)(row0 + r) * (in_features / D) + (size_t)c * (256 / D) + lane * V;
-      uint32_t a[V];
-      if constexpr (V == 4) {
-        const uint32_t w = *reinterpret_cast<const uint32_t*>(ap);
-        a[0] = w & 0xffu; a[1] = (w >> 8) & 0xffu; a[2] = (w >> 16) & 0xffu; a[3] = w >> 24;
-      } else if constexpr (V == 2) {
-        const uint32_t w = *reinterpret_cast<const uint16_t*>(ap);
-        a[0] = w & 0xffu; a[1] = w >> 8;
-      } else {
-        a[0] = *ap;
-      }
+    for (int r = 0; r < 8; ++r) {
+      x[r] = *reinterpret_cast<const float4*>(Wl + (size_t)(r0 + r) * in_features);
+      const uint8_t* ap = al + (size_t)(r0 + r) * (in_features / D);
+      if constexpr (V == 4) a[r] = *reinterpret_cast<const uint32_t*>(ap);
+      else if constexpr (V == 2) a[r] = *reinterpret_cast<const uint16_t*>(ap);
+      else a[r] = *ap;
+    }
+  };
+  auto add = [&](const float4 (&x)[8], const uint32_t (&a)[8]) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const float xr[4] = {x[r].x, x[r].y, x[r].z, x[r].w};
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        const uint32_t j = a[v] - m0;
-        if (j < (uint32_t)CP && a[v] < (uint32_t)K) {   // also keeps an out-of-range assignment byte out of the table
-          float* slot = row + j * 2 * D;
+        const uint32_t m = (a[r] >> (8 * v)) & 0xffu;
+        if (K == 256 || m < (uint32_t)K) {          // an assignment byte beyond the codebook counts nowhere
+          double* e = tab + ((r / RPG) * K + m) * Bins::kCopies + copy;
 #pragma unroll
-          for (int tt = 0; tt < D; ++tt) {
-            slot[tt] += h[v * D + tt] * x[v * D + tt];
-            slot[D + tt] += h[v * D + tt];
+          for (int t = 0; t < D; ++t) {
+            __builtin_amdgcn_ds_atomic_fadd_f64((lds_f64_ptr)(e + t * Bins::kStride), h[v * D + t] * (double)xr[v * D + t]);
+            __builtin_amdgcn_ds_atomic_fadd_f64((lds_f64_ptr)(e + (D + t) * Bins::kStride), h[v * D + t]);
           }
         }
       }
     }
-    wave_lds_sync();
-    float s = 0.f;
-    for (int l = 0; l < 64; ++l) s += red[l * kRedStride + lane];
-    tot[lane] = s;
-    wave_lds_sync();
-    if (lane < CP * D) {
-      const int j = lane / D, t = lane % D;
-      if (m0 + j < K) {
-        const float num = tot[j * 2 * D + t], den = tot[j * 2 * D + D + t];
-        cb_out[(g * K + m0 + j) * D + t] = den != 0.f ? num / den : 0.f;
+  };
+
+  // the next 8 rows are in flight while these are added
+  float4 x0[8], x1[8];
+  uint32_t a0[8], a1[8];
+  int r0 = 8 * sub;
+  if (r0 < rows_item) {
+    load(r0, x0, a0);
+    while (true) {
+      const int r1 = r0 + 8 * WPG, r2 = r1 + 8 * WPG;
+      if (r1 < rows_item) load(r1, x1, a1);
+      add(x0, a0);
+      if (r1 >= rows_item) break;
+      if (r2 < rows_item) load(r2, x0, a0);
+      add(x1, a1);
+      if (r2 >= rows_item) break;
+      r0 = r2;
+    }
+  }
+  if constexpr (WPG > 1) __syncthreads();
+  else wave_lds_sync();
+  if (!present) return;                             // no barrier below
+
+  const double* group_tab = tab_all + (size_t)(wave - sub) * Bins::kTable;
+  for (int i = sub * 64 + lane; i < NG * K * D; i += 64 * WPG) {
+    const int e = i / D, t = i % D;
+    double num = 0., den = 0.;
+#pragma unroll
+    for (int w = 0; w < WPG; ++w)
+#pragma unroll
+      for (int q = 0; q < Bins::kCopies; ++q) {
+        const double* p = group_tab + w * Bins::kTable + e * Bins::kCopies + q;
+        num += p[t * Bins::kStride];
+        den += p[(D + t) * Bins::kStride];
+      }
+    const long long g = NG > 1 ? (ir * NG + e / K) * n_cb + c : item;
+    cb_out[(g * K + e % K) * D + t] = den != 0. ? (float)num / (float)den : 0.f;
+  }
+}
+
+// M-step for small tables (NG * k * d <= 32) and groups of at most 32 rows: every lane has a table of its own,
+// [entry][lane] in LDS, so a vector costs one 2 * D-wide read and write (22 clocks of LDS per wave) instead of
+// 2 * D binary64 atomics (22..31 clocks each).  A lane sums its few vectors in binary32, the 64 lanes' sums are
+// added in runs of 8, the runs in binary64: a fixed order.  us at 4096 x 4096: d = 2, k = 16, 8 rows 17 (27 with
+// atomics); d = 1, k = 16, 8 rows 16 (28); d = 1, k = 4, 1 row 19 (53); d = 1, k = 8, 32 rows 20 (23).
+template <int K, int D, int NG>
+__global__ __launch_bounds__(64) void em_update_small_kernel(const float* __restrict__ W,
+                                                             const float* __restrict__ hdiag,
+                                                             const uint8_t* __restrict__ assign,
+                                                             float* __restrict__ cb_out, int n_cb,
+                                                             int in_features, int n_rows) {
+  constexpr int V = 4 / D;
+  constexpr int E = NG * K;                         // entries of 2 * D floats
+  constexpr int RPG = 8 / NG;
+  __shared__ __attribute__((aligned(16))) float tab[E * 64 * 2 * D];
+  const int lane = threadIdx.x;
+  const uint32_t ir = blockIdx.x / (uint32_t)n_cb;  // group row, or 8-row block where that holds several groups
+  const int c = (int)(blockIdx.x - ir * (uint32_t)n_cb);
+  const int rows_item = NG > 1 ? 8 : n_rows;
+
+  const float4 h4 = *reinterpret_cast<const float4*>(hdiag + (size_t)c * 256 + lane * 4);
+  const float h[4] = {h4.x, h4.y, h4.z, h4.w};
+  const float* Wi = W + (size_t)ir * rows_item * in_features + (size_t)c * 256;
+  const uint8_t* ai = assign + (size_t)ir * rows_item * (in_features / D) + (size_t)c * (256 / D);
+  float* mine = tab + lane * 2 * D;
+
+  auto load = [&](int r0, float4 (&x)[8], uint32_t (&a)[8]) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      x[r] = *reinterpret_cast<const float4*>(Wi + (size_t)(r0 + r) * in_features + (uint32_t)(lane * 4));
+      const uint8_t* ap = ai + (size_t)(r0 + r) * (in_features / D) + (uint32_t)(lane * V);
+      if constexpr (V == 4) a[r] = *reinterpret_cast<const uint32_t*>(ap);
+      else if constexpr (V == 2) a[r] = *reinterpret_cast<const uint16_t*>(ap);
+      else a[r] = *ap;
+    }
+  };
+  float4 x[8], xn[8];
+  uint32_t a[8], an[8];
+  load(0, x, a);
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+#pragma unroll
+    for (int j = 0; j < 2 * D; ++j) mine[e * 128 * D + j] = 0.f;
+  for (int r0 = 0;;) {
+    const bool more = r0 + 8 < rows_item;
+    if (more) load(r0 + 8, xn, an);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const float xr[4] = {x[r].x, x[r].y, x[r].z, x[r].w};
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const uint32_t m = (a[r] >> (8 * v)) & 0xffu;
+        if (m < (uint32_t)K) {                      // an assignment byte beyond the codebook counts nowhere
+          float* p = mine + ((r / RPG) * K + m) * 128 * D;
+          float q[2 * D];
+#pragma unroll
+          for (int j = 0; j < 2 * D; ++j) q[j] = p[j];
+#pragma unroll
+          for (int t = 0; t < D; ++t) {
+            q[t] += h[v * D + t] * xr[v * D + t];
+            q[D + t] += h[v * D + t];
+          }
+#pragma unroll
+          for (int j = 0; j < 2 * D; ++j) p[j] = q[j];
+        }
       }
     }
-    wave_lds_sync();   // tot and red are rewritten by the next set of centroids
+    if (!more) break;
+    r0 += 8;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      x[r] = xn[r];
+      a[r] = an[r];
+    }
+  }
+  wave_lds_sync();
+  // lane q sums quantity q % (2 D) of entry q / (2 D) (d * E <= 32: at most one per lane), starting at another
+  // lane for every entry so that the reads of a step hit different banks
+  const int e = min(lane / (2 * D), E - 1), j = lane % (2 * D);
+  double sum = 0.;
+#pragma unroll
+  for (int l0 = 0; l0 < 64; l0 += 8) {
+    float part = 0.f;
+#pragma unroll
+    for (int l = 0; l < 8; ++l) part += tab[(e * 64 + ((l0 + l + e) & 63)) * 2 * D + j];
+    sum += (double)part;
+  }
+  const double den = __shfl_down(sum, D, 64);
+  if (lane < 2 * D * E && j < D) {
+    const long long g = NG > 1 ? ((long long)ir * NG + e / K) * n_cb + c : (long long)blockIdx.x;
+    cb_out[(g * K + e % K) * D + j] = den != 0. ? (float)sum / (float)den : 0.f;
   }
 }
 
@@ -367,40 +442,55 @@ hipError_t launch_em_assign(const vq_desc& d, const void* W, const void* hdiag, 
   return hipGetLastError();
 }
 
+template <int K, int D, int NG, int WPG>
+static void launch_update(const vq_desc& d, const void* W, const void* hdiag, const void* assign, void* cb_out,
+                          hipStream_t s) {
+  const int n_cb = d.in_features / kGroupCols;
+  const long long n_items = (long long)(d.out_features / (NG > 1 ? kGroupRows : d.group_rows)) * n_cb;
+  if constexpr (NG * K * D <= 32 && WPG == 1) {
+    hipLaunchKernelGGL((em_update_small_kernel<K, D, NG>), dim3((unsigned)n_items), dim3(64), 0, s, (const float*)W,
+                       (const float*)hdiag, (const uint8_t*)assign, (float*)cb_out, n_cb, d.in_features, d.group_rows);
+  } else {
+    constexpr int waves = WPG > 4 ? WPG : 4, items_per_wg = waves / WPG;
+    hipLaunchKernelGGL((em_update_kernel<K, D, NG, WPG>), dim3((unsigned)((n_items + items_per_wg - 1) / items_per_wg)),
+                       dim3(64 * waves), 0, s, (const float*)W, (const float*)hdiag, (const uint8_t*)assign,
+                       (float*)cb_out, n_cb, n_items, d.in_features, d.group_rows);
+  }
+}
+
+// Waves per group: one up to 16 rows (32 with a small table), 4 from 32 and 8 from 128 rows on.  A wave's table
+// is 16 * k * d bytes, at most 16 KB (the 8 waves of a group with d = 4, k = 256 fill 128 KB of the CU's 160 KB).
+template <int K, int D>
+static void launch_update_rows(const vq_desc& d, const void* W, const void* hdiag, const void* assign, void* cb_out,
+                               hipStream_t s) {
+  if (d.group_rows == 1) {
+    if constexpr (K * D <= 64) launch_update<K, D, 8, 1>(d, W, hdiag, assign, cb_out, s);
+  } else if (d.group_rows == 4) {
+    if constexpr (D <= 2) launch_update<K, D, 2, 1>(d, W, hdiag, assign, cb_out, s);
+  } else if (d.group_rows < 32 || (d.group_rows == 32 && K * D <= 32)) {
+    launch_update<K, D, 1, 1>(d, W, hdiag, assign, cb_out, s);
+  } else if (d.group_rows < 128) {
+    launch_update<K, D, 1, 4>(d, W, hdiag, assign, cb_out, s);
+  } else {
+    launch_update<K, D, 1, 8>(d, W, hdiag, assign, cb_out, s);
+  }
+}
+
 hipError_t launch_em_update(const vq_desc& d, const void* W, const void* hdiag, const void* assign,
                             void* cb_out, hipStream_t s) {
-  const int k = d.k, out_features = d.out_features, in_features = d.in_features;
-  const int n_cb = in_features / kGroupCols;
-  const long long n_groups = (long long)(out_features / d.group_rows) * n_cb;
-  const unsigned grid = (unsigned)((n_groups + 1) / 2);
-  if (d.d == 2 && d.group_rows == kGroupRows && (k == 16 || k == 64 || k == 256)) {
-#define VQ_EM(K)                                                                                   \
-  hipLaunchKernelGGL(em_update_kernel<K>, dim3(grid), dim3(128), 0, s, (const float*)W,            \
-                     (const float*)hdiag, (const uint8_t*)assign, (float*)cb_out, n_cb, n_groups, in_features)
-    if (k == 16) VQ_EM(16);
-    else if (k == 64) VQ_EM(64);
-    else VQ_EM(256);
-#undef VQ_EM
-    return hipGetLastError();
-  }
-#define VQ_EM_ANY(K, D)                                                                                   \
-  hipLaunchKernelGGL((em_update_any_kernel<K, D>), dim3(grid), dim3(128), 0, s, (const float*)W,          \
-                     (const float*)hdiag, (const uint8_t*)assign, (float*)cb_out, n_cb, n_groups, in_features, \
-                     d.group_rows)
+#define VQ_F1(K) launch_update_rows<K, 1>(d, W, hdiag, assign, cb_out, s)
+#define VQ_F2(K) launch_update_rows<K, 2>(d, W, hdiag, assign, cb_out, s)
+#define VQ_F4(K) launch_update_rows<K, 4>(d, W, hdiag, assign, cb_out, s)
   if (d.d == 1) {
-#define VQ_F(K) VQ_EM_ANY(K, 1)
-    VQ_EM_K_SWITCH(k, VQ_F)
-#undef VQ_F
+    VQ_EM_K_SWITCH(d.k, VQ_F1)
   } else if (d.d == 2) {
-#define VQ_F(K) VQ_EM_ANY(K, 2)
-    VQ_EM_K_SWITCH(k, VQ_F)
-#undef VQ_F
+    VQ_EM_K_SWITCH(d.k, VQ_F2)
   } else {
-#define VQ_F(K) VQ_EM_ANY(K, 4)
-    VQ_EM_K_SWITCH(k, VQ_F)
-#undef VQ_F
+    VQ_EM_K_SWITCH(d.k, VQ_F4)
   }
-#undef VQ_EM_ANY
+#undef VQ_F1
+#undef VQ_F2
+#undef VQ_F4
   return hipGetLastError();
 }
 

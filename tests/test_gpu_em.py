@@ -250,3 +250,54 @@ def test_em_rounds_on_a_deployed_group_shape(env):
         cb = new
         last = oracle.em_objective(f, W, h, cb, a)
         assert last <= obj_e * (1 + 1e-6)
+
+
+# (out, in, k, d, group_rows): tables per lane (small k * d) and per wave, one wave and several per group, group
+# counts that are not multiples of a workgroup's
+M_SHAPES = [
+    (8, 256, 4, 1, 1), (40, 768, 16, 1, 4), (24, 768, 16, 2, 8), (64, 256, 8, 1, 32),        # a table per lane
+    (8, 256, 64, 1, 1), (24, 768, 16, 2, 4), (40, 768, 32, 2, 8), (96, 512, 64, 2, 16),      # a table per wave
+    (96, 768, 64, 2, 32), (192, 256, 4, 4, 64), (128, 512, 256, 1, 128), (512, 768, 256, 4, 256),
+]
+
+
+@pytest.mark.parametrize("shape", M_SHAPES, ids=str)
+def test_m_step_against_64_bit_sums_and_repeated(env, shape):
+    """Bytes beyond the codebook count nowhere, the result is the same on every run, and it is as near
+    to 64-bit sums as the kernels' arithmetic allows.  A table per wave holds binary64 sums of exact
+    products: numerator, denominator and quotient are rounded once each, 3 * 2^-24 of the centroid
+    (3.1 with second-order terms) beside n * 2^-53 of the summed magnitudes.  A table per lane adds
+    binary32 products: at most n_lane + 8 roundings of 2^-24 of the magnitudes, numerator and
+    denominator alike."""
+    torch, vq, vqdev = env
+    out_f, in_f, k, d, gr = shape
+    W, h, cb = _inputs_any(out_f, in_f, k, d, gr, 1400 + out_f + k + d, from_data=False)
+    rng = np.random.default_rng(out_f + k)
+    assign = rng.integers(0, min(k + k // 4, 256), (out_f, in_f // d)).astype(np.uint8)   # a fifth beyond the codebook
+    bits = {4: 2, 8: 3, 16: 4, 32: 5, 64: 6, 256: 8}[k]
+    desc = vq.make_desc(out_f, in_f, k, bits, group_rows=gr, d=d)
+    W_d, h_d, a_d = (vqdev.to_device_bytes(t) for t in (W, h, assign))
+    runs = []
+    for _ in range(5):
+        new = torch.full(cb.shape, 777.0, dtype=torch.float32, device="cuda:0")
+        vq.vq_em_update(desc, W_d, h_d, a_d, new)
+        torch.cuda.synchronize()
+        runs.append(new.cpu().numpy())
+    for r in runs[1:]:
+        np.testing.assert_array_equal(r, runs[0])
+    n_cb = in_f // 256
+    small = {1: 8, 4: 2}.get(gr, 1) * k * d <= 32 and gr <= 32
+    for g in range(cb.shape[0]):
+        gi, c = divmod(g, n_cb)
+        x = W[gi * gr:(gi + 1) * gr, c * 256:(c + 1) * 256].astype(np.float64).reshape(-1, d)
+        hv = np.broadcast_to(h[c * 256:(c + 1) * 256].astype(np.float64), (gr, 256)).reshape(-1, d)
+        a = assign[gi * gr:(gi + 1) * gr, c * (256 // d):(c + 1) * (256 // d)].reshape(-1)
+        for t in range(d):
+            num = np.bincount(a, hv[:, t] * x[:, t], 256)[:k]
+            mag = np.bincount(a, hv[:, t] * np.abs(x[:, t]), 256)[:k]
+            den = np.bincount(a, hv[:, t], 256)[:k]
+            safe = np.where(den != 0, den, 1)
+            want = np.where(den != 0, num / safe, 0)
+            per_lane = (gr * 4 // d + 8) * 2.0 ** -24 if small else gr * 256 * 2.0 ** -53
+            bound = 3.1 * 2.0 ** -24 * np.abs(want) + 2.1 * per_lane * mag / safe
+            assert np.all(np.abs(runs[0][g, :, t] - want) <= bound)
