@@ -9,8 +9,9 @@
 // em_assign_kernel: d = 2, groups of 8 x 256 weights.  One wave per group, lane L owns columns
 // 4L .. 4L+3 (two vectors) of the group's 8 rows, exactly as in the matrix-vector kernels.
 // em_assign_any_kernel: d = 1, 2 or 4 and groups of 1, 4, 8, 16, ... 256 rows x 256 columns (every group
-// shape the decode formats use), the same lane ownership.  em_update_small_kernel /
-// em_update_kernel: the M-step with a table per lane or per wave.
+// shape the decode formats use), the same lane ownership.  em_assign_mfma_kernel: large codebooks, where
+// the matrix cores leave 8 candidates of the k.  em_update_small_kernel / em_update_kernel: the M-step with
+// a table per lane or per wave.
 //
 // The E-step is a decision taken in floating point, so its arithmetic is fixed: binary32,
 // every operation rounded on its own (no fused multiply-add), in the order subtract, square,
@@ -147,6 +148,374 @@ __global__ __launch_bounds__(256) void em_assign_any_kernel(const float* __restr
       *reinterpret_cast<uint16_t*>(a) = (uint16_t)(arg[2 * r] | (arg[2 * r + 1] << 8));
     else
       *a = (uint8_t)arg[r];
+  }
+}
+
+// E-step on the matrix cores.  The objective without the part that all centroids share,
+//   s_m = sum_t h_t * c_m[t]^2 - 2 * (h_t * x_t) * c_m[t],
+// is a product of 2 * D features of the vector (h_t, h_t x_t) with 2 * D features of the centroid.  Each
+// feature is split into two fp16 halves and all four half products are taken (K = 16 for d = 2, twice 16
+// for d = 4, half of 16 for d = 1): v_mfma_f32_32x32x16_f16 gives the scores of 32 centroids x 32 vectors.
+// Powers of two bring the largest coordinate of the codebook and the largest weight of each vector to
+// [2^5, 2^6).  The scores are only a filter.  Per vector the smallest block of 8 centroids and the second
+// smallest are kept (7 instructions per 8 scores, the block number in the low bits of the score); if the
+// second lies above the first by more than the scores can be off by, the assignment is found in the first
+// block with the arithmetic that defines the E-step, otherwise in the whole codebook, so the result is the
+// defined one bit for bit.
+//   How far scores can be off: with X = sum h x^2, a centroid at weighted distance dist from the vector has
+// sum h c^2 + 2 h |x c| <= 5 X + 3 dist, and only centroids as near as the first block's matter.  Relative to
+// that sum the vector's halves (rounded towards zero) are off by 2^-20, the centroid's by 2^-22, rounded
+// features by 2^-22, the accumulation by less than 2^-20: 2.5 * 2^-20 for each of the two scores compared.  The
+// block number moves a score by 2^-18 of X + dist, and the defined arithmetic itself rounds to 2^-21 of dist.
+// Together 2^-20 * (33 X + 24 dist); with dist = first + X the margin taken is 2^-20 * (62.5 X + 27 first).
+// kScoreTiny covers halves that are subnormal: 2^-24 each (the matrix cores keep subnormals) times the largest
+// value of the feature they meet, at most 60,000.  Codebooks, weights or vectors outside the ranges checked
+// below (NaN, infinities, negative or very uneven weights) take the whole codebook.
+//   Bound: vector instructions, the minima first.  The loop over centroids that this replaces takes 18
+// (d = 4) or 11 (d = 2) instructions per centroid and vector.
+constexpr float kMarginX = 62.5f / 1048576.f, kMarginFirst = 1.f + 27.f / 1048576.f;
+constexpr float kScoreTiny = 0.0112f;      // per coordinate
+// h x^2 of a vector up to which |h x| <= sqrt(2^6 * 2^25) < 60,000 (scaled)
+constexpr float kMaxNorm = 0x1p25f;
+
+typedef _Float16 h8v_t __attribute__((ext_vector_type(8)));
+
+// v as two fp16 halves, each in both halves of a dword; rounded towards zero
+__device__ __forceinline__ void split_twice(float v, uint32_t& hi, uint32_t& lo) {
+  const auto h = __builtin_amdgcn_cvt_pkrtz(v, v);
+  const float rest = v - (float)h[0];
+  hi = __builtin_bit_cast(uint32_t, h);
+  lo = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(rest, rest));
+}
+// v as (high half, low half) of one dword; rounded to nearest
+__device__ __forceinline__ uint32_t split_once(float v) {
+  const _Float16 hi = (_Float16)v;
+  const _Float16 lo = (_Float16)(v - (float)hi);
+  return __builtin_bit_cast(uint16_t, hi) | ((uint32_t)__builtin_bit_cast(uint16_t, lo) << 16);
+}
+// The power of two that brings v (a positive normal number) to [2^5, 2^6).
+__device__ __forceinline__ float scale_to_32(float v) {
+  return __builtin_bit_cast(float, (uint32_t)(259 - (int)((__builtin_bit_cast(uint32_t, v) >> 23) & 0xffu)) << 23);
+}
+__device__ __forceinline__ float min_nn(float a, float b) { return __builtin_elementwise_minimum(a, b); }
+__device__ __forceinline__ float max_nn(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_or_inf(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0x7f800000, __builtin_bit_cast(int, v), CTRL, ROWS, 0xf, false));
+}
+// Minimum over the 64 lanes (no NaN), in every lane.
+__device__ __forceinline__ float wave_min(float v) {
+  v = min_nn(v, dpp_or_inf<0x111, 0xf>(v));   // row_shr 1, 2, 4, 8: lane 15 of a row of 16 holds the row's
+  v = min_nn(v, dpp_or_inf<0x112, 0xf>(v));
+  v = min_nn(v, dpp_or_inf<0x114, 0xf>(v));
+  v = min_nn(v, dpp_or_inf<0x118, 0xf>(v));
+  v = min_nn(v, dpp_or_inf<0x142, 0xa>(v));   // row_bcast 15 and 31: lane 63 holds the wave's
+  v = min_nn(v, dpp_or_inf<0x143, 0xc>(v));
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
+
+// The values that lanes L and L + 32 hold, in both of them.
+__device__ __forceinline__ void both_halves(uint32_t v, uint32_t& lower, uint32_t& upper) {
+  const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  lower = r[0];
+  upper = r[1];
+}
+__device__ __forceinline__ void both_halves(float v, float& lower, float& upper) {
+  uint32_t a, b;
+  both_halves(__builtin_bit_cast(uint32_t, v), a, b);
+  lower = __builtin_bit_cast(float, a);
+  upper = __builtin_bit_cast(float, b);
+}
+
+// The defined arithmetic: binary32, every operation rounded on its own.
+template <int D>
+__device__ __forceinline__ float em_distance(const float (&x)[D], const float (&h)[D], const float* cm) {
+#pragma clang fp contract(off)
+  const float e0 = x[0] - cm[0];
+  float dist = h[0] * (e0 * e0);
+#pragma unroll
+  for (int t = 1; t < D; ++t) {
+    const float e = x[t] - cm[t];
+    dist = dist + h[t] * (e * e);
+  }
+  return dist;
+}
+
+template <int D>
+__device__ __forceinline__ void load_coords(const float* p, float (&v)[D]) {
+  if constexpr (D == 4) {
+    const float4 t = *reinterpret_cast<const float4*>(p);
+    v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+  } else if constexpr (D == 2) {
+    const float2 t = *reinterpret_cast<const float2*>(p);
+    v[0] = t.x; v[1] = t.y;
+  } else {
+    v[0] = *p;
+  }
+}
+
+// The q-th coordinate whose features a half-wave holds: d = 4: 2 * half + q; d = 2: half; d = 1: the lower half only.
+template <int D>
+__device__ __forceinline__ float own_coord(const float (&v)[D], int q, int half) {
+  const float lower = v[D == 4 ? q : 0];
+  const float upper = D == 1 ? 0.f : v[D == 4 ? D / 2 + q : D - 1];
+  return half ? upper : lower;
+}
+
+// Where centroid m lies in LDS (floats): a gap after every eighth spreads the blocks that lanes read over the banks.
+template <int D>
+__device__ __forceinline__ int em_place(int m) { return D * (m + (m >> 3)); }
+
+// One wave per (8-row block, col-block).  A step is 32 vectors of one row: lanes L and
+// L + 32 share vector L, and each scores half of every tile of 32 centroids.
+template <int K, int D>
+__global__ __launch_bounds__(64, 2) void em_assign_mfma_kernel(const float* __restrict__ W,
+                                                                const float* __restrict__ hdiag,
+                                                                const float* __restrict__ cb,
+                                                                uint8_t* __restrict__ assign, int n_cb,
+                                                                int in_features,
+                                                                int group_rows) {
+#pragma clang fp contract(off)
+  constexpr int TILES = K / 32;
+  constexpr int SETS = 8 / D;                 // steps per row
+  constexpr int NM = D == 4 ? 2 : 1;          // coordinates per half-wave = matrix instructions per tile
+  constexpr uint32_t kBlockMask = 4 * TILES - 1;   // block number: tile, half-wave, upper or lower 8
+  constexpr int R = K * D > 512 ? 2 : 4;      // steps filtered together (what fits the registers)
+  __shared__ __attribute__((aligned(16))) float cbs[(K + K / 8) * D];
+  const int lane = threadIdx.x;
+  const int half = lane >> 5, n = lane & 31;
+  const uint32_t strip = blockIdx.x / (uint32_t)n_cb;
+  const int c = (int)(blockIdx.x - strip * (uint32_t)n_cb);
+  const long long row0 = (long long)strip * 8;
+
+  {
+    const float* cg = cb + ((long long)((uint32_t)row0 / (uint32_t)group_rows) * n_cb + c) * (K * D);
+#pragma unroll
+    for (int i = 0; i < (K + 63) / 64; ++i) {
+      const int m = i * 64 + lane;
+      if (m < K) {
+        float v[D];
+        load_coords<D>(cg + m * D, v);
+#pragma unroll
+        for (int t = 0; t < D; ++t) cbs[em_place<D>(m) + t] = v[t];
+      }
+    }
+  }
+  const float* Wb = W + (size_t)row0 * in_features + (size_t)c * 256;
+  const float* hb = hdiag + (size_t)c * 256;
+  uint8_t* ab = assign + (size_t)row0 * (in_features / D) + (size_t)c * (256 / D);
+  float xn[R][D];                             // the next R steps' vectors
+#pragma unroll
+  for (int r = 0; r < R; ++r) load_coords<D>(Wb + (size_t)r * in_features + n * D, xn[r]);
+  wave_lds_sync();
+
+  // Centroid features: row j of a tile is given centroid 16 * ((j >> 2) & 1) + 4 * (j >> 3) + (j & 3), so that a
+  // lane's 16 scores of a tile are those of centroids 16 * half .. + 15, in order.  K slots of a half-wave, per
+  // coordinate: (h hi, h hi, h lo, h lo, hx hi, hx hi, hx lo, hx lo) against (c^2 hi, c^2 lo, twice; -2c hi, -2c lo, twice).
+  float top = 0.f;                            // largest coordinate of the codebook (NaN if there is one)
+#pragma unroll
+  for (int i = 0; i < (K + 63) / 64; ++i)
+#pragma unroll
+    for (int t = 0; t < D; ++t) top = max_nn(top, __builtin_fabsf(cbs[em_place<D>((i * 64 + lane) % K) + t]));
+  const bool nan_c = __any(!(top >= 0.f));
+  top = -wave_min(nan_c ? 0.f : -top);
+  const bool ok_c = !nan_c && top >= 0x1p-40f && top <= 0x1p20f;
+  const float c_scale = ok_c ? scale_to_32(top) : 1.f;
+  const float margin_x = kMarginX * c_scale, max_norm = kMaxNorm / c_scale;   // X below lacks one factor c_scale
+  const int row_centroid = 16 * ((n >> 2) & 1) + 4 * (n >> 3) + (n & 3);
+  uint4 A[TILES][NM];
+#pragma unroll
+  for (int t = 0; t < TILES; ++t)
+#pragma unroll
+    for (int q = 0; q < NM; ++q) {
+      const bool has = D > 1 || half == 0;    // d = 1: the upper half-wave has no coordinate
+      const float cv = has ? c_scale * cbs[em_place<D>(32 * t + row_centroid) + (D > 1 ? NM * half + q : 0)] : 0.f;
+      const uint32_t sq = split_once(cv * cv), mul = split_once(-2.f * cv);
+      A[t][q] = make_uint4(sq, sq, mul, mul);
+    }
+
+  float h[D], hs[D];                          // weights, and weights times both scales
+  uint4 B[NM];
+  bool ok = false;
+#pragma unroll 1
+  for (int set = 0, row = 0; set < SETS;) {   // R steps each: 32 vectors of R rows
+    const int col = set * 32 + n;             // the vector's place in the row
+    if (row == 0) {
+      load_coords<D>(hb + col * D, h);
+      float h_top = h[0], h_low = h[0];
+#pragma unroll
+      for (int t = 1; t < D; ++t) {
+        h_top = max_nn(h_top, h[t]);
+        h_low = min_nn(h_low, h[t]);
+      }
+      // with h_low >= 2^-20 h_top the bound on h x below is one on x
+      const bool good = h_low >= 0x1p-30f && h_top <= 0x1p30f && h_low >= 0x1p-20f * h_top;
+      ok = ok_c && __all(good);
+      const float h_scale = good ? scale_to_32(h_top) : 1.f;
+      float hq[D];
+#pragma unroll
+      for (int t = 0; t < D; ++t) {
+        hq[t] = h[t] * h_scale;
+        hs[t] = hq[t] * c_scale;
+      }
+#pragma unroll
+      for (int p = 0; p < NM; ++p) split_twice(own_coord<D>(hq, p, half), B[p].x, B[p].y);
+    }
+    float xs[R][D];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int t = 0; t < D; ++t) xs[r][t] = xn[r][t];
+    const int row_now = row;
+    row = row + R < 8 ? row + R : 0;
+    set += row == 0 ? 1 : 0;
+    {   // past the end: a harmless re-read
+      const int ahead = set < SETS ? set : 0;
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        load_coords<D>(Wb + (size_t)(row + r) * in_features + (uint32_t)((ahead * 32 + n) * D), xn[r]);
+    }
+    uint32_t args[R], unsures[R];
+    bool in_upper[R];                         // which of lanes L and L + 32 holds the result
+    if (ok) {         // R steps' filters, without a branch between them
+      uint4 Bx[R][NM];
+      float X[R], m1[R], m2[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        float hx[D];
+        X[r] = 0.f;
+#pragma unroll
+        for (int t = 0; t < D; ++t) {
+          hx[t] = hs[t] * xs[r][t];
+          X[r] = __builtin_fmaf(hx[t], xs[r][t], X[r]);
+        }
+#pragma unroll
+        for (int p = 0; p < NM; ++p) {
+          Bx[r][p] = B[p];
+          split_twice(own_coord<D>(hx, p, half), Bx[r][p].z, Bx[r][p].w);
+        }
+        m1[r] = m2[r] = __builtin_inff();
+      }
+      // The scores of the next tile are on the matrix cores while this one's minima are taken; the compiler
+      // would put them one behind the other to save registers.
+      auto score = [&](int i, f16v_t& sc) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) sc[j] = 0.f;
+#pragma unroll
+        for (int p = 0; p < NM; ++p)
+          sc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8v_t, A[i % TILES][p]),
+                                                      __builtin_bit_cast(h8v_t, Bx[i / TILES][p]), sc, 0, 0, 0);
+      };
+      f16v_t sc[2];
+      score(0, sc[0]);
+#pragma unroll
+      for (int i = 0; i < R * TILES; ++i) {
+        if (i + 1 < R * TILES) score(i + 1, sc[(i + 1) & 1]);
+        const f16v_t& v = sc[i & 1];
+        const int r = i / TILES;
+#pragma unroll
+        for (int k8 = 0; k8 < 2; ++k8) {
+          float e = min_nn(min_nn(v[8 * k8], v[8 * k8 + 1]), v[8 * k8 + 2]);
+          e = min_nn(min_nn(e, v[8 * k8 + 3]), v[8 * k8 + 4]);
+          e = min_nn(min_nn(e, v[8 * k8 + 5]), v[8 * k8 + 6]);
+          e = min_nn(e, v[8 * k8 + 7]);
+          e = __builtin_bit_cast(float, (__builtin_bit_cast(uint32_t, e) & ~kBlockMask) | (uint32_t)(4 * (i % TILES) + k8));
+          m2[r] = __builtin_amdgcn_fmed3f(e, m1[r], m2[r]);   // m1 <= m2: the middle one is the new second smallest
+          m1[r] = min_nn(m1[r], e);
+        }
+        if (i + 1 < R * TILES) __builtin_amdgcn_sched_group_barrier(0x8, NM, 0);   // matrix instructions,
+        __builtin_amdgcn_sched_group_barrier(0x2, 14, 0);                          // then vector instructions
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        float lo1, hi1, lo2, hi2;      // both halves of the codebook
+        both_halves(__builtin_bit_cast(float, __builtin_bit_cast(uint32_t, m1[r]) | (uint32_t)(2 * half)), lo1, hi1);
+        both_halves(m2[r], lo2, hi2);
+        const float first = min_nn(lo1, hi1);
+        const float second = min_nn(max_nn(lo1, hi1), min_nn(lo2, hi2));
+        const float limit = __builtin_fmaf(first, kMarginFirst, __builtin_fmaf(X[r], margin_x, D * kScoreTiny));
+        // NaN anywhere makes a comparison false; lanes L and L + 32 agree
+        unsures[r] = ~((uint32_t)__ballot(second > limit) & (uint32_t)__ballot(X[r] <= max_norm));
+        // the 8 centroids of the first block, four per half-wave
+        const uint32_t blk = __builtin_bit_cast(uint32_t, first) & kBlockMask;
+        const float* cand = cbs + em_place<D>(8) * (int)blk + 4 * D * half;
+        float best = em_distance<D>(xs[r], h, cand);
+        uint32_t arg = 8 * blk + 4 * half;
+        const uint32_t m0 = arg;
+#pragma unroll
+        for (int j = 1; j < 4; ++j) {
+          const float dist = em_distance<D>(xs[r], h, cand + j * D);
+          if (dist < best) { best = dist; arg = m0 + j; }
+        }
+        float bl, bu;
+        both_halves(best, bl, bu);
+        args[r] = arg;
+        in_upper[r] = bu < bl;         // the lower half-wave holds the lower indices
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        args[r] = 0;
+        unsures[r] = 0xffffffffu;
+        in_upper[r] = false;
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const float (&x)[D] = xs[r];
+      const uint32_t unsure = unsures[r];
+      uint32_t arg = args[r];
+      if (unsure != 0) {
+        // one vector at a time costs about as much as 120 instructions of the loop over the codebook
+        if (__builtin_popcount(unsure) <= K * (4 * D + 3) / 240) {
+          uint32_t left = unsure;
+          while (left != 0) {      // K / 64 centroids per lane
+            const int src = __builtin_ctz(left);
+            left &= left - 1;
+            float xv[D], hv[D];
+#pragma unroll
+            for (int t = 0; t < D; ++t) {
+              xv[t] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[t]), src));
+              hv[t] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, h[t]), src));
+            }
+            float db = __builtin_inff();
+            int dj = 0;
+#pragma unroll
+            for (int j = 0; j < (K + 63) / 64; ++j) {
+              const float dist = em_distance<D>(xv, hv, cbs + em_place<D>((j * 64 + lane) % K));
+              if (dist < db) { db = dist; dj = j; }
+            }
+            // the lowest index that has the smallest distance; no distance below infinity: index 0
+            const float mn = wave_min(db);
+            int found = 0;
+            if (mn < __builtin_inff()) {
+              found = -1;
+#pragma unroll
+              for (int j = 0; j < (K + 63) / 64; ++j) {
+                const unsigned long long at = __ballot(db == mn && dj == j);
+                if (found < 0 && at != 0) found = j * 64 + __builtin_ctzll(at);
+              }
+            }
+            if (n == src) arg = (uint32_t)found;
+          }
+        } else {                   // all 32 vectors, half of the codebook per half-wave
+          float db = __builtin_inff();
+          uint32_t da = half * (K / 2);
+          for (int m = 0; m < K / 2; ++m) {
+            const float dist = em_distance<D>(x, h, cbs + em_place<D>(half * (K / 2) + m));
+            if (dist < db) { db = dist; da = half * (K / 2) + m; }
+          }
+          float bl, bu;
+          uint32_t al, au;
+          both_halves(db, bl, bu);
+          both_halves(da, al, au);
+          arg = bu < bl ? au : al;
+        }
+      }
+      uint8_t* const out = ab + (size_t)(row_now + r) * (in_features / D);
+      if (in_upper[r] == (half != 0)) out[(uint32_t)col] = (uint8_t)arg;
+    }
   }
 }
 
@@ -387,16 +756,29 @@ hipError_t launch_em_assign(const vq_desc& d, const void* W, const void* hdiag, 
   const int n_cb = in_features / kGroupCols;
   const long long n_blocks = (long long)(out_features / kGroupRows) * n_cb;
   const unsigned grid = (unsigned)((n_blocks + 3) / 4);
-  if (d.d == 2 && d.group_rows == kGroupRows && (k == 16 || k == 64 || k == 256)) {
+  if (d.d == 2 && d.group_rows == kGroupRows && (k == 16 || k == 64)) {
 #define VQ_EM(K)                                                                                   \
   hipLaunchKernelGGL(em_assign_kernel<K>, dim3(grid), dim3(256), 0, s, (const float*)W,            \
                      (const float*)hdiag, (const float*)cb, (uint8_t*)assign, n_cb, n_blocks, in_features)
     if (k == 16) VQ_EM(16);
-    else if (k == 64) VQ_EM(64);
-    else VQ_EM(256);
+    else VQ_EM(64);
 #undef VQ_EM
     return hipGetLastError();
   }
+  // Matrix cores where the loop over centroids costs most; us at 4096 x 4096, loop against matrix cores:
+  // d = 4, k = 256, 64 rows: 311, 120; d = 4, k = 64: 82, 53; d = 2, k = 256, 128 rows: 322, 124 (8 rows with 9 % of
+  // the centroids twice, where ties send vectors to the whole codebook: 332, 267); but d = 2, k = 64: 87, 82..110;
+  // d = 2, k = 32: 46, 62; d = 1, k = 64: 111, 170 (scalars lie too close for the filter).  Waves of
+  // 16 rows, which would split the centroids' features over twice the vectors, were slower (144 for 124).
+#define VQ_EM_MFMA(K, D)                                                                                \
+  if (k == K && d.d == D && d.group_rows >= kGroupRows) {                                               \
+    hipLaunchKernelGGL((em_assign_mfma_kernel<K, D>), dim3((unsigned)n_blocks), dim3(64), 0, s, \
+                       (const float*)W, (const float*)hdiag, (const float*)cb, (uint8_t*)assign, n_cb, \
+                       in_features, d.group_rows);                                                       \
+    return hipGetLastError();                                                                            \
+  }
+  VQ_EM_MFMA(256, 2) VQ_EM_MFMA(64, 4) VQ_EM_MFMA(256, 4)
+#undef VQ_EM_MFMA
 #define VQ_EM_ANY(K, D, NCB)                                                                             \
   hipLaunchKernelGGL((em_assign_any_kernel<K, D, NCB>), dim3(grid), dim3(256), 0, s, (const float*)W,     \
                      (const float*)hdiag, (const float*)cb, (uint8_t*)assign, n_cb, n_blocks, in_features, \

@@ -301,3 +301,49 @@ def test_m_step_against_64_bit_sums_and_repeated(env, shape):
             per_lane = (gr * 4 // d + 8) * 2.0 ** -24 if small else gr * 256 * 2.0 ** -53
             bound = 3.1 * 2.0 ** -24 * np.abs(want) + 2.1 * per_lane * mag / safe
             assert np.all(np.abs(runs[0][g, :, t] - want) <= bound)
+
+
+# the codebooks that the matrix cores filter: one tile and several, one group and several per strip of rows
+FILTERED = [(2, 256, 8, 24, 512), (2, 256, 128, 128, 256), (4, 64, 16, 48, 512), (4, 256, 8, 8, 768), (4, 256, 64, 64, 512)]
+
+
+@pytest.mark.parametrize("case", ["plain", "centroids twice", "zero centroids and weights", "all zero", "rounded to a grid",
+                                  "far from zero", "uneven weights", "zero weights", "negative weights", "huge", "tiny",
+                                  "nan and inf"])
+@pytest.mark.parametrize("shape", FILTERED, ids=str)
+def test_filtered_e_step_is_the_defined_one(env, shape, case):
+    """The scores that pick the candidates are approximate, the result is not: ties, vectors that the
+    filter cannot decide and values outside its ranges, all bit for bit."""
+    d, k, gr, out_f, in_f = shape
+    W, h, cb = _inputs_any(out_f, in_f, k, d, gr, 1500 + out_f + k + d, from_data=False)
+    rng = np.random.default_rng(out_f + d)
+    if case == "centroids twice":
+        cb[:, k // 2:] = cb[:, :k // 2]
+    elif case == "zero centroids and weights":
+        cb[:, ::3] = 0
+        W[rng.random(W.shape) < 0.5] = 0
+    elif case == "all zero":
+        W[:] = 0
+        cb[:, 1::2] = 0
+    elif case == "rounded to a grid":
+        W, cb, h = np.round(W * 100) / np.float32(100), np.round(cb * 100) / np.float32(100), np.ones_like(h)
+    elif case == "far from zero":
+        W, cb = W + np.float32(1), cb + np.float32(1)
+    elif case == "uneven weights":
+        h = (10.0 ** rng.uniform(-6, 6, in_f)).astype(np.float32)
+    elif case == "zero weights":
+        h[::2] = 0
+    elif case == "negative weights":
+        h[::7] *= -1
+    elif case == "huge":
+        W = W * np.float32(1e30)
+    elif case == "tiny":
+        W, cb = W * np.float32(1e-25), cb * np.float32(1e-25)
+    elif case == "nan and inf":
+        W[rng.random(W.shape) < 0.01] = np.nan
+        W[rng.random(W.shape) < 0.01] = np.inf
+    f = oracle.VQFormat(out_f, in_f, k, 8, gr, 256, d)
+    with np.errstate(all="ignore"):
+        want = oracle.em_assign(f, W, h, cb)
+    a, _ = _gpu_em_any(env, (out_f, in_f, k, d, gr), W, h, cb)
+    np.testing.assert_array_equal(a, want)
