@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import Sequence
 
 __all__ = [
@@ -42,6 +43,9 @@ class VQLoraDesc(ctypes.Structure):
     """Mirror of `vq_lora_desc` (include/vq.h)."""
     _fields_ = [("A_f16", ctypes.c_void_p), ("B_f16", ctypes.c_void_p),
                 ("rank", ctypes.c_int32), ("reserved", ctypes.c_int32)]
+
+
+_LORA_STRUCT = struct.Struct("=QQii")   # the fields of VQLoraDesc
 
 
 class VQError(RuntimeError):
@@ -117,10 +121,20 @@ def _ptr(t) -> int:
     return t.data_ptr()
 
 
+_torch = None
+
+
 def _stream(stream) -> int:
+    # The current stream's handle without building a Stream object: 0.3 us of a call's host time in place
+    # of 2.8.
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        global _torch
+        if _torch is None:
+            import torch
+            _torch = torch
+        if not _torch.cuda.is_initialized():
+            return _torch.cuda.current_stream().cuda_stream
+        return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -203,13 +217,21 @@ def vq_gemv_lora(desc: VQDesc, idx_dev, cb_dev, x, A, B, rank: int, workspace, y
                               _ptr(workspace), nb, _ptr(y), y_dtype, _stream(stream)), "vq_gemv_lora")
 
 
+def _lora_array(As, Bs, ranks: Sequence[int]):
+    """The adapters' descriptors as one array, filled from packed bytes (a structure object per adapter
+    costs about 1 us)."""
+    n = len(ranks)
+    packed = b"".join([_LORA_STRUCT.pack(_ptr(a), _ptr(b), r, 0) for a, b, r in zip(As, Bs, ranks)])
+    return (VQLoraDesc * n).from_buffer_copy(packed)
+
+
 def vq_gemv_lora_multi(args: GemvMultiArgs, As, Bs, ranks: Sequence[int], workspace,
                        y_dtype: int = VQ_F16, stream=None, workspace_bytes: int | None = None) -> None:
     """args as for vq_gemv_multi; As/Bs/ranks: one adapter per product (rank 0 = none)."""
     n = args.count
     if not (len(As) == len(Bs) == len(ranks) == n):
         raise ValueError("vq_gemv_lora_multi: argument lists differ in length")
-    lora = (VQLoraDesc * n)(*[VQLoraDesc(_ptr(a), _ptr(b), r, 0) for a, b, r in zip(As, Bs, ranks)])
+    lora = _lora_array(As, Bs, ranks)
     nb = workspace.numel() * workspace.element_size() if workspace_bytes is None else workspace_bytes
     _check(lib().vq_gemv_lora_multi(n, args.descs, args.idx, args.cb, args.x, lora, _ptr(workspace), nb,
                                     args.y, y_dtype, _stream(stream)), "vq_gemv_lora_multi")
@@ -221,7 +243,7 @@ def vq_gemv_lora_multi_static(args: GemvMultiArgs, As, Bs, ranks: Sequence[int],
     n = args.count
     if not (len(As) == len(Bs) == len(ranks) == n):
         raise ValueError("vq_gemv_lora_multi_static: argument lists differ in length")
-    lora = (VQLoraDesc * n)(*[VQLoraDesc(_ptr(a), _ptr(b), r, 0) for a, b, r in zip(As, Bs, ranks)])
+    lora = _lora_array(As, Bs, ranks)
     _check(lib().vq_gemv_lora_multi_static(n, args.descs, args.idx, args.cb, args.x, lora, args.y, y_dtype,
                                            _stream(stream)), "vq_gemv_lora_multi_static")
 
