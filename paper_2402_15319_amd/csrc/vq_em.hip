@@ -9,8 +9,8 @@
 // em_assign_kernel: d = 2, groups of 8 x 256 weights.  One wave per group, lane L owns columns
 // 4L .. 4L+3 (two vectors) of the group's 8 rows, exactly as in the matrix-vector kernels.
 // em_assign_any_kernel: d = 1, 2 or 4 and groups of 1, 4, 8, 16, ... 256 rows x 256 columns (every group
-// shape the decode formats use), the same lane ownership.  em_assign_mfma_kernel: large codebooks, where
-// the matrix cores leave 8 candidates of the k.  em_update_small_kernel / em_update_kernel: the M-step with
+// shape the decode formats use), the same lane ownership.  Both take large codebooks through
+// em_assign_filtered, where the matrix cores leave 8 candidates of the k.  em_update_small_kernel / em_update_kernel: the M-step with
 // a table per lane or per wave.
 //
 // The E-step is a decision taken in floating point, so its arithmetic is fixed: binary32,
@@ -22,134 +22,6 @@
 
 namespace vq {
 namespace {
-
-template <int K>
-__global__ __launch_bounds__(256) void em_assign_kernel(const float* __restrict__ W,
-                                                        const float* __restrict__ hdiag,
-                                                        const float* __restrict__ cb,
-                                                        uint8_t* __restrict__ assign, int n_cb,
-                                                        long long n_groups, int in_features) {
-#pragma clang fp contract(off)
-  __shared__ __attribute__((aligned(16))) float2 cbs_all[4][K];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  float2* cbs = cbs_all[wave];
-  const long long g = (long long)blockIdx.x * 4 + wave;
-  if (g >= n_groups) return;   // whole waves leave; no workgroup barrier below
-  const long long rb = g / n_cb;
-  const int c = (int)(g - rb * n_cb);
-
-  const float2* cg = reinterpret_cast<const float2*>(cb) + g * K;
-#pragma unroll
-  for (int i = 0; i < (K + 63) / 64; ++i)
-    if (i * 64 + lane < K) cbs[i * 64 + lane] = cg[i * 64 + lane];
-  const float4 h = *reinterpret_cast<const float4*>(hdiag + (size_t)c * 256 + lane * 4);
-  float4 x[8];
-#pragma unroll
-  for (int r = 0; r < 8; ++r)
-    x[r] = *reinterpret_cast<const float4*>(W + (size_t)(rb * 8 + r) * in_features + (size_t)c * 256 + lane * 4);
-  wave_lds_sync();
-
-  float best[16];
-  uint32_t arg[16];
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    best[v] = __builtin_inff();
-    arg[v] = 0;
-  }
-  for (int m = 0; m < K; ++m) {
-    const float2 cm = cbs[m];   // the same address in every lane: one broadcast read
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const float ea0 = x[r].x - cm.x, ea1 = x[r].y - cm.y;
-      const float eb0 = x[r].z - cm.x, eb1 = x[r].w - cm.y;
-      const float da = h.x * (ea0 * ea0) + h.y * (ea1 * ea1);
-      const float db = h.z * (eb0 * eb0) + h.w * (eb1 * eb1);
-      if (da < best[2 * r]) { best[2 * r] = da; arg[2 * r] = m; }
-      if (db < best[2 * r + 1]) { best[2 * r + 1] = db; arg[2 * r + 1] = m; }
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < 8; ++r)
-    *reinterpret_cast<uint16_t*>(assign + (size_t)(rb * 8 + r) * (in_features / 2) + (size_t)c * 128 + lane * 2) =
-        (uint16_t)(arg[2 * r] | (arg[2 * r + 1] << 8));
-}
-
-// ---- any dimensionality and group height ---------------------------------------------------
-// E-step.  One wave per (8-row block, col-block); the codebook is that of the group the block
-// lies in (NCB = 1), one codebook per row (NCB = 8: groups of one row) or one per 4 rows (NCB = 2).
-// D values per centroid, 4 / D vectors per row and lane.  Same arithmetic as em_assign_kernel:
-// unfused binary32, sum over t in order.
-template <int K, int D, int NCB>
-__global__ __launch_bounds__(256) void em_assign_any_kernel(const float* __restrict__ W,
-                                                            const float* __restrict__ hdiag,
-                                                            const float* __restrict__ cb,
-                                                            uint8_t* __restrict__ assign, int n_cb,
-                                                            long long n_blocks, int in_features,
-                                                            int group_rows) {
-#pragma clang fp contract(off)
-  constexpr int V = 4 / D;                 // vectors per row and lane
-  constexpr int RPC = 8 / NCB;             // rows of the block that share a codebook
-  __shared__ __attribute__((aligned(16))) float cbs_all[4][NCB * K * D];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  float* cbs = cbs_all[wave];
-  const long long b = (long long)blockIdx.x * 4 + wave;
-  if (b >= n_blocks) return;   // whole waves leave; no workgroup barrier below
-  const long long rb = b / n_cb;
-  const int c = (int)(b - rb * n_cb);
-
-#pragma unroll
-  for (int q = 0; q < NCB; ++q) {
-    const long long g = ((rb * 8 + q * RPC) / group_rows) * n_cb + c;
-    const float* cg = cb + g * (K * D);
-    for (int i = lane; i < K * D; i += 64) cbs[q * K * D + i] = cg[i];
-  }
-  const float4 h4 = *reinterpret_cast<const float4*>(hdiag + (size_t)c * 256 + lane * 4);
-  const float h[4] = {h4.x, h4.y, h4.z, h4.w};
-  float x[8][4];
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const float4 t = *reinterpret_cast<const float4*>(W + (size_t)(rb * 8 + r) * in_features + (size_t)c * 256 + lane * 4);
-    x[r][0] = t.x; x[r][1] = t.y; x[r][2] = t.z; x[r][3] = t.w;
-  }
-  wave_lds_sync();
-
-  float best[8 * V];
-  uint32_t arg[8 * V];
-#pragma unroll
-  for (int v = 0; v < 8 * V; ++v) {
-    best[v] = __builtin_inff();
-    arg[v] = 0;
-  }
-  for (int m = 0; m < K; ++m) {
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const float* cm = cbs + (r / RPC) * K * D + m * D;   // the same address in every lane: broadcast reads
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const float e0 = x[r][v * D] - cm[0];
-        float dist = h[v * D] * (e0 * e0);
-#pragma unroll
-        for (int t = 1; t < D; ++t) {
-          const float e = x[r][v * D + t] - cm[t];
-          dist = dist + h[v * D + t] * (e * e);
-        }
-        if (dist < best[r * V + v]) { best[r * V + v] = dist; arg[r * V + v] = m; }
-      }
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    uint8_t* a = assign + (size_t)(rb * 8 + r) * (in_features / D) + (size_t)c * (256 / D) + lane * V;
-    if constexpr (V == 4)
-      *reinterpret_cast<uint32_t*>(a) = arg[4 * r] | (arg[4 * r + 1] << 8) | (arg[4 * r + 2] << 16) | (arg[4 * r + 3] << 24);
-    else if constexpr (V == 2)
-      *reinterpret_cast<uint16_t*>(a) = (uint16_t)(arg[2 * r] | (arg[2 * r + 1] << 8));
-    else
-      *a = (uint8_t)arg[r];
-  }
-}
 
 // E-step on the matrix cores.  The objective without the part that all centroids share,
 //   s_m = sum_t h_t * c_m[t]^2 - 2 * (h_t * x_t) * c_m[t],
@@ -197,6 +69,7 @@ __device__ __forceinline__ uint32_t split_once(float v) {
 __device__ __forceinline__ float scale_to_32(float v) {
   return __builtin_bit_cast(float, (uint32_t)(259 - (int)((__builtin_bit_cast(uint32_t, v) >> 23) & 0xffu)) << 23);
 }
+__device__ __forceinline__ float power_inverse(float p) { return __builtin_bit_cast(float, 0x7f000000u - __builtin_bit_cast(uint32_t, p)); }
 __device__ __forceinline__ float min_nn(float a, float b) { return __builtin_elementwise_minimum(a, b); }
 __device__ __forceinline__ float max_nn(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 
@@ -267,15 +140,12 @@ __device__ __forceinline__ float own_coord(const float (&v)[D], int q, int half)
 template <int D>
 __device__ __forceinline__ int em_place(int m) { return D * (m + (m >> 3)); }
 
-// One wave per (8-row block, col-block).  A step is 32 vectors of one row: lanes L and
+// Workgroups of one wave, one per (8-row block, col-block).  A step is 32 vectors of one row: lanes L and
 // L + 32 share vector L, and each scores half of every tile of 32 centroids.
 template <int K, int D>
-__global__ __launch_bounds__(64, 2) void em_assign_mfma_kernel(const float* __restrict__ W,
-                                                                const float* __restrict__ hdiag,
-                                                                const float* __restrict__ cb,
-                                                                uint8_t* __restrict__ assign, int n_cb,
-                                                                int in_features,
-                                                                int group_rows) {
+__device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, const float* __restrict__ hdiag,
+                                                   const float* __restrict__ cb, uint8_t* __restrict__ assign,
+                                                   int n_cb, int in_features, int group_rows) {
 #pragma clang fp contract(off)
   constexpr int TILES = K / 32;
   constexpr int SETS = 8 / D;                 // steps per row
@@ -322,7 +192,7 @@ __global__ __launch_bounds__(64, 2) void em_assign_mfma_kernel(const float* __re
   top = -wave_min(nan_c ? 0.f : -top);
   const bool ok_c = !nan_c && top >= 0x1p-40f && top <= 0x1p20f;
   const float c_scale = ok_c ? scale_to_32(top) : 1.f;
-  const float margin_x = kMarginX * c_scale, max_norm = kMaxNorm / c_scale;   // X below lacks one factor c_scale
+  const float margin_x = kMarginX * c_scale, max_norm = kMaxNorm * power_inverse(c_scale);   // X below lacks one factor c_scale
   const int row_centroid = 16 * ((n >> 2) & 1) + 4 * (n >> 3) + (n & 3);
   uint4 A[TILES][NM];
 #pragma unroll
@@ -388,7 +258,7 @@ __global__ __launch_bounds__(64, 2) void em_assign_mfma_kernel(const float* __re
 #pragma unroll
         for (int t = 0; t < D; ++t) {
           hx[t] = hs[t] * xs[r][t];
-          X[r] = __builtin_fmaf(hx[t], xs[r][t], X[r]);
+          X[r] = X[r] + hx[t] * xs[r][t];
         }
 #pragma unroll
         for (int p = 0; p < NM; ++p) {
@@ -434,7 +304,7 @@ __global__ __launch_bounds__(64, 2) void em_assign_mfma_kernel(const float* __re
         both_halves(m2[r], lo2, hi2);
         const float first = min_nn(lo1, hi1);
         const float second = min_nn(max_nn(lo1, hi1), min_nn(lo2, hi2));
-        const float limit = __builtin_fmaf(first, kMarginFirst, __builtin_fmaf(X[r], margin_x, D * kScoreTiny));
+        const float limit = first * kMarginFirst + (X[r] * margin_x + D * kScoreTiny);
         // NaN anywhere makes a comparison false; lanes L and L + 32 agree
         unsures[r] = ~((uint32_t)__ballot(second > limit) & (uint32_t)__ballot(X[r] <= max_norm));
         // the 8 centroids of the first block, four per half-wave
@@ -516,6 +386,151 @@ __global__ __launch_bounds__(64, 2) void em_assign_mfma_kernel(const float* __re
       uint8_t* const out = ab + (size_t)(row_now + r) * (in_features / D);
       if (in_upper[r] == (half != 0)) out[(uint32_t)col] = (uint8_t)arg;
     }
+  }
+}
+
+// Which codebooks take the filter; us at 4096 x 4096, loop over the centroids against filter: d = 4, k = 256,
+// 64 rows: 311, 120; d = 4, k = 64: 82, 53; d = 2, k = 256, 128 rows: 322, 124 (8 rows with 9 % of the centroids
+// twice, where ties send vectors to the whole codebook: 332, 267); but d = 2, k = 64: 87, 82..110; d = 2, k = 32:
+// 46, 62; d = 1, k = 64: 111, 170 (scalars lie too close for the filter).  Waves of 16 rows, which would split
+// the centroids' features over twice the vectors, were slower (144 for 124).
+template <int K, int D> constexpr bool em_filtered() { return (D == 2 && K == 256) || (D == 4 && K >= 64); }
+template <int K, int D> constexpr int em_threads() { return em_filtered<K, D>() ? 64 : 256; }
+template <int K, int D> constexpr int em_waves() { return em_filtered<K, D>() ? 2 : 1; }   // per SIMD: 256 registers each
+
+template <int K>
+__global__ __launch_bounds__((em_threads<K, 2>()), (em_waves<K, 2>())) void em_assign_kernel(const float* __restrict__ W,
+                                                        const float* __restrict__ hdiag,
+                                                        const float* __restrict__ cb,
+                                                        uint8_t* __restrict__ assign, int n_cb,
+                                                        long long n_groups, int in_features) {
+#pragma clang fp contract(off)
+  if constexpr (em_filtered<K, 2>()) {
+    em_assign_filtered<K, 2>(W, hdiag, cb, assign, n_cb, in_features, 8);
+  } else {
+  __shared__ __attribute__((aligned(16))) float2 cbs_all[4][K];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float2* cbs = cbs_all[wave];
+  const long long g = (long long)blockIdx.x * 4 + wave;
+  if (g >= n_groups) return;   // whole waves leave; no workgroup barrier below
+  const long long rb = g / n_cb;
+  const int c = (int)(g - rb * n_cb);
+
+  const float2* cg = reinterpret_cast<const float2*>(cb) + g * K;
+#pragma unroll
+  for (int i = 0; i < (K + 63) / 64; ++i)
+    if (i * 64 + lane < K) cbs[i * 64 + lane] = cg[i * 64 + lane];
+  const float4 h = *reinterpret_cast<const float4*>(hdiag + (size_t)c * 256 + lane * 4);
+  float4 x[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r)
+    x[r] = *reinterpret_cast<const float4*>(W + (size_t)(rb * 8 + r) * in_features + (size_t)c * 256 + lane * 4);
+  wave_lds_sync();
+
+  float best[16];
+  uint32_t arg[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    best[v] = __builtin_inff();
+    arg[v] = 0;
+  }
+  for (int m = 0; m < K; ++m) {
+    const float2 cm = cbs[m];   // the same address in every lane: one broadcast read
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const float ea0 = x[r].x - cm.x, ea1 = x[r].y - cm.y;
+      const float eb0 = x[r].z - cm.x, eb1 = x[r].w - cm.y;
+      const float da = h.x * (ea0 * ea0) + h.y * (ea1 * ea1);
+      const float db = h.z * (eb0 * eb0) + h.w * (eb1 * eb1);
+      if (da < best[2 * r]) { best[2 * r] = da; arg[2 * r] = m; }
+      if (db < best[2 * r + 1]) { best[2 * r + 1] = db; arg[2 * r + 1] = m; }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 8; ++r)
+    *reinterpret_cast<uint16_t*>(assign + (size_t)(rb * 8 + r) * (in_features / 2) + (size_t)c * 128 + lane * 2) =
+        (uint16_t)(arg[2 * r] | (arg[2 * r + 1] << 8));
+  }
+}
+
+// ---- any dimensionality and group height ---------------------------------------------------
+// E-step.  One wave per (8-row block, col-block); the codebook is that of the group the block
+// lies in (NCB = 1), one codebook per row (NCB = 8: groups of one row) or one per 4 rows (NCB = 2).
+// D values per centroid, 4 / D vectors per row and lane.  Same arithmetic as em_assign_kernel:
+// unfused binary32, sum over t in order.
+template <int K, int D, int NCB>
+__global__ __launch_bounds__((NCB == 1 ? em_threads<K, D>() : 256), (NCB == 1 ? em_waves<K, D>() : 1)) void em_assign_any_kernel(const float* __restrict__ W,
+                                                            const float* __restrict__ hdiag,
+                                                            const float* __restrict__ cb,
+                                                            uint8_t* __restrict__ assign, int n_cb,
+                                                            long long n_blocks, int in_features,
+                                                            int group_rows) {
+#pragma clang fp contract(off)
+  if constexpr (NCB == 1 && em_filtered<K, D>()) {
+    em_assign_filtered<K, D>(W, hdiag, cb, assign, n_cb, in_features, group_rows);
+  } else {
+  constexpr int V = 4 / D;                 // vectors per row and lane
+  constexpr int RPC = 8 / NCB;             // rows of the block that share a codebook
+  __shared__ __attribute__((aligned(16))) float cbs_all[4][NCB * K * D];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float* cbs = cbs_all[wave];
+  const long long b = (long long)blockIdx.x * 4 + wave;
+  if (b >= n_blocks) return;   // whole waves leave; no workgroup barrier below
+  const long long rb = b / n_cb;
+  const int c = (int)(b - rb * n_cb);
+
+#pragma unroll
+  for (int q = 0; q < NCB; ++q) {
+    const long long g = ((rb * 8 + q * RPC) / group_rows) * n_cb + c;
+    const float* cg = cb + g * (K * D);
+    for (int i = lane; i < K * D; i += 64) cbs[q * K * D + i] = cg[i];
+  }
+  const float4 h4 = *reinterpret_cast<const float4*>(hdiag + (size_t)c * 256 + lane * 4);
+  const float h[4] = {h4.x, h4.y, h4.z, h4.w};
+  float x[8][4];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const float4 t = *reinterpret_cast<const float4*>(W + (size_t)(rb * 8 + r) * in_features + (size_t)c * 256 + lane * 4);
+    x[r][0] = t.x; x[r][1] = t.y; x[r][2] = t.z; x[r][3] = t.w;
+  }
+  wave_lds_sync();
+
+  float best[8 * V];
+  uint32_t arg[8 * V];
+#pragma unroll
+  for (int v = 0; v < 8 * V; ++v) {
+    best[v] = __builtin_inff();
+    arg[v] = 0;
+  }
+  for (int m = 0; m < K; ++m) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const float* cm = cbs + (r / RPC) * K * D + m * D;   // the same address in every lane: broadcast reads
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const float e0 = x[r][v * D] - cm[0];
+        float dist = h[v * D] * (e0 * e0);
+#pragma unroll
+        for (int t = 1; t < D; ++t) {
+          const float e = x[r][v * D + t] - cm[t];
+          dist = dist + h[v * D + t] * (e * e);
+        }
+        if (dist < best[r * V + v]) { best[r * V + v] = dist; arg[r * V + v] = m; }
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    uint8_t* a = assign + (size_t)(rb * 8 + r) * (in_features / D) + (size_t)c * (256 / D) + lane * V;
+    if constexpr (V == 4)
+      *reinterpret_cast<uint32_t*>(a) = arg[4 * r] | (arg[4 * r + 1] << 8) | (arg[4 * r + 2] << 16) | (arg[4 * r + 3] << 24);
+    else if constexpr (V == 2)
+      *reinterpret_cast<uint16_t*>(a) = (uint16_t)(arg[2 * r] | (arg[2 * r + 1] << 8));
+    else
+      *a = (uint8_t)arg[r];
+  }
   }
 }
 
@@ -750,37 +765,30 @@ __global__ __launch_bounds__(64) void em_update_small_kernel(const float* __rest
     default: F(256); break;  \
   }
 
+// Workgroups of one block each (filtered) or of four.
+template <int K, int D> static unsigned em_grid(long long n_blocks) {
+  return (unsigned)(em_filtered<K, D>() ? n_blocks : (n_blocks + 3) / 4);
+}
+
 hipError_t launch_em_assign(const vq_desc& d, const void* W, const void* hdiag, const void* cb, void* assign,
                             hipStream_t s) {
   const int k = d.k, out_features = d.out_features, in_features = d.in_features;
   const int n_cb = in_features / kGroupCols;
   const long long n_blocks = (long long)(out_features / kGroupRows) * n_cb;
   const unsigned grid = (unsigned)((n_blocks + 3) / 4);
-  if (d.d == 2 && d.group_rows == kGroupRows && (k == 16 || k == 64)) {
+  if (d.d == 2 && d.group_rows == kGroupRows && (k == 16 || k == 64 || k == 256)) {
 #define VQ_EM(K)                                                                                   \
-  hipLaunchKernelGGL(em_assign_kernel<K>, dim3(grid), dim3(256), 0, s, (const float*)W,            \
+  hipLaunchKernelGGL(em_assign_kernel<K>, dim3((em_grid<K, 2>(n_blocks))), dim3((em_threads<K, 2>())), 0, s, (const float*)W, \
                      (const float*)hdiag, (const float*)cb, (uint8_t*)assign, n_cb, n_blocks, in_features)
     if (k == 16) VQ_EM(16);
-    else VQ_EM(64);
+    else if (k == 64) VQ_EM(64);
+    else VQ_EM(256);
 #undef VQ_EM
     return hipGetLastError();
   }
-  // Matrix cores where the loop over centroids costs most; us at 4096 x 4096, loop against matrix cores:
-  // d = 4, k = 256, 64 rows: 311, 120; d = 4, k = 64: 82, 53; d = 2, k = 256, 128 rows: 322, 124 (8 rows with 9 % of
-  // the centroids twice, where ties send vectors to the whole codebook: 332, 267); but d = 2, k = 64: 87, 82..110;
-  // d = 2, k = 32: 46, 62; d = 1, k = 64: 111, 170 (scalars lie too close for the filter).  Waves of
-  // 16 rows, which would split the centroids' features over twice the vectors, were slower (144 for 124).
-#define VQ_EM_MFMA(K, D)                                                                                \
-  if (k == K && d.d == D && d.group_rows >= kGroupRows) {                                               \
-    hipLaunchKernelGGL((em_assign_mfma_kernel<K, D>), dim3((unsigned)n_blocks), dim3(64), 0, s, \
-                       (const float*)W, (const float*)hdiag, (const float*)cb, (uint8_t*)assign, n_cb, \
-                       in_features, d.group_rows);                                                       \
-    return hipGetLastError();                                                                            \
-  }
-  VQ_EM_MFMA(256, 2) VQ_EM_MFMA(64, 4) VQ_EM_MFMA(256, 4)
-#undef VQ_EM_MFMA
 #define VQ_EM_ANY(K, D, NCB)                                                                             \
-  hipLaunchKernelGGL((em_assign_any_kernel<K, D, NCB>), dim3(grid), dim3(256), 0, s, (const float*)W,     \
+  hipLaunchKernelGGL((em_assign_any_kernel<K, D, NCB>), dim3((NCB == 1 ? em_grid<K, D>(n_blocks) : grid)), \
+                     dim3((NCB == 1 ? em_threads<K, D>() : 256)), 0, s, (const float*)W,                   \
                      (const float*)hdiag, (const float*)cb, (uint8_t*)assign, n_cb, n_blocks, in_features, \
                      d.group_rows)
   if (d.group_rows == 1) {   // a codebook per row: k * d <= 64 (checked by the caller)
