@@ -18,15 +18,6 @@
 namespace vq {
 namespace {
 
-__device__ __forceinline__ int find_problem_d4(const GemvBatch& batch, int item) {
-  int lo = 0, hi = batch.count;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (batch.p[mid].wg_begin <= item) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
 struct D4Step {
   uint4 w;        // the lane's 8 + 8 index bytes of the pair
   uint2 xa, xb;   // its activations in the two col-blocks
@@ -40,16 +31,16 @@ struct D4Step {
 // with a scale.  MODE 2 (BN): int8 tables with blockwise normalisation (appendix "Blockwise data
 // normalization"): the group's 16 block-scale levels sit next to its table in LDS, and per row
 // the looked-up vector is multiplied by the scale of the lane's 32-weight block before the dot2.
-template <bool LORA, int MODE>
-__global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LORA>::type arg) {
+template <bool LORA, int MODE, int CAP>
+__global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LORA, CAP>::type arg) {
   constexpr bool F16 = MODE == 1, BN = MODE == 2;
-  const GemvBatch& batch = base_of(arg);
+  const GemvBatchT<CAP>& batch = base_of(arg);
   __shared__ __attribute__((aligned(16))) uint2 tabs[2][2][256];   // [buffer][col-block of the pair][entry]
   __shared__ uint32_t levs[2][2][16];                               // BN: the tables' levels, the value in both halves
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int pi = find_problem_d4(batch, blockIdx.x);
+  const int pi = find_problem(batch, (int)blockIdx.x);
   const GemvProblem& P = batch.p[pi];
   const int oct = blockIdx.x - P.wg_begin;          // which 64 rows
   const int n_cb = P.n_cb, n_pairs = (n_cb + 1) >> 1;
@@ -157,15 +148,15 @@ struct K256Step {
 };
 
 // BN: with blockwise normalisation; the plain C++ inner block replaces the hand-scheduled one.
-template <bool LORA, bool BN>
-__global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf<LORA>::type arg) {
-  const GemvBatch& batch = base_of(arg);
+template <bool LORA, bool BN, int CAP>
+__global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf<LORA, CAP>::type arg) {
+  const GemvBatchT<CAP>& batch = base_of(arg);
   __shared__ __attribute__((aligned(16))) uint32_t tabs[2][2][256];   // [buffer][col-block of the pair][entry]
   __shared__ uint32_t levs[2][2][16];                                  // BN: the tables' levels, the value in both halves
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int pi = find_problem_d4(batch, blockIdx.x);
+  const int pi = find_problem(batch, (int)blockIdx.x);
   const GemvProblem& P = batch.p[pi];
   const int oct = blockIdx.x - P.wg_begin;          // which 64 rows
   const int n_cb = P.n_cb, n_pairs = (n_cb + 1) >> 1;
@@ -244,35 +235,43 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
 
 }  // namespace
 
-#define VQ_LAUNCH_WIDE(...) hipLaunchKernelGGL((__VA_ARGS__), dim3((unsigned)total_wgs), dim3(512), 0, s, batch)
+// (kernel, template arguments before CAP)
+#define VQ_LAUNCH_WIDE(KERNEL, ...)                                                                              \
+  do {                                                                                                           \
+    const dim3 grid((unsigned)total_wgs);                                                                        \
+    if (base_of_host(batch).count <= kFewProblems)                                                               \
+      hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFewProblems>), grid, dim3(512), 0, s, few_problems(batch));       \
+    else                                                                                                         \
+      hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kMaxProblemsPerLaunch>), grid, dim3(512), 0, s, batch);            \
+  } while (0)
 
 hipError_t launch_gemv_k256i8(const GemvBatch& batch, int total_wgs, hipStream_t s, int fmt) {
-  if (fmt == kFmtK256I8BN) VQ_LAUNCH_WIDE(gemv_k256i8_kernel<false, true>);
-  else if (fmt == kFmtK256I8) VQ_LAUNCH_WIDE(gemv_k256i8_kernel<false, false>);
+  if (fmt == kFmtK256I8BN) VQ_LAUNCH_WIDE(gemv_k256i8_kernel, false, true);
+  else if (fmt == kFmtK256I8) VQ_LAUNCH_WIDE(gemv_k256i8_kernel, false, false);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 hipError_t launch_gemv_d4(const GemvBatch& batch, int total_wgs, hipStream_t s, int fmt) {
-  if (fmt == kFmtD4F16) VQ_LAUNCH_WIDE(gemv_d4_kernel<false, 1>);
-  else if (fmt == kFmtD4BN) VQ_LAUNCH_WIDE(gemv_d4_kernel<false, 2>);
-  else if (fmt == kFmtD4) VQ_LAUNCH_WIDE(gemv_d4_kernel<false, 0>);
+  if (fmt == kFmtD4F16) VQ_LAUNCH_WIDE(gemv_d4_kernel, false, 1);
+  else if (fmt == kFmtD4BN) VQ_LAUNCH_WIDE(gemv_d4_kernel, false, 2);
+  else if (fmt == kFmtD4) VQ_LAUNCH_WIDE(gemv_d4_kernel, false, 0);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 // The same kernels with the low-rank adapter term added to every row before it is stored.
 hipError_t launch_gemv_k256i8_lora(const GemvBatchLora& batch, int total_wgs, hipStream_t s, int fmt) {
-  if (fmt == kFmtK256I8BN) VQ_LAUNCH_WIDE(gemv_k256i8_kernel<true, true>);
-  else if (fmt == kFmtK256I8) VQ_LAUNCH_WIDE(gemv_k256i8_kernel<true, false>);
+  if (fmt == kFmtK256I8BN) VQ_LAUNCH_WIDE(gemv_k256i8_kernel, true, true);
+  else if (fmt == kFmtK256I8) VQ_LAUNCH_WIDE(gemv_k256i8_kernel, true, false);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 hipError_t launch_gemv_d4_lora(const GemvBatchLora& batch, int total_wgs, hipStream_t s, int fmt) {
-  if (fmt == kFmtD4F16) VQ_LAUNCH_WIDE(gemv_d4_kernel<true, 1>);
-  else if (fmt == kFmtD4BN) VQ_LAUNCH_WIDE(gemv_d4_kernel<true, 2>);
-  else if (fmt == kFmtD4) VQ_LAUNCH_WIDE(gemv_d4_kernel<true, 0>);
+  if (fmt == kFmtD4F16) VQ_LAUNCH_WIDE(gemv_d4_kernel, true, 1);
+  else if (fmt == kFmtD4BN) VQ_LAUNCH_WIDE(gemv_d4_kernel, true, 2);
+  else if (fmt == kFmtD4) VQ_LAUNCH_WIDE(gemv_d4_kernel, true, 0);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

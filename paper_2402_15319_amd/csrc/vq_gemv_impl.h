@@ -437,10 +437,10 @@ __device__ __forceinline__ void store_rows(void* y, int y_f32, int rb, int lane,
 // issued together with the loads of the row-block's last chunk) and t[8j .. 8j+7] (t = A x, fp32,
 // loaded once per problem); lanes with 8j >= rank hold zeros.  Eight fp32 multiply-adds, then
 // the same three lane exchanges that end wave_reduce8.
-template <bool LORA> struct BatchOf { using type = GemvBatch; };
-template <> struct BatchOf<true> { using type = GemvBatchLora; };
-__device__ __forceinline__ const GemvBatch& base_of(const GemvBatch& b) { return b; }
-__device__ __forceinline__ const GemvBatch& base_of(const GemvBatchLora& b) { return b.base; }
+template <bool LORA, int CAP = kMaxProblemsPerLaunch> struct BatchOf { using type = GemvBatchT<CAP>; };
+template <int CAP> struct BatchOf<true, CAP> { using type = GemvBatchLoraT<CAP>; };
+template <int CAP> __device__ __forceinline__ const GemvBatchT<CAP>& base_of(const GemvBatchT<CAP>& b) { return b; }
+template <int CAP> __device__ __forceinline__ const GemvBatchT<CAP>& base_of(const GemvBatchLoraT<CAP>& b) { return b.base; }
 
 __device__ __forceinline__ uint4 lora_load_b(const LoraProblem& L, const void* fallback, int rb, int lane) {
   const int r = (lane >> 3) & 7, j = lane & 7;
@@ -471,8 +471,9 @@ __device__ __forceinline__ float lora_term(uint4 lb, const float (&tv)[8]) {
   return s;
 }
 
-// Which problem does work item `item` belong to (item_begin is ascending, p[0].item_begin = 0).
-__device__ __forceinline__ int find_problem(const GemvBatch& batch, int item) {
+// Which problem does work item `item` belong to (wg_begin is ascending, p[0].wg_begin = 0).
+template <int CAP>
+__device__ __forceinline__ int find_problem(const GemvBatchT<CAP>& batch, int item) {
   int lo = 0, hi = batch.count;
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
@@ -962,9 +963,9 @@ __device__ __forceinline__ void consume_at_priority(const C& chunk, uint32_t* lu
 // per chunk (4096 x 11008 with k = 256: three chunks per wave), and with UP = 1 the second chunk
 // buffer and its registers disappear.  UP = 0: strips of any length, two chunk buffers ping-pong.
 // WPW: waves per workgroup, 4 or 8 (8 when 8 waves share a row-block).
-template <int K, int UP, int WPW, bool LORA>
-__global__ __launch_bounds__(64 * WPW) void gemv_split_kernel(const typename BatchOf<LORA>::type arg) {
-  const GemvBatch& batch = base_of(arg);
+template <int K, int UP, int WPW, bool LORA, int CAP>
+__global__ __launch_bounds__(64 * WPW) void gemv_split_kernel(const typename BatchOf<LORA, CAP>::type arg) {
+  const GemvBatchT<CAP>& batch = base_of(arg);
   __shared__ __attribute__((aligned(16))) uint32_t lut_all[WPW][(UP == 1 ? 1 : 2) * Chunk<K>::kLutDwords];
   __shared__ float part[WPW][8];
 
@@ -1145,38 +1146,51 @@ inline int chunk_units_impl(int fmt) {
   return units;
 }
 
-template <bool LORA>
-hipError_t launch_gemv_impl(int fmt, const typename BatchOf<LORA>::type& batch, int mode, int grid_wgs,
-                            int max_n_cb, hipStream_t s, int wpw) {
+inline const GemvBatch& base_of_host(const GemvBatch& b) { return b; }
+inline const GemvBatch& base_of_host(const GemvBatchLora& b) { return b.base; }
+
+template <bool LORA, int CAP>
+hipError_t launch_split(int fmt, const typename BatchOf<LORA, CAP>::type& batch, int mode, int grid_wgs, hipStream_t s,
+                        int wpw) {
   const dim3 grid(grid_wgs), block(64 * wpw);
-  if (mode == 1) {
-    const size_t lds = stream_lds_bytes_impl(fmt, max_n_cb);
-    const dim3 sblock(kStreamWaves * 64);
-#define VQ_F(K) hipLaunchKernelGGL((gemv_stream_kernel<K, LORA>), grid, sblock, lds, s, batch)
-    VQ_FMT_SWITCH(fmt, VQ_F)
-#undef VQ_F
-  } else if (mode == 2) {
+  if (mode == 2) {
 #define VQ_F(K)                                                                                   \
-  if (wpw == 8) hipLaunchKernelGGL((gemv_split_kernel<K, 1, 8, LORA>), grid, block, 0, s, batch); \
-  else hipLaunchKernelGGL((gemv_split_kernel<K, 1, 4, LORA>), grid, block, 0, s, batch)
+  if (wpw == 8) hipLaunchKernelGGL((gemv_split_kernel<K, 1, 8, LORA, CAP>), grid, block, 0, s, batch); \
+  else hipLaunchKernelGGL((gemv_split_kernel<K, 1, 4, LORA, CAP>), grid, block, 0, s, batch)
     VQ_FMT_SWITCH(fmt, VQ_F)
 #undef VQ_F
   } else if (wpw != 8) {
     return hipErrorInvalidValue;    // strips longer than one chunk are always shared by 8 waves
   } else if (mode == 3) {
-#define VQ_F(K) hipLaunchKernelGGL((gemv_split_kernel<K, 2, 8, LORA>), grid, block, 0, s, batch)
+#define VQ_F(K) hipLaunchKernelGGL((gemv_split_kernel<K, 2, 8, LORA, CAP>), grid, block, 0, s, batch)
     VQ_FMT_SWITCH(fmt, VQ_F)
 #undef VQ_F
   } else if (mode == 4) {
-#define VQ_F(K) hipLaunchKernelGGL((gemv_split_kernel<K, 3, 8, LORA>), grid, block, 0, s, batch)
+#define VQ_F(K) hipLaunchKernelGGL((gemv_split_kernel<K, 3, 8, LORA, CAP>), grid, block, 0, s, batch)
     VQ_FMT_SWITCH(fmt, VQ_F)
 #undef VQ_F
   } else {
-#define VQ_F(K) hipLaunchKernelGGL((gemv_split_kernel<K, 0, 8, LORA>), grid, block, 0, s, batch)
+#define VQ_F(K) hipLaunchKernelGGL((gemv_split_kernel<K, 0, 8, LORA, CAP>), grid, block, 0, s, batch)
     VQ_FMT_SWITCH(fmt, VQ_F)
 #undef VQ_F
   }
   return hipGetLastError();
+}
+
+template <bool LORA>
+hipError_t launch_gemv_impl(int fmt, const typename BatchOf<LORA>::type& batch, int mode, int grid_wgs,
+                            int max_n_cb, hipStream_t s, int wpw) {
+  if (mode == 1) {
+    const size_t lds = stream_lds_bytes_impl(fmt, max_n_cb);
+    const dim3 grid(grid_wgs), block(kStreamWaves * 64);
+#define VQ_F(K) hipLaunchKernelGGL((gemv_stream_kernel<K, LORA>), grid, block, lds, s, batch)
+    VQ_FMT_SWITCH(fmt, VQ_F)
+#undef VQ_F
+    return hipGetLastError();
+  }
+  if (base_of_host(batch).count <= kFewProblems)
+    return launch_split<LORA, kFewProblems>(fmt, few_problems(batch), mode, grid_wgs, s, wpw);
+  return launch_split<LORA, kMaxProblemsPerLaunch>(fmt, batch, mode, grid_wgs, s, wpw);
 }
 
 }  // namespace

@@ -12,7 +12,8 @@ namespace {
 // first four pieces (rows of up to 8,192 columns) are all loaded before the first is used, so a
 // row costs one round trip to memory.  fp32 multiply-adds, lanes summed by a halving exchange,
 // the four waves' sums added in wave order: a fixed order, the same result on every call.
-__global__ __launch_bounds__(256) void lora_down_kernel(const LoraDownBatch batch) {
+template <int CAP>
+__global__ __launch_bounds__(256) void lora_down_kernel(const LoraDownBatchT<CAP> batch) {
   __shared__ float part[4];
   const int tid = threadIdx.x;
   const int row = blockIdx.x;
@@ -60,7 +61,9 @@ __global__ __launch_bounds__(256) void lora_down_kernel(const LoraDownBatch batc
 
 hipError_t launch_lora_down(const LoraDownBatch& batch, hipStream_t s) {
   if (batch.total_rows == 0) return hipSuccess;
-  hipLaunchKernelGGL(lora_down_kernel, dim3(batch.total_rows), dim3(256), 0, s, batch);
+  const dim3 grid(batch.total_rows);
+  if (batch.count <= kFewProblems) hipLaunchKernelGGL(lora_down_kernel<kFewProblems>, grid, dim3(256), 0, s, few_problems(batch));
+  else hipLaunchKernelGGL(lora_down_kernel<kMaxProblemsPerLaunch>, grid, dim3(256), 0, s, batch);
   return hipGetLastError();
 }
 

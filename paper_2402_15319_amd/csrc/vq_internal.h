@@ -76,13 +76,20 @@ struct GemvProblem {
   int32_t rb_per_cb;    // 8-row blocks that share one codebook (group_rows / 8)
 };
 
-struct GemvBatch {
+// The kernel argument of a launch of at most CAP products.  The host fills the widest one; launches of
+// up to kFewProblems products get the narrow one (few_problems below): 240 instead of 14,352 bytes for the
+// runtime to copy, about 1 us of a call's host time (a decoder layer's launches hold one to three products).
+// The kernels search either table alike: loading all four entries at once measured the same.
+template <int CAP>
+struct GemvBatchT {
   int32_t count;
   int32_t y_f32;
   int32_t total_wgs;    // work items in the launch
   int32_t total_cost;   // groups in the launch
-  GemvProblem p[kMaxProblemsPerLaunch];
+  GemvProblem p[CAP];
 };
+constexpr int kFewProblems = 4;
+using GemvBatch = GemvBatchT<kMaxProblemsPerLaunch>;
 
 // Low-rank adapter of one problem (y = W x + B (A x)): what the GEMV epilogue needs.
 struct LoraProblem {
@@ -94,10 +101,12 @@ struct LoraProblem {
 constexpr int kMaxLoraRank = 64;
 constexpr int kLoraWorkspaceFloats = kMaxLoraRank;   // fp32 slots of workspace per problem
 
-struct GemvBatchLora {
-  GemvBatch base;
-  LoraProblem l[kMaxProblemsPerLaunch];
+template <int CAP>
+struct GemvBatchLoraT {
+  GemvBatchT<CAP> base;
+  LoraProblem l[CAP];
 };
+using GemvBatchLora = GemvBatchLoraT<kMaxProblemsPerLaunch>;
 
 // t = A x of every problem of a launch: one wave per row of A.
 struct LoraDownProblem {
@@ -107,11 +116,30 @@ struct LoraDownProblem {
   int32_t in_features;
   int32_t row_begin;    // rows of A of all earlier problems of the launch
 };
-struct LoraDownBatch {
+template <int CAP>
+struct LoraDownBatchT {
   int32_t count;
   int32_t total_rows;
-  LoraDownProblem p[kMaxProblemsPerLaunch];
+  LoraDownProblem p[CAP];
 };
+using LoraDownBatch = LoraDownBatchT<kMaxProblemsPerLaunch>;
+
+// The narrow form of a launch's argument (count <= kFewProblems).
+inline GemvBatchT<kFewProblems> few_problems(const GemvBatch& b) {
+  GemvBatchT<kFewProblems> f = {b.count, b.y_f32, b.total_wgs, b.total_cost, {}};
+  for (int i = 0; i < b.count && i < kFewProblems; ++i) f.p[i] = b.p[i];
+  return f;
+}
+inline GemvBatchLoraT<kFewProblems> few_problems(const GemvBatchLora& b) {
+  GemvBatchLoraT<kFewProblems> f = {few_problems(b.base), {}};
+  for (int i = 0; i < b.base.count && i < kFewProblems; ++i) f.l[i] = b.l[i];
+  return f;
+}
+inline LoraDownBatchT<kFewProblems> few_problems(const LoraDownBatch& b) {
+  LoraDownBatchT<kFewProblems> f = {b.count, b.total_rows, {}};
+  for (int i = 0; i < b.count && i < kFewProblems; ++i) f.p[i] = b.p[i];
+  return f;
+}
 
 // Launchers (each returns the hipError_t of its launch).
 hipError_t launch_pack(const vq_desc& d, const void* idx_canon, const void* cb_canon,
