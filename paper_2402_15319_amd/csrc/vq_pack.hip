@@ -276,79 +276,91 @@ __global__ __launch_bounds__(256) void pack_tab_d1k4_kernel(const uint32_t* __re
   reinterpret_cast<uint16_t*>(rec + kD1K4ScaleOffset)[r] = ok ? scale_canon[g] : (uint16_t)0;
 }
 
-// ---- k = 64: 6-bit indices, int8 tables with a scale per group, groups of 8*rpc rows -------
-// One thread per (8-row block, quad of col-blocks, lane): gathers the lane's 4 x 16 indices
-// from the canonical little-endian 6-bit stream of their groups and re-packs them as four
-// 96-bit streams (index 2*row + e at bits [6i, 6i+6)), written as three 16-byte planes.
-__global__ __launch_bounds__(256) void pack_idx64_kernel(const uint8_t* __restrict__ canon,
-                                                         uint8_t* __restrict__ dev, int n_cb,
-                                                         long long n_rb8, int rpc) {
-  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-  const long long slot = t >> 6;
-  const int lane = (int)(t & 63);
-  const int n_quads = k64_quads(n_cb);
-  if (slot >= n_rb8 * n_quads) return;
-  const long long rb8 = slot / n_quads;
-  const int q = (int)(slot - rb8 * n_quads);
-  const long long grow = rb8 / rpc;              // row of groups
-  const int sub = (int)(rb8 - grow * rpc);       // 8-row block inside the group
-  const size_t group_bytes = (size_t)rpc * 8 * 96;   // rows x 128 vectors x 6 bits
+// ---- k = 64 (and d = 1, k = 8): 6-bit fields, int8 tables with a scale per group, groups of 8*rpc rows ----
+// One launch for everything: workgroups [0, idx_wgs) re-pack indices, the next tab_wgs tables, the rest block
+// codes (blockwise normalisation).  Bound: memory; per workgroup of indices 12 KB are read and written in
+// 16-byte pieces.  4096 x 11008 with blockwise normalisation: 35 -> 7.3 us (indices lane by lane in single bytes,
+// three launches, 64-bit divisions in every thread before).
+struct Pack64 {
+  const uint8_t* idx_canon;
+  uint8_t* idx_dev;
+  const uint8_t* q_canon;         // int8 tables
+  const uint16_t* scale_canon;
+  const uint16_t* level_canon;    // NULL without blockwise normalisation
+  const uint8_t* code_canon;
+  uint8_t* tab_dev;
+  uint32_t* code_dev;
+  int32_t n_cb, rpc;
+  uint32_t n_rb8, n_grow;         // 8-row blocks, rows of groups
+  uint32_t idx_wgs, tab_wgs;
+};
+
+// A wave owns a (8-row block, quad of col-blocks): 4 x 768 bytes of the canonical little-endian stream, which go
+// through LDS.  A row of a col-block is 96 bytes, 12 bits (two fields) per lane; the lane's eight 12-bit pieces of
+// a col-block form a 96-bit stream (index 2*row + e at bits [6i, 6i+6)), written as parts of three 16-byte planes.
+__device__ __forceinline__ void pack_idx64(const Pack64& a, uint32_t wg, uint32_t (&stage)[4][772]) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t* st = stage[wave];
+  const uint32_t n_quads = (uint32_t)k64_quads(a.n_cb), slot = wg * 4 + wave;
+  if (slot >= a.n_rb8 * n_quads) return;        // whole waves leave; no workgroup barrier here
+  const uint32_t rb8 = slot / n_quads, q = slot - rb8 * n_quads;
+  const uint32_t grow = rb8 / (uint32_t)a.rpc, sub = rb8 - grow * (uint32_t)a.rpc;
+  const size_t group_bytes = (size_t)a.rpc * 768;
+  // 192 pieces of 16 bytes, 48 per col-block
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    const int piece = p * 64 + lane, j = piece / 48, c = 4 * (int)q + j;
+    const uint8_t* src = a.idx_canon + ((size_t)grow * a.n_cb + (c < a.n_cb ? c : 0)) * group_bytes + sub * 768 + (piece - 48 * j) * 16;
+    const uint4 v = *reinterpret_cast<const uint4*>(src);
+    *reinterpret_cast<uint4*>(st + piece * 4) = c < a.n_cb ? v : make_uint4(0u, 0u, 0u, 0u);
+  }
+  wave_lds_sync();
   uint32_t d[12];
 #pragma unroll
   for (int i = 0; i < 12; ++i) d[i] = 0u;
+  const int word = (12 * lane) >> 5, shift = (12 * lane) & 31;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int c = 4 * q + j;
-    if (c >= n_cb) continue;
-    const uint8_t* g = canon + (size_t)(grow * n_cb + c) * group_bytes;
+  for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int v = (sub * 8 + (i >> 1)) * 128 + 2 * lane + (i & 1);
-      const int bit = 6 * v, b = bit >> 3, sh = bit & 7;
-      uint32_t val = g[b] >> sh;
-      if (sh > 2) val |= (uint32_t)g[b + 1] << (8 - sh);   // the field continues in the next byte
-      val &= 63u;
-      const int pos = 6 * i, dw = 3 * j + (pos >> 5), off = pos & 31;
+    for (int r = 0; r < 8; ++r) {
+      const uint32_t* w = st + j * 192 + r * 24 + word;      // the second word may lie behind the row: not used then
+      const uint32_t val = __builtin_amdgcn_alignbit(w[1], w[0], shift) & 0xfffu;
+      const int pos = 12 * r, dw = 3 * j + (pos >> 5), off = pos & 31;
       d[dw] |= val << off;
-      if (off > 26) d[dw + 1] |= val >> (32 - off);
+      if (off > 20) d[dw + 1] |= val >> (32 - off);
     }
-  }
 #pragma unroll
   for (int p = 0; p < 3; ++p)
-    *reinterpret_cast<uint4*>(dev + ((size_t)slot * 3 + p) * 1024 + lane * 16) =
+    *reinterpret_cast<uint4*>(a.idx_dev + ((size_t)slot * 3 + p) * 1024 + lane * 16) =
         make_uint4(d[4 * p], d[4 * p + 1], d[4 * p + 2], d[4 * p + 3]);
 }
 
 // Tables: per (row of groups, quad) four int8 tables of 128 bytes, then their four scales;
 // with blockwise normalisation (level_canon != nullptr, 672-byte records) also the four
 // col-blocks' 16 fp16 levels.
-__global__ __launch_bounds__(256) void pack_tab64_kernel(const uint8_t* __restrict__ q_canon,
-                                                         const uint16_t* __restrict__ scale_canon,
-                                                         const uint16_t* __restrict__ level_canon,
-                                                         uint8_t* __restrict__ dev, int n_cb,
-                                                         long long n_grow) {
-  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-  const long long slot = t >> 6;
-  const int lane = (int)(t & 63);
-  const int n_quads = k64_quads(n_cb);
-  if (slot >= n_grow * n_quads) return;
-  const long long grow = slot / n_quads;
-  const int q = (int)(slot - grow * n_quads);
+__device__ __forceinline__ void pack_tab64(const Pack64& a, uint32_t wg) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t n_quads = (uint32_t)k64_quads(a.n_cb), slot = wg * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (slot >= a.n_grow * n_quads) return;
+  const uint32_t grow = slot / n_quads;
+  const int q = (int)(slot - grow * n_quads), n_cb = a.n_cb;
+  const size_t g0 = (size_t)grow * n_cb;
   const int c = 4 * q + (lane >> 4);
-  uint8_t* dst = dev + (size_t)slot * (level_canon ? kK64NQuadTabBytes : kK64QuadTabBytes);
-  if (level_canon) {
+  uint8_t* dst = a.tab_dev + (size_t)slot * (a.level_canon ? kK64NQuadTabBytes : kK64QuadTabBytes);
+  if (a.level_canon) {
     reinterpret_cast<uint16_t*>(dst + kK64NLevelOffset)[lane] =
-        c < n_cb ? level_canon[(grow * n_cb + c) * 16 + (lane & 15)] : (uint16_t)0;
+        c < n_cb ? a.level_canon[(g0 + c) * 16 + (lane & 15)] : (uint16_t)0;
     if (lane < 8) reinterpret_cast<uint16_t*>(dst + kK64NLevelOffset + 128)[lane] = 0;   // padding
   }
   const uint2 v = c < n_cb
-      ? *reinterpret_cast<const uint2*>(q_canon + (size_t)(grow * n_cb + c) * 128 + (lane & 15) * 8)
+      ? *reinterpret_cast<const uint2*>(a.q_canon + (g0 + c) * 128 + (lane & 15) * 8)
       : make_uint2(0u, 0u);
   *reinterpret_cast<uint2*>(dst + lane * 8) = v;
   if (lane < 8) {
     const int cs = 4 * q + lane;
     reinterpret_cast<uint16_t*>(dst + 512)[lane] =
-        (lane < 4 && cs < n_cb) ? scale_canon[grow * n_cb + cs] : (uint16_t)0;
+        (lane < 4 && cs < n_cb) ? a.scale_canon[g0 + cs] : (uint16_t)0;
   }
 }
 
@@ -356,23 +368,19 @@ __global__ __launch_bounds__(256) void pack_tab64_kernel(const uint8_t* __restri
 // (48 bytes).  One thread per record.
 // With blockwise normalisation (level_canon != nullptr): 176-byte records, the four col-blocks'
 // 16 fp16 levels behind the 48 bytes.
-__global__ __launch_bounds__(256) void pack_tab_d1k8_kernel(const uint8_t* __restrict__ q_canon,
-                                                            const uint16_t* __restrict__ scale_canon,
-                                                            const uint16_t* __restrict__ level_canon,
-                                                            uint8_t* __restrict__ dev, int n_cb,
-                                                            long long n_grow) {
-  const long long slot = (long long)blockIdx.x * 256 + threadIdx.x;
-  const int n_quads = k64_quads(n_cb);
-  if (slot >= n_grow * n_quads) return;
-  const long long grow = slot / n_quads;
-  const int q = (int)(slot - grow * n_quads);
-  uint8_t* dst = dev + (size_t)slot * (level_canon ? kD1K8NQuadTabBytes : kD1K8QuadTabBytes);
-  if (level_canon) {
+__device__ __forceinline__ void pack_tab_d1k8(const Pack64& a, uint32_t wg) {
+  const uint32_t n_quads = (uint32_t)k64_quads(a.n_cb), slot = wg * 256 + threadIdx.x;
+  if (slot >= a.n_grow * n_quads) return;
+  const uint32_t grow = slot / n_quads;
+  const int q = (int)(slot - grow * n_quads), n_cb = a.n_cb;
+  const size_t g0 = (size_t)grow * n_cb;
+  uint8_t* dst = a.tab_dev + (size_t)slot * (a.level_canon ? kD1K8NQuadTabBytes : kD1K8QuadTabBytes);
+  if (a.level_canon) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int c = 4 * q + j;
       uint4* lv = reinterpret_cast<uint4*>(dst + kD1K8NLevelOffset + j * 32);
-      const uint4* src = reinterpret_cast<const uint4*>(level_canon + (size_t)(grow * n_cb + (c < n_cb ? c : 0)) * 16);
+      const uint4* src = reinterpret_cast<const uint4*>(a.level_canon + (g0 + (c < n_cb ? c : 0)) * 16);
       lv[0] = c < n_cb ? src[0] : make_uint4(0, 0, 0, 0);
       lv[1] = c < n_cb ? src[1] : make_uint4(0, 0, 0, 0);
     }
@@ -382,8 +390,8 @@ __global__ __launch_bounds__(256) void pack_tab_d1k8_kernel(const uint8_t* __res
     const int c = 4 * q + j;
     const bool ok = c < n_cb;
     *reinterpret_cast<uint2*>(dst + j * 8) =
-        ok ? *reinterpret_cast<const uint2*>(q_canon + (size_t)(grow * n_cb + c) * 8) : make_uint2(0u, 0u);
-    reinterpret_cast<uint16_t*>(dst + kD1K8ScaleOffset)[j] = ok ? scale_canon[grow * n_cb + c] : (uint16_t)0;
+        ok ? *reinterpret_cast<const uint2*>(a.q_canon + (g0 + c) * 8) : make_uint2(0u, 0u);
+    reinterpret_cast<uint16_t*>(dst + kD1K8ScaleOffset)[j] = ok ? a.scale_canon[g0 + c] : (uint16_t)0;
   }
   *reinterpret_cast<uint2*>(dst + 40) = make_uint2(0u, 0u);
 }
@@ -391,27 +399,31 @@ __global__ __launch_bounds__(256) void pack_tab_d1k8_kernel(const uint8_t* __res
 // Block codes: canonical code[r][c/32] (two per byte, even block in the low nibble, 4*n_cb
 // bytes per row) -> per (8-row block, quad) 32 dwords, dword 4*b + j = codes of block b of
 // col-block 4q + j, row r in bits [4r, 4r+4).  One thread per dword.
-__global__ __launch_bounds__(256) void pack_codes64_kernel(const uint8_t* __restrict__ canon,
-                                                           uint32_t* __restrict__ dev, int n_cb,
-                                                           long long n_rb8) {
-  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-  const int n_quads = k64_quads(n_cb);
-  if (t >= n_rb8 * n_quads * 32) return;
-  const long long slot = t >> 5;
-  const int b = (int)(t & 31) >> 2, j = (int)(t & 3);
-  const long long rb8 = slot / n_quads;
-  const int q = (int)(slot - rb8 * n_quads);
-  const int c = 4 * q + j;
+__device__ __forceinline__ void pack_codes64(const Pack64& a, uint32_t wg) {
+  const uint32_t n_quads = (uint32_t)k64_quads(a.n_cb), slot = wg * 8 + (threadIdx.x >> 5);
+  if (slot >= a.n_rb8 * n_quads) return;
+  const int b = (int)(threadIdx.x & 31) >> 2, j = (int)(threadIdx.x & 3);
+  const uint32_t rb8 = slot / n_quads;
+  const int c = 4 * (int)(slot - rb8 * n_quads) + j;
   uint32_t w = 0;
-  if (c < n_cb) {
+  if (c < a.n_cb) {
     const int blk = c * 8 + b;                       // block index inside the row
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
-      const uint32_t byte = canon[(size_t)(rb8 * 8 + r) * (4 * n_cb) + (blk >> 1)];
+      const uint32_t byte = a.code_canon[((size_t)rb8 * 8 + r) * (4 * a.n_cb) + (blk >> 1)];
       w |= ((blk & 1) ? byte >> 4 : byte & 15u) << (4 * r);
     }
   }
-  dev[t] = w;
+  a.code_dev[(size_t)slot * 32 + (threadIdx.x & 31)] = w;
+}
+
+template <bool D1>
+__global__ __launch_bounds__(256) void pack64_kernel(const Pack64 a) {
+  __shared__ __attribute__((aligned(16))) uint32_t stage[4][772];   // 3 KB per wave and a word behind it
+  const uint32_t wg = blockIdx.x;
+  if (wg < a.idx_wgs) pack_idx64(a, wg, stage);
+  else if (wg < a.idx_wgs + a.tab_wgs) D1 ? pack_tab_d1k8(a, wg - a.idx_wgs) : pack_tab64(a, wg - a.idx_wgs);
+  else pack_codes64(a, wg - a.idx_wgs - a.tab_wgs);
 }
 
 // d = 4 indices: canonical group (row of groups, c) holds group_rows x 64 bytes, byte r*64 + L =
@@ -482,42 +494,34 @@ hipError_t launch_pack(const vq_desc& d, const void* idx_canon, const void* cb_c
     return hipGetLastError();
   }
   if (d.k == 64 || (d.d == 1 && d.k == 8)) {   // 6-bit fields: k = 64, or two 3-bit indices of d = 1
-    const int rpc = d.group_rows / kGroupRows;
     const long long n_grow = d.out_features / d.group_rows;
     const int n_quads = k64_quads(n_cb);
-    hipLaunchKernelGGL(pack_idx64_kernel, dim3((unsigned)((n_rb * n_quads * 64 + 255) / 256)), dim3(256),
-                       0, s, (const uint8_t*)idx_canon, (uint8_t*)idx_dev, n_cb, n_rb, rpc);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (d.d == 1) {   // k = 8 scalar tables: 8 bytes per group, padded to 16 in total, then the scales
-      const size_t q8 = ((size_t)n_grow * n_cb * 8 + 15) / 16 * 16;
-      const bool bn8 = d.codebook_dtype == VQ_I8_BN;
-      const size_t s8 = ((size_t)n_grow * n_cb * 2 + 15) / 16 * 16;        // levels follow the padded scales
-      const uint8_t* canon8 = (const uint8_t*)cb_canon;
-      hipLaunchKernelGGL(pack_tab_d1k8_kernel, dim3((unsigned)((n_grow * n_quads + 255) / 256)), dim3(256), 0, s,
-                         canon8, (const uint16_t*)(canon8 + q8),
-                         bn8 ? (const uint16_t*)(canon8 + q8 + s8) : (const uint16_t*)nullptr,
-                         (uint8_t*)cb_dev, n_cb, n_grow);
-      e = hipGetLastError();
-      if (e != hipSuccess || !bn8) return e;
-      hipLaunchKernelGGL(pack_codes64_kernel, dim3((unsigned)((n_rb * n_quads * 32 + 255) / 256)), dim3(256),
-                         0, s, canon8 + q8 + s8 + (size_t)n_grow * n_cb * 32,
-                         (uint32_t*)((uint8_t*)cb_dev + (size_t)n_grow * n_quads * kD1K8NQuadTabBytes), n_cb, n_rb);
-      return hipGetLastError();
-    }
-    const size_t q_bytes = ((size_t)n_grow * n_cb * 128 + 15) / 16 * 16;   // scales follow the tables
-    const bool bn = d.codebook_dtype == VQ_I8_BN;
-    const size_t s_bytes = ((size_t)n_grow * n_cb * 2 + 15) / 16 * 16;     // levels follow the padded scales
+    const bool d1 = d.d == 1, bn = d.codebook_dtype == VQ_I8_BN;
+    // canonical tables, padded to 16 bytes; scales; with blockwise normalisation padded too, then levels and codes
+    const size_t q_bytes = ((size_t)n_grow * n_cb * (d1 ? 8 : 128) + 15) / 16 * 16;
+    const size_t s_bytes = ((size_t)n_grow * n_cb * 2 + 15) / 16 * 16;
     const uint8_t* canon = (const uint8_t*)cb_canon;
-    hipLaunchKernelGGL(pack_tab64_kernel, dim3((unsigned)((n_grow * n_quads * 64 + 255) / 256)),
-                       dim3(256), 0, s, canon, (const uint16_t*)(canon + q_bytes),
-                       bn ? (const uint16_t*)(canon + q_bytes + s_bytes) : (const uint16_t*)nullptr,
-                       (uint8_t*)cb_dev, n_cb, n_grow);
-    e = hipGetLastError();
-    if (e != hipSuccess || !bn) return e;
-    hipLaunchKernelGGL(pack_codes64_kernel, dim3((unsigned)((n_rb * n_quads * 32 + 255) / 256)), dim3(256),
-                       0, s, canon + q_bytes + s_bytes + (size_t)n_grow * n_cb * 32,
-                       (uint32_t*)((uint8_t*)cb_dev + (size_t)n_grow * n_quads * kK64NQuadTabBytes), n_cb, n_rb);
+    Pack64 a = {};
+    a.idx_canon = (const uint8_t*)idx_canon;
+    a.idx_dev = (uint8_t*)idx_dev;
+    a.q_canon = canon;
+    a.scale_canon = (const uint16_t*)(canon + q_bytes);
+    a.tab_dev = (uint8_t*)cb_dev;
+    if (bn) {
+      a.level_canon = (const uint16_t*)(canon + q_bytes + s_bytes);
+      a.code_canon = canon + q_bytes + s_bytes + (size_t)n_grow * n_cb * 32;
+      a.code_dev = (uint32_t*)((uint8_t*)cb_dev + (size_t)n_grow * n_quads * (d1 ? kD1K8NQuadTabBytes : kK64NQuadTabBytes));
+    }
+    a.n_cb = n_cb;
+    a.rpc = d.group_rows / kGroupRows;
+    a.n_rb8 = (uint32_t)n_rb;
+    a.n_grow = (uint32_t)n_grow;
+    const long long idx_slots = n_rb * n_quads, tab_slots = n_grow * n_quads;    // at most 2^27 (out * in <= 2^40)
+    a.idx_wgs = (uint32_t)((idx_slots + 3) / 4);
+    a.tab_wgs = (uint32_t)(d1 ? (tab_slots + 255) / 256 : (tab_slots + 3) / 4);
+    const uint32_t wgs = a.idx_wgs + a.tab_wgs + (bn ? (uint32_t)((idx_slots + 7) / 8) : 0u);
+    if (d1) hipLaunchKernelGGL(pack64_kernel<true>, dim3(wgs), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(pack64_kernel<false>, dim3(wgs), dim3(256), 0, s, a);
     return hipGetLastError();
   }
   const int fmt = format_tag(d);
