@@ -132,10 +132,11 @@ template <> struct GroupRegs<kFmtK16BN> {
   uint32_t lev;          // block-scale level lane & 15 (fp16)
 };
 
+// grow, n_grows: the row of groups that row-block rb lies in, and their number (callers divide once, not per col-block).
 template <int K>
 __device__ __forceinline__ void load_group(GroupRegs<K>& g, const uint8_t* idx, const uint32_t* cb,
                                            long long rb, int c, int n_cb, int lane, int n_rb,
-                                           int rpc) {
+                                           long long grow, int n_grows) {
   if constexpr (K == 16) {
     const int slots = 2 * k16_pairs(n_cb);
     g.w = *reinterpret_cast<const uint2*>(idx + (size_t)rb * slots * 512 + k16_chunk_offset(c, lane));
@@ -175,13 +176,13 @@ __device__ __forceinline__ void load_group(GroupRegs<K>& g, const uint8_t* idx, 
     g.sc = *reinterpret_cast<const uint16_t*>(rec + kD1K4ScaleOffset + (lane >> 3) * 2);
   } else if constexpr (K == kFmtD4F16) {
     const uint8_t* tab = reinterpret_cast<const uint8_t*>(cb);
-    const size_t gi = (size_t)(rb / rpc) * n_cb + c;
+    const size_t gi = (size_t)grow * n_cb + c;
     g.w = *reinterpret_cast<const uint2*>(idx + ((size_t)rb * ((n_cb + 1) >> 1) + (c >> 1)) * 1024 + lane * 16 + (c & 1) * 8);
     g.q0 = *reinterpret_cast<const uint4*>(tab + gi * 2048 + lane * 32);
     g.q1 = *reinterpret_cast<const uint4*>(tab + gi * 2048 + lane * 32 + 16);
   } else if constexpr (K == kFmtD4 || K == kFmtD4BN) {
     const uint8_t* tab = reinterpret_cast<const uint8_t*>(cb);
-    const size_t gi = (size_t)(rb / rpc) * n_cb + c, n_groups = (size_t)(n_rb / rpc) * n_cb;
+    const size_t gi = (size_t)grow * n_cb + c, n_groups = (size_t)n_grows * n_cb;
     g.w = *reinterpret_cast<const uint2*>(idx + ((size_t)rb * ((n_cb + 1) >> 1) + (c >> 1)) * 1024 + lane * 16 + (c & 1) * 8);
     g.q = *reinterpret_cast<const uint4*>(tab + gi * 1024 + lane * 16);
     g.sc = reinterpret_cast<const uint16_t*>(tab + n_groups * 1024)[gi];
@@ -192,7 +193,7 @@ __device__ __forceinline__ void load_group(GroupRegs<K>& g, const uint8_t* idx, 
     }
   } else if constexpr (K == kFmtK256I8 || K == kFmtK256I8BN) {
     const uint8_t* tab = reinterpret_cast<const uint8_t*>(cb);
-    const size_t gt = (size_t)(rb / rpc) * n_cb + c, n_tabs = (size_t)(n_rb / rpc) * n_cb;
+    const size_t gt = (size_t)grow * n_cb + c, n_tabs = (size_t)n_grows * n_cb;
     g.w = *reinterpret_cast<const uint4*>(idx + ((size_t)rb * n_cb + c) * 1024 + lane * 16);
     g.q = *reinterpret_cast<const uint2*>(tab + gt * 512 + lane * 8);
     g.sc = reinterpret_cast<const uint16_t*>(tab + n_tabs * 512)[gt];
@@ -218,7 +219,7 @@ __device__ __forceinline__ void load_group(GroupRegs<K>& g, const uint8_t* idx, 
     g.d1 = *reinterpret_cast<const uint32_t*>(iq + (w1 >> 2) * 1024 + (w1 & 3) * 4);
     g.d2 = *reinterpret_cast<const uint32_t*>(iq + (w2 >> 2) * 1024 + (w2 & 3) * 4);
     const uint8_t* tq = reinterpret_cast<const uint8_t*>(cb) +
-                        ((size_t)(rb / rpc) * n_quads + q) * tab_bytes;
+                        ((size_t)grow * n_quads + q) * tab_bytes;
     if constexpr (K == kFmtD1K8 || K == kFmtD1K8BN) {
       g.two = d1k8_pair(*reinterpret_cast<const uint2*>(tq + j * 8), lane);
       g.sc = *reinterpret_cast<const uint16_t*>(tq + kD1K8ScaleOffset + 2 * j);
@@ -229,7 +230,7 @@ __device__ __forceinline__ void load_group(GroupRegs<K>& g, const uint8_t* idx, 
     if constexpr (K == kFmtK64BN || K == kFmtD1K8BN) {
       g.lev = *reinterpret_cast<const uint16_t*>(tq + level_offset + j * 32 + (lane & 15) * 2);
       g.cw = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(cb) +
-                                                (size_t)(n_rb / rpc) * n_quads * tab_bytes +
+                                                (size_t)n_grows * n_quads * tab_bytes +
                                                 ((size_t)rb * n_quads + q) * kK64NQuadCodeBytes +
                                                 (lane >> 3) * 16 + j * 4);
     }
@@ -494,11 +495,17 @@ __global__ __launch_bounds__(256 * WM, WM == 1 ? 2 : 1) void gemm_kernel(const u
   GroupRegs<K> g[RBW];
   long long rbs[RBW];
   bool rb_ok[RBW];
+  // Rows of groups.  Divided once for the 32 x 128 tile, where a col-block is short (4096 x 4096, B = 256 26.0 ->
+  // 24.4 us with 6-bit indices); the larger tiles hide the scalar division behind other waves and lose by the
+  // earlier loads (11008 x 4096, B = 203: 48.2 us dividing per col-block, 48.9 once).
+  int grows[RBW];
+  auto grow_of = [&](int a) { return RBW == 1 ? (long long)grows[a] : (rb_ok[a] ? rbs[a] : 0) / rpc; };
 #pragma unroll
   for (int a = 0; a < RBW; ++a) {
     rbs[a] = rb0 + (long long)mt * (4 * RBW * WM) + wave * RBW + a;
     rb_ok[a] = rbs[a] < rb_end;
-    load_group<K>(g[a], idx, cb, rb_ok[a] ? rbs[a] : 0, 0, n_cb, lane, n_rb, rpc);
+    grows[a] = rb_ok[a] ? (int)rbs[a] / rpc : 0;
+    load_group<K>(g[a], idx, cb, rb_ok[a] ? rbs[a] : 0, 0, n_cb, lane, n_rb, grow_of(a), n_rb / rpc);
   }
   XRows ring[D];   // slot t % D holds sub-tile t + 1 when sub-step t starts
   {
@@ -527,7 +534,7 @@ __global__ __launch_bounds__(256 * WM, WM == 1 ? 2 : 1) void gemm_kernel(const u
           *reinterpret_cast<uint2*>(Wt + wt_half_index(m0 + r, 4 * lane)) = make_uint2(0u, 0u);
       }
       // next col-block's registers (clamped on the last one: a harmless re-read)
-      load_group<K>(g[a], idx, cb, rb_ok[a] ? rbs[a] : 0, min(c + 1, n_cb - 1), n_cb, lane, n_rb, rpc);
+      load_group<K>(g[a], idx, cb, rb_ok[a] ? rbs[a] : 0, min(c + 1, n_cb - 1), n_cb, lane, n_rb, grow_of(a), n_rb / rpc);
     }
     __syncthreads();   // Wt of this col-block and the X sub-tile in Xs[cur] are complete
 
@@ -584,30 +591,31 @@ __global__ __launch_bounds__(256 * WM, WM == 1 ? 2 : 1) void gemm_kernel(const u
 
 // ---- tiny batches (B <= 16 per workgroup column): latency- and bandwidth-bound --------
 // 16 rows (two row-blocks) x 16 batch columns per workgroup, v_mfma_f32_16x16x32_f16.  The
-// four waves split K by col-block (wave w takes col-blocks w, w+4, ...) and share nothing
+// NW waves split K by col-block (wave w takes col-blocks w, w+NW, ...) and share nothing
 // until the end: each wave decodes its two groups into a private LDS tile Wt[16][256],
 // copies its X tile unchanged into a private Xt[256 k][16 columns] (the matrix-core operand is
 // formed by the transposing LDS read), and multiplies; there is
 // no workgroup barrier inside the K loop, so the waves of a CU run out of step and hide
 // each other's latencies.  Indices, codebooks and X of the wave's next col-block load
-// into registers while the current one is processed.  The four partial 16 x 16 tiles meet
+// into registers while the current one is processed.  The partial 16 x 16 tiles meet
 // in LDS at the end.  Many small workgroups (out/16 per 16 columns) keep every CU streaming.
 typedef float f4v_t __attribute__((ext_vector_type(4)));
 constexpr int kTinyXRows = 64;                 // rows of X a wave stages at a time
 constexpr int kTinyXPasses = kTinyXRows / 32;  // 32-row passes (1 KB each) per staging step
 
-template <int K>
-__global__ __launch_bounds__(256, 2) void gemm_tiny_kernel(const uint8_t* __restrict__ idx,
+// NW: waves per workgroup.  4; 8 where the workgroups do not outnumber the CUs (see launch_gemm).
+template <int K, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void gemm_tiny_kernel(const uint8_t* __restrict__ idx,
                                                            const uint32_t* __restrict__ cb,
                                                            const uint16_t* __restrict__ X, int B,
                                                            int ldx, void* __restrict__ Y, int ldy,
                                                            int y_f32, int n_rb, int n_cb, int rpc) {
-  __shared__ __attribute__((aligned(16))) uint16_t Wt_all[4][16 * WS];
+  __shared__ __attribute__((aligned(16))) uint16_t Wt_all[NW][16 * WS];
   // [k][16 columns], as in memory; a quarter of a col-block at a time, which keeps the workgroup
   // under a third of the LDS for every format but d = 4 (three workgroups per CU; fewer than 170
   // registers, so the registers allow three as well)
-  __shared__ __attribute__((aligned(16))) uint16_t Xt_all[4][kTinyXRows * 16];
-  __shared__ __attribute__((aligned(16))) uint32_t lut_all[4][2 * lut_dwords<K>()];
+  __shared__ __attribute__((aligned(16))) uint16_t Xt_all[NW][kTinyXRows * 16];
+  __shared__ __attribute__((aligned(16))) uint32_t lut_all[NW][2 * lut_dwords<K>()];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -618,6 +626,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tiny_kernel(const uint8_t* __rest
 
   const long long rb0 = 2ll * blockIdx.x;
   const long long rb1 = min(rb0 + 1, (long long)n_rb - 1);   // odd tail: decoded twice, stored once
+  const int grow0 = (int)rb0 / rpc, grow1 = (int)rb1 / rpc, n_grows = n_rb / rpc;   // rows of groups
   const int n0 = blockIdx.y * 16;
 
   // X of a col-block (256 rows x 16 columns) is copied to LDS unchanged in 8 passes of 32 rows:
@@ -647,8 +656,8 @@ __global__ __launch_bounds__(256, 2) void gemm_tiny_kernel(const uint8_t* __rest
 #define VQ_ISSUE(SLOT, C)                                                              \
   {                                                                                    \
     const int cc = min((C), n_cb - 1);                                                 \
-    load_group<K>(g[SLOT][0], idx, cb, rb0, cc, n_cb, lane, n_rb, rpc);                           \
-    load_group<K>(g[SLOT][1], idx, cb, rb1, cc, n_cb, lane, n_rb, rpc);                           \
+    load_group<K>(g[SLOT][0], idx, cb, rb0, cc, n_cb, lane, n_rb, grow0, n_grows);     \
+    load_group<K>(g[SLOT][1], idx, cb, rb1, cc, n_cb, lane, n_rb, grow1, n_grows);     \
     _Pragma("unroll") for (int j = 0; j < 8; ++j)                                      \
       xr[SLOT][j] = *reinterpret_cast<const u32x4_t*>(X + ((size_t)cc * 256 + 32 * j) * ldx + x_lane); \
   }
@@ -673,25 +682,27 @@ __global__ __launch_bounds__(256, 2) void gemm_tiny_kernel(const uint8_t* __rest
   }
 
   VQ_ISSUE(0, wave)
-  for (int c = wave; c < n_cb; c += 8) {
-    VQ_ISSUE(1, c + 4)
+  for (int c = wave; c < n_cb; c += 2 * NW) {
+    VQ_ISSUE(1, c + NW)
     VQ_PROCESS(0)
-    VQ_ISSUE(0, c + 8)
-    if (c + 4 < n_cb) VQ_PROCESS(1)
+    VQ_ISSUE(0, c + 2 * NW)
+    if (c + NW < n_cb) VQ_PROCESS(1)
   }
 #undef VQ_ISSUE
 #undef VQ_PROCESS
 
-  // four partial 16 x 16 tiles -> LDS -> sum -> Y   (lane l holds rows 4*(l/16)+i, column l%16)
+  // NW partial 16 x 16 tiles -> LDS -> sum -> Y   (lane l holds rows 4*(l/16)+i, column l%16)
   __syncthreads();
-  float* part = reinterpret_cast<float*>(Wt_all[0]);      // 4 x 256 floats
+  float* part = reinterpret_cast<float*>(Wt_all[0]);      // NW x 256 floats
   const f4v_t acc = acc0 + acc1;
 #pragma unroll
   for (int i = 0; i < 4; ++i) part[wave * 256 + (4 * (lane >> 4) + i) * 16 + (lane & 15)] = acc[i];
   __syncthreads();
-  {
+  if (tid < 256) {
     const int m = tid >> 4, nl = tid & 15;
-    const float sum = part[tid] + part[256 + tid] + part[512 + tid] + part[768 + tid];
+    float sum = part[tid];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) sum += part[w * 256 + tid];
     const long long row = rb0 * 8 + m;
     const int n = n0 + nl;
     if (row < (long long)n_rb * 8 && n < B) {
@@ -704,11 +715,15 @@ __global__ __launch_bounds__(256, 2) void gemm_tiny_kernel(const uint8_t* __rest
 
 template <int K>
 hipError_t launch_tiny(const vq_desc& d, const void* idx_dev, const void* cb_dev, const void* X,
-                       int B, int ldx, void* Y, int ldy, int y_f32, hipStream_t s) {
+                       int B, int ldx, void* Y, int ldy, int y_f32, hipStream_t s, bool eight_waves) {
   const int n_rb = d.out_features / kGroupRows, n_cb = d.in_features / kGroupCols;
   const dim3 grid((unsigned)((n_rb + 1) / 2), (unsigned)((B + 15) / 16));
-  hipLaunchKernelGGL((gemm_tiny_kernel<K>), grid, dim3(256), 0, s, (const uint8_t*)idx_dev,
-                     (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y, ldy, y_f32, n_rb, n_cb, d.group_rows / kGroupRows);
+  if (eight_waves)
+    hipLaunchKernelGGL((gemm_tiny_kernel<K, 8>), grid, dim3(512), 0, s, (const uint8_t*)idx_dev,
+                       (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y, ldy, y_f32, n_rb, n_cb, d.group_rows / kGroupRows);
+  else
+    hipLaunchKernelGGL((gemm_tiny_kernel<K, 4>), grid, dim3(256), 0, s, (const uint8_t*)idx_dev,
+                       (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y, ldy, y_f32, n_rb, n_cb, d.group_rows / kGroupRows);
   return hipGetLastError();
 }
 
@@ -761,6 +776,7 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(const uint8_t* __res
   const long long rb = (long long)mt * 4 + wave;
   const bool rb_ok = rb < n_rb;
   const long long rb_ld = rb_ok ? rb : 0;
+  const int grow = (int)rb_ld / rpc, n_grows = n_rb / rpc;   // row of groups
   const int m0 = wave * 8;
 
   // Few workgroups are resident per CU here, so memory latency is hidden by depth
@@ -776,7 +792,7 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(const uint8_t* __res
 #pragma unroll
   for (int j = 0; j < D; ++j) {
     const int cj = min(j, n_cb - 1);
-    load_group<K>(g[j], idx, cb, rb_ld, cj, n_cb, lane, n_rb, rpc);
+    load_group<K>(g[j], idx, cb, rb_ld, cj, n_cb, lane, n_rb, grow, n_grows);
     VQ_LOAD_X(j, cj)
   }
 
@@ -797,7 +813,7 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(const uint8_t* __res
           x_ok ? xp[j].r[pass] : u32x4_t{0u, 0u, 0u, 0u};                                       \
     if (REFILL) {                                                                               \
       const int cn = min((c) + D, n_cb - 1);                                                    \
-      load_group<K>(g[j], idx, cb, rb_ld, cn, n_cb, lane, n_rb, rpc);                           \
+      load_group<K>(g[j], idx, cb, rb_ld, cn, n_cb, lane, n_rb, grow, n_grows);                 \
       VQ_LOAD_X(j, cn)                                                                          \
     }                                                                                           \
   }
@@ -941,10 +957,14 @@ hipError_t launch_wide(const vq_desc& d, const void* idx_dev, const void* cb_dev
 
 hipError_t launch_gemm(const vq_desc& d, const void* idx_dev, const void* cb_dev, const void* X,
                        int B, int ldx, void* Y, int ldy, int y_f32, hipStream_t s) {
-  // B <= 16: 16 x 16 tiles, barrier-free (gemm_tiny_kernel).  It re-decodes W once per 16
-  // columns, which still pays at 32 columns when the matrix is too short to fill the CUs
-  // with the 32-row tiles of the other kernels (4096 x 4096 at B = 48 / 64: 15.0 / 22.5 us with
-  // it, 13.7 / 13.9 us with the 32 x 32 tiles).  Then 32 x 32 tiles (gemm_small_kernel,
+  // 16 x 16 tiles, barrier-free (gemm_tiny_kernel), for B <= 16 and as long as there are at most two workgroups
+  // per CU.  They re-decode W once per 16 columns, which pays while the 32-row tiles of the other kernels leave
+  // CUs idle; us with 6-bit indices, tiny against 32 x 32 tiles, at the workgroups of tiny: 512 x 4096,
+  // B = 128 (256) 8.9, 15.3; 2048 x 4096, B = 64 (512) 14.2, 15.6, B = 96 (768) 19.9, 15.7; 1024 x 11008, B = 64 (256)
+  // 16.9, 35.7, B = 128 (512) 29.3, 36.3; 4096 x 4096, B = 32 (512) 10.4, 15.3, B = 48 (768) 17.1, 15.5.  Up to one
+  // workgroup per CU they get 8 waves, which halves the col-blocks a wave walks one after the other:
+  // 4096 x 11008, B = 16 15.1 -> 12.4, 1024 x 11008, B = 64 18.4 -> 16.9; beyond that 4 (1024 x 11008, B = 96 (384)
+  // 27.5, with 8 waves 29.2), and also where a wave has a single col-block anyway.  Then 32 x 32 tiles (gemm_small_kernel,
   // bandwidth-bound) while they are few enough to run in about one wave of workgroups, then
   // gemm_kernel with 32 x 128 tiles while those fit the CUs once, and beyond that the cheapest
   // of four tilings by a small cost model: 64 x 128 and 64 x 256 (4 waves, two workgroups per
@@ -955,12 +975,13 @@ hipError_t launch_gemm(const vq_desc& d, const void* idx_dev, const void* cb_dev
   // scales with in_features and only the ratios matter here; the 4-wave tiles run two per CU, so
   // their per-tile slope scales with 256 / CUs.
   const int n_rb = d.out_features / kGroupRows;
-  const bool short_matrix = n_rb < 1024;
-  const bool tiny = B <= 16 || (B <= 32 && short_matrix);
+  const long long tiles_tiny = (long long)((n_rb + 1) / 2) * ((B + 15) / 16);
   const long long tiles_small = (long long)((n_rb + 3) / 4) * ((B + 31) / 32);
   const long long rows64 = (n_rb + 7) / 8, rows128 = (n_rb + 15) / 16;
   const long long cols128 = (B + 127) / 128, cols256 = (B + 255) / 256;
   const long long cus = device_cus();
+  const bool tiny = B <= 16 || tiles_tiny <= 2 * cus;
+  const bool eight_waves = tiles_tiny <= cus && d.in_features / kGroupCols > 4;
   const bool small = B <= 32 || tiles_small <= 3 * cus;
   const bool one_round_32x128 = rows64 * cols128 <= cus / 2;
   const double per_cu = 256.0 / (double)cus;
@@ -973,7 +994,7 @@ hipError_t launch_gemm(const vq_desc& d, const void* idx_dev, const void* cb_dev
     if (est[i] < est[best]) best = i;
 #define VQ_GEMM_DISPATCH(K)                                                                       \
   {                                                                                               \
-    if (tiny) return launch_tiny<K>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);             \
+    if (tiny) return launch_tiny<K>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s, eight_waves); \
     if (small) return launch_small<K>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);           \
     if (one_round_32x128)                                                                         \
       return launch_one<K, 1, 128>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);              \
