@@ -496,8 +496,8 @@ __global__ __launch_bounds__(256 * WM, WM == 1 ? 2 : 1) void gemm_kernel(const u
   long long rbs[RBW];
   bool rb_ok[RBW];
   // Rows of groups.  Divided once for the 32 x 128 tile, where a col-block is short (4096 x 4096, B = 256 26.0 ->
-  // 24.4 us with 6-bit indices); the larger tiles hide the scalar division behind other waves and lose by the
-  // earlier loads (11008 x 4096, B = 203: 48.2 us dividing per col-block, 48.9 once).
+  // 24.4 us with 6-bit indices); the larger tiles hide the scalar division and are no faster without it
+  // (11008 x 4096, B = 203, k = 256: 48.2 us dividing per col-block, 48.9 once).
   int grows[RBW];
   auto grow_of = [&](int a) { return RBW == 1 ? (long long)grows[a] : (rb_ok[a] ? rbs[a] : 0) / rpc; };
 #pragma unroll

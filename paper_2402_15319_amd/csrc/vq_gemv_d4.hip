@@ -13,38 +13,49 @@
 // the next table entry are loaded one step ahead.  A lane owns columns 4L .. 4L+3 of a
 // col-block and keeps 8 row accumulators, reduced over the wave at the end exactly as in the
 // other GEMV kernels.
+//
+// KS > 1 (launches of few 64-row items): KS workgroups share an item, each owns 8 / KS of its row-blocks, and
+// KS groups of 8 / KS waves split the col-block pairs between them, each with tables of its own; the partial
+// sums meet in LDS in a fixed order.  A 4096-row matrix is 64 items, a quarter of the CUs (rule and figures:
+// wide_splits below).
 #include "vq_gemv_impl.h"
 
 namespace vq {
 namespace {
 
+template <int KS>
 struct D4Step {
   uint4 w;        // the lane's 8 + 8 index bytes of the pair
   uint2 xa, xb;   // its activations in the two col-blocks
-  uint2 q;        // this thread's table entry of col-block (tid >> 8) of the pair: 4 int8 in .x, or 4 fp16
-  uint32_t sc;    // int8 tables: that table's fp16 scale
+  uint2 q[KS];      // this thread's table entries: 4 int8 in .x, or 4 fp16
+  uint32_t sc[KS];  // int8 tables: the fp16 scales of their tables
   uint2 cw;       // blockwise normalisation: the lane's block codes in the two col-blocks (row r in bits [4r, 4r+4))
-  uint32_t lv;    // ... and level (tid & 15) of this thread's table (fp16)
+  uint32_t lv[KS];  // ... and level (entry & 15) of their tables (fp16)
 };
 
 // MODE 1 (F16): the tables are fp16 (2 KB per group, copied to LDS as they are) instead of int8
 // with a scale.  MODE 2 (BN): int8 tables with blockwise normalisation (appendix "Blockwise data
 // normalization"): the group's 16 block-scale levels sit next to its table in LDS, and per row
 // the looked-up vector is multiplied by the scale of the lane's 32-weight block before the dot2.
-template <bool LORA, int MODE, int CAP>
+template <bool LORA, int MODE, int CAP, int KS>
 __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LORA, CAP>::type arg) {
   constexpr bool F16 = MODE == 1, BN = MODE == 2;
   const GemvBatchT<CAP>& batch = base_of(arg);
-  __shared__ __attribute__((aligned(16))) uint2 tabs[2][2][256];   // [buffer][col-block of the pair][entry]
-  __shared__ uint32_t levs[2][2][16];                               // BN: the tables' levels, the value in both halves
+  constexpr int RBW = 8 / KS, THREADS = 512 / KS;   // row-blocks of a workgroup; threads that share tables
+  __shared__ __attribute__((aligned(16))) uint2 tabs_all[KS][2][2][256];   // [buffer][col-block of the pair][entry]
+  __shared__ uint32_t levs_all[KS][2][2][16];                               // BN: the tables' levels, the value in both halves
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int pi = find_problem(batch, (int)blockIdx.x);
+  const int item = (int)blockIdx.x / KS;
+  const int pi = find_problem(batch, item);
   const GemvProblem& P = batch.p[pi];
-  const int oct = blockIdx.x - P.wg_begin;          // which 64 rows
+  const int oct = item - P.wg_begin;                // which 64 rows
+  const int split = KS == 1 ? 0 : wave / RBW;       // which pairs of col-blocks
+  auto& tabs = tabs_all[split];
+  auto& levs = levs_all[split];
   const int n_cb = P.n_cb, n_pairs = (n_cb + 1) >> 1;
-  const int rb = oct * 8 + wave;                    // n_rb is a multiple of 8 (groups are >= 64 rows)
+  const int rb = oct * 8 + (KS == 1 ? wave : ((int)blockIdx.x - item * KS) * RBW + wave % RBW);   // n_rb is a multiple of 8 (groups are >= 64 rows)
   const long long grow = (long long)(oct * 8) / P.rb_per_cb;
   const uint8_t* tab = reinterpret_cast<const uint8_t*>(P.cb);
   const long long n_groups = (long long)(P.n_rb / P.rb_per_cb) * n_cb;
@@ -54,28 +65,31 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
   (void)levels; (void)codes_lane;
   const uint8_t* idx_lane = P.idx + (size_t)rb * n_pairs * 1024 + lane * 16;
   const uint16_t* x_lane = P.x + lane * 4;
-  const int h = tid >> 8, e = tid & 255;            // table duty of this thread
+  const int st = tid % THREADS;                     // table duty of this thread: entries st, st + THREADS, .. of the two
+  const int p_begin = n_pairs * split / KS, p_end = n_pairs * (split + 1) / KS;
+  const int steps = (n_pairs + KS - 1) / KS;        // of the longest split: all take as many barriers
 
-  auto load = [&](int p, D4Step& s) {
+  auto load = [&](int p, D4Step<KS>& s) {
     const int c0 = 2 * p, c1 = 2 * p + 1;
     const bool ok1 = c1 < n_cb;
-    const int cme = (h == 0 || ok1) ? c0 + h : c0;  // an absent second col-block re-reads the first (not used)
-    const long long g = grow * n_cb + cme;
     s.w = *reinterpret_cast<const uint4*>(idx_lane + (size_t)p * 1024);
     s.xa = *reinterpret_cast<const uint2*>(x_lane + (size_t)c0 * 256);
     const uint2 xb = *reinterpret_cast<const uint2*>(x_lane + (size_t)(ok1 ? c1 : c0) * 256);
     s.xb = ok1 ? xb : make_uint2(0u, 0u);
-    if constexpr (F16) {
-      s.q = *reinterpret_cast<const uint2*>(tab + g * 2048 + e * 8);
-      s.sc = 0;
-    } else {
-      s.q = make_uint2(*reinterpret_cast<const uint32_t*>(tab + g * 1024 + e * 4), 0u);
-      s.sc = scales[g];
+#pragma unroll
+    for (int i = 0; i < KS; ++i) {
+      const int h = (st + i * THREADS) >> 8, e = (st + i * THREADS) & 255;
+      const long long g = grow * n_cb + ((h == 0 || ok1) ? c0 + h : c0);  // an absent second col-block re-reads the first (not used)
+      if constexpr (F16) {
+        s.q[i] = *reinterpret_cast<const uint2*>(tab + g * 2048 + e * 8);
+        s.sc[i] = 0;
+      } else {
+        s.q[i] = make_uint2(*reinterpret_cast<const uint32_t*>(tab + g * 1024 + e * 4), 0u);
+        s.sc[i] = scales[g];
+      }
+      if constexpr (BN) s.lv[i] = levels[g * 16 + (e & 15)];
     }
-    if constexpr (BN) {
-      s.cw = *reinterpret_cast<const uint2*>(codes_lane + (size_t)p * 64);
-      s.lv = levels[g * 16 + (e & 15)];
-    }
+    if constexpr (BN) s.cw = *reinterpret_cast<const uint2*>(codes_lane + (size_t)p * 64);
   };
 
   float acc[8];
@@ -89,18 +103,25 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
     lb = lora_load_b(arg.l[pi], P.x, rb, lane);
   }
 
-  D4Step cur, nxt;
-  load(0, cur);
-  for (int p = 0; p < n_pairs; ++p) {
-    load(p + 1 < n_pairs ? p + 1 : p, nxt);         // one step ahead (a harmless re-read at the end)
-    const int buf = p & 1;
-    const bool mine = h == 0 || 2 * p + 1 < n_cb;   // the absent col-block of an odd matrix gets a zero table
-    tabs[buf][h][e] = !mine ? make_uint2(0u, 0u)
-                      : F16 ? cur.q : d4_dequant_entry(cur.q.x, __builtin_bit_cast(_Float16, (uint16_t)cur.sc));
-    if constexpr (BN) {
-      if (e < 16) levs[buf][h][e] = mine ? cur.lv * 0x10001u : 0u;
+  D4Step<KS> cur, nxt;
+  const int p_last = p_end > p_begin ? p_end - 1 : 0;
+  load(min(p_begin, p_last), cur);
+  for (int step = 0; step < steps; ++step) {
+    const int p = p_begin + step;
+    load(min(p + 1, p_last), nxt);                  // one step ahead (a harmless re-read at the end)
+    const int buf = step & 1;
+#pragma unroll
+    for (int i = 0; i < KS; ++i) {
+      const int h = (st + i * THREADS) >> 8, e = (st + i * THREADS) & 255;
+      const bool mine = h == 0 || 2 * p + 1 < n_cb; // the absent col-block of an odd matrix gets a zero table
+      tabs[buf][h][e] = !mine ? make_uint2(0u, 0u)
+                        : F16 ? cur.q[i] : d4_dequant_entry(cur.q[i].x, __builtin_bit_cast(_Float16, (uint16_t)cur.sc[i]));
+      if constexpr (BN) {
+        if (e < 16) levs[buf][h][e] = mine ? cur.lv[i] * 0x10001u : 0u;
+      }
     }
     __syncthreads();   // tables of this step complete; the other buffer is free again (see header)
+    if (KS > 1 && p >= p_end) break;                // the longest splits' last step
     const uint2* T0 = tabs[buf][0];
     const uint2* T1 = tabs[buf][1];
 #pragma unroll
@@ -122,6 +143,15 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
   }
 
   float v = wave_reduce8(acc, lane);   // every lane: the total of row (lane >> 3) & 7
+  if constexpr (KS > 1) {              // the splits' sums in order, by the waves of split 0
+    __shared__ float part[8][8];
+    if ((lane & 7) == 0) part[wave][lane >> 3] = v;
+    __syncthreads();
+    if (split > 0) return;
+    v = 0.f;
+#pragma unroll
+    for (int q = 0; q < KS; ++q) v += part[q * RBW + wave][lane >> 3];
+  }
   if constexpr (LORA) v += lora_term(lb, tv);
   if ((lane & 7) == 0) {
     const size_t o = (size_t)rb * 8 + (lane >> 3);
@@ -138,29 +168,35 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
 // every wave runs the k = 256 inner block (16 lookups and 16 dot2 per col-block and lane) on
 // its own 8 rows.  Indices are laid out as for k = 256 with fp16 codebooks (1 KB per 8-row
 // block and col-block); the tables keep the canonical order (512 bytes per group, then scales).
+template <int KS>
 struct K256Step {
   uint4 w0, w1;   // the lane's 16 index bytes in the two col-blocks of the pair
   uint2 xa, xb;   // its activations there
-  uint32_t q;     // this thread's table entry (2 int8) of col-block (tid >> 8) of the pair
-  uint32_t sc;    // that table's fp16 scale
+  uint32_t q[KS];   // this thread's table entries (2 int8)
+  uint32_t sc[KS];  // the fp16 scales of their tables
   uint2 cw;       // blockwise normalisation: the lane's block codes in the two col-blocks
-  uint32_t lv;    // ... and level (tid & 15) of this thread's table (fp16)
+  uint32_t lv[KS];  // ... and level (entry & 15) of their tables (fp16)
 };
 
 // BN: with blockwise normalisation; the plain C++ inner block replaces the hand-scheduled one.
-template <bool LORA, bool BN, int CAP>
+template <bool LORA, bool BN, int CAP, int KS>
 __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf<LORA, CAP>::type arg) {
   const GemvBatchT<CAP>& batch = base_of(arg);
-  __shared__ __attribute__((aligned(16))) uint32_t tabs[2][2][256];   // [buffer][col-block of the pair][entry]
-  __shared__ uint32_t levs[2][2][16];                                  // BN: the tables' levels, the value in both halves
+  constexpr int RBW = 8 / KS, THREADS = 512 / KS;   // row-blocks of a workgroup; threads that share tables
+  __shared__ __attribute__((aligned(16))) uint32_t tabs_all[KS][2][2][256];   // [buffer][col-block of the pair][entry]
+  __shared__ uint32_t levs_all[KS][2][2][16];                                  // BN: the tables' levels, the value in both halves
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int pi = find_problem(batch, (int)blockIdx.x);
+  const int item = (int)blockIdx.x / KS;
+  const int pi = find_problem(batch, item);
   const GemvProblem& P = batch.p[pi];
-  const int oct = blockIdx.x - P.wg_begin;          // which 64 rows
+  const int oct = item - P.wg_begin;                // which 64 rows
+  const int split = KS == 1 ? 0 : wave / RBW;       // which pairs of col-blocks
+  auto& tabs = tabs_all[split];
+  auto& levs = levs_all[split];
   const int n_cb = P.n_cb, n_pairs = (n_cb + 1) >> 1;
-  const int rb = oct * 8 + wave;
+  const int rb = oct * 8 + (KS == 1 ? wave : ((int)blockIdx.x - item * KS) * RBW + wave % RBW);   // n_rb is a multiple of 8 (groups are >= 64 rows)
   const long long grow = (long long)(oct * 8) / P.rb_per_cb;
   const uint8_t* tab = reinterpret_cast<const uint8_t*>(P.cb);
   const long long n_groups = (long long)(P.n_rb / P.rb_per_cb) * n_cb;
@@ -170,24 +206,28 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
   (void)levels; (void)codes_lane;
   const uint8_t* idx_lane = P.idx + (size_t)rb * n_cb * 1024 + lane * 16;
   const uint16_t* x_lane = P.x + lane * 4;
-  const int h = tid >> 8, e = tid & 255;            // table duty of this thread
+  const int st = tid % THREADS;                     // table duty of this thread: entries st, st + THREADS, .. of the two
+  const int p_begin = n_pairs * split / KS, p_end = n_pairs * (split + 1) / KS;
+  const int steps = (n_pairs + KS - 1) / KS;        // of the longest split: all take as many barriers
 
-  auto load = [&](int p, K256Step& s) {
+  auto load = [&](int p, K256Step<KS>& s) {
     const int c0 = 2 * p, c1 = 2 * p + 1;
     const bool ok1 = c1 < n_cb;
     const int c1_ld = ok1 ? c1 : c0;                // an absent second col-block re-reads the first (not used)
-    const long long g = grow * n_cb + (h == 0 ? c0 : c1_ld);
     s.w0 = *reinterpret_cast<const uint4*>(idx_lane + (size_t)c0 * 1024);
     s.w1 = *reinterpret_cast<const uint4*>(idx_lane + (size_t)c1_ld * 1024);
     s.xa = *reinterpret_cast<const uint2*>(x_lane + (size_t)c0 * 256);
     const uint2 xb = *reinterpret_cast<const uint2*>(x_lane + (size_t)c1_ld * 256);
     s.xb = ok1 ? xb : make_uint2(0u, 0u);
-    s.q = *reinterpret_cast<const uint16_t*>(tab + g * 512 + e * 2);
-    s.sc = scales[g];
-    if constexpr (BN) {
-      s.cw = *reinterpret_cast<const uint2*>(codes_lane + (size_t)p * 64);
-      s.lv = levels[g * 16 + (e & 15)];
+#pragma unroll
+    for (int i = 0; i < KS; ++i) {
+      const int h = (st + i * THREADS) >> 8, e = (st + i * THREADS) & 255;
+      const long long g = grow * n_cb + (h == 0 ? c0 : c1_ld);
+      s.q[i] = *reinterpret_cast<const uint16_t*>(tab + g * 512 + e * 2);
+      s.sc[i] = scales[g];
+      if constexpr (BN) s.lv[i] = levels[g * 16 + (e & 15)];
     }
+    if constexpr (BN) s.cw = *reinterpret_cast<const uint2*>(codes_lane + (size_t)p * 64);
   };
 
   float acc[8];
@@ -201,17 +241,24 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
     lb = lora_load_b(arg.l[pi], P.x, rb, lane);
   }
 
-  K256Step cur, nxt;
-  load(0, cur);
-  for (int p = 0; p < n_pairs; ++p) {
-    load(p + 1 < n_pairs ? p + 1 : p, nxt);         // one step ahead (a harmless re-read at the end)
-    const int buf = p & 1;
-    const bool mine = h == 0 || 2 * p + 1 < n_cb;   // the absent col-block of an odd matrix gets a zero table
-    tabs[buf][h][e] = mine ? k64_dequant_pair(cur.q, __builtin_bit_cast(_Float16, (uint16_t)cur.sc)) : 0u;
-    if constexpr (BN) {
-      if (e < 16) levs[buf][h][e] = mine ? cur.lv * 0x10001u : 0u;
+  K256Step<KS> cur, nxt;
+  const int p_last = p_end > p_begin ? p_end - 1 : 0;
+  load(min(p_begin, p_last), cur);
+  for (int step = 0; step < steps; ++step) {
+    const int p = p_begin + step;
+    load(min(p + 1, p_last), nxt);                  // one step ahead (a harmless re-read at the end)
+    const int buf = step & 1;
+#pragma unroll
+    for (int i = 0; i < KS; ++i) {
+      const int h = (st + i * THREADS) >> 8, e = (st + i * THREADS) & 255;
+      const bool mine = h == 0 || 2 * p + 1 < n_cb; // the absent col-block of an odd matrix gets a zero table
+      tabs[buf][h][e] = mine ? k64_dequant_pair(cur.q[i], __builtin_bit_cast(_Float16, (uint16_t)cur.sc[i])) : 0u;
+      if constexpr (BN) {
+        if (e < 16) levs[buf][h][e] = mine ? cur.lv[i] * 0x10001u : 0u;
+      }
     }
     __syncthreads();   // tables of this step complete; the other buffer is free again
+    if (KS > 1 && p >= p_end) break;                // the longest splits' last step
     if constexpr (BN) {
       k256_group_scaled(cur.w0.x, cur.w0.y, cur.w0.z, cur.w0.w, cur.cw.x, tabs[buf][0], levs[buf][0], cur.xa.x, cur.xa.y, acc);
       k256_group_scaled(cur.w1.x, cur.w1.y, cur.w1.z, cur.w1.w, cur.cw.y, tabs[buf][1], levs[buf][1], cur.xb.x, cur.xb.y, acc);
@@ -225,6 +272,15 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
   }
 
   float v = wave_reduce8(acc, lane);   // every lane: the total of row (lane >> 3) & 7
+  if constexpr (KS > 1) {              // the splits' sums in order, by the waves of split 0
+    __shared__ float part[8][8];
+    if ((lane & 7) == 0) part[wave][lane >> 3] = v;
+    __syncthreads();
+    if (split > 0) return;
+    v = 0.f;
+#pragma unroll
+    for (int q = 0; q < KS; ++q) v += part[q * RBW + wave][lane >> 3];
+  }
   if constexpr (LORA) v += lora_term(lb, tv);
   if ((lane & 7) == 0) {
     const size_t o = (size_t)rb * 8 + (lane >> 3);
@@ -235,14 +291,31 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
 
 }  // namespace
 
+// Workgroups per 64-row item.
+static int wide_splits(const GemvBatch& b) {
+  // us per launch at 1, 2, 4, 8 splits on 256 CUs (int8 tables): d = 4, 64 items of 8 pairs 9.4, 6.7, 5.2, 5.4, of
+  // 22 pairs 20.9, 13.1, 9.4, 8.9; 192 items of 8 pairs 10.0, 8.8, 8.1, 10.8; 344 items 11.9, 11.1, 11.7, 16.9.
+  // d = 2, k = 256: 64 items 12.3, 8.4, 6.4, 6.6 and 28.9, 16.8, 11.7, 11.2; 192 13.9, 11.9, 10.9, 11.5; 344 19.6,
+  // 17.3, 16.8, 18.8.  A layer in order: d = 4 61 -> 36, k = 256 82 -> 48.  No more splits than pairs.
+  int pairs = 1;
+  for (int i = 0; i < b.count; ++i) pairs = max(pairs, (b.p[i].n_cb + 1) / 2);
+  if (b.count > kFewProblems || b.total_wgs > 512) return 1;
+  const int most = pairs >= 4 ? 4 : pairs >= 2 ? 2 : 1;
+  if (b.total_wgs <= 64 && pairs >= 16) return 8;
+  return b.total_wgs <= 192 ? most : min(most, 2);
+}
+
 // (kernel, template arguments before CAP)
 #define VQ_LAUNCH_WIDE(KERNEL, ...)                                                                              \
   do {                                                                                                           \
-    const dim3 grid((unsigned)total_wgs);                                                                        \
-    if (base_of_host(batch).count <= kFewProblems)                                                               \
-      hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFewProblems>), grid, dim3(512), 0, s, few_problems(batch));       \
-    else                                                                                                         \
-      hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kMaxProblemsPerLaunch>), grid, dim3(512), 0, s, batch);            \
+    const int ks = wide_splits(base_of_host(batch));                                                             \
+    const dim3 grid((unsigned)(total_wgs * ks));                                                                 \
+    if (base_of_host(batch).count > kFewProblems)                                                                \
+      hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kMaxProblemsPerLaunch, 1>), grid, dim3(512), 0, s, batch);         \
+    else if (ks == 8) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFewProblems, 8>), grid, dim3(512), 0, s, few_problems(batch)); \
+    else if (ks == 4) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFewProblems, 4>), grid, dim3(512), 0, s, few_problems(batch)); \
+    else if (ks == 2) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFewProblems, 2>), grid, dim3(512), 0, s, few_problems(batch)); \
+    else hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFewProblems, 1>), grid, dim3(512), 0, s, few_problems(batch)); \
   } while (0)
 
 hipError_t launch_gemv_k256i8(const GemvBatch& batch, int total_wgs, hipStream_t s, int fmt) {
