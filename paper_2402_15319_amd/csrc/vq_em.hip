@@ -556,7 +556,14 @@ struct EmBins {
   static constexpr int kEntries = NG * K;
   static constexpr int kCopies = kEntries >= 64 ? 1 : 64 / kEntries;
   static constexpr int kStride = kEntries * kCopies;        // doubles per quantity
-  static constexpr int kTable = 2 * D * kStride;            // doubles per wave
+  // Counted: in tall groups with d = 4, k = 256 the weights' sums come from counts, 16 bits per centroid and vector
+  // position of a row for the whole workgroup (at most 256 rows): one 32-bit atomic (8 clocks) in place of four
+  // binary64 ones (22 to 31 each), and den[t] = sum over the positions of count * h, exact products, at the end.
+  // M-step at 11008 x 4096, 256-row groups: 86.6 -> 65 us.  With d = 2 the counts are as large as the tables, which
+  // leaves one workgroup on a CU where two fit: 29.9 -> 31.5 us at 4096 x 4096, not done.
+  static constexpr bool kCounted = WPG == 8 && K == 256 && D == 4;
+  static constexpr int kWords = 32;                         // dwords of counts per centroid: positions i and i + 32
+  static constexpr int kTable = (kCounted ? 1 : 2) * D * kStride;   // doubles per wave
 };
 
 template <int K, int D, int NG, int WPG>
@@ -571,6 +578,9 @@ __global__ __launch_bounds__(WPG > 4 ? 64 * WPG : 256) void em_update_kernel(con
   constexpr int WAVES = WPG > 4 ? WPG : 4;
   constexpr int RPG = 8 / NG;                       // rows of an 8-row block that share a codebook
   __shared__ __attribute__((aligned(16))) double tab_all[WAVES * Bins::kTable];
+  constexpr int CW = Bins::kWords + 1;              // a gap spreads the centroids over the banks (108 KB in all)
+  __shared__ uint32_t counts[Bins::kCounted ? K * CW : 1];
+  __shared__ double h_all[Bins::kCounted ? 256 : 1], den_all[Bins::kCounted ? K * D : 1];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int sub = wave % WPG;                       // this wave's place among those that share its group
@@ -589,7 +599,13 @@ __global__ __launch_bounds__(WPG > 4 ? 64 * WPG : 256) void em_update_kernel(con
   const float* Wl = W + (size_t)row0 * in_features + (size_t)c * 256 + lane * 4;
   const uint8_t* al = assign + (size_t)row0 * (in_features / D) + (size_t)c * (256 / D) + lane * V;
   const int copy = Bins::kCopies > 1 ? lane % Bins::kCopies : 0;
-  wave_lds_sync();
+  if constexpr (Bins::kCounted) {
+    for (int i = threadIdx.x; i < K * CW; i += 64 * WPG) counts[i] = 0u;
+    if (threadIdx.x < 256) h_all[threadIdx.x] = hdiag[(size_t)c * 256 + threadIdx.x];
+    __syncthreads();
+  } else {
+    wave_lds_sync();
+  }
 
   auto load = [&](int r0, float4 (&x)[8], uint32_t (&a)[8]) {
 #pragma unroll
@@ -613,8 +629,11 @@ __global__ __launch_bounds__(WPG > 4 ? 64 * WPG : 256) void em_update_kernel(con
 #pragma unroll
           for (int t = 0; t < D; ++t) {
             __builtin_amdgcn_ds_atomic_fadd_f64((lds_f64_ptr)(e + t * Bins::kStride), h[v * D + t] * (double)xr[v * D + t]);
-            __builtin_amdgcn_ds_atomic_fadd_f64((lds_f64_ptr)(e + (D + t) * Bins::kStride), h[v * D + t]);
+            if constexpr (!Bins::kCounted)
+              __builtin_amdgcn_ds_atomic_fadd_f64((lds_f64_ptr)(e + (D + t) * Bins::kStride), h[v * D + t]);
           }
+          if constexpr (Bins::kCounted)
+            atomicAdd(counts + m * CW + (lane & 31), 1u << (16 * (lane >> 5)));
         }
       }
     }
@@ -639,6 +658,31 @@ __global__ __launch_bounds__(WPG > 4 ? 64 * WPG : 256) void em_update_kernel(con
   }
   if constexpr (WPG > 1) __syncthreads();
   else wave_lds_sync();
+  if constexpr (Bins::kCounted) {                   // one item per workgroup: all waves are here
+    const int m = threadIdx.x >> 1, half = threadIdx.x & 1;   // two lanes per centroid
+    const uint32_t* n = counts + m * CW + half * (Bins::kWords / 2);
+    const double* hp = h_all + half * 4 * (Bins::kWords / 2);
+    double den[D] = {};
+#pragma unroll 4
+    for (int i = 0; i < Bins::kWords / 2; ++i) {
+      const double lo = n[i] & 0xffffu, hi = n[i] >> 16;
+#pragma unroll
+      for (int t = 0; t < D; ++t) den[t] += lo * hp[4 * i + t] + hi * hp[4 * i + 128 + t];
+    }
+#pragma unroll
+    for (int t = 0; t < D; ++t) {
+      if (den[t] != den[t]) {                       // 0 * infinity or NaN: such a weight counts only where it is used
+        den[t] = 0.;
+        for (int i = 0; i < Bins::kWords / 2; ++i) {
+          if (n[i] & 0xffffu) den[t] += (double)(n[i] & 0xffffu) * hp[4 * i + t];
+          if (n[i] >> 16) den[t] += (double)(n[i] >> 16) * hp[4 * i + 128 + t];
+        }
+      }
+      den[t] += __shfl_xor(den[t], 1, 64);
+      if (half == 0) den_all[m * D + t] = den[t];
+    }
+    __syncthreads();
+  }
   if (!present) return;                             // no barrier below
 
   const double* group_tab = tab_all + (size_t)(wave - sub) * Bins::kTable;
@@ -651,8 +695,9 @@ __global__ __launch_bounds__(WPG > 4 ? 64 * WPG : 256) void em_update_kernel(con
       for (int q = 0; q < Bins::kCopies; ++q) {
         const double* p = group_tab + w * Bins::kTable + e * Bins::kCopies + q;
         num += p[t * Bins::kStride];
-        den += p[(D + t) * Bins::kStride];
+        if constexpr (!Bins::kCounted) den += p[(D + t) * Bins::kStride];
       }
+    if constexpr (Bins::kCounted) den = den_all[i];
     const long long g = NG > 1 ? (ir * NG + e / K) * n_cb + c : item;
     cb_out[(g * K + e % K) * D + t] = den != 0. ? (float)num / (float)den : 0.f;
   }
@@ -849,7 +894,7 @@ static void launch_update(const vq_desc& d, const void* W, const void* hdiag, co
 }
 
 // Waves per group: one up to 16 rows (32 with a small table), 4 from 32 and 8 from 128 rows on.  A wave's table
-// is 16 * k * d bytes, at most 16 KB (the 8 waves of a group with d = 4, k = 256 fill 128 KB of the CU's 160 KB).
+// is 16 * k * d bytes, at most 16 KB, and half of it beside counts (d = 4, k = 256, from 128 rows on: 108 KB in all of the CU's 160 KB).
 template <int K, int D>
 static void launch_update_rows(const vq_desc& d, const void* W, const void* hdiag, const void* assign, void* cb_out,
                                hipStream_t s) {

@@ -303,6 +303,36 @@ def test_m_step_against_64_bit_sums_and_repeated(env, shape):
             assert np.all(np.abs(runs[0][g, :, t] - want) <= bound)
 
 
+@pytest.mark.parametrize("rows", [128, 256])
+def test_m_step_by_counts_at_full_positions_and_infinite_weights(env, rows):
+    """Tall groups with d = 4, k = 256: every row's vector of a position in one centroid (counts up to the
+    number of rows, both halves of a counter), and weights that are infinite or NaN count for the
+    centroids that use them alone.  Powers of two and small integers: every sum is exact, so is the quotient
+    of equal weights."""
+    torch, vq, vqdev = env
+    out_f, in_f, k, d = rows, 512, 256, 4
+    W = np.broadcast_to(np.arange(in_f, dtype=np.float32) - 200, (out_f, in_f)).copy()
+    h = np.ones(in_f, np.float32)
+    h[4:8], h[132:136], h[300] = np.inf, np.nan, np.inf
+    assign = np.broadcast_to(np.arange(in_f // d, dtype=np.uint8) % 64, (out_f, in_f // d)).copy()
+    assign[:, 20] = 19                             # lower half: two positions in one centroid
+    assign[:, 50] = 19                             # and one of the upper half
+    desc = vq.make_desc(out_f, in_f, k, 8, group_rows=rows, d=d)
+    new = torch.full((2, k, d), 777.0, dtype=torch.float32, device="cuda:0")
+    vq.vq_em_update(desc, vqdev.to_device_bytes(W), vqdev.to_device_bytes(h), vqdev.to_device_bytes(assign), new)
+    got = new.cpu().numpy()
+    hw = np.broadcast_to(h, W.shape).astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        for c in range(2):
+            for m in range(k):
+                used = assign[:, 64 * c:64 * (c + 1)] == m
+                for t in range(d):
+                    x, hv = (z[:, 256 * c + t:256 * (c + 1):4][used].astype(np.float64) for z in (W, hw))
+                    num, den = (hv * x).sum(), hv.sum()
+                    want = np.float32(num) / np.float32(den) if den != 0 else np.float32(0)
+                    np.testing.assert_equal(got[c, m, t], want)
+
+
 # the codebooks that the matrix cores filter: one tile and several, one group and several per strip of rows
 FILTERED = [(2, 256, 8, 24, 512), (2, 256, 128, 128, 256), (4, 64, 16, 48, 512), (4, 256, 8, 8, 768), (4, 256, 64, 64, 512)]
 
