@@ -65,7 +65,8 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
   (void)levels; (void)codes_lane;
   const uint8_t* idx_lane = P.idx + (size_t)rb * n_pairs * 1024 + lane * 16;
   const uint16_t* x_lane = P.x + lane * 4;
-  const int st = tid % THREADS;                     // table duty of this thread: entries st, st + THREADS, .. of the two
+  const int st = KS == 1 ? tid : tid % THREADS;                     // table duty of this thread: entries st, st + THREADS, .. of the two
+  const int h1 = tid >> 8, e1 = tid & 255;          // KS = 1: its one entry
   const int p_begin = n_pairs * split / KS, p_end = n_pairs * (split + 1) / KS;
   const int steps = (n_pairs + KS - 1) / KS;        // of the longest split: all take as many barriers
 
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
     s.xb = ok1 ? xb : make_uint2(0u, 0u);
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
-      const int h = (st + i * THREADS) >> 8, e = (st + i * THREADS) & 255;
+      const int h = KS == 1 ? h1 : (st + i * THREADS) >> 8, e = KS == 1 ? e1 : (st + i * THREADS) & 255;
       const long long g = grow * n_cb + ((h == 0 || ok1) ? c0 + h : c0);  // an absent second col-block re-reads the first (not used)
       if constexpr (F16) {
         s.q[i] = *reinterpret_cast<const uint2*>(tab + g * 2048 + e * 8);
@@ -105,14 +106,14 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
 
   D4Step<KS> cur, nxt;
   const int p_last = p_end > p_begin ? p_end - 1 : 0;
-  load(min(p_begin, p_last), cur);
+  load(KS == 1 ? 0 : min(p_begin, p_last), cur);
   for (int step = 0; step < steps; ++step) {
     const int p = p_begin + step;
-    load(min(p + 1, p_last), nxt);                  // one step ahead (a harmless re-read at the end)
+    load(KS == 1 ? (p + 1 < n_pairs ? p + 1 : p) : min(p + 1, p_last), nxt);                  // one step ahead (a harmless re-read at the end)
     const int buf = step & 1;
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
-      const int h = (st + i * THREADS) >> 8, e = (st + i * THREADS) & 255;
+      const int h = KS == 1 ? h1 : (st + i * THREADS) >> 8, e = KS == 1 ? e1 : (st + i * THREADS) & 255;
       const bool mine = h == 0 || 2 * p + 1 < n_cb; // the absent col-block of an odd matrix gets a zero table
       tabs[buf][h][e] = !mine ? make_uint2(0u, 0u)
                         : F16 ? cur.q[i] : d4_dequant_entry(cur.q[i].x, __builtin_bit_cast(_Float16, (uint16_t)cur.sc[i]));
