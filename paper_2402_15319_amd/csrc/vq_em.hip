@@ -799,7 +799,7 @@ __global__ __launch_bounds__(64) void em_update_small_kernel(const float* __rest
 
 }  // namespace
 
-// Calls F(K) for the codebook size k (4, 8, 16, 64 or 256).
+// Calls F(K) for the codebook size k (4, 8, 16, 32, 64 or 256).
 #define VQ_EM_K_SWITCH(k, F) \
   switch (k) {               \
     case 4: F(4); break;     \
@@ -838,15 +838,15 @@ hipError_t launch_em_assign(const vq_desc& d, const void* W, const void* hdiag, 
                      d.group_rows)
   if (d.group_rows == 1) {   // a codebook per row: k * d <= 64 (checked by the caller)
     if (d.d == 1) {
-#define VQ_F(K) if constexpr (K <= 64) VQ_EM_ANY(K, 1, 8)
+#define VQ_F(K) if constexpr (K <= 64) VQ_EM_ANY(K, 1, 8); else return hipErrorInvalidValue
       VQ_EM_K_SWITCH(k, VQ_F)
 #undef VQ_F
     } else if (d.d == 2) {
-#define VQ_F(K) if constexpr (K <= 16) VQ_EM_ANY(K, 2, 8)
+#define VQ_F(K) if constexpr (K <= 32) VQ_EM_ANY(K, 2, 8); else return hipErrorInvalidValue
       VQ_EM_K_SWITCH(k, VQ_F)
 #undef VQ_F
     } else {
-#define VQ_F(K) if constexpr (K <= 16) VQ_EM_ANY(K, 4, 8)
+#define VQ_F(K) if constexpr (K <= 16) VQ_EM_ANY(K, 4, 8); else return hipErrorInvalidValue
       VQ_EM_K_SWITCH(k, VQ_F)
 #undef VQ_F
     }
@@ -896,12 +896,14 @@ static void launch_update(const vq_desc& d, const void* W, const void* hdiag, co
 // Waves per group: one up to 16 rows (32 with a small table), 4 from 32 and 8 from 128 rows on.  A wave's table
 // is 16 * k * d bytes, at most 16 KB, and half of it beside counts (d = 4, k = 256, from 128 rows on: 108 KB in all of the CU's 160 KB).
 template <int K, int D>
-static void launch_update_rows(const vq_desc& d, const void* W, const void* hdiag, const void* assign, void* cb_out,
+static hipError_t launch_update_rows(const vq_desc& d, const void* W, const void* hdiag, const void* assign, void* cb_out,
                                hipStream_t s) {
   if (d.group_rows == 1) {
     if constexpr (K * D <= 64) launch_update<K, D, 8, 1>(d, W, hdiag, assign, cb_out, s);
+    else return hipErrorInvalidValue;
   } else if (d.group_rows == 4) {
     if constexpr (D <= 2) launch_update<K, D, 2, 1>(d, W, hdiag, assign, cb_out, s);
+    else return hipErrorInvalidValue;
   } else if (d.group_rows < 32 || (d.group_rows == 32 && K * D <= 32)) {
     launch_update<K, D, 1, 1>(d, W, hdiag, assign, cb_out, s);
   } else if (d.group_rows < 128) {
@@ -909,13 +911,14 @@ static void launch_update_rows(const vq_desc& d, const void* W, const void* hdia
   } else {
     launch_update<K, D, 1, 8>(d, W, hdiag, assign, cb_out, s);
   }
+  return hipGetLastError();
 }
 
 hipError_t launch_em_update(const vq_desc& d, const void* W, const void* hdiag, const void* assign,
                             void* cb_out, hipStream_t s) {
-#define VQ_F1(K) launch_update_rows<K, 1>(d, W, hdiag, assign, cb_out, s)
-#define VQ_F2(K) launch_update_rows<K, 2>(d, W, hdiag, assign, cb_out, s)
-#define VQ_F4(K) launch_update_rows<K, 4>(d, W, hdiag, assign, cb_out, s)
+#define VQ_F1(K) return launch_update_rows<K, 1>(d, W, hdiag, assign, cb_out, s)
+#define VQ_F2(K) return launch_update_rows<K, 2>(d, W, hdiag, assign, cb_out, s)
+#define VQ_F4(K) return launch_update_rows<K, 4>(d, W, hdiag, assign, cb_out, s)
   if (d.d == 1) {
     VQ_EM_K_SWITCH(d.k, VQ_F1)
   } else if (d.d == 2) {
@@ -926,7 +929,7 @@ hipError_t launch_em_update(const vq_desc& d, const void* W, const void* hdiag, 
 #undef VQ_F1
 #undef VQ_F2
 #undef VQ_F4
-  return hipGetLastError();
+  return hipErrorInvalidValue;   // not reached: the switch covers every k
 }
 
 }  // namespace vq

@@ -190,6 +190,7 @@ ANY_SHAPES = [
     (8, 256, 16, 2, 4), (40, 768, 16, 2, 4), (24, 512, 16, 1, 4),   # groups of 4 rows: two codebooks per 8-row block
     (8, 256, 32, 2, 8), (40, 768, 32, 2, 8),          # k = 32 (5-bit indices)
     (16, 256, 16, 4, 8), (8, 256, 4, 2, 1),           # combinations no decode format uses, same kernels
+    (8, 256, 32, 2, 1), (24, 512, 64, 1, 1), (16, 256, 16, 4, 1),   # the largest codebooks of one-row groups
 ]
 
 
@@ -256,7 +257,7 @@ def test_em_rounds_on_a_deployed_group_shape(env):
 # counts that are not multiples of a workgroup's
 M_SHAPES = [
     (8, 256, 4, 1, 1), (40, 768, 16, 1, 4), (24, 768, 16, 2, 8), (64, 256, 8, 1, 32),        # a table per lane
-    (8, 256, 64, 1, 1), (24, 768, 16, 2, 4), (40, 768, 32, 2, 8), (96, 512, 64, 2, 16),      # a table per wave
+    (8, 256, 64, 1, 1), (8, 256, 32, 2, 1), (24, 768, 16, 2, 4), (40, 768, 32, 2, 8), (96, 512, 64, 2, 16),      # a table per wave
     (96, 768, 64, 2, 32), (192, 256, 4, 4, 64), (128, 512, 256, 1, 128), (512, 768, 256, 4, 256),
 ]
 
