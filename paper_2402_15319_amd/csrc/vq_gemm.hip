@@ -720,10 +720,10 @@ hipError_t launch_tiny(const vq_desc& d, const void* idx_dev, const void* cb_dev
   const dim3 grid((unsigned)((n_rb + 1) / 2), (unsigned)((B + 15) / 16));
   if (eight_waves)
     hipLaunchKernelGGL((gemm_tiny_kernel<K, 8>), grid, dim3(512), 0, s, (const uint8_t*)idx_dev,
-                       (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y, ldy, y_f32, n_rb, n_cb, d.group_rows / kGroupRows);
+                       (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y, ldy, y_f32, n_rb, n_cb, blocks_per_group(d));
   else
     hipLaunchKernelGGL((gemm_tiny_kernel<K, 4>), grid, dim3(256), 0, s, (const uint8_t*)idx_dev,
-                       (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y, ldy, y_f32, n_rb, n_cb, d.group_rows / kGroupRows);
+                       (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y, ldy, y_f32, n_rb, n_cb, blocks_per_group(d));
   return hipGetLastError();
 }
 
@@ -880,7 +880,7 @@ hipError_t launch_small(const vq_desc& d, const void* idx_dev, const void* cb_de
   const int tiles_m = (n_rb + 3) / 4, tiles_n = (B + 31) / 32;
   hipLaunchKernelGGL((gemm_small_kernel<K>), dim3((unsigned)(tiles_m * tiles_n)), dim3(256), 0, s,
                      (const uint8_t*)idx_dev, (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y,
-                     ldy, y_f32, n_rb, n_cb, tiles_n, d.group_rows / kGroupRows);
+                     ldy, y_f32, n_rb, n_cb, tiles_n, blocks_per_group(d));
   return hipGetLastError();
 }
 
@@ -893,7 +893,7 @@ hipError_t launch_one(const vq_desc& d, const void* idx_dev, const void* cb_dev,
   const int tiles_m = (rb_end - rb0 + 4 * RBW * WM - 1) / (4 * RBW * WM), tiles_n = (B + NT - 1) / NT;
   hipLaunchKernelGGL((gemm_kernel<K, RBW, NT, WM>), dim3((unsigned)(tiles_m * tiles_n)), dim3(256 * WM), 0, s,
                      (const uint8_t*)idx_dev, (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y,
-                     ldy, y_f32, n_rb, n_cb, tiles_n, d.group_rows / kGroupRows, rb0, rb_end);
+                     ldy, y_f32, n_rb, n_cb, tiles_n, blocks_per_group(d), rb0, rb_end);
   return hipGetLastError();
 }
 

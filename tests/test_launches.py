@@ -61,3 +61,29 @@ def test_every_accepted_em_shape_launches_one_kernel(launches, op):
     got = launches([(op, max(gr, 8) * 3, 512, gr, d, k, vq.VQ_F16) for k, d, gr in shapes])
     bad = [(s, st, len(ls)) for s, (st, ls) in zip(shapes, got) if st != 0 or len(ls) != 1]
     assert bad == []
+
+
+# (group_rows, d, k, dtype) of every representation the decode side takes
+DECODE_FORMATS = [(8, 2, 16, vq.VQ_F16), (8, 2, 256, vq.VQ_F16), (4, 2, 16, vq.VQ_I8), (8, 2, 16, vq.VQ_I8), (8, 2, 32, vq.VQ_I8),
+                  (8, 1, 16, vq.VQ_F16), (1, 1, 4, vq.VQ_I8), (8, 2, 16, vq.VQ_I8_BN)]
+DECODE_FORMATS += [(gr, 2, 64, t) for gr in (8, 16, 32) for t in (vq.VQ_I8, vq.VQ_I8_BN)]
+DECODE_FORMATS += [(gr, 1, 8, t) for gr in (8, 16, 32) for t in (vq.VQ_I8, vq.VQ_I8_BN)]
+DECODE_FORMATS += [(gr, 2, 256, t) for gr in (64, 128, 256) for t in (vq.VQ_I8, vq.VQ_I8_BN)]
+DECODE_FORMATS += [(gr, 4, 256, t) for gr in (64, 128, 256) for t in (vq.VQ_I8, vq.VQ_I8_BN, vq.VQ_F16)]
+
+
+def test_batched_product_divides_by_no_zero(launches):
+    """The batched kernels divide row-blocks by the number that share a codebook: at least 1 in every
+    format, also where a codebook covers one or four rows only."""
+    sizes = [(256, 512, 3), (256, 2560, 40), (4096, 1024, 96), (11008, 512, 2048)]
+    calls = [("gemm", out // gr * gr, inp, gr, d, k, t, B) for gr, d, k, t in DECODE_FORMATS for out, inp, B in sizes]
+    where = {"gemm_tiny_kernel": 2, "gemm_small_kernel": 3, "gemm_kernel": 3}
+    seen = set()
+    for call, (status, ls) in zip(calls, launches(calls)):
+        assert status == 0 and ls, call
+        for name, _, _, ints in ls:
+            kernel = next(n for n in where if n in name)
+            seen.add(kernel)
+            assert ints[0] == call[1] // 8 and ints[1] == call[2] // 256, (call, name, ints)   # n_rb, n_cb: the right arguments
+            assert ints[where[kernel]] == max(1, call[3] // 8), (call, name, ints)
+    assert seen == set(where)
