@@ -953,18 +953,55 @@ hipError_t launch_wide(const vq_desc& d, const void* idx_dev, const void* cb_dev
   }
 }
 
+// Whether the 16 x 16 tiles (tiles_tiny of them) beat the 32 x 32 ones (tiles_small).  They re-decode W once per
+// 16 columns, which pays while the 32-row tiles leave CUs idle.  us, 16 x 16 against 32 x 32 tiles, 256 CUs:
+//   B <= 16: half of a 32-column tile is padding: always.
+//   B <= 32, up to two workgroups per CU: 4096 x 4096 (512) 10.4, 15.3 with 6-bit indices: always.  A third fits the
+// LDS of a CU with small tables only: 5120 x 11008, B = 17 (640) 30.0, 35.3 (k = 64), 26.5, 30.3 (k = 16), B = 32 32.5,
+// 35.7; but 26.1, 22.9 with d = 4 and fp16 tables (4160 x 4096), 9.1, 8.8 with int8 ones (5120 x 2048, B = 24; with few
+// of them and long rows 31.0, 33.7: 4224 x 11008, 128-row groups) and 31.4, 30.6 with k = 256 fp16 codebooks (8.1, 8.4
+// at 4224 x 2048).  Formats that decode longer need longer rows to hide it: k = 64 with block scales 8.0, 6.7
+// (4160 x 1024), 10.2, 10.5 (5120 x 2048); k = 256 with block scales 10.6, 10.3 (6144 x 2048), 38.3, 41.4 (4160 x 11008);
+// k = 16 with int8 tables 6.0, 5.6 (6144 x 1024), 8.0, 8.4 (5120 x 2048).
+//   B > 32, up to two: 2048 x 4096, B = 64 (512) 14.2, 15.6 (k = 64); three lose (2048 x 4096, B = 96 (768) 19.9, 15.7).
+// d = 4 with fp16 tables (2 KB a group): 1024 x 1024, B = 64 (256) 0.65 times as fast, x 4096 0.92 (512 x 4096 (128)
+// 1.19), x 11008 31.1, 38.4.  k = 256 fp16 codebooks: 2560 x 4096, B = 48 (480) 1.15 times as fast, 1024 x 4096, B = 128
+// (512) 0.97.  Many columns, few rows: 256 x 4096, B = 512 (512) 0.87 .. 1.00 times, with block scales 1.01 .. 1.07.  Rows
+// of four col-blocks, one to a wave, where the 32-column tile has no padding: 1024 x 1024, B = 96 (384) 0.89 .. 0.95 and
+// B = 128 0.80 .. 0.98 times, other than the formats named in the code: 1.05 .. 1.12 and up to 1.08.
+template <int K>
+bool tiny_pays(long long tiles_tiny, long long tiles_small, const vq_desc& d, int B, long long cus) {
+  constexpr bool kBlockNorm = K == kFmtK64BN || K == kFmtD1K8BN || K == kFmtK256I8BN || K == kFmtD4BN || K == kFmtK16BN;
+  const int n_cb = d.in_features / kGroupCols;
+  if (B <= 16) return true;
+  if (B <= 32) {
+    if (tiles_tiny <= 2 * cus) return true;
+    if (tiles_tiny > 3 * cus || K == kFmtD4F16 || K == kFmtD4BN) return false;
+    if (K == kFmtD4) return n_cb >= 32 && d.group_rows >= 128;
+    if (K == 256) return n_cb <= 8;
+    if (K == kFmtK256I8BN) return n_cb >= 16;
+    return n_cb >= 8 || K == 16 || K == 64 || K == kFmtD1K16 || K == kFmtD1K8 || K == kFmtD1K4 || K == kFmtK256I8;
+  }
+  if (tiles_tiny > 2 * cus) return false;
+  if (K == kFmtD4F16) return n_cb >= 32 || (n_cb >= 16 && 4 * tiles_tiny <= 3 * cus);
+  if (K == 256 && n_cb >= 16 && 8 * tiles_tiny > 15 * cus) return false;
+  if (!kBlockNorm && B > 256 && n_cb >= 16 && 2 * tiles_tiny > 3 * cus) return false;
+  if ((n_cb == 3 || n_cb == 4) && tiles_tiny > 3 * tiles_small) {
+    if (K == kFmtD1K16 || K == kFmtD1K4 || K == kFmtD4 || K == kFmtD4BN || K == kFmtK256I8) return true;
+    return 4 * tiles_tiny <= (K == 64 || K == 256 || K == kFmtD1K8 ? 6 : 5) * cus;
+  }
+  return true;
+}
+
 }  // namespace
 
 hipError_t launch_gemm(const vq_desc& d, const void* idx_dev, const void* cb_dev, const void* X,
                        int B, int ldx, void* Y, int ldy, int y_f32, hipStream_t s) {
-  // 16 x 16 tiles, barrier-free (gemm_tiny_kernel), for B <= 16 and as long as there are at most two workgroups
-  // per CU.  They re-decode W once per 16 columns, which pays while the 32-row tiles of the other kernels leave
-  // CUs idle; us with 6-bit indices, tiny against 32 x 32 tiles, at the workgroups of tiny: 512 x 4096,
-  // B = 128 (256) 8.9, 15.3; 2048 x 4096, B = 64 (512) 14.2, 15.6, B = 96 (768) 19.9, 15.7; 1024 x 11008, B = 64 (256)
-  // 16.9, 35.7, B = 128 (512) 29.3, 36.3; 4096 x 4096, B = 32 (512) 10.4, 15.3, B = 48 (768) 17.1, 15.5.  Up to one
-  // workgroup per CU they get 8 waves, which halves the col-blocks a wave walks one after the other:
-  // 4096 x 11008, B = 16 15.1 -> 12.4, 1024 x 11008, B = 64 18.4 -> 16.9; beyond that 4 (1024 x 11008, B = 96 (384)
-  // 27.5, with 8 waves 29.2), and also where a wave has a single col-block anyway.  Then 32 x 32 tiles (gemm_small_kernel,
+  // 16 x 16 tiles, barrier-free (gemm_tiny_kernel), where tiny_pays says so.  Up to one workgroup per CU they get
+  // 8 waves, which halves the col-blocks a wave walks one after the other: 4096 x 11008, B = 16 15.1 -> 12.4 us
+  // (6-bit indices), 1024 x 11008, B = 64 18.4 -> 16.9; beyond that 4 (1024 x 11008, B = 96 (384 workgroups) 27.5,
+  // with 8 waves 29.2), where a wave has a single col-block anyway, and for the formats that decode longest where
+  // four waves take two each (k = 64 with block scales, 1024 x 2048 5.7, with 8 waves 6.1).  Then 32 x 32 tiles (gemm_small_kernel,
   // bandwidth-bound) while they are few enough to run in about one wave of workgroups, then
   // gemm_kernel with 32 x 128 tiles while those fit the CUs once, and beyond that the cheapest
   // of four tilings by a small cost model: 64 x 128 and 64 x 256 (4 waves, two workgroups per
@@ -980,8 +1017,8 @@ hipError_t launch_gemm(const vq_desc& d, const void* idx_dev, const void* cb_dev
   const long long rows64 = (n_rb + 7) / 8, rows128 = (n_rb + 15) / 16;
   const long long cols128 = (B + 127) / 128, cols256 = (B + 255) / 256;
   const long long cus = device_cus();
-  const bool tiny = B <= 16 || tiles_tiny <= 2 * cus;
-  const bool eight_waves = tiles_tiny <= cus && d.in_features / kGroupCols > 4;
+  const int n_cb = d.in_features / kGroupCols;
+  const bool eight_waves = tiles_tiny <= cus && n_cb > 4;
   const bool small = B <= 32 || tiles_small <= 3 * cus;
   const bool one_round_32x128 = rows64 * cols128 <= cus / 2;
   const double per_cu = 256.0 / (double)cus;
@@ -994,7 +1031,9 @@ hipError_t launch_gemm(const vq_desc& d, const void* idx_dev, const void* cb_dev
     if (est[i] < est[best]) best = i;
 #define VQ_GEMM_DISPATCH(K)                                                                       \
   {                                                                                               \
-    if (tiny) return launch_tiny<K>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s, eight_waves); \
+    if (tiny_pays<K>(tiles_tiny, tiles_small, d, B, cus))                                         \
+      return launch_tiny<K>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s,                      \
+                            eight_waves && !((K == kFmtK64BN || K == kFmtD1K8BN) && (n_cb == 7 || n_cb == 8))); \
     if (small) return launch_small<K>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);           \
     if (one_round_32x128)                                                                         \
       return launch_one<K, 1, 128>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);              \

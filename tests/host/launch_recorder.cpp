@@ -57,7 +57,7 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
   return hipSuccess;
 }
 hipError_t hipGetLastError() { return hipSuccess; }
-hipError_t hipGetDevice(int* d) { *d = g_cus % 64; return hipSuccess; }   // a device per number of compute units: the library asks once per device
+hipError_t hipGetDevice(int* d) { *d = g_cus / 8 % 64; return hipSuccess; }   // a device per number of compute units: the library asks once per device
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = g_cus; return hipSuccess; }
 hipError_t hipGetSymbolAddress(void** p, const void*) { *p = reinterpret_cast<void*>(uintptr_t(1) << 40); return hipSuccess; }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = 2; return hipSuccess; }

@@ -87,3 +87,28 @@ def test_batched_product_divides_by_no_zero(launches):
             assert ints[0] == call[1] // 8 and ints[1] == call[2] // 256, (call, name, ints)   # n_rb, n_cb: the right arguments
             assert ints[where[kernel]] == max(1, call[3] // 8), (call, name, ints)
     assert seen == set(where)
+
+
+# (format, rows, columns, B, kernel): which tiles a batched product takes, on both sides of the rule (256 CUs); the
+# times behind it are at the rule
+K16, K64, K256 = (8, 2, 16, vq.VQ_F16), (32, 2, 64, vq.VQ_I8), (8, 2, 256, vq.VQ_F16)
+K64_BN, K256_BN, D4, D4_F16 = (32, 2, 64, vq.VQ_I8_BN), (64, 2, 256, vq.VQ_I8_BN), (64, 4, 256, vq.VQ_I8), (64, 4, 256, vq.VQ_F16)
+TILES = [
+    (K64, 11008, 4096, 16, "tiny"), (K64, 4096, 4096, 32, "tiny"), (K64, 5120, 11008, 17, "tiny"), (K64, 6144, 4096, 32, "tiny"),
+    (K64, 6176, 4096, 32, "small"), (K16, 5120, 4096, 24, "tiny"), (K256, 5120, 11008, 32, "small"), (K256, 4224, 2048, 17, "tiny"),
+    (D4, 5120, 2048, 24, "small"), ((128, 4, 256, vq.VQ_I8), 4224, 11008, 17, "tiny"), (D4_F16, 4160, 4096, 32, "small"),
+    (K64_BN, 4160, 1024, 32, "small"), (K64_BN, 4160, 4096, 17, "tiny"), (K256_BN, 6144, 2048, 32, "small"), (K256_BN, 4160, 11008, 17, "tiny"),
+    (K64, 2048, 4096, 64, "tiny"), (K64, 2048, 4096, 96, "small"), (D4_F16, 1024, 1024, 64, "small"), (D4_F16, 512, 4096, 64, "tiny"),
+    (D4_F16, 1024, 11008, 64, "tiny"), (K256, 2560, 4096, 48, "tiny"), (K256, 1024, 4096, 128, "small"),
+    (K16, 256, 4096, 512, "small"), (K64_BN, 256, 4096, 512, "tiny"), (K16, 1024, 1024, 128, "small"), (K16, 1024, 1024, 80, "tiny"),
+    (K64, 1024, 1024, 96, "tiny"), (K16, 2048, 1024, 48, "tiny"), (D4, 1024, 1024, 128, "tiny"),
+]
+
+
+def test_batched_product_takes_the_faster_tiles(launches):
+    calls = [("gemm", out, inp, *fmt, B) for fmt, out, inp, B, _ in TILES]
+    calls += [("gemm", out, inp, *fmt, B, 1, 128) for fmt, out, inp, B, _ in TILES[1:2]]     # half the CUs: twice the rounds
+    got = [ls[0][0] for _, ls in launches(calls)]
+    wrong = [(t, name) for t, name in zip(TILES, got) if "gemm_" + t[4] not in name]
+    assert wrong == []
+    assert "gemm_small" in got[-1]
