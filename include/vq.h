@@ -159,7 +159,9 @@ VQ_API int vq_gemv(const vq_desc* desc, const void* idx_dev, const void* cb_dev,
  * during the call and need not outlive it (the problem table travels in the
  * kernel arguments, up to 256 problems per launch).  All y_i share y_dtype and
  * all descriptors share one representation (d, k, codebook_dtype).  Each
- * product obeys the rules of vq_gemv.
+ * product obeys the rules of vq_gemv.  How the fp32 partial sums of a row are grouped
+ * depends on the products that share a launch, so the last bits of y may differ
+ * from those of a single call; the same call gives the same y every time.
  * count in [1, 65536].
  */
 VQ_API int vq_gemv_multi(int count, const vq_desc* descs, const void* const* idx_dev,

@@ -897,23 +897,6 @@ hipError_t launch_one(const vq_desc& d, const void* idx_dev, const void* cb_dev,
   return hipGetLastError();
 }
 
-// Compute units of the current device: the 8-wave tiles run one workgroup per CU, so their time
-// moves in whole rounds of that many tiles.  Asked once per device, then cached.
-int device_cus() {
-  static std::atomic<int> cached[64];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-  int cus = cached[dev].load(std::memory_order_relaxed);
-  if (cus == 0) {
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
-      (void)hipGetLastError();
-      return 256;
-    }
-    cached[dev].store(cus, std::memory_order_relaxed);
-  }
-  return cus;
-}
-
 // Large batches on the 128-row tiles: 128 x 512 tiles decode W once per 512 batch columns instead
 // of once per 256 and take 1.73 times as long as 128 x 256 tiles for twice the area, but a launch
 // pays for whole rounds of one workgroup per CU.  So the first m_a tile rows run with 512-column
@@ -994,6 +977,21 @@ bool tiny_pays(long long tiles_tiny, long long tiles_small, const vq_desc& d, in
 }
 
 }  // namespace
+
+int device_cus() {
+  static std::atomic<int> cached[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
+  int cus = cached[dev].load(std::memory_order_relaxed);
+  if (cus == 0) {
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
+      (void)hipGetLastError();
+      return 256;
+    }
+    cached[dev].store(cus, std::memory_order_relaxed);
+  }
+  return cus;
+}
 
 hipError_t launch_gemm(const vq_desc& d, const void* idx_dev, const void* cb_dev, const void* X,
                        int B, int ldx, void* Y, int ldy, int y_f32, hipStream_t s) {

@@ -292,24 +292,43 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
 
 }  // namespace
 
-// Workgroups per 64-row item.
-static int wide_splits(const GemvBatch& b) {
-  // us per launch at 1, 2, 4, 8 splits on 256 CUs (int8 tables): d = 4, 64 items of 8 pairs 9.4, 6.7, 5.2, 5.4, of
-  // 22 pairs 20.9, 13.1, 9.4, 8.9; 192 items of 8 pairs 10.0, 8.8, 8.1, 10.8; 344 items 11.9, 11.1, 11.7, 16.9.
-  // d = 2, k = 256: 64 items 12.3, 8.4, 6.4, 6.6 and 28.9, 16.8, 11.7, 11.2; 192 13.9, 11.9, 10.9, 11.5; 344 19.6,
-  // 17.3, 16.8, 18.8.  A layer in order: d = 4 61 -> 36, k = 256 82 -> 48.  No more splits than pairs.
+// Workgroups per 64-row item.  us per launch at 1, 2, 4, 8 splits on 256 CUs (a pair: two col-blocks), d = 4 with int8
+// tables / d = 2, k = 256:
+//   64 items, 8 pairs 7.2, 5.3, 4.1, 4.4 / 10.1, 6.7, 4.8, 4.9; 22 pairs 16.5, 11.0, 8.1, 8.2 / 24.0, 14.4, 10.0, 9.4
+//   128, 2 pairs 3.4, 3.2, 4.0 / 4.3, 3.6, 4.2; 8 pairs 7.3, 5.5, 5.3, 6.7 / 11.6, 7.7, 6.4, 6.9
+//   192, 2 pairs 3.5, 3.8 / 4.3, 4.3 (block scales 5.4, 5.6); 4 pairs 4.7, 5.0, 4.8 / 6.2, 6.1, 5.3; 8 pairs 7.9, 7.0, 6.6 / 11.6, 10.3, 9.3
+//   256, 4 pairs 4.8, 5.0 / 7.0, 6.1; 8 pairs 9.5, 7.2, 7.9 / 12.1, 11.1, 11.8
+//   320, 2 pairs 4.3, 4.4 / 5.7, 5.0; 4 pairs 6.2, 6.0 / 9.8, 7.5; 16 pairs 19.0, 17.1, 17.6 / 32.5, 25.2, 24.7
+//   448, 4 pairs 6.2, 6.9 / 11.0, 10.0; 16 pairs 19.7, 21.1 / 33.6, 32.2; 512, 8 pairs 12.2, 12.8 / 19.2, 20.5
+// d = 4 with fp16 tables stages twice the bytes: 192 items, 8 pairs 7.2, 6.6, 7.9; 320, 4 pairs 5.9, 5.6, 8 pairs 10.3,
+// 10.9, 16 pairs 18.9, 18.7; 64 items, 16 pairs at 4 and 8 splits 5.5, 8.9, 32 items 5.4, 4.7.  So d = 4 splits less
+// than d = 2 and neither much beyond one and a half items per CU.  The widest product of a launch decides, as a
+// narrow one beside it costs little: 3 x 1024 x 256 + 64 x 11008 16.2, 10.4, 7.3, 6.3 / 23.8, 13.8, 9.2, 7.1;
+// 11008 x 256 + 1024 x 11008 16.6, 11.2, 8.6, 10.3 / 24.2, 14.8, 10.4, 10.1, with fp16 tables 16.2, 10.4, 8.4, 11.5.
+static int wide_splits(const GemvBatch& b, int fmt) {
   int pairs = 1;
   for (int i = 0; i < b.count; ++i) pairs = max(pairs, (b.p[i].n_cb + 1) / 2);
-  if (b.count > kFewProblems || b.total_wgs > 512) return 1;
-  const int most = pairs >= 4 ? 4 : pairs >= 2 ? 2 : 1;
-  if (b.total_wgs <= 64 && pairs >= 16) return 8;
-  return b.total_wgs <= 192 ? most : min(most, 2);
+  const long long items = b.total_wgs, cus = device_cus();
+  long long work = 0;
+  for (int i = 0; i < b.count; ++i) work += (long long)(b.p[i].n_rb / 8) * ((b.p[i].n_cb + 1) / 2);
+  const long long full = work / pairs;              // items of full width with the same work
+  if (b.count > kFewProblems || pairs < 2 || items > 2 * cus) return 1;
+  const bool d2 = fmt == kFmtK256I8 || fmt == kFmtK256I8BN, f16 = fmt == kFmtD4F16;
+  if (4 * items <= cus && pairs >= 16 && (!f16 || 8 * full <= cus)) return 8;
+  if (2 * items <= cus) return pairs >= 4 ? 4 : 2;
+  if (d2 && items <= cus && pairs < 4) return 1;
+  if (d2 && 4 * items <= 3 * cus) return 4;
+  if (d2) return 2 * items <= 3 * cus || pairs >= 16 || (pairs >= 4 && pairs < 8) ? 2 : 1;
+  if (2 * items > 3 * cus) return 1;
+  if (4 * items <= 3 * cus && pairs >= 8) return f16 && 2 * full > cus ? 2 : 4;
+  if (items <= cus) return pairs >= 8 ? 2 : 1;
+  return pairs >= 4 && !(f16 && pairs >= 8 && pairs < 16) ? 2 : 1;
 }
 
 // (kernel, template arguments before CAP)
 #define VQ_LAUNCH_WIDE(KERNEL, ...)                                                                              \
   do {                                                                                                           \
-    const int ks = wide_splits(base_of_host(batch));                                                             \
+    const int ks = wide_splits(base_of_host(batch), fmt);                                                        \
     const dim3 grid((unsigned)(total_wgs * ks));                                                                 \
     if (base_of_host(batch).count > kFewProblems)                                                                \
       hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kMaxProblemsPerLaunch, 1>), grid, dim3(512), 0, s, batch);         \

@@ -144,6 +144,10 @@ inline LoraDownBatchT<kFewProblems> few_problems(const LoraDownBatch& b) {
 // 8-row blocks that share a codebook; 1 also for groups of one or four rows: kernels divide by it.
 inline int blocks_per_group(const vq_desc& d) { return d.group_rows < kGroupRows ? 1 : d.group_rows / kGroupRows; }
 
+// Compute units of the current device, asked once per device, then cached: the rules that choose tiles and splits
+// count workgroups against it.
+int device_cus();
+
 // Launchers (each returns the hipError_t of its launch).
 hipError_t launch_pack(const vq_desc& d, const void* idx_canon, const void* cb_canon,
                        void* idx_dev, void* cb_dev, hipStream_t s);

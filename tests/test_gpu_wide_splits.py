@@ -12,10 +12,15 @@ FORMATS = {
     "d4": dict(d=4, int8_tables=True), "d4_f16": dict(d=4), "d4_bn": dict(d=4, int8_tables=True, block_norm=True),
     "k256_i8": dict(int8_tables=True), "k256_bn": dict(int8_tables=True, block_norm=True),
 }
-# (rows, columns, products): one pair of col-blocks (no split); two and three pairs; nine, an odd number of
-# col-blocks (four splits of unequal length); 17 and 18 pairs (eight); more than 192 and more than 512 items
-SIZES = [(64, 256, 1), (128, 768, 2), (192, 1280, 3), (64, 4352, 1), (64, 8448, 1), (128, 8960, 2), (4288, 512, 3),
-         (16448, 512, 2), (64, 768, 5)]
+# (rows, columns, products); columns may differ between products: a narrow one beside a wide one has empty splits.
+# Workgroups per 64 rows on 256 CUs behind each (d = 2; d = 4; d = 4 with fp16 tables, or one figure for all).
+SIZES = [
+    (64, 256, 1), (128, 768, 2), (192, 1280, 3), (64, 4352, 1), (64, 8448, 1), (128, 8960, 2),   # 1, 2, 2, 4, 8, 8
+    (64, 768, 5), (4160, 1024, 2), (4288, 2048, 3), (4288, 512, 3), (8512, 2048, 2),             # 1; 1; 2, 1, 1; 1; 2
+    (12352, 1024, 2), (16448, 1024, 2),                                                          # 1, 1
+    (64, (256, 8448), 2), (192, (8448, 256, 768, 512), 4), (2048, (256, 2304), 2),               # 8, 8, 4
+    (4160, (256, 4352), 2), (4288, (512, 4352, 256), 3),                                         # 4, 4, 2; 2
+]
 
 
 @pytest.mark.parametrize("size", SIZES, ids=str)
@@ -24,12 +29,14 @@ def test_splits(fmt, size):
     import torch
     import paper_2402_15319_amd as vq
     from paper_2402_15319_amd import device as vqdev
-    out_f, in_f, count = size
-    s = workloads.VQShape(out_f, in_f, 256, 8, 64, **FORMATS[fmt])
-    desc = vqdev.desc_from_shape(s)
+    out_f, widths, count = size
+    widths = widths if isinstance(widths, tuple) else (widths,) * count
     rank = 16
-    mats, xs, ys, zs, As, Bs, want, want_lora, bound = [], [], [], [], [], [], [], [], []
-    for i in range(count):
+    descs, mats, xs, ys, zs, As, Bs, want, want_lora, bound = [], [], [], [], [], [], [], [], [], []
+    for i, in_f in enumerate(widths):
+        s = workloads.VQShape(out_f, in_f, 256, 8, 64, **FORMATS[fmt])
+        desc = vqdev.desc_from_shape(s)
+        descs.append(desc)
         seed = 60 + in_f + i
         if s.block_norm:
             idx, *tables = workloads.make_weights_bn(s, seed)
@@ -58,10 +65,10 @@ def test_splits(fmt, size):
         # exact products; at most in_f additions in binary32 (and in_f + rank with the adapter)
         bound.append((in_f + rank + 2) * 2.0 ** -24 * mag)
     idx_d, cb_d = [m[0] for m in mats], [m[1] for m in mats]
-    args = vq.GemvMultiArgs([desc] * count, idx_d, cb_d, xs, ys)
+    args = vq.GemvMultiArgs(descs, idx_d, cb_d, xs, ys)
     vq.vq_gemv_multi(args, y_dtype=vq.VQ_F32)
     ws = torch.zeros(vq.vq_lora_workspace_bytes(count), dtype=torch.uint8, device="cuda:0")
-    vq.vq_gemv_lora_multi(vq.GemvMultiArgs([desc] * count, idx_d, cb_d, xs, zs), As, Bs, [rank] * count, ws, vq.VQ_F32)
+    vq.vq_gemv_lora_multi(vq.GemvMultiArgs(descs, idx_d, cb_d, xs, zs), As, Bs, [rank] * count, ws, vq.VQ_F32)
     torch.cuda.synchronize()
     for i in range(count):
         assert np.all(np.abs(ys[i].cpu().numpy() - want[i]) <= bound[i])

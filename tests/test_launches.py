@@ -112,3 +112,28 @@ def test_batched_product_takes_the_faster_tiles(launches):
     wrong = [(t, name) for t, name in zip(TILES, got) if "gemm_" + t[4] not in name]
     assert wrong == []
     assert "gemm_small" in got[-1]
+
+
+# (format, rows of the products, columns, CUs, workgroups per 64 rows): on both sides of the lines of the rule
+K256_I8, D4_BN = (64, 2, 256, vq.VQ_I8), (64, 4, 256, vq.VQ_I8_BN)
+WIDE = [
+    (D4, [4096], [8192], 256, 8), (D4, [4160], [8192], 256, 4), (D4_F16, [2048], [8192], 256, 8), (D4_F16, [4096], [8192], 256, 4),
+    (D4_F16, [1024] * 3 + [64], [256] * 3 + [11008], 256, 8), (D4_F16, [11008, 1024], [256, 11008], 256, 4),
+    (K256_I8, [28672], [2048], 256, 2), (K256_I8, [28672], [4096], 256, 1), (K256_I8, [4096], [8192], 256, 8), (K256_I8, [4160], [8192], 256, 4),
+    (D4, [4096], [7680], 256, 4), (D4, [8192], [1024], 256, 2), (D4, [8256], [1024], 256, 1), (K256_I8, [12288], [1024], 256, 1), (K256_I8, [20480], [1024], 256, 2),
+    (D4, [8192], [512], 256, 1), (D4, [64], [512], 256, 1), (D4, [64], [768], 256, 2), (D4, [8192], [2048], 256, 4),
+    (D4, [12288], [4096], 256, 4), (D4_BN, [12288], [4096], 256, 4), (D4_F16, [12288], [4096], 256, 2), (K256_I8, [12288], [2048], 256, 4),
+    (D4, [12288], [2048], 256, 1), (D4, [12352], [4096], 256, 2), (D4, [16384], [2048], 256, 1), (K256_I8, [12352], [4096], 256, 2),
+    (D4, [16448], [2048], 256, 2), (D4, [20480], [1024], 256, 1), (D4_F16, [20480], [4096], 256, 1), (D4_F16, [20480], [8192], 256, 2),
+    (D4, [24576], [4096], 256, 2), (D4, [24640], [4096], 256, 1), (K256_I8, [24640], [4096], 256, 1), (K256_I8, [32768], [8192], 256, 2),
+    (K256_I8, [32832], [8192], 256, 1), (D4, [4096, 4096], [256, 8448], 256, 4), (D4, [1024] * 5, [4096] * 5, 256, 1),
+    (D4, [24576], [4096], 128, 1), (D4, [4864], [8192], 304, 8),      # counted against the CUs of the device
+]
+
+
+def test_wide_gemv_splits(launches):
+    calls = [("gemv", outs, ins, *fmt, 1, 1, cus) for fmt, outs, ins, cus, _ in WIDE]
+    got = launches(calls)
+    wrong = [(w, ls[0][1][0]) for w, (st, ls) in zip(WIDE, got)
+             if st != 0 or len(ls) != 1 or ls[0][1][0] != sum(w[1]) // 64 * w[4] or f"Li{w[4]}E" not in ls[0][0]]
+    assert wrong == []
