@@ -140,6 +140,61 @@ __device__ __forceinline__ float own_coord(const float (&v)[D], int q, int half)
 template <int D>
 __device__ __forceinline__ int em_place(int m) { return D * (m + (m >> 3)); }
 
+// The whole codebook for 8 rows of 32 vectors: lanes L and L + 32 take four rows each of the vectors in column
+// place L, so that a read of a centroid serves four vectors.  Per 8 centroids only the smallest distance is kept
+// (the first block that has it), and its place is found in that block afterwards: 8 (d = 2) or 15 (d = 4)
+// instructions per centroid and vector where keeping the place takes 10 or 18.  A NaN distance is never the smallest.
+template <int K, int D>
+__device__ __forceinline__ void em_assign_whole(const float* cbs, const float* __restrict__ Wl, int in_features,
+                                                const float (&h)[D], uint8_t* __restrict__ out) {
+#pragma clang fp contract(off)
+  float x[4][D], best[4];
+  uint32_t blk[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    load_coords<D>(Wl + (size_t)r * in_features, x[r]);
+    best[r] = __builtin_inff();
+    blk[r] = 0;
+  }
+  float ahead[8][D];                          // the next 8 centroids; the same address in every lane
+#pragma unroll
+  for (int j = 0; j < 8; ++j) load_coords<D>(cbs + j * D, ahead[j]);
+#pragma unroll 1
+  for (uint32_t b = 0; b < K / 8; ++b) {
+    float cm[8][D], low[4];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int t = 0; t < D; ++t) cm[j][t] = ahead[j][t];
+    const float* next = cbs + em_place<D>(8) * (int)(b + 1 < K / 8 ? b + 1 : b);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) load_coords<D>(next + j * D, ahead[j]);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float dist = em_distance<D>(x[r], h, cm[j]);
+        low[r] = j == 0 ? dist : __builtin_fminf(low[r], dist);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (low[r] < best[r]) { best[r] = low[r]; blk[r] = b; }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const float* cand = cbs + em_place<D>(8) * (int)blk[r];
+    float low = __builtin_inff();
+    uint32_t arg = 8 * blk[r];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float dist = em_distance<D>(x[r], h, cand + j * D);
+      if (dist < low) { low = dist; arg = 8 * blk[r] + j; }
+    }
+    out[(size_t)r * (in_features / D)] = (uint8_t)arg;
+  }
+}
+
 // Workgroups of one wave, one per (8-row block, col-block).  A step is 32 vectors of one row: lanes L and
 // L + 32 share vector L, and each scores half of every tile of 32 centroids.
 template <int K, int D>
@@ -151,7 +206,12 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
   constexpr int SETS = 8 / D;                 // steps per row
   constexpr int NM = D == 4 ? 2 : 1;          // coordinates per half-wave = matrix instructions per tile
   constexpr uint32_t kBlockMask = 4 * TILES - 1;   // block number: tile, half-wave, upper or lower 8
-  constexpr int R = K * D > 512 ? 2 : 4;      // steps filtered together (what fits the registers)
+  constexpr int R = D == 4 ? 2 : 4;           // steps filtered together
+  // Undecided vectors of a step from which the whole codebook is faster: a vector taken by itself costs 25, 17, 13 us
+  // per 4096 x 4096 and vector of a step, the filter 106, 85, 40, the whole codebook 300, 300, 85 (d = 2 and d = 4 with
+  // k = 256, d = 4 with k = 64).  Judged by the first rows of a set; later ones, whose set would be done twice, need
+  // twice as many.
+  constexpr int kMostUndecided = D == 2 ? 7 : K == 256 ? 13 : 3;
   __shared__ __attribute__((aligned(16))) float cbs[(K + K / 8) * D];
   const int lane = threadIdx.x;
   const int half = lane >> 5, n = lane & 31;
@@ -207,9 +267,10 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
 
   float h[D], hs[D];                          // weights, and weights times both scales
   uint4 B[NM];
-  bool ok = false;
+  bool filter = ok_c;
 #pragma unroll 1
   for (int set = 0, row = 0; set < SETS;) {   // R steps each: 32 vectors of R rows
+    bool whole = !filter;                     // this set's vectors against the whole codebook
     const int col = set * 32 + n;             // the vector's place in the row
     if (row == 0) {
       load_coords<D>(hb + col * D, h);
@@ -221,7 +282,7 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
       }
       // with h_low >= 2^-20 h_top the bound on h x below is one on x
       const bool good = h_low >= 0x1p-30f && h_top <= 0x1p30f && h_low >= 0x1p-20f * h_top;
-      ok = ok_c && __all(good);
+      whole = whole || !__all(good);
       const float h_scale = good ? scale_to_32(h_top) : 1.f;
       float hq[D];
 #pragma unroll
@@ -248,7 +309,7 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
     }
     uint32_t args[R], unsures[R];
     bool in_upper[R];                         // which of lanes L and L + 32 holds the result
-    if (ok) {         // R steps' filters, without a branch between them
+    if (!whole) {     // R steps' filters, without a branch between them
       uint4 Bx[R][NM];
       float X[R], m1[R], m2[R];
 #pragma unroll
@@ -323,77 +384,84 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
         args[r] = arg;
         in_upper[r] = bu < bl;         // the lower half-wave holds the lower indices
       }
-    } else {
+      uint32_t any = 0;
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        args[r] = 0;
-        unsures[r] = 0xffffffffu;
-        in_upper[r] = false;
-      }
-    }
+      for (int r = 0; r < R; ++r) any |= unsures[r];
+      if (any != 0) {
+        int undecided = 0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const float (&x)[D] = xs[r];
-      const uint32_t unsure = unsures[r];
-      uint32_t arg = args[r];
-      if (unsure != 0) {
-        // one vector at a time costs about as much as 120 instructions of the loop over the codebook
-        if (__builtin_popcount(unsure) <= K * (4 * D + 3) / 240) {
-          uint32_t left = unsure;
-          while (left != 0) {      // K / 64 centroids per lane
-            const int src = __builtin_ctz(left);
-            left &= left - 1;
-            float xv[D], hv[D];
-#pragma unroll
-            for (int t = 0; t < D; ++t) {
-              xv[t] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[t]), src));
-              hv[t] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, h[t]), src));
-            }
-            float db = __builtin_inff();
-            int dj = 0;
-#pragma unroll
-            for (int j = 0; j < (K + 63) / 64; ++j) {
-              const float dist = em_distance<D>(xv, hv, cbs + em_place<D>((j * 64 + lane) % K));
-              if (dist < db) { db = dist; dj = j; }
-            }
-            // the lowest index that has the smallest distance; no distance below infinity: index 0
-            const float mn = wave_min(db);
-            int found = 0;
-            if (mn < __builtin_inff()) {
-              found = -1;
-#pragma unroll
-              for (int j = 0; j < (K + 63) / 64; ++j) {
-                const unsigned long long at = __ballot(db == mn && dj == j);
-                if (found < 0 && at != 0) found = j * 64 + __builtin_ctzll(at);
-              }
-            }
-            if (n == src) arg = (uint32_t)found;
-          }
-        } else {                   // all 32 vectors, half of the codebook per half-wave
-          float db = __builtin_inff();
-          uint32_t da = half * (K / 2);
-          for (int m = 0; m < K / 2; ++m) {
-            const float dist = em_distance<D>(x, h, cbs + em_place<D>(half * (K / 2) + m));
-            if (dist < db) { db = dist; da = half * (K / 2) + m; }
-          }
-          float bl, bu;
-          uint32_t al, au;
-          both_halves(db, bl, bu);
-          both_halves(da, al, au);
-          arg = bu < bl ? au : al;
+        for (int r = 0; r < R; ++r) undecided += __builtin_popcount(unsures[r]);
+        if (undecided > kMostUndecided * R * (row_now == 0 ? 1 : 2)) {
+          filter = false;                     // the sets to come will be no better
+          goto whole_codebook;
         }
       }
-      uint8_t* const out = ab + (size_t)(row_now + r) * (in_features / D);
-      if (in_upper[r] == (half != 0)) out[(uint32_t)col] = (uint8_t)arg;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const float (&x)[D] = xs[r];
+        uint32_t arg = args[r], left = unsures[r];
+        while (left != 0) {      // one vector at a time, K / 64 centroids per lane
+          const int src = __builtin_ctz(left);
+          left &= left - 1;
+          float xv[D], hv[D];
+#pragma unroll
+          for (int t = 0; t < D; ++t) {
+            xv[t] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[t]), src));
+            hv[t] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, h[t]), src));
+          }
+          float db = __builtin_inff();
+          int dj = 0;
+#pragma unroll
+          for (int j = 0; j < K / 64; ++j) {
+            const float dist = em_distance<D>(xv, hv, cbs + em_place<D>(j * 64 + lane));
+            if (dist < db) { db = dist; dj = j; }
+          }
+          // the lowest index that has the smallest distance; no distance below infinity: index 0
+          const float mn = wave_min(db);
+          int found = 0;
+          if (mn < __builtin_inff()) {
+            found = -1;
+#pragma unroll
+            for (int j = 0; j < K / 64; ++j) {
+              const unsigned long long at = __ballot(db == mn && dj == j);
+              if (found < 0 && at != 0) found = j * 64 + __builtin_ctzll(at);
+            }
+          }
+          if (n == src) arg = (uint32_t)found;
+        }
+        uint8_t* const out = ab + (size_t)(row_now + r) * (in_features / D);
+        if (in_upper[r] == (half != 0)) out[(uint32_t)col] = (uint8_t)arg;
+      }
+      continue;
     }
+  whole_codebook:
+    const int now = row == 0 ? set - 1 : set;
+    set = now + 1;
+    row = 0;
+    const int ahead = set < SETS ? set : 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r)   // before the stores, as on the way past this: a wait for them is one for these too
+      load_coords<D>(Wb + (size_t)r * in_features + (uint32_t)((ahead * 32 + n) * D), xn[r]);
+    em_assign_whole<K, D>(cbs, Wb + (size_t)(4 * half) * in_features + (now * 32 + n) * D, in_features, h,
+                          ab + (size_t)(4 * half) * (in_features / D) + (now * 32 + n));
   }
 }
 
-// Which codebooks take the filter; us at 4096 x 4096, loop over the centroids against filter: d = 4, k = 256,
-// 64 rows: 311, 120; d = 4, k = 64: 82, 53; d = 2, k = 256, 128 rows: 322, 124 (8 rows with 9 % of the centroids
-// twice, where ties send vectors to the whole codebook: 332, 267); but d = 2, k = 64: 87, 82..110; d = 2, k = 32:
-// 46, 62; d = 1, k = 64: 111, 170 (scalars lie too close for the filter).  Waves of 16 rows, which would split
-// the centroids' features over twice the vectors, were slower (144 for 124).
+// Which codebooks take the filter; us at 4096 x 4096, loop over the centroids against filter (11008 x 4096 behind):
+//                                        d = 2, k = 256, 8 rows     d = 4, k = 256, 256 rows    d = 4, k = 64, 16 rows
+//   distinct centroids                   340, 109 (870, 283)        314, 84 (800, 220)          85, 40
+//   vectors of the group, drawn with replacement (11, 1.5, 3 % of the centroids repeated, d = 2 with 8 rows most)
+//                                        342, 269 (875, 623)        314, 94 (796, 237)          85, 64
+//   half of W and a quarter of the centroids zero
+//                                        332, 346                   308, 278 (786, 691)         82, 92
+//   every centroid twice, or W far from zero: no vector is decided
+//                                        340, 314                   310, 308 (794, 830)         85, 91
+//   zero, negative or very uneven weights in every set of 32 vectors: no filter
+//                                        338, 303                   309, 299 (794, 799)         85, 87
+// Equal centroids cost so much because all vectors nearest to them are undecided; an M-step leaves the zero vector in
+// the place of every empty cluster.  Not for d = 2, k = 64: 87, 82..110; d = 2, k = 32: 46, 62; d = 1, k = 64: 111, 170
+// (scalars lie too close for the filter).  Waves of 16 rows, which would split the centroids' features over twice the
+// vectors, were slower (144 for 124).
 template <int K, int D> constexpr bool em_filtered() { return (D == 2 && K == 256) || (D == 4 && K >= 64); }
 template <int K, int D> constexpr int em_threads() { return em_filtered<K, D>() ? 64 : 256; }
 template <int K, int D> constexpr int em_waves() { return em_filtered<K, D>() ? 2 : 1; }   // per SIMD: 256 registers each

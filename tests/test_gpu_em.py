@@ -340,7 +340,7 @@ FILTERED = [(2, 256, 8, 24, 512), (2, 256, 128, 128, 256), (4, 64, 16, 48, 512),
 
 @pytest.mark.parametrize("case", ["plain", "centroids twice", "zero centroids and weights", "all zero", "rounded to a grid",
                                   "far from zero", "uneven weights", "zero weights", "negative weights", "huge", "tiny",
-                                  "nan and inf"])
+                                  "nan and inf", "zero weights in one set", "equal centroids for the later rows"])
 @pytest.mark.parametrize("shape", FILTERED, ids=str)
 def test_filtered_e_step_is_the_defined_one(env, shape, case):
     """The scores that pick the candidates are approximate, the result is not: ties, vectors that the
@@ -373,8 +373,49 @@ def test_filtered_e_step_is_the_defined_one(env, shape, case):
     elif case == "nan and inf":
         W[rng.random(W.shape) < 0.01] = np.nan
         W[rng.random(W.shape) < 0.01] = np.inf
+    elif case == "zero weights in one set":        # the second 32 vectors of a col-block
+        h[32 * d:64 * d] = 0
+    elif case == "equal centroids for the later rows":   # decided at first, undecided in rows 4 .. 7 of every 8
+        cb[:, ::2] = 0
+        W.reshape(-1, 8, in_f)[:, 4:] = 0
     f = oracle.VQFormat(out_f, in_f, k, 8, gr, 256, d)
     with np.errstate(all="ignore"):
         want = oracle.em_assign(f, W, h, cb)
     a, _ = _gpu_em_any(env, (out_f, in_f, k, d, gr), W, h, cb)
     np.testing.assert_array_equal(a, want)
+
+
+@pytest.mark.parametrize("shape", [(2, 256, 8), (4, 64, 16), (4, 256, 64)], ids=str)
+def test_undecided_vectors_cost_no_more_than_a_loop_over_the_codebook(env, shape):
+    """Ties everywhere, and weights that the filter does not take: such vectors meet the whole codebook, and that
+    must not take longer than the kernels without a filter do (by the one for d = 2, k = 32, per coordinate and
+    centroid: 0.75 to 0.97 of its time, 1.4 and more when a read of a centroid served one vector)."""
+    torch, vq, vqdev = env
+    d, k, gr = shape
+    n = 4096
+    g = torch.Generator("cuda").manual_seed(5)
+    W = torch.randn((n, n), device="cuda", generator=g) * 0.02
+    h = 0.2 + 4.8 * torch.rand(n, device="cuda", generator=g)
+
+    def us(desc, h, cb):
+        a = torch.empty((n, n // desc.d), dtype=torch.uint8, device="cuda")
+        best = 1e9
+        for _ in range(6):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            for _ in range(5):
+                vq.vq_em_assign(desc, W, h, cb, a)
+            t1.record()
+            torch.cuda.synchronize()
+            best = min(best, t0.elapsed_time(t1) * 200)
+        return best
+
+    loop = us(vq.make_desc(n, n, 32, 5), h, torch.randn((n // 8 * 16, 32, 2), device="cuda", generator=g) * 0.02)
+    per_coordinate = loop / (32 * n * n)                     # d coordinates a vector, n * n / d vectors
+    cb = torch.randn((n // gr * 16, k, d), device="cuda", generator=g) * 0.02
+    tied = cb[:, :1].expand(-1, k, -1).contiguous()
+    desc = vq.make_desc(n, n, k, {64: 6, 256: 8}[k], group_rows=gr, d=d)
+    zeros = h.clone()
+    zeros[::2] = 0
+    ratio = [us(desc, h, tied) / (per_coordinate * k * n * n), us(desc, zeros, cb) / (per_coordinate * k * n * n)]
+    assert max(ratio) < 1.1, ratio
