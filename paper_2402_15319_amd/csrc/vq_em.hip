@@ -35,17 +35,23 @@ namespace {
 // block with the arithmetic that defines the E-step, otherwise in the whole codebook, so the result is the
 // defined one bit for bit.
 //   How far scores can be off: with X = sum h x^2, a centroid at weighted distance dist from the vector has
-// sum h c^2 + 2 h |x c| <= 5 X + 3 dist, and only centroids as near as the first block's matter.  Relative to
-// that sum the vector's halves (rounded towards zero) are off by 2^-20, the centroid's by 2^-22, rounded
-// features by 2^-22, the accumulation by less than 2^-20: 2.5 * 2^-20 for each of the two scores compared.  The
-// block number moves a score by 2^-18 of X + dist, and the defined arithmetic itself rounds to 2^-21 of dist.
-// Together 2^-20 * (33 X + 24 dist); with dist = first + X the margin taken is 2^-20 * (62.5 X + 27 first).
+// S = sum h c^2 + 2 h |x c| <= 5 X + 3 dist, and only centroids as near as the first block's matter.  Relative to S
+// the vector's halves (rounded towards zero) are off by 2^-20, the centroid's by 2^-22, rounded features by 2^-22, and
+// the accumulation of 8 D products by 2^-20 D if every addition truncates (2^-23 of the sum so far): kScoreError
+// * 2^-20 in all, for each of the two scores compared.  The block number moves a score by 2^-18 of X + dist, and the
+// defined arithmetic itself rounds to 2^-21 of dist.  With dist = first + X that is, in 2^-20,
+// (16 kScoreError + 17) X + (6 kScoreError + 9) first; a tenth is added for the terms of second order.
 // kScoreTiny covers halves that are subnormal: 2^-24 each (the matrix cores keep subnormals) times the largest
 // value of the feature they meet, at most 60,000.  Codebooks, weights or vectors outside the ranges checked
 // below (NaN, infinities, negative or very uneven weights) take the whole codebook.
 //   Bound: vector instructions, the minima first.  The loop over centroids that this replaces takes 18
 // (d = 4) or 11 (d = 2) instructions per centroid and vector.
-constexpr float kMarginX = 62.5f / 1048576.f, kMarginFirst = 1.f + 27.f / 1048576.f;
+template <int D>
+struct EmMargin {
+  static constexpr float kScoreError = 1.5f + 1.0f * D;
+  static constexpr float kX = 1.1f * (16.f * kScoreError + 17.f) / 1048576.f;
+  static constexpr float kFirst = 1.f + 1.1f * (6.f * kScoreError + 9.f) / 1048576.f;
+};
 constexpr float kScoreTiny = 0.0112f;      // per coordinate
 // h x^2 of a vector up to which |h x| <= sqrt(2^6 * 2^25) < 60,000 (scaled)
 constexpr float kMaxNorm = 0x1p25f;
@@ -252,7 +258,7 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
   top = -wave_min(nan_c ? 0.f : -top);
   const bool ok_c = !nan_c && top >= 0x1p-40f && top <= 0x1p20f;
   const float c_scale = ok_c ? scale_to_32(top) : 1.f;
-  const float margin_x = kMarginX * c_scale, max_norm = kMaxNorm * power_inverse(c_scale);   // X below lacks one factor c_scale
+  const float margin_x = EmMargin<D>::kX * c_scale, max_norm = kMaxNorm * power_inverse(c_scale);   // X below lacks one factor c_scale
   const int row_centroid = 16 * ((n >> 2) & 1) + 4 * (n >> 3) + (n & 3);
   uint4 A[TILES][NM];
 #pragma unroll
@@ -365,7 +371,7 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
         both_halves(m2[r], lo2, hi2);
         const float first = min_nn(lo1, hi1);
         const float second = min_nn(max_nn(lo1, hi1), min_nn(lo2, hi2));
-        const float limit = first * kMarginFirst + (X[r] * margin_x + D * kScoreTiny);
+        const float limit = first * EmMargin<D>::kFirst + (X[r] * margin_x + D * kScoreTiny);
         // NaN anywhere makes a comparison false; lanes L and L + 32 agree
         unsures[r] = ~((uint32_t)__ballot(second > limit) & (uint32_t)__ballot(X[r] <= max_norm));
         // the 8 centroids of the first block, four per half-wave
