@@ -258,7 +258,8 @@ VQ_API int vq_decode_dense(const vq_desc* desc, const void* idx_dev, const void*
  * vq_em_update (M-step, closed form below eq. "hessian_m_step"):
  *   cb_out[g][m][t] = sum h[c+t]*W[r][c+t] / sum h[c+t] over the vectors of group g with
  *   assign = m, and 0 where that sum of weights is 0 (the pseudoinverse of the text: an empty
- *   cluster becomes the zero vector).  Sums of binary32 precision or better, the same on every run.
+ *   cluster becomes the zero vector).  Sums of binary32 precision or better, added so that no order
+ *   of arrival shows: the same on every run.
  *   Assignment bytes >= k are ignored.
  * All pointers are device memory, 16-byte aligned; cb_out must not alias the inputs.
  */

@@ -11,12 +11,13 @@
 // em_assign_any_kernel: d = 1, 2 or 4 and groups of 1, 4, 8, 16, ... 256 rows x 256 columns (every group
 // shape the decode formats use), the same lane ownership.  Both take large codebooks through
 // em_assign_filtered, where the matrix cores leave 8 candidates of the k.  em_update_small_kernel / em_update_kernel: the M-step with
-// a table per lane or per wave.
+// a table per lane or per group.
 //
 // The E-step is a decision taken in floating point, so its arithmetic is fixed: binary32,
 // every operation rounded on its own (no fused multiply-add), in the order subtract, square,
 // times weight, add; the smallest distance wins, the lowest m wins a tie.  The M-step's sums are
 // deterministic (see there).
+#include <type_traits>
 #include "vq_device.h"
 #include "vq_internal.h"
 
@@ -608,172 +609,370 @@ __global__ __launch_bounds__((NCB == 1 ? em_threads<K, D>() : 256), (NCB == 1 ? 
   }
 }
 
-// M-step.  A wave walks 8-row blocks of one group (NG = 1) or owns one 8-row block that holds NG = 8 / n_rows
-// groups (groups of 1 or 4 rows); WPG waves share a group and take its 8-row blocks in turn.  Every vector
-// adds its weighted coordinates and its weights to its centroid's entries of the wave's own table in LDS,
-// in binary64: W is read once, whatever k is.  The sums of the waves (and of the copies below) are then
-// added in order, divided, and written.
-//   Bound: the reads of W and LDS atomics (2 * D per vector, 22 clocks per wave and CU; binary32 atomics take
-// 194).  us at 4096 x 4096, against a wave that kept 64 binary32 partial sums per lane and walked the group's
-// rows once per 32 / D centroids: d = 4, k = 256, 64 rows 33 (1,081); d = 2, k = 256, 128 rows 30 (899), 8 rows
-// 31 (181); k = 64, 32 rows 31 (81); 11008 x 4096, d = 4, k = 256, 256 rows: 86 (4,120).
-//   Order: a wave's additions reach an entry in program order, lanes that meet in one instruction in the
-// order in which the LDS serves them.  The terms are exact products of two binary32 numbers and the sums
-// carry 29 more bits than the result, so even another order could only show where a sum lies within 2^-40 of
-// a rounding boundary.
-//   Small tables are kept in COPIES copies, lane L using copy L % COPIES, which bounds the lanes that meet
-// in one entry; quantity-major order ([2 D][entries]) keeps the lanes of an addition on different banks.
-typedef __attribute__((address_space(3))) double* lds_f64_ptr;
-
-template <int K, int D, int NG, int WPG>
-struct EmBins {
+// M-step.  An item is a group (NG = 1) or an 8-row block that holds NG = 8 / n_rows groups (groups of 1 or 4 rows);
+// a wave holds RB 8-row blocks of it in registers (of 256 rows half at a time), and the waves of an item share its
+// tables in LDS: per centroid and coordinate the sum of h x, and that of h.
+//   Order: which of the vectors of a centroid arrives first is for the LDS to say, so the sums are in fixed point, where
+// order makes no difference.  A first pass over the registers finds the largest |x| of every entry (a maximum has no
+// order either); in the second the products h x, exact in binary64, are rounded to 2^-kBits of the power of two above
+// that |x| times the col-block's largest weight, and added as 64-bit integers, which cannot overflow.  The weights'
+// sums are exact.  That holds while the weights of the col-block (256 columns) are finite and within 2^kSpread of each
+// other, zeros aside; otherwise (kAny) both sums are scaled by an entry's own largest |h x| and |h|.  Either way a sum
+// is off by at most n * 2^(kSpread - kBits) = n * 2^-36 of its largest term, by n * 2^-45 for weights within 2^5.
+//   Skew: lanes that meet in one entry are served one after the other (64 of them: 130 clocks an atomic, 8 to 13 where
+// they spread).  A wave therefore picks the centroid that most lanes share, if 12 do, and keeps its sums in registers,
+// a binary64 sum per lane, added up over the lanes and then over the waves in a fixed order.
+//   Bound: the reads of W and the LDS (clocks a wave and CU: maximum 8, addition 13, gather 7; binary64 additions,
+// which depend on order, take 22 .. 31, binary32 ones 194).  us at 11008 x 4096, uniform assignments, one centroid for
+// all, and in brackets both with binary64 additions: d = 2, k = 64, 32 rows 67, 32 (75, 456); d = 2, k = 256, 8 rows 77,
+// 45 (72, 459), 128 rows 73, 39 (77, 501); d = 4, k = 256, 64 rows 69, 40 (81, 469), 256 rows 82, 59 (64, 270), where
+// the second half of the rows is read twice.  Weights further apart than 2^kSpread: 35 .. 64 for 28 .. 36 at 4096 x 4096.
+template <int K, int D, int NG, int GPW, int RB>
+struct EmTables {
   static constexpr int kEntries = NG * K;
   static constexpr int kCopies = kEntries >= 64 ? 1 : 64 / kEntries;
-  static constexpr int kStride = kEntries * kCopies;        // doubles per quantity
-  // Counted: in tall groups with d = 4, k = 256 the weights' sums come from counts, 16 bits per centroid and vector
-  // position of a row for the whole workgroup (at most 256 rows): one 32-bit atomic (8 clocks) in place of four
-  // binary64 ones (22 to 31 each), and den[t] = sum over the positions of count * h, exact products, at the end.
-  // M-step at 11008 x 4096, 256-row groups: 86.6 -> 65 us.  With d = 2 the counts are as large as the tables, which
-  // leaves one workgroup on a CU where two fit: 29.9 -> 31.5 us at 4096 x 4096, not done.
-  static constexpr bool kCounted = WPG == 8 && K == 256 && D == 4;
+  static constexpr int kStride = kEntries * kCopies;        // entries per quantity
+  // Counted: in tall groups with d = 4, k = 256 the weights' sums come from counts, 16 bits per centroid and vector position of a row for
+  // the whole item (at most 256 rows): one 32-bit atomic in place of eight, and den[t] = sum over the positions of
+  // count * h, exact products, at the end.
+  static constexpr bool kCounted = RB > 1 && K == 256 && D == 4;
   static constexpr int kWords = 32;                         // dwords of counts per centroid: positions i and i + 32
-  static constexpr int kTable = (kCounted ? 1 : 2) * D * kStride;   // doubles per wave
+  static constexpr int kQuantities = kCounted ? D : 2 * D;
+  static constexpr int kTable = kQuantities * kStride;      // entries per item
+  static constexpr int kMaxWaves = GPW > 1 ? GPW : 8;
+  // an item has at most 2^kLog2N vectors; 51 bits are what the conversion below takes
+  static constexpr int kLog2N = (GPW > 1 ? 11 : RB > 1 ? 16 : 14) - (D == 4 ? 2 : D == 2 ? 1 : 0);
+  static constexpr int kBits = 62 - kLog2N < 51 ? 62 - kLog2N : 51;
+  static constexpr int kSpread = kBits - 36;
 };
 
-template <int K, int D, int NG, int WPG>
-__global__ __launch_bounds__(WPG > 4 ? 64 * WPG : 256) void em_update_kernel(const float* __restrict__ W,
-                                                                             const float* __restrict__ hdiag,
-                                                                             const uint8_t* __restrict__ assign,
-                                                                             float* __restrict__ cb_out, int n_cb,
-                                                                             long long n_items, int in_features,
-                                                                             int n_rows) {
-  using Bins = EmBins<K, D, NG, WPG>;
+__device__ __forceinline__ uint32_t high_magnitude(double v) {
+  return (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32) & 0x7fffffffu;
+}
+// v * 2^(scale - 1023) + 1.5 * 2^52, rounded once: its low bits are that product as an integer (below 2^51).
+__device__ __forceinline__ unsigned long long to_fixed(double v, uint32_t scale_high) {
+  const double scale = __builtin_bit_cast(double, (uint64_t)scale_high << 32);
+  return __builtin_bit_cast(uint64_t, __builtin_fma(v, scale, 0x1.8p52)) - 0x4338000000000000ull;
+}
+__device__ __forceinline__ double from_fixed(unsigned long long sum, int scale) {
+  return (double)(long long)sum * __builtin_bit_cast(double, (uint64_t)scale << 52);
+}
+// An entry that has met infinities or NaN holds what it has met: 1 +inf, 2 -inf, 4 NaN.
+__device__ __forceinline__ void add_nonfinite(unsigned long long* sum, double v) {
+  if (!(__builtin_fabs(v) < __builtin_inf())) atomicOr(sum, v != v ? 4ull : v > 0. ? 1ull : 2ull);
+}
+__device__ __forceinline__ double from_nonfinite(unsigned long long sum) {
+  return sum == 1 ? __builtin_inf() : sum == 2 ? -__builtin_inf() : __builtin_nan("");
+}
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_zero(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u, CTRL, ROWS, 0xf, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, ROWS, 0xf, false);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+// Sum over the 64 lanes, in lane 63 (as wave_min).
+__device__ __forceinline__ double wave_sum63(double v) {
+  v += dpp_or_zero<0x111, 0xf>(v);
+  v += dpp_or_zero<0x112, 0xf>(v);
+  v += dpp_or_zero<0x114, 0xf>(v);
+  v += dpp_or_zero<0x118, 0xf>(v);
+  v += dpp_or_zero<0x142, 0xa>(v);
+  v += dpp_or_zero<0x143, 0xc>(v);
+  return v;
+}
+
+template <int K, int D, int NG, int GPW, int RB>
+__global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB>::kMaxWaves), (GPW > 1 ? 1 : 4)) void em_update_kernel(
+    const float* __restrict__ W, const float* __restrict__ hdiag, const uint8_t* __restrict__ assign,
+    float* __restrict__ cb_out, int n_cb, long long n_items, int in_features, int n_rows) {
+  using Tab = EmTables<K, D, NG, GPW, RB>;
   constexpr int V = 4 / D;                          // vectors per row and lane
-  constexpr int WAVES = WPG > 4 ? WPG : 4;
   constexpr int RPG = 8 / NG;                       // rows of an 8-row block that share a codebook
-  __shared__ __attribute__((aligned(16))) double tab_all[WAVES * Bins::kTable];
-  constexpr int CW = Bins::kWords + 1;              // a gap spreads the centroids over the banks (108 KB in all)
-  __shared__ uint32_t counts[Bins::kCounted ? K * CW : 1];
-  __shared__ double h_all[Bins::kCounted ? 256 : 1], den_all[Bins::kCounted ? K * D : 1];
+  constexpr int CW = Tab::kWords + 1;               // a gap spreads the centroids over the banks
+  constexpr uint32_t kNone = 0x100;
+  __shared__ __attribute__((aligned(16))) unsigned long long sum_all[GPW * Tab::kTable];
+  __shared__ uint32_t top_all[GPW * Tab::kTable];
+  __shared__ uint32_t counts[Tab::kCounted ? K * CW : 1];
+  __shared__ double h_all[Tab::kCounted ? 256 : 1];
+  __shared__ double hot_sums[Tab::kMaxWaves][NG][2 * D];
+  __shared__ uint32_t hot_of[Tab::kMaxWaves][NG];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int sub = wave % WPG;                       // this wave's place among those that share its group
-  double* tab = tab_all + wave * Bins::kTable;
-  const long long item_raw = (long long)blockIdx.x * (WAVES / WPG) + wave / WPG;
-  const bool present = item_raw < n_items;          // absent items repeat the last one and store nothing
-  const long long item = present ? item_raw : n_items - 1;
+  const int waves = GPW > 1 ? 1 : (int)blockDim.x / 64;   // of this item
+  const int parts = RB > 1 ? n_rows / (8 * RB * waves) : 1;   // what a wave takes one after the other, 8 * RB rows each
+  const int sub = GPW > 1 ? 0 : wave;               // this wave's place among them
+  const int slot = GPW > 1 ? wave : 0;
+  const int t_item = sub * 64 + lane, t_count = waves * 64;
+  unsigned long long* sums = sum_all + slot * Tab::kTable;
+  uint32_t* tops = top_all + slot * Tab::kTable;
+  const long long item = (long long)blockIdx.x * GPW + slot;
+  if (GPW > 1 && item >= n_items) return;           // whole waves leave; no workgroup barrier with GPW > 1
   const long long ir = item / n_cb;                 // group row, or 8-row block where that holds several groups
   const int c = (int)(item - ir * n_cb);
-  const int rows_item = NG > 1 ? 8 : n_rows;
-  const long long row0 = ir * rows_item;
+  const long long row0 = ir * (NG > 1 ? 8 : n_rows) + sub * 8 * RB;
+  auto item_sync = [] {
+    if constexpr (GPW > 1) wave_lds_sync();
+    else __syncthreads();
+  };
 
-  for (int i = lane; i < Bins::kTable / 2; i += 64) reinterpret_cast<double2*>(tab)[i] = make_double2(0., 0.);
   const float4 h4 = *reinterpret_cast<const float4*>(hdiag + (size_t)c * 256 + lane * 4);
-  const double h[4] = {h4.x, h4.y, h4.z, h4.w};
   const float* Wl = W + (size_t)row0 * in_features + (size_t)c * 256 + lane * 4;
   const uint8_t* al = assign + (size_t)row0 * (in_features / D) + (size_t)c * (256 / D) + lane * V;
-  const int copy = Bins::kCopies > 1 ? lane % Bins::kCopies : 0;
-  if constexpr (Bins::kCounted) {
-    for (int i = threadIdx.x; i < K * CW; i += 64 * WPG) counts[i] = 0u;
-    if (threadIdx.x < 256) h_all[threadIdx.x] = hdiag[(size_t)c * 256 + threadIdx.x];
-    __syncthreads();
-  } else {
-    wave_lds_sync();
+  auto load = [&](int r, float4& xr, uint32_t& ar) {
+    xr = *reinterpret_cast<const float4*>(Wl + (size_t)r * in_features);
+    const uint8_t* ap = al + (size_t)r * (in_features / D);
+    if constexpr (V == 4) ar = *reinterpret_cast<const uint32_t*>(ap);
+    else if constexpr (V == 2) ar = *reinterpret_cast<const uint16_t*>(ap);
+    else ar = *ap;
+  };
+  float4 x[8 * RB];
+  uint32_t a[8 * RB];
+  auto load_part = [&](int p) {
+#pragma unroll
+    for (int r = 0; r < 8 * RB; ++r) load(p * waves * 8 * RB + r, x[r], a[r]);
+  };
+  load_part(0);
+  for (int i = t_item; i < Tab::kTable; i += t_count) {
+    sums[i] = 0ull;
+    tops[i] = 0u;
+  }
+  if constexpr (Tab::kCounted) {
+    for (int i = t_item; i < K * CW; i += t_count) counts[i] = 0u;
+    for (int i = t_item; i < 256; i += t_count) h_all[i] = hdiag[(size_t)c * 256 + i];
+  }
+  item_sync();
+
+  const float h[4] = {h4.x, h4.y, h4.z, h4.w};
+  const int copy = Tab::kCopies > 1 ? lane % Tab::kCopies : 0;
+  // the centroid of each group that the most lanes of a row share, among a few that are asked
+  uint32_t hot[NG];
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    hot[g] = kNone;
+    int most = 11;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const uint32_t m = a[g * RPG + j % RPG] & 0xffu;
+      const uint32_t asked = (uint32_t)__builtin_amdgcn_readlane((int)m, 8 * j + 3);
+      const int n = __builtin_popcountll(__ballot(m == asked));
+      if (n > most && (K == 256 || asked < (uint32_t)K)) { most = n; hot[g] = asked; }
+    }
   }
 
-  auto load = [&](int r0, float4 (&x)[8], uint32_t (&a)[8]) {
+  // are the weights of the col-block finite and near each other (every wave of the item sees the same ones)
+  uint32_t h_exp;                                   // exponent field of the largest
+  bool any_h;
+  {
+    float big = 0.f, small = __builtin_inff();
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      x[r] = *reinterpret_cast<const float4*>(Wl + (size_t)(r0 + r) * in_features);
-      const uint8_t* ap = al + (size_t)(r0 + r) * (in_features / D);
-      if constexpr (V == 4) a[r] = *reinterpret_cast<const uint32_t*>(ap);
-      else if constexpr (V == 2) a[r] = *reinterpret_cast<const uint16_t*>(ap);
-      else a[r] = *ap;
+    for (int t = 0; t < 4; ++t) {
+      const float v = __builtin_fabsf(h[t]);
+      big = max_nn(big, v);
+      small = __builtin_fminf(small, v == 0.f ? __builtin_inff() : v);
     }
+    const bool finite = !__any(!(big < __builtin_inff()));
+    big = -wave_min(finite ? -big : 0.f);
+    small = wave_min(finite ? small : 0.f);
+    h_exp = __builtin_bit_cast(uint32_t, big) >> 23;
+    any_h = !finite || h_exp < 32 || __builtin_bit_cast(uint32_t, small) >> 23 < h_exp - Tab::kSpread;
+  }
+  constexpr int P = Tab::kBits;
+  auto finish = [&](int g, const double (&own)[2 * D]) {   // the wave's sums of the centroid kept in registers
+    if (hot[g] != kNone) {
+#pragma unroll
+      for (int q = 0; q < (Tab::kCounted ? D : 2 * D); ++q) {
+        const double sum = wave_sum63(own[q]);
+        if (lane == 63) hot_sums[wave][g][q] = sum;
+      }
+    }
+    if (lane == 63) hot_of[wave][g] = hot[g];
   };
-  auto add = [&](const float4 (&x)[8], const uint32_t (&a)[8]) {
+  auto count = [&](uint32_t m) {
+    if constexpr (Tab::kCounted) atomicAdd(counts + m * CW + (lane & 31), 1u << (16 * (lane >> 5)));
+  };
+  if (any_h) {
+    // Entries scaled by their largest |h x| and |h|, as high words of binary64 (|term| < 2^(field - 1022)).  Rare: rows are read
+    // again one by one.
+    if constexpr (NG > 1) {
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const float xr[4] = {x[r].x, x[r].y, x[r].z, x[r].w};
+      for (int g = 0; g < NG; ++g) hot[g] = kNone;
+    }
+    double own[2 * D] = {};
+    auto pass = [&](auto second) {
+#pragma unroll 1
+      for (int r = 0; r < 8 * RB * parts; ++r) {
+        float4 xr4;
+        uint32_t ar;
+        load(RB > 1 ? r / (8 * RB) * waves * 8 * RB + r % (8 * RB) : r, xr4, ar);
+        const float xr[4] = {xr4.x, xr4.y, xr4.z, xr4.w};
 #pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const uint32_t m = (a[r] >> (8 * v)) & 0xffu;
-        if (K == 256 || m < (uint32_t)K) {          // an assignment byte beyond the codebook counts nowhere
-          double* e = tab + ((r / RPG) * K + m) * Bins::kCopies + copy;
+        for (int v = 0; v < V; ++v) {
+          const uint32_t m = (ar >> (8 * v)) & 0xffu;
+          if constexpr (!decltype(second)::value) count(m);
+          if (K < 256 && m >= (uint32_t)K) continue;
+          const bool kept = NG == 1 && m == hot[0];
+          const int e = ((NG > 1 ? r / RPG : 0) * K + m) * Tab::kCopies + copy;
 #pragma unroll
-          for (int t = 0; t < D; ++t) {
-            __builtin_amdgcn_ds_atomic_fadd_f64((lds_f64_ptr)(e + t * Bins::kStride), h[v * D + t] * (double)xr[v * D + t]);
-            if constexpr (!Bins::kCounted)
-              __builtin_amdgcn_ds_atomic_fadd_f64((lds_f64_ptr)(e + (D + t) * Bins::kStride), h[v * D + t]);
+          for (int q = 0; q < Tab::kQuantities; ++q) {
+            const double hv = h[v * D + q % D], term = q < D ? hv * (double)xr[v * D + q % D] : hv;
+            const int i = e + q * Tab::kStride;
+            if constexpr (!decltype(second)::value) {
+              if (!kept) atomicMax(tops + i, high_magnitude(term));
+            } else if (kept) {
+              own[q] += term;
+            } else {
+              const uint32_t top = tops[i];
+              if (top >= 0x7ff00000u) add_nonfinite(sums + i, term);
+              else atomicAdd(sums + i, to_fixed(term, ((P + 2045u) << 20) - (top & 0x7ff00000u)));
+            }
           }
-          if constexpr (Bins::kCounted)
-            atomicAdd(counts + m * CW + (lane & 31), 1u << (16 * (lane >> 5)));
+        }
+      }
+    };
+    pass(std::false_type{});
+    item_sync();
+    pass(std::true_type{});
+#pragma unroll
+    for (int g = 0; g < NG; ++g) finish(g, own);
+  } else {
+    // Entries scaled by their largest |x|, as binary32 (|x| < 2^(field - 126)), and all by the largest weight.
+#pragma unroll 1
+    for (int p = 0; p < parts; ++p) {
+      if (p > 0) load_part(p);
+#pragma unroll
+      for (int r = 0; r < 8 * RB; ++r) {
+        const int g = NG > 1 ? r / RPG : 0;
+        const float xr[4] = {x[r].x, x[r].y, x[r].z, x[r].w};
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          const uint32_t m = (a[r] >> (8 * v)) & 0xffu;
+          count(m);
+          if (m != hot[g] && (K == 256 || m < (uint32_t)K)) {
+            uint32_t* e = tops + (g * K + m) * Tab::kCopies + copy;
+#pragma unroll
+            for (int t = 0; t < D; ++t) atomicMax(e + t * Tab::kStride, __builtin_bit_cast(uint32_t, xr[v * D + t]) & 0x7fffffffu);
+          }
         }
       }
     }
-  };
-
-  // the next 8 rows are in flight while these are added
-  float4 x0[8], x1[8];
-  uint32_t a0[8], a1[8];
-  int r0 = 8 * sub;
-  if (r0 < rows_item) {
-    load(r0, x0, a0);
-    while (true) {
-      const int r1 = r0 + 8 * WPG, r2 = r1 + 8 * WPG;
-      if (r1 < rows_item) load(r1, x1, a1);
-      add(x0, a0);
-      if (r1 >= rows_item) break;
-      if (r2 < rows_item) load(r2, x0, a0);
-      add(x1, a1);
-      if (r2 >= rows_item) break;
-      r0 = r2;
+    item_sync();
+    unsigned long long h_fixed[4];                  // |h| < 2^(h_exp - 126)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) h_fixed[t] = to_fixed((double)h[t], (P + 1149u - h_exp) << 20);
+    double own[2 * D] = {};
+#pragma unroll 1
+    for (int p = parts - 1; p >= 0; --p) {          // the part at hand first
+      if (p < parts - 1) load_part(p);
+      // what this pass needs is computed again: kept from the first, it would not fit the registers
+#pragma unroll
+      for (int r = 0; r < 8 * RB; ++r)
+        asm volatile("" : "+v"(x[r].x), "+v"(x[r].y), "+v"(x[r].z), "+v"(x[r].w), "+v"(a[r]));
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        constexpr int ROWS = NG > 1 ? RPG : 8 * RB;
+#pragma unroll
+        for (int r = g * ROWS; r < (g + 1) * ROWS; ++r) {
+          const float xr[4] = {x[r].x, x[r].y, x[r].z, x[r].w};
+#pragma unroll
+          for (int v = 0; v < V; ++v) {
+            const uint32_t m = (a[r] >> (8 * v)) & 0xffu;
+            if (m == hot[g]) {
+#pragma unroll
+              for (int t = 0; t < D; ++t) {
+                own[t] += (double)h[v * D + t] * (double)xr[v * D + t];
+                if constexpr (!Tab::kCounted) own[D + t] += (double)h[v * D + t];
+              }
+            } else if (K == 256 || m < (uint32_t)K) {
+              const int e = (g * K + m) * Tab::kCopies + copy;
+#pragma unroll
+              for (int t = 0; t < D; ++t) {
+                const int i = e + t * Tab::kStride;
+                const uint32_t top = tops[i];
+                const double hx = (double)h[v * D + t] * (double)xr[v * D + t];
+                if (top >= 0x7f800000u) add_nonfinite(sums + i, hx);
+                else atomicAdd(sums + i, to_fixed(hx, ((P + 1275u - h_exp) << 20) - ((top >> 3) & 0x0ff00000u)));
+                if constexpr (!Tab::kCounted) atomicAdd(sums + i + D * Tab::kStride, h_fixed[v * D + t]);
+              }
+            }
+          }
+        }
+        if constexpr (NG > 1) {                       // one part
+          finish(g, own);
+#pragma unroll
+          for (int q = 0; q < 2 * D; ++q) own[q] = 0.;
+        }
+      }
     }
+    if constexpr (NG == 1) finish(0, own);
   }
-  if constexpr (WPG > 1) __syncthreads();
-  else wave_lds_sync();
-  if constexpr (Bins::kCounted) {                   // one item per workgroup: all waves are here
-    const int m = threadIdx.x >> 1, half = threadIdx.x & 1;   // two lanes per centroid
-    const uint32_t* n = counts + m * CW + half * (Bins::kWords / 2);
-    const double* hp = h_all + half * 4 * (Bins::kWords / 2);
-    double den[D] = {};
+  item_sync();
+  if constexpr (Tab::kCounted) {
+    for (int i = t_item; i < 2 * K; i += t_count) {           // two lanes per centroid
+      const int m = i >> 1, half = i & 1;
+      const uint32_t* n = counts + m * CW + half * (Tab::kWords / 2);
+      const double* hp = h_all + half * 4 * (Tab::kWords / 2);
+      double den[D] = {};
 #pragma unroll 4
-    for (int i = 0; i < Bins::kWords / 2; ++i) {
-      const double lo = n[i] & 0xffffu, hi = n[i] >> 16;
+      for (int w = 0; w < Tab::kWords / 2; ++w) {
+        const double lo = n[w] & 0xffffu, hi = n[w] >> 16;
 #pragma unroll
-      for (int t = 0; t < D; ++t) den[t] += lo * hp[4 * i + t] + hi * hp[4 * i + 128 + t];
-    }
+        for (int t = 0; t < D; ++t) den[t] += lo * hp[4 * w + t] + hi * hp[4 * w + 128 + t];
+      }
 #pragma unroll
-    for (int t = 0; t < D; ++t) {
-      if (den[t] != den[t]) {                       // 0 * infinity or NaN: such a weight counts only where it is used
-        den[t] = 0.;
-        for (int i = 0; i < Bins::kWords / 2; ++i) {
-          if (n[i] & 0xffffu) den[t] += (double)(n[i] & 0xffffu) * hp[4 * i + t];
-          if (n[i] >> 16) den[t] += (double)(n[i] >> 16) * hp[4 * i + 128 + t];
+      for (int t = 0; t < D; ++t) {
+        if (den[t] != den[t]) {                     // 0 * infinity or NaN: such a weight counts only where it is used
+          den[t] = 0.;
+          for (int w = 0; w < Tab::kWords / 2; ++w) {
+            if (n[w] & 0xffffu) den[t] += (double)(n[w] & 0xffffu) * hp[4 * w + t];
+            if (n[w] >> 16) den[t] += (double)(n[w] >> 16) * hp[4 * w + 128 + t];
+          }
         }
       }
-      den[t] += __shfl_xor(den[t], 1, 64);
-      if (half == 0) den_all[m * D + t] = den[t];
+#pragma unroll
+      for (int t = 0; t < D; ++t) den[t] += __shfl_xor(den[t], 1, 64);
+      if (half == 0) {                              // in the place of the centroid's counts, which both lanes have read
+        uint32_t* out = counts + m * CW;
+#pragma unroll
+        for (int t = 0; t < D; ++t) {
+          const uint64_t u = __builtin_bit_cast(uint64_t, den[t]);
+          out[2 * t] = (uint32_t)u;
+          out[2 * t + 1] = (uint32_t)(u >> 32);
+        }
+      }
     }
-    __syncthreads();
+    item_sync();
   }
-  if (!present) return;                             // no barrier below
 
-  const double* group_tab = tab_all + (size_t)(wave - sub) * Bins::kTable;
-  for (int i = sub * 64 + lane; i < NG * K * D; i += 64 * WPG) {
-    const int e = i / D, t = i % D;
+  for (int i = t_item; i < NG * K * D; i += t_count) {
+    const int e = i / D, t = i % D, g = e / K;
     double num = 0., den = 0.;
 #pragma unroll
-    for (int w = 0; w < WPG; ++w)
-#pragma unroll
-      for (int q = 0; q < Bins::kCopies; ++q) {
-        const double* p = group_tab + w * Bins::kTable + e * Bins::kCopies + q;
-        num += p[t * Bins::kStride];
-        if constexpr (!Bins::kCounted) den += p[(D + t) * Bins::kStride];
+    for (int q = 0; q < Tab::kCopies; ++q) {
+      const int p = t * Tab::kStride + e * Tab::kCopies + q, p_h = p + D * Tab::kStride;
+      const uint32_t top = tops[p];
+      if (any_h) {
+        if (top != 0) num += top >= 0x7ff00000u ? from_nonfinite(sums[p]) : from_fixed(sums[p], (int)(top >> 20) + 1 - P);
+        if constexpr (!Tab::kCounted) {
+          const uint32_t top_h = tops[p_h];
+          if (top_h != 0) den += top_h >= 0x7ff00000u ? from_nonfinite(sums[p_h]) : from_fixed(sums[p_h], (int)(top_h >> 20) + 1 - P);
+        }
+      } else {
+        num += top >= 0x7f800000u ? from_nonfinite(sums[p]) : from_fixed(sums[p], (int)(top >> 23) + (int)h_exp + 771 - P);
+        if constexpr (!Tab::kCounted) den += from_fixed(sums[p_h], (int)h_exp + 897 - P);
       }
-    if constexpr (Bins::kCounted) den = den_all[i];
-    const long long g = NG > 1 ? (ir * NG + e / K) * n_cb + c : item;
-    cb_out[(g * K + e % K) * D + t] = den != 0. ? (float)num / (float)den : 0.f;
+    }
+    for (int w = 0; w < waves; ++w) {
+      if (hot_of[wave - sub + w][g] == (uint32_t)(e % K)) {
+        num += hot_sums[wave - sub + w][g][t];
+        if constexpr (!Tab::kCounted) den += hot_sums[wave - sub + w][g][D + t];
+      }
+    }
+    if constexpr (Tab::kCounted)
+      den = __builtin_bit_cast(double, (uint64_t)counts[e * CW + 2 * t + 1] << 32 | counts[e * CW + 2 * t]);
+    const long long gi = NG > 1 ? (ir * NG + g) * n_cb + c : item;
+    cb_out[(gi * K + e % K) * D + t] = den != 0. ? (float)num / (float)den : 0.f;
   }
 }
 
@@ -951,39 +1150,41 @@ hipError_t launch_em_assign(const vq_desc& d, const void* W, const void* hdiag, 
   return hipGetLastError();
 }
 
-template <int K, int D, int NG, int WPG>
+template <int K, int D, int NG, int GPW, int RB>
 static void launch_update(const vq_desc& d, const void* W, const void* hdiag, const void* assign, void* cb_out,
                           hipStream_t s) {
   const int n_cb = d.in_features / kGroupCols;
   const long long n_items = (long long)(d.out_features / (NG > 1 ? kGroupRows : d.group_rows)) * n_cb;
-  if constexpr (NG * K * D <= 32 && WPG == 1) {
-    hipLaunchKernelGGL((em_update_small_kernel<K, D, NG>), dim3((unsigned)n_items), dim3(64), 0, s, (const float*)W,
-                       (const float*)hdiag, (const uint8_t*)assign, (float*)cb_out, n_cb, d.in_features, d.group_rows);
-  } else {
-    constexpr int waves = WPG > 4 ? WPG : 4, items_per_wg = waves / WPG;
-    hipLaunchKernelGGL((em_update_kernel<K, D, NG, WPG>), dim3((unsigned)((n_items + items_per_wg - 1) / items_per_wg)),
-                       dim3(64 * waves), 0, s, (const float*)W, (const float*)hdiag, (const uint8_t*)assign,
-                       (float*)cb_out, n_cb, n_items, d.in_features, d.group_rows);
+  if constexpr (NG * K * D <= 32) {
+    if (d.group_rows <= 32) {
+      hipLaunchKernelGGL((em_update_small_kernel<K, D, NG>), dim3((unsigned)n_items), dim3(64), 0, s, (const float*)W,
+                         (const float*)hdiag, (const uint8_t*)assign, (float*)cb_out, n_cb, d.in_features, d.group_rows);
+      return;
+    }
   }
+  const int waves = GPW > 1 ? GPW : RB > 1 ? 8 : d.group_rows / kGroupRows;
+  hipLaunchKernelGGL((em_update_kernel<K, D, NG, GPW, RB>), dim3((unsigned)((n_items + GPW - 1) / GPW)), dim3(64 * waves), 0, s,
+                     (const float*)W, (const float*)hdiag, (const uint8_t*)assign, (float*)cb_out, n_cb, n_items,
+                     d.in_features, d.group_rows);
 }
 
-// Waves per group: one up to 16 rows (32 with a small table), 4 from 32 and 8 from 128 rows on.  A wave's table
-// is 16 * k * d bytes, at most 16 KB, and half of it beside counts (d = 4, k = 256, from 128 rows on: 108 KB in all of the CU's 160 KB).
+// Up to 8 rows a group to a wave and four waves to a workgroup; beyond that a workgroup to a group, a wave to 8 rows up to
+// 64 rows, then eight waves.
 template <int K, int D>
 static hipError_t launch_update_rows(const vq_desc& d, const void* W, const void* hdiag, const void* assign, void* cb_out,
                                hipStream_t s) {
   if (d.group_rows == 1) {
-    if constexpr (K * D <= 64) launch_update<K, D, 8, 1>(d, W, hdiag, assign, cb_out, s);
+    if constexpr (K * D <= 64) launch_update<K, D, 8, 4, 1>(d, W, hdiag, assign, cb_out, s);
     else return hipErrorInvalidValue;
   } else if (d.group_rows == 4) {
-    if constexpr (D <= 2) launch_update<K, D, 2, 1>(d, W, hdiag, assign, cb_out, s);
+    if constexpr (D <= 2) launch_update<K, D, 2, 4, 1>(d, W, hdiag, assign, cb_out, s);
     else return hipErrorInvalidValue;
-  } else if (d.group_rows < 32 || (d.group_rows == 32 && K * D <= 32)) {
-    launch_update<K, D, 1, 1>(d, W, hdiag, assign, cb_out, s);
-  } else if (d.group_rows < 128) {
-    launch_update<K, D, 1, 4>(d, W, hdiag, assign, cb_out, s);
+  } else if (d.group_rows == 8) {
+    launch_update<K, D, 1, 4, 1>(d, W, hdiag, assign, cb_out, s);
+  } else if (d.group_rows <= 64) {
+    launch_update<K, D, 1, 1, 1>(d, W, hdiag, assign, cb_out, s);
   } else {
-    launch_update<K, D, 1, 8>(d, W, hdiag, assign, cb_out, s);
+    launch_update<K, D, 1, 1, 2>(d, W, hdiag, assign, cb_out, s);
   }
   return hipGetLastError();
 }

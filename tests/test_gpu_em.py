@@ -265,11 +265,11 @@ M_SHAPES = [
 @pytest.mark.parametrize("shape", M_SHAPES, ids=str)
 def test_m_step_against_64_bit_sums_and_repeated(env, shape):
     """Bytes beyond the codebook count nowhere, the result is the same on every run, and it is as near
-    to 64-bit sums as the kernels' arithmetic allows.  A table per wave holds binary64 sums of exact
-    products: numerator, denominator and quotient are rounded once each, 3 * 2^-24 of the centroid
-    (3.1 with second-order terms) beside n * 2^-53 of the summed magnitudes.  A table per lane adds
-    binary32 products: at most n_lane + 8 roundings of 2^-24 of the magnitudes, numerator and
-    denominator alike."""
+    to 64-bit sums as the kernels' arithmetic allows.  A table per group holds sums in fixed point, n * 2^-46 or
+    better of their largest term: numerator, denominator and quotient are rounded once each, 3 * 2^-24 of
+    the centroid (3.1 with second-order terms) beside gr * 256 * 2^-53 of the summed magnitudes (an entry of these inputs
+    has fewer than 1,000 vectors).  A table per lane adds binary32 products: at most n_lane + 8 roundings of
+    2^-24 of the magnitudes, numerator and denominator alike."""
     torch, vq, vqdev = env
     out_f, in_f, k, d, gr = shape
     W, h, cb = _inputs_any(out_f, in_f, k, d, gr, 1400 + out_f + k + d, from_data=False)
@@ -332,6 +332,87 @@ def test_m_step_by_counts_at_full_positions_and_infinite_weights(env, rows):
                     num, den = (hv * x).sum(), hv.sum()
                     want = np.float32(num) / np.float32(den) if den != 0 else np.float32(0)
                     np.testing.assert_equal(got[c, m, t], want)
+
+
+# tables per group (without copies, which lanes would share by their number): four groups to a workgroup, one with waves
+# of 8 rows, and one with waves of 16 (twice with 256 rows)
+ORDER_SHAPES = [(32, 512, 64, 2, 8), (16, 256, 32, 2, 4), (16, 256, 32, 1, 1), (64, 512, 256, 2, 32), (128, 256, 64, 1, 128),
+                (256, 512, 256, 4, 256)]
+
+
+@pytest.mark.parametrize("uneven", [False, True], ids=["even weights", "uneven weights"])
+@pytest.mark.parametrize("shape", ORDER_SHAPES, ids=str)
+def test_m_step_does_not_depend_on_the_order_of_the_vectors(env, shape, uneven):
+    """The vectors of a group in another order, as the lanes of a wave might reach an entry in another order: sums that
+    cancel down to 2^-40 of their terms come out the same to the bit."""
+    torch, vq, vqdev = env
+    out_f, in_f, k, d, gr = shape
+    n_cb, rng = in_f // 256, np.random.default_rng(out_f + k + d)
+    groups, n = out_f // gr * n_cb, gr * 256 // d
+    x = rng.normal(0, 1, (groups, n, d)) * 2.0 ** rng.integers(0, 40, (groups, n, 1))
+    x[:, 1::2] = -x[:, ::2] + rng.normal(0, 1e-3, (groups, n // 2, d))       # pairs that nearly cancel
+    a = rng.integers(0, k, (groups, n // 2)).repeat(2, axis=1).astype(np.uint8)
+    h = np.ones(in_f, np.float32) * (2.0 ** rng.integers(-15, 16) if uneven else 1)
+    if uneven:
+        h[0::256] = np.float32(2.0 ** -30)              # far from the others, the same for every order (x = 0 there)
+
+    def matrix(v, width):
+        return np.ascontiguousarray(v.reshape(out_f // gr, n_cb, gr, 256 // d, width).transpose(0, 2, 1, 3, 4)
+                                    .reshape(out_f, -1))
+
+    desc = vq.make_desc(out_f, in_f, k, {16: 4, 32: 5, 64: 6, 256: 8}[k], group_rows=gr, d=d)
+    h_d, results = vqdev.to_device_bytes(h), []
+    for order in range(3):
+        p = rng.permutation(n) if order else np.arange(n)
+        W = matrix(x[:, p].astype(np.float32), d)
+        if uneven:
+            W[:, 0::256] = 0
+            if order:
+                continue
+        new = torch.full((groups, k, d), 777.0, dtype=torch.float32, device="cuda:0")
+        vq.vq_em_update(desc, vqdev.to_device_bytes(W), h_d, vqdev.to_device_bytes(matrix(a[:, p][:, :, None], 1)), new)
+        results.append(new.cpu().numpy())
+        if uneven:                                      # the rows in another order instead: columns keep their weights
+            for _ in range(2):
+                rows = np.concatenate([g * gr + rng.permutation(gr) for g in range(out_f // gr)])
+                new = torch.full((groups, k, d), 777.0, dtype=torch.float32, device="cuda:0")
+                vq.vq_em_update(desc, vqdev.to_device_bytes(W[rows]), h_d,
+                                vqdev.to_device_bytes(matrix(a[:, :, None], 1)[rows]), new)
+                results.append(new.cpu().numpy())
+    for r in results[1:]:
+        np.testing.assert_array_equal(r.view(np.uint32), results[0].view(np.uint32))
+
+
+@pytest.mark.parametrize("shape", [(64, 2, 32), (256, 2, 8), (32, 2, 8), (64, 4, 16), (256, 4, 64)], ids=str)
+def test_m_step_with_one_centroid_for_all_costs_no_more(env, shape):
+    """Assignments that meet in one entry of the table, as zeroed weights leave them, against uniform ones: 0.5 .. 1.0 of
+    the time (three to six times it while every lane added to that entry)."""
+    torch, vq, vqdev = env
+    k, d, gr = shape
+    n = 4096
+    g = torch.Generator("cuda").manual_seed(6)
+    W = torch.randn((n, n), device="cuda", generator=g) * 0.02
+    h = 0.2 + 4.8 * torch.rand(n, device="cuda", generator=g)
+    uniform = torch.randint(0, k, (n, n // d), dtype=torch.uint8, device="cuda", generator=g)
+    half = torch.where(torch.rand(uniform.shape, device="cuda", generator=g) < 0.5, torch.ones_like(uniform), uniform)
+    new = torch.empty((n // gr * 16, k, d), device="cuda")
+    desc = vq.make_desc(n, n, k, {32: 5, 64: 6, 256: 8}[k], group_rows=gr, d=d)
+
+    def us(assign):
+        best = 1e9
+        for _ in range(6):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            for _ in range(20):
+                vq.vq_em_update(desc, W, h, assign, new)
+            t1.record()
+            torch.cuda.synchronize()
+            best = min(best, t0.elapsed_time(t1) * 50)
+        return best
+
+    base = us(uniform)
+    assert us(torch.ones_like(uniform)) < 1.4 * base
+    assert us(half) < 1.6 * base
 
 
 # the codebooks that the matrix cores filter: one tile and several, one group and several per strip of rows

@@ -187,3 +187,19 @@ def test_e_step_kernel_has_no_fused_multiply_add(tmp_path):
             fused.append(line.strip())
     assert seen == 3 + 25 + 10 + 7        # d = 2, 8-row groups: k = 16, 64, 256; 25 kernels for the other (k, d, group) cases; 10 for 4-row groups; 7 for k = 32
     assert fused == []
+
+
+@pytest.mark.skipif(shutil.which(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")) is None,
+                    reason="hipcc not available")
+def test_m_step_adds_no_floating_point_in_lds(tmp_path):
+    """The M-step's sums are the same on every run: lanes that meet in one entry of a table in LDS are served in an order
+    that nothing defines, so what they add there has to be integers."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    out = tmp_path / "vq_em.s"
+    flags = [f for f in vqbuild.HIPCC_FLAGS if f != "-fPIC"]
+    cmd = [hipcc, *flags, "-S", "--cuda-device-only", "-o", str(out), os.path.join(vqbuild.CSRC, "vq_em.hip")]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    text = out.read_text()
+    assert len(re.findall(r"\bds_add_u64\b", text)) > 100      # the tables' additions are in there
+    assert re.findall(r"\b(?:ds|global|flat|buffer)_(?:pk_)?add(?:_rtn)?_f(?:16|32|64)\b|\bglobal_atomic_\w+|\bds_cmpst\w+", text) == []
