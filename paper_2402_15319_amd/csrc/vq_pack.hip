@@ -277,9 +277,9 @@ __global__ __launch_bounds__(256) void pack_tab_d1k4_kernel(const uint32_t* __re
 }
 
 // ---- k = 64 (and d = 1, k = 8): 6-bit fields, int8 tables with a scale per group, groups of 8*rpc rows ----
-// One launch for everything: workgroups [0, idx_wgs) re-pack indices, the next tab_wgs tables, the rest block
+// One launch for everything (more only beyond 2^23 workgroups): workgroups [0, idx_wgs) re-pack indices, the next tab_wgs tables, the rest block
 // codes (blockwise normalisation).  Bound: memory; per workgroup of indices 12 KB are read and written in
-// 16-byte pieces.  4096 x 11008 with blockwise normalisation: 35 -> 7.3 us (indices lane by lane in single bytes,
+// 16-byte pieces.  4096 x 11008 with blockwise normalisation: 39 -> 7.8 us (indices lane by lane in single bytes,
 // three launches, 64-bit divisions in every thread before).
 struct Pack64 {
   const uint8_t* idx_canon;
@@ -293,6 +293,7 @@ struct Pack64 {
   int32_t n_cb, rpc;
   uint32_t n_rb8, n_grow;         // 8-row blocks, rows of groups
   uint32_t idx_wgs, tab_wgs;
+  uint32_t first_wg;              // of this launch
 };
 
 // A wave owns a (8-row block, quad of col-blocks): 4 x 768 bytes of the canonical little-endian stream, which go
@@ -420,7 +421,7 @@ __device__ __forceinline__ void pack_codes64(const Pack64& a, uint32_t wg) {
 template <bool D1>
 __global__ __launch_bounds__(256) void pack64_kernel(const Pack64 a) {
   __shared__ __attribute__((aligned(16))) uint32_t stage[4][772];   // 3 KB per wave and a word behind it
-  const uint32_t wg = blockIdx.x;
+  const uint32_t wg = a.first_wg + blockIdx.x;
   if (wg < a.idx_wgs) pack_idx64(a, wg, stage);
   else if (wg < a.idx_wgs + a.tab_wgs) D1 ? pack_tab_d1k8(a, wg - a.idx_wgs) : pack_tab64(a, wg - a.idx_wgs);
   else pack_codes64(a, wg - a.idx_wgs - a.tab_wgs);
@@ -516,13 +517,19 @@ hipError_t launch_pack(const vq_desc& d, const void* idx_canon, const void* cb_c
     a.rpc = d.group_rows / kGroupRows;
     a.n_rb8 = (uint32_t)n_rb;
     a.n_grow = (uint32_t)n_grow;
-    const long long idx_slots = n_rb * n_quads, tab_slots = n_grow * n_quads;    // at most 2^27 (out * in <= 2^40)
+    const long long idx_slots = n_rb * n_quads, tab_slots = n_grow * n_quads;    // at most 2^28 (out < 2^31, out * in <= 2^40)
     a.idx_wgs = (uint32_t)((idx_slots + 3) / 4);
     a.tab_wgs = (uint32_t)(d1 ? (tab_slots + 255) / 256 : (tab_slots + 3) / 4);
     const uint32_t wgs = a.idx_wgs + a.tab_wgs + (bn ? (uint32_t)((idx_slots + 7) / 8) : 0u);
-    if (d1) hipLaunchKernelGGL(pack64_kernel<true>, dim3(wgs), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(pack64_kernel<false>, dim3(wgs), dim3(256), 0, s, a);
-    return hipGetLastError();
+    constexpr uint32_t kMost = 1u << 23;       // a launch takes fewer than 2^32 threads
+    for (; a.first_wg < wgs; a.first_wg += kMost) {
+      const dim3 grid(wgs - a.first_wg < kMost ? wgs - a.first_wg : kMost);
+      if (d1) hipLaunchKernelGGL(pack64_kernel<true>, grid, dim3(256), 0, s, a);
+      else hipLaunchKernelGGL(pack64_kernel<false>, grid, dim3(256), 0, s, a);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   }
   const int fmt = format_tag(d);
   if (fmt == kFmtK256I8 || fmt == kFmtK256I8BN) {   // indices as for k = 256, gathered from groups of rpc 8-row blocks; tables copied

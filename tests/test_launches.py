@@ -137,3 +137,17 @@ def test_wide_gemv_splits(launches):
     wrong = [(w, ls[0][1][0]) for w, (st, ls) in zip(WIDE, got)
              if st != 0 or len(ls) != 1 or ls[0][1][0] != sum(w[1]) // 64 * w[4] or f"Li{w[4]}E" not in ls[0][0]]
     assert wrong == []
+
+
+@pytest.mark.parametrize("fmt", [K64, K64_BN, (8, 2, 64, vq.VQ_I8_BN), (8, 1, 8, vq.VQ_I8), (8, 1, 8, vq.VQ_I8_BN)], ids=str)
+def test_re_layout_of_the_6_bit_formats_keeps_to_the_size_of_a_launch(launches, fmt):
+    """A launch takes fewer than 2^32 threads; matrices that fit the memory (2^28 rows x 256 columns: 160 GB in all with
+    block scales) are re-packed in several.  Workgroups: 4 (8-row block, quad)s of indices or of table records (256
+    records with d = 1), 8 of block codes."""
+    rows = 2 ** 28
+    slots, tables = rows // 8, rows // fmt[0]
+    want = slots // 4 + (tables // 256 if fmt[1] == 1 else tables // 4) + (slots // 8 if fmt[3] == vq.VQ_I8_BN else 0)
+    (status, ls), (status1, ls1) = launches([("pack", rows, 256, *fmt), ("pack", 4096, 11008, *fmt)])
+    assert status == 0 and sum(l[1][0] for l in ls) == want
+    assert all(l[1][0] * l[2] < 2 ** 32 for l in ls)
+    assert status1 == 0 and len(ls1) == 1
