@@ -126,7 +126,7 @@ _torch = None
 
 def _stream(stream) -> int:
     # The current stream's handle without building a Stream object: 0.3 us of a call's host time in place
-    # of 2.8.
+    # of 2.8.  A torch without these two functions (they are not part of its public interface) gets the Stream object.
     if stream is None:
         global _torch
         if _torch is None:
@@ -134,7 +134,10 @@ def _stream(stream) -> int:
             _torch = torch
         if not _torch.cuda.is_initialized():
             return _torch.cuda.current_stream().cuda_stream
-        return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
+        try:
+            return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
+        except AttributeError:
+            return _torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
