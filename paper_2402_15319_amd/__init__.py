@@ -224,7 +224,10 @@ def _lora_array(As, Bs, ranks: Sequence[int]):
     """The adapters' descriptors as one array, filled from packed bytes (a structure object per adapter
     costs about 1 us)."""
     n = len(ranks)
-    packed = b"".join([_LORA_STRUCT.pack(_ptr(a), _ptr(b), r, 0) for a, b, r in zip(As, Bs, ranks)])
+    try:
+        packed = b"".join([_LORA_STRUCT.pack(_ptr(a), _ptr(b), r, 0) for a, b, r in zip(As, Bs, ranks)])
+    except struct.error:   # a value that does not fit its field: as a structure takes it, for the library to judge
+        return (VQLoraDesc * n)(*[VQLoraDesc(_ptr(a), _ptr(b), r, 0) for a, b, r in zip(As, Bs, ranks)])
     return (VQLoraDesc * n).from_buffer_copy(packed)
 
 
