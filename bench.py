@@ -33,8 +33,8 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 # build of the kernel: it is reported only while the library still has the version it was
 # measured on (vq_version() is raised whenever a kernel, the device layout or the set of entry
 # points changes).
-TRAFFIC_BYTES_PER_LAUNCH = 1857737421
-TRAFFIC_MEASURED_ON_VERSION = 2
+TRAFFIC_BYTES_PER_LAUNCH = 1857703283
+TRAFFIC_MEASURED_ON_VERSION = 3
 MFMA_F16_PEAK_TFLOPS = 2500.0  # MI355X published dense fp16 matrix peak
 FP32_VECTOR_PEAK_TFLOPS = 157.3   # published fp32 vector peak (fused multiply-add = 2 flops)
 

@@ -22,3 +22,11 @@ def test_algorithmic_bytes_of_the_headline_pass():
     for (_, _, s, _) in workloads.llama7b_pass_shapes():
         total += sum(workloads.canonical_sizes(s)) + 2 * s.in_features + 2 * s.out_features
     assert total == 1826373632
+
+
+def test_the_library_version_says_that_kernels_changed_and_the_traffic_belongs_to_it():
+    """The version is raised whenever a kernel of the decode path is rewritten (3: narrow launch arguments, workgroups that
+    share 64 rows, eight waves on small batched products), and the measured traffic is quoted for one version only."""
+    import bench
+    import paper_2402_15319_amd as vq
+    assert vq.vq_version() == bench.TRAFFIC_MEASURED_ON_VERSION == 3
