@@ -28,7 +28,7 @@ namespace {
 //   s_m = sum_t h_t * c_m[t]^2 - 2 * (h_t * x_t) * c_m[t],
 // is a product of 2 * D features of the vector (h_t, h_t x_t) with 2 * D features of the centroid.  Each
 // feature is split into two fp16 halves and all four half products are taken (K = 16 for d = 2, twice 16
-// for d = 4, half of 16 for d = 1): v_mfma_f32_32x32x16_f16 gives the scores of 32 centroids x 32 vectors.
+// for d = 4): v_mfma_f32_32x32x16_f16 gives the scores of 32 centroids x 32 vectors.
 // Powers of two bring the largest coordinate of the codebook and the largest weight of each vector to
 // [2^5, 2^6).  The scores are only a filter.  Per vector the smallest block of 8 centroids and the second
 // smallest are kept (7 instructions per 8 scores, the block number in the low bits of the score); if the
@@ -127,21 +127,15 @@ __device__ __forceinline__ void load_coords(const float* p, float (&v)[D]) {
   if constexpr (D == 4) {
     const float4 t = *reinterpret_cast<const float4*>(p);
     v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-  } else if constexpr (D == 2) {
+  } else {
     const float2 t = *reinterpret_cast<const float2*>(p);
     v[0] = t.x; v[1] = t.y;
-  } else {
-    v[0] = *p;
   }
 }
 
-// The q-th coordinate whose features a half-wave holds: d = 4: 2 * half + q; d = 2: half; d = 1: the lower half only.
+// The q-th coordinate whose features a half-wave holds: d = 4: 2 * half + q; d = 2: half.
 template <int D>
-__device__ __forceinline__ float own_coord(const float (&v)[D], int q, int half) {
-  const float lower = v[D == 4 ? q : 0];
-  const float upper = D == 1 ? 0.f : v[D == 4 ? D / 2 + q : D - 1];
-  return half ? upper : lower;
-}
+__device__ __forceinline__ float own_coord(const float (&v)[D], int q, int half) { return half ? v[D / 2 + q] : v[q]; }
 
 // Where centroid m lies in LDS (floats): a gap after every eighth spreads the blocks that lanes read over the banks.
 template <int D>
@@ -209,9 +203,10 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
                                                    const float* __restrict__ cb, uint8_t* __restrict__ assign,
                                                    int n_cb, int in_features, int group_rows) {
 #pragma clang fp contract(off)
+  static_assert((D == 2 || D == 4) && K % 64 == 0, "half-waves share the coordinates, lanes the centroids");
   constexpr int TILES = K / 32;
   constexpr int SETS = 8 / D;                 // steps per row
-  constexpr int NM = D == 4 ? 2 : 1;          // coordinates per half-wave = matrix instructions per tile
+  constexpr int NM = D / 2;                   // coordinates per half-wave = matrix instructions per tile
   constexpr uint32_t kBlockMask = 4 * TILES - 1;   // block number: tile, half-wave, upper or lower 8
   constexpr int R = D == 4 ? 2 : 4;           // steps filtered together
   // Undecided vectors of a step from which the whole codebook is faster: a vector taken by itself costs 25, 17, 13 us
@@ -229,14 +224,12 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
   {
     const float* cg = cb + ((long long)((uint32_t)row0 / (uint32_t)group_rows) * n_cb + c) * (K * D);
 #pragma unroll
-    for (int i = 0; i < (K + 63) / 64; ++i) {
+    for (int i = 0; i < K / 64; ++i) {
       const int m = i * 64 + lane;
-      if (m < K) {
-        float v[D];
-        load_coords<D>(cg + m * D, v);
+      float v[D];
+      load_coords<D>(cg + m * D, v);
 #pragma unroll
-        for (int t = 0; t < D; ++t) cbs[em_place<D>(m) + t] = v[t];
-      }
+      for (int t = 0; t < D; ++t) cbs[em_place<D>(m) + t] = v[t];
     }
   }
   const float* Wb = W + (size_t)row0 * in_features + (size_t)c * 256;
@@ -252,9 +245,9 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
   // coordinate: (h hi, h hi, h lo, h lo, hx hi, hx hi, hx lo, hx lo) against (c^2 hi, c^2 lo, twice; -2c hi, -2c lo, twice).
   float top = 0.f;                            // largest coordinate of the codebook (NaN if there is one)
 #pragma unroll
-  for (int i = 0; i < (K + 63) / 64; ++i)
+  for (int i = 0; i < K / 64; ++i)
 #pragma unroll
-    for (int t = 0; t < D; ++t) top = max_nn(top, __builtin_fabsf(cbs[em_place<D>((i * 64 + lane) % K) + t]));
+    for (int t = 0; t < D; ++t) top = max_nn(top, __builtin_fabsf(cbs[em_place<D>(i * 64 + lane) + t]));
   const bool nan_c = __any(!(top >= 0.f));
   top = -wave_min(nan_c ? 0.f : -top);
   const bool ok_c = !nan_c && top >= 0x1p-40f && top <= 0x1p20f;
@@ -266,8 +259,7 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
   for (int t = 0; t < TILES; ++t)
 #pragma unroll
     for (int q = 0; q < NM; ++q) {
-      const bool has = D > 1 || half == 0;    // d = 1: the upper half-wave has no coordinate
-      const float cv = has ? c_scale * cbs[em_place<D>(32 * t + row_centroid) + (D > 1 ? NM * half + q : 0)] : 0.f;
+      const float cv = c_scale * cbs[em_place<D>(32 * t + row_centroid) + NM * half + q];
       const uint32_t sq = split_once(cv * cv), mul = split_once(-2.f * cv);
       A[t][q] = make_uint4(sq, sq, mul, mul);
     }
