@@ -611,11 +611,13 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_tiny_kernel(const uint8_t* __
                                                            int ldx, void* __restrict__ Y, int ldy,
                                                            int y_f32, int n_rb, int n_cb, int rpc) {
   __shared__ __attribute__((aligned(16))) uint16_t Wt_all[NW][16 * WS];
-  // [k][16 columns], as in memory; a quarter of a col-block at a time, which keeps the workgroup
-  // under a third of the LDS for every format but d = 4 (three workgroups per CU; fewer than 170
-  // registers, so the registers allow three as well)
+  // [k][16 columns], as in memory; a quarter of a col-block at a time, which keeps four waves under a
+  // third of the LDS for every format but d = 4 (three workgroups per CU; fewer than 170
+  // registers, so the registers allow three as well).  Eight waves take 83 KB and more, up to all 160 KB
+  // with d = 4: one workgroup per CU, which is all they are launched for.
   __shared__ __attribute__((aligned(16))) uint16_t Xt_all[NW][kTinyXRows * 16];
   __shared__ __attribute__((aligned(16))) uint32_t lut_all[NW][2 * lut_dwords<K>()];
+  static_assert(sizeof(Wt_all) + sizeof(Xt_all) + sizeof(lut_all) <= 160 * 1024, "the LDS of a CU");
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
