@@ -14,9 +14,11 @@ FORMATS = {
     "d4": dict(k=256, index_bits=8, group_rows=64, d=4, int8_tables=True),
 }
 # (rows in multiples of the group height's, columns, batch): one col-block a wave (4 and 5 of them: four and
-# eight waves), more col-blocks than waves, an odd number of row-blocks, batches that are not multiples of 16,
-# and more than two workgroups per CU
-SIZES = [(1, 1024, 3), (1, 1280, 16), (3, 2304, 17), (5, 2816, 40), (2, 4352, 130), (33, 1280, 200)]
+# eight waves), more col-blocks than waves, an odd number of row-blocks, batches that are not multiples of 16;
+# then more than one 16 x 16 tile per CU and at most two (33 groups of 8 rows, 323 tiles with four waves that walk
+# nine col-blocks; the same columns with the taller groups pass the line), and up to three for 17..32 columns
+SIZES = [(1, 1024, 3), (1, 1280, 16), (3, 2304, 17), (5, 2816, 40), (2, 4352, 130), (33, 1280, 200),
+         (33, 2304, 300), (9, 2304, 250), (129, 2304, 32)]
 
 
 @pytest.mark.parametrize("size", SIZES, ids=str)
