@@ -610,7 +610,7 @@ __global__ __launch_bounds__((NCB == 1 ? em_threads<K, D>() : 256), (NCB == 1 ? 
 // that |x| times the col-block's largest weight, and added as 64-bit integers, which cannot overflow.  The weights'
 // sums are exact.  That holds while the weights of the col-block (256 columns) are finite and within 2^kSpread of each
 // other, zeros aside; otherwise (kAny) both sums are scaled by an entry's own largest |h x| and |h|.  Either way a sum
-// is off by at most n * 2^(kSpread - kBits) = n * 2^-36 of its largest term, by n * 2^-45 for weights within 2^5.
+// is off by at most n * 2^(kSpread - kBits) = n * 2^-36 of its largest term, by n * 2^-41 or less for weights within 2^5.
 //   Skew: lanes that meet in one entry are served one after the other (64 of them: 130 clocks an atomic, 8 to 13 where
 // they spread).  A wave therefore picks the centroid that most lanes share, if 12 do, and keeps its sums in registers,
 // a binary64 sum per lane, added up over the lanes and then over the waves in a fixed order.
