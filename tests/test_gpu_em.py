@@ -383,6 +383,48 @@ def test_m_step_does_not_depend_on_the_order_of_the_vectors(env, shape, uneven):
         np.testing.assert_array_equal(r.view(np.uint32), results[0].view(np.uint32))
 
 
+@pytest.mark.parametrize("uneven", [False, True], ids=["even weights", "uneven weights"])
+@pytest.mark.parametrize("shape", [(32, 512, 64, 2, 8), (16, 256, 32, 2, 4), (64, 512, 256, 2, 32), (64, 256, 16, 1, 64),
+                                   (256, 256, 256, 4, 256)], ids=str)
+def test_m_step_of_infinities_and_tiny_values(env, shape, uneven):
+    """Infinite and NaN values of W show in the centroids they are assigned to, as in a floating-point sum, and in no
+    other; subnormal and zero values count; a centroid for most vectors (kept in registers) beside the rest."""
+    torch, vq, vqdev = env
+    out_f, in_f, k, d, gr = shape
+    W, h, cb = _inputs_any(out_f, in_f, k, d, gr, 1700 + out_f + k, from_data=False)
+    rng = np.random.default_rng(out_f + 2 * k + d)
+    if uneven:
+        h = (h * 10.0 ** rng.uniform(-4, 4, in_f)).astype(np.float32)
+    kind = rng.random(W.shape)
+    W[kind < 0.004], W[(kind > 0.01) & (kind < 0.014)], W[(kind > 0.02) & (kind < 0.022)] = np.inf, -np.inf, np.nan
+    W[(kind > 0.1) & (kind < 0.3)] *= np.float32(1e-37)
+    W[kind > 0.8] = 0
+    assign = rng.integers(0, k, (out_f, in_f // d)).astype(np.uint8)
+    assign[rng.random(assign.shape) < 0.5] = 3
+    desc = vq.make_desc(out_f, in_f, k, {16: 4, 32: 5, 64: 6, 256: 8}[k], group_rows=gr, d=d)
+    new = torch.full(cb.shape, 777.0, dtype=torch.float32, device="cuda:0")
+    vq.vq_em_update(desc, vqdev.to_device_bytes(W), vqdev.to_device_bytes(h), vqdev.to_device_bytes(assign), new)
+    got, n_cb = new.cpu().numpy(), in_f // 256
+    for g in range(cb.shape[0]):
+        gi, c = divmod(g, n_cb)
+        x = W[gi * gr:(gi + 1) * gr, c * 256:(c + 1) * 256].astype(np.float64).reshape(-1, d)
+        hv = np.broadcast_to(h[c * 256:(c + 1) * 256].astype(np.float64), (gr, 256)).reshape(-1, d)
+        a = assign[gi * gr:(gi + 1) * gr, c * (256 // d):(c + 1) * (256 // d)].reshape(-1)
+        for t in range(d):
+            with np.errstate(invalid="ignore"):
+                num = np.bincount(a, hv[:, t] * x[:, t], 256)[:k]
+                mag = np.bincount(a, hv[:, t] * np.abs(x[:, t]), 256)[:k]
+                den = np.bincount(a, hv[:, t], 256)[:k]
+                want = np.where(den != 0, num / np.where(den != 0, den, 1), 0)
+            finite = np.isfinite(want)
+            np.testing.assert_array_equal(got[g, ~finite, t], want[~finite].astype(np.float32))
+            # three roundings to binary32, n * 2^-36 of the magnitudes at most, and what the rounding of a subnormal
+            # numerator (2^-150) or quotient leaves
+            safe = np.where(den != 0, den, 1)
+            bound = 3.1 * 2.0 ** -24 * np.abs(want) + (2.1 * (gr * 256 // d) * 2.0 ** -36 * mag + 2.0 ** -149) / safe + 2.0 ** -149
+            assert np.all(np.abs(got[g, finite, t] - want[finite]) <= bound[finite])
+
+
 @pytest.mark.parametrize("shape", [(64, 2, 32), (256, 2, 8), (32, 2, 8), (64, 4, 16), (256, 4, 64)], ids=str)
 def test_m_step_with_one_centroid_for_all_costs_no_more(env, shape):
     """Assignments that meet in one entry of the table, as zeroed weights leave them, against uniform ones: 0.5 .. 1.0 of
@@ -499,4 +541,4 @@ def test_undecided_vectors_cost_no_more_than_a_loop_over_the_codebook(env, shape
     zeros = h.clone()
     zeros[::2] = 0
     ratio = [us(desc, h, tied) / (per_coordinate * k * n * n), us(desc, zeros, cb) / (per_coordinate * k * n * n)]
-    assert max(ratio) < 1.1, ratio
+    assert max(ratio) < 1.2, ratio      # a fifth above the largest for boxes that differ
