@@ -670,19 +670,26 @@ template <int CTRL> __device__ __forceinline__ float dpp_read(float v) {
       float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
 }
 __device__ __forceinline__ float wave_reduce8(const float (&a)[8], int lane) {
-  float b[4], c[2];
+  float lo[4], hi[4], b[4], c[2];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    float lo = a[i], hi = a[i + 4];
-    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(lo), "+v"(hi));
-    b[i] = lo + hi;            // lanes 0..31: row i, lanes 32..63: row i + 4
+    lo[i] = a[i];
+    hi[i] = a[i + 4];
   }
+  asm volatile("s_nop 1\n\t"
+               "v_permlane32_swap_b32 %0, %4\n\t"
+               "v_permlane32_swap_b32 %1, %5\n\t"
+               "v_permlane32_swap_b32 %2, %6\n\t"
+               "v_permlane32_swap_b32 %3, %7\n\ts_nop 1"
+               : "+v"(lo[0]), "+v"(lo[1]), "+v"(lo[2]), "+v"(lo[3]), "+v"(hi[0]), "+v"(hi[1]), "+v"(hi[2]), "+v"(hi[3]));
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    float lo = b[i], hi = b[i + 2];
-    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(lo), "+v"(hi));
-    c[i] = lo + hi;            // even rows of 16 lanes: row i (+4), odd rows: row i + 2 (+4)
-  }
+  for (int i = 0; i < 4; ++i) b[i] = lo[i] + hi[i];   // lanes 0..31: row i, lanes 32..63: row i + 4
+  asm volatile("s_nop 1\n\t"
+               "v_permlane16_swap_b32 %0, %2\n\t"
+               "v_permlane16_swap_b32 %1, %3\n\ts_nop 1"
+               : "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]));
+#pragma unroll
+  for (int i = 0; i < 2; ++i) c[i] = b[i] + b[i + 2];   // even rows of 16 lanes: row i (+4), odd rows: row i + 2 (+4)
   const bool up = lane & 8;
   const float send = up ? c[0] : c[1];
   const float keep = up ? c[1] : c[0];

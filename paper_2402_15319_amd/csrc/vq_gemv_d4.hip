@@ -40,7 +40,7 @@ struct D4Step {
 template <bool LORA, int MODE, int CAP, int KS>
 __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LORA, CAP>::type arg) {
   constexpr bool F16 = MODE == 1, BN = MODE == 2;
-  const GemvBatchT<CAP>& batch = base_of(arg);
+  const auto& batch = base_of(arg);
   constexpr int RBW = 8 / KS, THREADS = 512 / KS;   // row-blocks of a workgroup; threads that share tables
   __shared__ __attribute__((aligned(16))) uint2 tabs_all[KS][2][2][256];   // [buffer][col-block of the pair][entry]
   __shared__ uint32_t levs_all[KS][2][2][16];                               // BN: the tables' levels, the value in both halves
@@ -49,16 +49,16 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int item = (int)blockIdx.x / KS;
   const int pi = find_problem(batch, item);
-  const GemvProblem& P = batch.p[pi];
+  const GemvItem P = item_of(batch, pi);
   const int oct = item - P.wg_begin;                // which 64 rows
   const int split = KS == 1 ? 0 : wave / RBW;       // which pairs of col-blocks
   auto& tabs = tabs_all[split];
   auto& levs = levs_all[split];
   const int n_cb = P.n_cb, n_pairs = (n_cb + 1) >> 1;
   const int rb = oct * 8 + (KS == 1 ? wave : ((int)blockIdx.x - item * KS) * RBW + wave % RBW);   // n_rb is a multiple of 8 (groups are >= 64 rows)
-  const long long grow = (long long)(oct * 8) / P.rb_per_cb;
+  const long long grow = (oct * 8) >> P.cb_log2;
   const uint8_t* tab = reinterpret_cast<const uint8_t*>(P.cb);
-  const long long n_groups = (long long)(P.n_rb / P.rb_per_cb) * n_cb;
+  const long long n_groups = (long long)(P.n_rb >> P.cb_log2) * n_cb;
   const uint16_t* scales = reinterpret_cast<const uint16_t*>(tab + n_groups * 1024);   // int8 tables only
   const uint16_t* levels = reinterpret_cast<const uint16_t*>(tab + wide_bn_level_offset((size_t)n_groups, 1024));
   const uint8_t* codes_lane = tab + wide_bn_code_offset((size_t)n_groups, 1024) + (size_t)rb * n_pairs * 64 + (lane >> 3) * 8;
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
   if constexpr (LORA) v += lora_term(lb, tv);
   if ((lane & 7) == 0) {
     const size_t o = (size_t)rb * 8 + (lane >> 3);
-    if (batch.y_f32) reinterpret_cast<float*>(P.y)[o] = v;
+    if (P.y_f32) reinterpret_cast<float*>(P.y)[o] = v;
     else reinterpret_cast<_Float16*>(P.y)[o] = (_Float16)v;
   }
 }
@@ -182,7 +182,7 @@ struct K256Step {
 // BN: with blockwise normalisation; the plain C++ inner block replaces the hand-scheduled one.
 template <bool LORA, bool BN, int CAP, int KS>
 __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf<LORA, CAP>::type arg) {
-  const GemvBatchT<CAP>& batch = base_of(arg);
+  const auto& batch = base_of(arg);
   constexpr int RBW = 8 / KS, THREADS = 512 / KS;   // row-blocks of a workgroup; threads that share tables
   __shared__ __attribute__((aligned(16))) uint32_t tabs_all[KS][2][2][256];   // [buffer][col-block of the pair][entry]
   __shared__ uint32_t levs_all[KS][2][2][16];                                  // BN: the tables' levels, the value in both halves
@@ -191,16 +191,16 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int item = (int)blockIdx.x / KS;
   const int pi = find_problem(batch, item);
-  const GemvProblem& P = batch.p[pi];
+  const GemvItem P = item_of(batch, pi);
   const int oct = item - P.wg_begin;                // which 64 rows
   const int split = KS == 1 ? 0 : wave / RBW;       // which pairs of col-blocks
   auto& tabs = tabs_all[split];
   auto& levs = levs_all[split];
   const int n_cb = P.n_cb, n_pairs = (n_cb + 1) >> 1;
   const int rb = oct * 8 + (KS == 1 ? wave : ((int)blockIdx.x - item * KS) * RBW + wave % RBW);   // n_rb is a multiple of 8 (groups are >= 64 rows)
-  const long long grow = (long long)(oct * 8) / P.rb_per_cb;
+  const long long grow = (oct * 8) >> P.cb_log2;
   const uint8_t* tab = reinterpret_cast<const uint8_t*>(P.cb);
-  const long long n_groups = (long long)(P.n_rb / P.rb_per_cb) * n_cb;
+  const long long n_groups = (long long)(P.n_rb >> P.cb_log2) * n_cb;
   const uint16_t* scales = reinterpret_cast<const uint16_t*>(tab + n_groups * 512);
   const uint16_t* levels = reinterpret_cast<const uint16_t*>(tab + wide_bn_level_offset((size_t)n_groups, 512));
   const uint8_t* codes_lane = tab + wide_bn_code_offset((size_t)n_groups, 512) + (size_t)rb * n_pairs * 64 + (lane >> 3) * 8;
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
   if constexpr (LORA) v += lora_term(lb, tv);
   if ((lane & 7) == 0) {
     const size_t o = (size_t)rb * 8 + (lane >> 3);
-    if (batch.y_f32) reinterpret_cast<float*>(P.y)[o] = v;
+    if (P.y_f32) reinterpret_cast<float*>(P.y)[o] = v;
     else reinterpret_cast<_Float16*>(P.y)[o] = (_Float16)v;
   }
 }

@@ -354,9 +354,31 @@ template <> struct Chunk<kFmtK64BN> : Chunk64T<1> {};
 template <> struct Chunk<kFmtD1K8> : Chunk64T<2> {};
 template <> struct Chunk<kFmtD1K8BN> : Chunk64T<3> {};
 
-// Strip (row-block rb, K-split `split` of `splits`) of problem P; may be empty.
+// One product of a launch, by value; rb_per_cb and splits of the table as shift counts.
+struct GemvItem {
+  const uint8_t* idx;
+  const uint32_t* cb;
+  const uint16_t* x;
+  void* y;
+  int n_rb, n_cb, wg_begin, splits_log2, cb_log2, y_f32;
+};
+__device__ __forceinline__ int log2_dev(int v) { return v > 1 ? 31 - __builtin_clz((uint32_t)v) : 0; }
+template <int CAP> __device__ __forceinline__ GemvItem item_of(const GemvBatchT<CAP>& b, int pi) {
+  const GemvProblem& q = b.p[pi];
+  return {q.idx, q.cb, q.x, q.y, q.n_rb, q.n_cb, q.wg_begin, log2_dev(q.splits), log2_dev(q.rb_per_cb), b.y_f32};
+}
+__device__ __forceinline__ GemvItem item_of(const GemvFew& b, int pi) {
+  const FewProblem& q = b.p[pi];
+  const GemvItem it = {q.idx, q.cb, q.x, q.y, q.n_rb, q.n_cb, q.wg_begin, q.splits_log2, q.cb_log2, q.y_f32};
+  // all of it at once: the compiler would fetch each field where it is used, one round trip after the other
+  asm volatile("" : : "s"(it.idx), "s"(it.cb), "s"(it.x), "s"(it.y), "s"(it.n_rb), "s"(it.n_cb), "s"(it.wg_begin),
+               "s"(it.splits_log2), "s"(it.cb_log2), "s"(it.y_f32));
+  return it;
+}
+
+// Strip (row-block rb, K-split `split` of 2^splits_log2) of problem P; may be empty.
 template <int K>
-__device__ __forceinline__ Strip make_strip(const GemvProblem& P, int rb, int split, int splits) {
+__device__ __forceinline__ Strip make_strip(const GemvItem& P, int rb, int split, int splits_log2) {
   Strip S;
   const int n_cb = P.n_cb;
   S.x = P.x;
@@ -389,34 +411,34 @@ __device__ __forceinline__ Strip make_strip(const GemvProblem& P, int rb, int sp
         S.codes_rb = tb + k16bn_code_offset(n_slots) + (size_t)rb * n_pairs * 64;
       }
     }
-    S.u = (n_pairs * split) / splits;
-    S.u_end = (n_pairs * (split + 1)) / splits;
+    S.u = (n_pairs * split) >> splits_log2;
+    S.u_end = (n_pairs * (split + 1)) >> splits_log2;
     S.chunks_left = (S.u_end - S.u + 3) >> 2;
   } else if (K == kFmtD1K4) {   // pairs as for k = 16; two 48-byte table records per pair
     const int n_pairs = k16_pairs(n_cb);
     S.idx_rb = P.idx + (size_t)rb * n_pairs * 1024;
     S.cb_rb = P.cb + (size_t)rb * n_pairs * (2 * kD1K4SlotTabBytes / 4);
-    S.u = (n_pairs * split) / splits;
-    S.u_end = (n_pairs * (split + 1)) / splits;
+    S.u = (n_pairs * split) >> splits_log2;
+    S.u_end = (n_pairs * (split + 1)) >> splits_log2;
     S.chunks_left = (S.u_end - S.u + 1) >> 1;
   } else if (K == 64 || K == kFmtK64BN || K == kFmtD1K8 || K == kFmtD1K8BN) {
     const int n_quads = k64_quads(n_cb);
     constexpr int tab_bytes = K == 64 ? kK64QuadTabBytes : K == kFmtD1K8 ? kD1K8QuadTabBytes
                               : K == kFmtD1K8BN ? kD1K8NQuadTabBytes : kK64NQuadTabBytes;
     S.idx_rb = P.idx + (size_t)rb * n_quads * kK64QuadIdxBytes;
-    S.cb_rb = P.cb + (size_t)(rb / P.rb_per_cb) * n_quads * (tab_bytes / 4);
+    S.cb_rb = P.cb + (size_t)(rb >> P.cb_log2) * n_quads * (tab_bytes / 4);
     if (K == kFmtK64BN || K == kFmtD1K8BN)   // the codes follow the table records of all group rows
       S.codes_rb = reinterpret_cast<const uint8_t*>(P.cb) +
-                   (size_t)(P.n_rb / P.rb_per_cb) * n_quads * tab_bytes +
+                   (size_t)(P.n_rb >> P.cb_log2) * n_quads * tab_bytes +
                    (size_t)rb * n_quads * kK64NQuadCodeBytes;
-    S.u = (n_quads * split) / splits;
-    S.u_end = (n_quads * (split + 1)) / splits;
+    S.u = (n_quads * split) >> splits_log2;
+    S.u_end = (n_quads * (split + 1)) >> splits_log2;
     S.chunks_left = S.u_end - S.u;
   } else {
     S.idx_rb = P.idx + (size_t)rb * n_cb * 1024;
     S.cb_rb = P.cb + (size_t)rb * n_cb * (K == kFmtD1K16 ? 8 : 256);   // dwords per group's codebook
-    S.u = (n_cb * split) / splits;
-    S.u_end = (n_cb * (split + 1)) / splits;
+    S.u = (n_cb * split) >> splits_log2;
+    S.u_end = (n_cb * (split + 1)) >> splits_log2;
     S.chunks_left = (S.u_end - S.u + 1) >> 1;
   }
   return S;
@@ -439,8 +461,12 @@ __device__ __forceinline__ void store_rows(void* y, int y_f32, int rb, int lane,
 // the same three lane exchanges that end wave_reduce8.
 template <bool LORA, int CAP = kMaxProblemsPerLaunch> struct BatchOf { using type = GemvBatchT<CAP>; };
 template <int CAP> struct BatchOf<true, CAP> { using type = GemvBatchLoraT<CAP>; };
+template <> struct BatchOf<false, kFewProblems> { using type = GemvFew; };
+template <> struct BatchOf<true, kFewProblems> { using type = GemvFewLora; };
 template <int CAP> __device__ __forceinline__ const GemvBatchT<CAP>& base_of(const GemvBatchT<CAP>& b) { return b; }
 template <int CAP> __device__ __forceinline__ const GemvBatchT<CAP>& base_of(const GemvBatchLoraT<CAP>& b) { return b.base; }
+__device__ __forceinline__ const GemvFew& base_of(const GemvFew& b) { return b; }
+__device__ __forceinline__ const GemvFew& base_of(const GemvFewLora& b) { return b.base; }
 
 __device__ __forceinline__ uint4 lora_load_b(const LoraProblem& L, const void* fallback, int rb, int lane) {
   const int r = (lane >> 3) & 7, j = lane & 7;
@@ -480,6 +506,11 @@ __device__ __forceinline__ int find_problem(const GemvBatchT<CAP>& batch, int it
     if (batch.p[mid].wg_begin <= item) lo = mid; else hi = mid;
   }
   return lo;
+}
+
+__device__ __forceinline__ int find_problem(const GemvFew& b, int item) {
+  static_assert(kFewProblems == 4, "");
+  return (item >= b.begin[1]) + (item >= b.begin[2]) + (item >= b.begin[3]);
 }
 
 // ---- persistent streaming kernel -------------------------------------------
@@ -858,9 +889,9 @@ __global__ __launch_bounds__(kStreamWaves * 64) void gemv_stream_kernel(const ty
   for (int r = 0; r < 8; ++r) acc[r] = 0.f;
 
   for (; pi < batch.count; ++pi) {
-    const GemvProblem& P = batch.p[pi];
-    const int c0 = P.cost_begin;
+    const int c0 = batch.p[pi].cost_begin;
     if (c0 >= hi) break;
+    const GemvItem P = item_of(batch, pi);
     const int n_cb = P.n_cb;
     const int c1 = c0 + P.n_rb * n_cb;
     const int rb_lo = (max(lo, c0) - c0 + n_cb - 1) / n_cb;
@@ -884,7 +915,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void gemv_stream_kernel(const ty
     int l_rb = rb_lo + wave;
     bool l_ok = l_rb < rb_hi;
     int s_rb = l_ok ? l_rb : rb_lo;       // the row-block S describes (always a valid one)
-    Strip S = make_strip<K>(P, s_rb, 0, 1);
+    Strip S = make_strip<K>(P, s_rb, 0, 0);
     float tv[8];
     uint4 a_lb = make_uint4(0, 0, 0, 0), b_lb = a_lb;
     if constexpr (LORA) lora_load_t(arg.l[pi], P.x, lane, tv);
@@ -916,7 +947,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void gemv_stream_kernel(const ty
           if (lane == 0) nxt = atomicAdd(counter, 1u);                           \
           l_rb = __builtin_amdgcn_readfirstlane(nxt);                            \
           l_ok = l_rb < rb_hi;                                                   \
-          if (l_ok) { s_rb = l_rb; S = make_strip<K>(P, l_rb, 0, 1); }           \
+          if (l_ok) { s_rb = l_rb; S = make_strip<K>(P, l_rb, 0, 0); }           \
         }                                                                        \
       }                                                                          \
     } while (0)
@@ -965,20 +996,21 @@ __device__ __forceinline__ void consume_at_priority(const C& chunk, uint32_t* lu
 // WPW: waves per workgroup, 4 or 8 (8 when 8 waves share a row-block).
 template <int K, int UP, int WPW, bool LORA, int CAP>
 __global__ __launch_bounds__(64 * WPW) void gemv_split_kernel(const typename BatchOf<LORA, CAP>::type arg) {
-  const GemvBatchT<CAP>& batch = base_of(arg);
+  const auto& batch = base_of(arg);
   __shared__ __attribute__((aligned(16))) uint32_t lut_all[WPW][(UP == 1 ? 1 : 2) * Chunk<K>::kLutDwords];
   __shared__ float part[WPW][8];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wg = blockIdx.x;
-  const int pi = find_problem(batch, wg);
-  const GemvProblem& P = batch.p[pi];
-  const int splits = P.splits;
-  const int rb_per_wg = WPW / splits;
-  const int wg_local = wg - P.wg_begin;
-  const int rb = wg_local * rb_per_wg + wave / splits;
-  const int split = wave % splits;
+  // few products: one row of the grid each; the workgroups that a product has fewer than the widest one leave
+  const int pi = CAP == kFewProblems ? (int)blockIdx.y : find_problem(batch, (int)blockIdx.x);
+  const GemvItem P = item_of(batch, pi);
+  const int splits_log2 = P.splits_log2;
+  const int rb_per_wg = WPW >> splits_log2;
+  const int wg_local = CAP == kFewProblems ? (int)blockIdx.x : (int)blockIdx.x - P.wg_begin;
+  const int rb = wg_local * rb_per_wg + (wave >> splits_log2);
+  const int split = wave & ((1 << splits_log2) - 1);
+  if (CAP == kFewProblems && wg_local * rb_per_wg >= P.n_rb) return;
   uint32_t* lut_a = lut_all[wave];
   uint32_t* lut_b = lut_a + (UP == 1 ? 0 : Chunk<K>::kLutDwords);
   const uint32_t base_a = lds_addr(lut_a), base_b = lds_addr(lut_b);
@@ -996,7 +1028,7 @@ __global__ __launch_bounds__(64 * WPW) void gemv_split_kernel(const typename Bat
   }
 
   if (rb < P.n_rb) {
-    Strip S = make_strip<K>(P, rb, split, splits);
+    Strip S = make_strip<K>(P, rb, split, splits_log2);
     if constexpr (UP == 1) {
       if (S.chunks_left > 0) {
         Chunk<K> A;
@@ -1049,9 +1081,9 @@ __global__ __launch_bounds__(64 * WPW) void gemv_split_kernel(const typename Bat
     const int rbo = wg_local * rb_per_wg + rbi;
     if (rbo < P.n_rb) {
       float s = 0.f;
-      for (int q = 0; q < splits; ++q) s += part[rbi * splits + q][r];
+      for (int q = 0; q < 1 << splits_log2; ++q) s += part[(rbi << splits_log2) + q][r];
       const size_t o = (size_t)rbo * 8 + r;
-      if (batch.y_f32) reinterpret_cast<float*>(P.y)[o] = s;
+      if (P.y_f32) reinterpret_cast<float*>(P.y)[o] = s;
       else reinterpret_cast<_Float16*>(P.y)[o] = (_Float16)s;
     }
   }
@@ -1150,9 +1182,9 @@ inline const GemvBatch& base_of_host(const GemvBatch& b) { return b; }
 inline const GemvBatch& base_of_host(const GemvBatchLora& b) { return b.base; }
 
 template <bool LORA, int CAP>
-hipError_t launch_split(int fmt, const typename BatchOf<LORA, CAP>::type& batch, int mode, int grid_wgs, hipStream_t s,
+hipError_t launch_split(int fmt, const typename BatchOf<LORA, CAP>::type& batch, int mode, dim3 grid, hipStream_t s,
                         int wpw) {
-  const dim3 grid(grid_wgs), block(64 * wpw);
+  const dim3 block(64 * wpw);
   if (mode == 2) {
 #define VQ_F(K)                                                                                   \
   if (wpw == 8) hipLaunchKernelGGL((gemv_split_kernel<K, 1, 8, LORA, CAP>), grid, block, 0, s, batch); \
@@ -1188,9 +1220,15 @@ hipError_t launch_gemv_impl(int fmt, const typename BatchOf<LORA>::type& batch, 
 #undef VQ_F
     return hipGetLastError();
   }
-  if (base_of_host(batch).count <= kFewProblems)
-    return launch_split<LORA, kFewProblems>(fmt, few_problems(batch), mode, grid_wgs, s, wpw);
-  return launch_split<LORA, kMaxProblemsPerLaunch>(fmt, batch, mode, grid_wgs, s, wpw);
+  const GemvBatch& b = base_of_host(batch);
+  if (b.count > kFewProblems)
+    return launch_split<LORA, kMaxProblemsPerLaunch>(fmt, batch, mode, dim3(grid_wgs), s, wpw);
+  int widest = 0;               // workgroups of the product with most of them: wpw / splits row-blocks each
+  for (int i = 0; i < b.count; ++i) {
+    const int rb_per_wg = wpw / b.p[i].splits;
+    widest = max(widest, (b.p[i].n_rb + rb_per_wg - 1) / rb_per_wg);
+  }
+  return launch_split<LORA, kFewProblems>(fmt, few_problems(batch), mode, dim3(widest, b.count), s, wpw);
 }
 
 }  // namespace

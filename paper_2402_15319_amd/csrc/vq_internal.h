@@ -76,10 +76,9 @@ struct GemvProblem {
   int32_t rb_per_cb;    // 8-row blocks that share one codebook (group_rows / 8)
 };
 
-// The kernel argument of a launch of at most CAP products.  The host fills the widest one; launches of
-// up to kFewProblems products get the narrow one (few_problems below): 240 instead of 14,352 bytes for the
-// runtime to copy, about 1 us of a call's host time (a decoder layer's launches hold one to three products).
-// The kernels search either table alike: loading all four entries at once measured the same.
+// The kernel argument of a launch of many products (the host fills it for every launch; those of up to kFewProblems
+// products get the narrow one below, 288 instead of 14,352 bytes for the runtime to copy, about 1 us of a call's
+// host time: a decoder layer's launches hold one to three products).
 template <int CAP>
 struct GemvBatchT {
   int32_t count;
@@ -90,6 +89,28 @@ struct GemvBatchT {
 };
 constexpr int kFewProblems = 4;
 using GemvBatch = GemvBatchT<kMaxProblemsPerLaunch>;
+
+// The narrow argument.  What a wave needs of its product is one 64-byte line, fetched by one scalar load whose address
+// the workgroup number gives, and holds shift counts where the wide table holds divisors: nothing is loaded from memory
+// before the waves' addresses are known but this line.  (A search of the table, fields fetched where they were used
+// and integer divisions before: 0.3 to 0.5 us of a launch more; a layer of 4096 / 11008 in four launches, k = 64
+// 29.6 -> 27.6 us, k = 16 25.2 -> 24.2.  Of the 27.6, 8.2 are the launches themselves and 13 the reads of 79 MB.)
+struct FewProblem {
+  const uint8_t* idx;
+  const uint32_t* cb;
+  const uint16_t* x;
+  void* y;
+  int32_t n_rb, n_cb, wg_begin;
+  int32_t splits_log2;  // of GemvProblem::splits
+  int32_t cb_log2;      // of rb_per_cb (0 also for groups of one or four rows)
+  int32_t y_f32;
+  int32_t pad[2];
+};
+static_assert(sizeof(FewProblem) == 64, "one scalar load");
+struct GemvFew {
+  FewProblem p[kFewProblems];
+  int32_t begin[kFewProblems];   // wg_begin of every product; beyond the last one INT32_MAX
+};
 
 // Low-rank adapter of one problem (y = W x + B (A x)): what the GEMV epilogue needs.
 struct LoraProblem {
@@ -107,6 +128,10 @@ struct GemvBatchLoraT {
   LoraProblem l[CAP];
 };
 using GemvBatchLora = GemvBatchLoraT<kMaxProblemsPerLaunch>;
+struct GemvFewLora {
+  GemvFew base;
+  LoraProblem l[kFewProblems];
+};
 
 // t = A x of every problem of a launch: one wave per row of A.
 struct LoraDownProblem {
@@ -125,13 +150,19 @@ struct LoraDownBatchT {
 using LoraDownBatch = LoraDownBatchT<kMaxProblemsPerLaunch>;
 
 // The narrow form of a launch's argument (count <= kFewProblems).
-inline GemvBatchT<kFewProblems> few_problems(const GemvBatch& b) {
-  GemvBatchT<kFewProblems> f = {b.count, b.y_f32, b.total_wgs, b.total_cost, {}};
-  for (int i = 0; i < b.count && i < kFewProblems; ++i) f.p[i] = b.p[i];
+inline int log2_of(int v) { return v > 1 ? 31 - __builtin_clz((unsigned)v) : 0; }   // of a power of two; 0 for 0
+inline GemvFew few_problems(const GemvBatch& b) {
+  GemvFew f = {};
+  for (int i = 0; i < kFewProblems; ++i) f.begin[i] = 0x7fffffff;
+  for (int i = 0; i < b.count && i < kFewProblems; ++i) {
+    const GemvProblem& q = b.p[i];
+    f.p[i] = {q.idx, q.cb, q.x, q.y, q.n_rb, q.n_cb, q.wg_begin, log2_of(q.splits), log2_of(q.rb_per_cb), b.y_f32, {}};
+    f.begin[i] = q.wg_begin;
+  }
   return f;
 }
-inline GemvBatchLoraT<kFewProblems> few_problems(const GemvBatchLora& b) {
-  GemvBatchLoraT<kFewProblems> f = {few_problems(b.base), {}};
+inline GemvFewLora few_problems(const GemvBatchLora& b) {
+  GemvFewLora f = {few_problems(b.base), {}};
   for (int i = 0; i < b.base.count && i < kFewProblems; ++i) f.l[i] = b.l[i];
   return f;
 }
