@@ -6,12 +6,10 @@
 //   M-step:  c_m[t] = sum_{i in I_m} h[c_i+t] * x_i[t] / sum_{i in I_m} h[c_i+t]   (0 if the sum of weights is 0)
 //
 // with x_i = W[r, c .. c+d-1] and h[c] = 1 / [H^-1]_cc, the diagonal weight of column c.
-// em_assign_kernel: d = 2, groups of 8 x 256 weights.  One wave per group, lane L owns columns
-// 4L .. 4L+3 (two vectors) of the group's 8 rows, exactly as in the matrix-vector kernels.
-// em_assign_any_kernel: d = 1, 2 or 4 and groups of 1, 4, 8, 16, ... 256 rows x 256 columns (every group
-// shape the decode formats use), the same lane ownership.  Both take large codebooks through
-// em_assign_filtered, where the matrix cores leave 8 candidates of the k.  em_update_small_kernel / em_update_kernel: the M-step with
-// a table per lane or per group.
+// em_assign_kernel (d = 2, groups of 8 x 256 weights) and em_assign_any_kernel (d = 1, 2 or 4 and groups of 1, 4, 8, 16,
+// ... 256 rows x 256 columns: every group shape the decode formats use): large codebooks through em_assign_filtered,
+// where the matrix cores leave 8 candidates of the k, the others through em_assign_loop.  em_update_small_kernel /
+// em_update_kernel: the M-step with a table per lane or per group.
 //
 // The E-step is a decision taken in floating point, so its arithmetic is fixed: binary32,
 // every operation rounded on its own (no fused multiply-add), in the order subtract, square,
@@ -31,7 +29,7 @@ namespace {
 // for d = 4): v_mfma_f32_32x32x16_f16 gives the scores of 32 centroids x 32 vectors.
 // Powers of two bring the largest coordinate of the codebook and the largest weight of each vector to
 // [2^5, 2^6).  The scores are only a filter.  Per vector the smallest block of 8 centroids and the second
-// smallest are kept (7 instructions per 8 scores, the block number in the low bits of the score); if the
+// smallest are kept (6.5 instructions per 8 scores, the block number in the low bits of the score); if the
 // second lies above the first by more than the scores can be off by, the assignment is found in the first
 // block with the arithmetic that defines the E-step, otherwise in the whole codebook, so the result is the
 // defined one bit for bit.
@@ -45,8 +43,8 @@ namespace {
 // kScoreTiny covers halves that are subnormal: 2^-24 each (the matrix cores keep subnormals) times the largest
 // value of the feature they meet, at most 60,000.  Codebooks, weights or vectors outside the ranges checked
 // below (NaN, infinities, negative or very uneven weights) take the whole codebook.
-//   Bound: vector instructions, the minima first.  The loop over centroids that this replaces takes 18
-// (d = 4) or 11 (d = 2) instructions per centroid and vector.
+//   Bound: vector instructions (80 % of the time with d = 4, k = 256), the minima first: 6.5 per 8 scores.  The loop over
+// centroids that this replaces takes 18 (d = 4) or 10 (d = 2) instructions per centroid and vector.
 template <int D>
 struct EmMargin {
   static constexpr float kScoreError = 1.5f + 1.0f * D;
@@ -141,18 +139,18 @@ __device__ __forceinline__ float own_coord(const float (&v)[D], int q, int half)
 template <int D>
 __device__ __forceinline__ int em_place(int m) { return D * (m + (m >> 3)); }
 
-// The whole codebook for 8 rows of 32 vectors: lanes L and L + 32 take four rows each of the vectors in column
-// place L, so that a read of a centroid serves four vectors.  Per 8 centroids only the smallest distance is kept
+// The whole codebook for 2 * RR rows of 32 vectors: lanes L and L + 32 take RR rows each of the vectors in column
+// place L, so that a read of a centroid serves RR vectors.  Per 8 centroids only the smallest distance is kept
 // (the first block that has it), and its place is found in that block afterwards: 8 (d = 2) or 15 (d = 4)
 // instructions per centroid and vector where keeping the place takes 10 or 18.  A NaN distance is never the smallest.
-template <int K, int D>
+template <int K, int D, int RR>
 __device__ __forceinline__ void em_assign_whole(const float* cbs, const float* __restrict__ Wl, int in_features,
                                                 const float (&h)[D], uint8_t* __restrict__ out) {
 #pragma clang fp contract(off)
-  float x[4][D], best[4];
-  uint32_t blk[4];
+  float x[RR][D], best[RR];
+  uint32_t blk[RR];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
+  for (int r = 0; r < RR; ++r) {
     load_coords<D>(Wl + (size_t)r * in_features, x[r]);
     best[r] = __builtin_inff();
     blk[r] = 0;
@@ -162,7 +160,7 @@ __device__ __forceinline__ void em_assign_whole(const float* cbs, const float* _
   for (int j = 0; j < 8; ++j) load_coords<D>(cbs + j * D, ahead[j]);
 #pragma unroll 1
   for (uint32_t b = 0; b < K / 8; ++b) {
-    float cm[8][D], low[4];
+    float cm[8][D], low[RR];
 #pragma unroll
     for (int j = 0; j < 8; ++j)
 #pragma unroll
@@ -173,17 +171,17 @@ __device__ __forceinline__ void em_assign_whole(const float* cbs, const float* _
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
+      for (int r = 0; r < RR; ++r) {
         const float dist = em_distance<D>(x[r], h, cm[j]);
         low[r] = j == 0 ? dist : __builtin_fminf(low[r], dist);
       }
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < RR; ++r)
       if (low[r] < best[r]) { best[r] = low[r]; blk[r] = b; }
   }
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
+  for (int r = 0; r < RR; ++r) {
     const float* cand = cbs + em_place<D>(8) * (int)blk[r];
     float low = __builtin_inff();
     uint32_t arg = 8 * blk[r];
@@ -196,53 +194,136 @@ __device__ __forceinline__ void em_assign_whole(const float* cbs, const float* _
   }
 }
 
-// Workgroups of one wave, one per (8-row block, col-block).  A step is 32 vectors of one row: lanes L and
-// L + 32 share vector L, and each scores half of every tile of 32 centroids.
+// Workgroups of four waves, one per (strip of 8, 16 or 32 rows, col-block).  A step is 32 vectors of one row: lanes L
+// and L + 32 share vector L, and each scores half of every tile of 32 centroids.  A wave keeps to one place of 32
+// vectors in the rows (its weights and their features are made once) and takes all rows of the strip (d = 2) or
+// half of them (d = 4).  The centroids' features are made once per workgroup, in LDS, from where a wave reads those of
+// a tile for R rows (64 registers and a prologue in every wave otherwise, which left two waves per SIMD).
+//   Equal centroids: a vector nearest to one would see the same score in two blocks and be undecided.  Centroids are
+// therefore compared through a table of their hashes; if some are equal, the filter works on the distinct ones (the
+// lowest index of each), spread over the blocks, whose other places repeat the first of their block, and `origin`
+// leads back.  Blocks list their centroids in the order of the codebook, so the lowest index still wins a tie.
 template <int K, int D>
 __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, const float* __restrict__ hdiag,
                                                    const float* __restrict__ cb, uint8_t* __restrict__ assign,
-                                                   int n_cb, int in_features, int group_rows) {
+                                                   int n_cb, int in_features, int group_rows, int strip_rows) {
 #pragma clang fp contract(off)
-  static_assert((D == 2 || D == 4) && K % 64 == 0, "half-waves share the coordinates, lanes the centroids");
-  constexpr int TILES = K / 32;
-  constexpr int SETS = 8 / D;                 // steps per row
-  constexpr int NM = D / 2;                   // coordinates per half-wave = matrix instructions per tile
+  static_assert((D == 2 || D == 4) && K % 64 == 0 && K <= 256, "half-waves share the coordinates, lanes the centroids");
+  constexpr int TILES = K / 32, NB = K / 8;
+  constexpr int SETS = 8 / D;                 // places of 32 vectors in the 256 columns of a row
+  constexpr int PARTS = 4 / SETS;             // waves that share a place
+  constexpr int NM = D / 2;                   // coordinates per half-wave = matrix instructions of a tile's features
   constexpr uint32_t kBlockMask = 4 * TILES - 1;   // block number: tile, half-wave, upper or lower 8
-  constexpr int R = D == 4 ? 2 : 4;           // steps filtered together
-  // Undecided vectors of a step from which the whole codebook is faster: a vector taken by itself costs 25, 17, 13 us
-  // per 4096 x 4096 and vector of a step, the filter 106, 85, 40, the whole codebook 300, 300, 85 (d = 2 and d = 4 with
-  // k = 256, d = 4 with k = 64).  Judged by the first rows of a set; later ones, whose set would be done twice, need
-  // twice as many.
-  constexpr int kMostUndecided = D == 2 ? 7 : K == 256 ? 13 : 3;
+  constexpr int R = 4;                        // steps filtered together
+  // Undecided vectors of a step from which the whole codebook is faster (judged by the first rows of a run of 8 or 4; later
+  // ones, whose run would be done twice, need twice as many).  A vector taken by itself costs 25, 17, 13 us per
+  // 4096 x 4096 and vector of a step (d = 2, d = 4 with k = 256, d = 4 with k = 64).
+  constexpr int kMostUndecided = D == 2 ? (K == 256 ? 7 : 3) : K == 256 ? 13 : 3;
   __shared__ __attribute__((aligned(16))) float cbs[(K + K / 8) * D];
-  const int lane = threadIdx.x;
+  __shared__ __attribute__((aligned(16))) float distinct[(K + K / 8) * D];
+  __shared__ uint8_t origin[K];
+  __shared__ int n_distinct[4];
+  __shared__ __attribute__((aligned(16))) uint4 feat[TILES * NM * 64];
+  static_assert(sizeof(feat) >= 8 * K * sizeof(uint32_t), "the hash tables lie where the features will");
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = lane >> 5, n = lane & 31;
   const uint32_t strip = blockIdx.x / (uint32_t)n_cb;
   const int c = (int)(blockIdx.x - strip * (uint32_t)n_cb);
-  const long long row0 = (long long)strip * 8;
+  const int rows = strip_rows / PARTS;        // of this wave
+  const int set = wave % SETS, col = set * 32 + n;   // the vector's place in the row
+  const long long row_strip = (long long)strip * strip_rows, row0 = row_strip + (wave / SETS) * rows;
 
+  const float* Wb = W + (size_t)row0 * in_features + (size_t)c * 256 + col * D;
+  uint8_t* ab = assign + (size_t)row0 * (in_features / D) + (size_t)c * (256 / D) + col;
+  float xn[R][D], h[D];                       // the next R steps' vectors
+#pragma unroll
+  for (int r = 0; r < R; ++r) load_coords<D>(Wb + (size_t)r * in_features, xn[r]);
+  load_coords<D>(hdiag + (size_t)c * 256 + col * D, h);
+
+  // the codebook, and which of its centroids are the first of their value
+  const float* fcb = cbs;                     // what the filter works on
+  bool repeats, filter = true;
   {
-    const float* cg = cb + ((long long)((uint32_t)row0 / (uint32_t)group_rows) * n_cb + c) * (K * D);
+    uint32_t* table = reinterpret_cast<uint32_t*>(feat);   // two of 4 K entries: a value that loses its place in both to others counts as distinct
+    float v[D];
+    uint32_t slot[2] = {0u, 4u * K};
+    const bool mine = tid < K;
+    for (int i = tid; i < 8 * K; i += 256) table[i] = K;
+    if (mine) {
+      const float* cg = cb + ((long long)((uint32_t)row_strip / (uint32_t)group_rows) * n_cb + c) * (K * D);
+      load_coords<D>(cg + tid * D, v);
+      uint32_t mix = 0;
 #pragma unroll
-    for (int i = 0; i < K / 64; ++i) {
-      const int m = i * 64 + lane;
-      float v[D];
-      load_coords<D>(cg + m * D, v);
+      for (int t = 0; t < D; ++t) {
+        cbs[em_place<D>(tid) + t] = v[t];
+        mix = (mix ^ __builtin_bit_cast(uint32_t, v[t] + 0.f)) * 0x9e3779b1u;   // the two zeros are equal
+        mix ^= mix >> 15;
+      }
+      slot[0] += mix % (4u * K);
+      slot[1] += (mix >> 12) % (4u * K);
+    }
+    __syncthreads();
+    if (mine) {
+      atomicMin(table + slot[0], (uint32_t)tid);
+      atomicMin(table + slot[1], (uint32_t)tid);
+    }
+    __syncthreads();
+    bool first = mine;
+    if (mine) {
 #pragma unroll
-      for (int t = 0; t < D; ++t) cbs[em_place<D>(m) + t] = v[t];
+      for (int i = 0; i < 2; ++i) {
+        const uint32_t m = table[slot[i]];
+        if (m != (uint32_t)tid) {
+          bool same = true;
+#pragma unroll
+          for (int t = 0; t < D; ++t) same = same && v[t] == cbs[em_place<D>(m) + t];
+          first = first && !same;
+        }
+      }
+    }
+    const unsigned long long firsts = __ballot(first);
+    if (lane == 0) n_distinct[wave] = __builtin_popcountll(firsts);
+    __syncthreads();
+    int before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const int nw = n_distinct[w];
+      before += w < wave ? nw : 0;
+      all += nw;
+    }
+    all = __builtin_amdgcn_readfirstlane(all);
+    repeats = all < K;
+    if (repeats) {
+      if (all < NB) {                         // a block for each would leave some empty
+        filter = false;
+      } else {
+        const int rank = before + __builtin_popcountll(firsts & ((1ull << lane) - 1ull));
+        if (first) {
+          const int m = 8 * (rank % NB) + rank / NB;
+#pragma unroll
+          for (int t = 0; t < D; ++t) distinct[em_place<D>(m) + t] = v[t];
+          origin[m] = (uint8_t)tid;
+        }
+        __syncthreads();
+        if (mine && (tid & 7) * NB + (tid >> 3) >= all) {   // a place that no distinct centroid has
+          const int m = tid & ~7;
+#pragma unroll
+          for (int t = 0; t < D; ++t) distinct[em_place<D>(tid) + t] = distinct[em_place<D>(m) + t];
+          origin[tid] = origin[m];
+        }
+        __syncthreads();
+        fcb = distinct;
+      }
     }
   }
-  const float* Wb = W + (size_t)row0 * in_features + (size_t)c * 256;
-  const float* hb = hdiag + (size_t)c * 256;
-  uint8_t* ab = assign + (size_t)row0 * (in_features / D) + (size_t)c * (256 / D);
-  float xn[R][D];                             // the next R steps' vectors
-#pragma unroll
-  for (int r = 0; r < R; ++r) load_coords<D>(Wb + (size_t)r * in_features + n * D, xn[r]);
-  wave_lds_sync();
 
   // Centroid features: row j of a tile is given centroid 16 * ((j >> 2) & 1) + 4 * (j >> 3) + (j & 3), so that a
   // lane's 16 scores of a tile are those of centroids 16 * half .. + 15, in order.  K slots of a half-wave, per
   // coordinate: (h hi, h hi, h lo, h lo, hx hi, hx hi, hx lo, hx lo) against (c^2 hi, c^2 lo, twice; -2c hi, -2c lo, twice).
+  // d = 2: both in one matrix instruction; d = 4: the first four of the half-wave's two coordinates in one, which serves
+  // the R rows, the last four in another.
   float top = 0.f;                            // largest coordinate of the codebook (NaN if there is one)
 #pragma unroll
   for (int i = 0; i < K / 64; ++i)
@@ -254,108 +335,116 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
   const float c_scale = ok_c ? scale_to_32(top) : 1.f;
   const float margin_x = EmMargin<D>::kX * c_scale, max_norm = kMaxNorm * power_inverse(c_scale);   // X below lacks one factor c_scale
   const int row_centroid = 16 * ((n >> 2) & 1) + 4 * (n >> 3) + (n & 3);
-  uint4 A[TILES][NM];
-#pragma unroll
-  for (int t = 0; t < TILES; ++t)
+  for (int t = wave; t < TILES; t += 4) {
+    uint32_t sq[NM], mul[NM];
 #pragma unroll
     for (int q = 0; q < NM; ++q) {
-      const float cv = c_scale * cbs[em_place<D>(32 * t + row_centroid) + NM * half + q];
-      const uint32_t sq = split_once(cv * cv), mul = split_once(-2.f * cv);
-      A[t][q] = make_uint4(sq, sq, mul, mul);
+      const float cv = c_scale * fcb[em_place<D>(32 * t + row_centroid) + NM * half + q];
+      sq[q] = split_once(cv * cv);
+      mul[q] = split_once(-2.f * cv);
     }
+    if constexpr (D == 2) {
+      feat[t * 64 + lane] = make_uint4(sq[0], sq[0], mul[0], mul[0]);
+    } else {
+      feat[(2 * t) * 64 + lane] = make_uint4(sq[0], sq[0], sq[1], sq[1]);
+      feat[(2 * t + 1) * 64 + lane] = make_uint4(mul[0], mul[0], mul[1], mul[1]);
+    }
+  }
+  __syncthreads();                            // the last one: waves leave at different times
 
-  float h[D], hs[D];                          // weights, and weights times both scales
-  uint4 B[NM];
-  bool filter = ok_c;
-#pragma unroll 1
-  for (int set = 0, row = 0; set < SETS;) {   // R steps each: 32 vectors of R rows
-    bool whole = !filter;                     // this set's vectors against the whole codebook
-    const int col = set * 32 + n;             // the vector's place in the row
-    if (row == 0) {
-      load_coords<D>(hb + col * D, h);
-      float h_top = h[0], h_low = h[0];
+  uint4 Bh = make_uint4(0, 0, 0, 0);          // the weights' halves (d = 2: .x and .y of the operand)
+  float hs[D];                                // weights times both scales
+  {
+    float h_top = h[0], h_low = h[0];
 #pragma unroll
-      for (int t = 1; t < D; ++t) {
-        h_top = max_nn(h_top, h[t]);
-        h_low = min_nn(h_low, h[t]);
-      }
-      // with h_low >= 2^-20 h_top the bound on h x below is one on x
-      const bool good = h_low >= 0x1p-30f && h_top <= 0x1p30f && h_low >= 0x1p-20f * h_top;
-      whole = whole || !__all(good);
-      const float h_scale = good ? scale_to_32(h_top) : 1.f;
-      float hq[D];
-#pragma unroll
-      for (int t = 0; t < D; ++t) {
-        hq[t] = h[t] * h_scale;
-        hs[t] = hq[t] * c_scale;
-      }
-#pragma unroll
-      for (int p = 0; p < NM; ++p) split_twice(own_coord<D>(hq, p, half), B[p].x, B[p].y);
+    for (int t = 1; t < D; ++t) {
+      h_top = max_nn(h_top, h[t]);
+      h_low = min_nn(h_low, h[t]);
     }
+    // with h_low >= 2^-20 h_top the bound on h x below is one on x
+    const bool good = h_low >= 0x1p-30f && h_top <= 0x1p30f && h_low >= 0x1p-20f * h_top;
+    filter = filter && ok_c && __all(good);
+    const float h_scale = good ? scale_to_32(h_top) : 1.f;
+    float hq[D];
+#pragma unroll
+    for (int t = 0; t < D; ++t) {
+      hq[t] = h[t] * h_scale;
+      hs[t] = hq[t] * c_scale;
+    }
+    split_twice(own_coord<D>(hq, 0, half), Bh.x, Bh.y);
+    if constexpr (D == 4) split_twice(own_coord<D>(hq, 1, half), Bh.z, Bh.w);
+  }
+  const int run = rows < 8 ? rows : 8;        // rows that are taken again together: 8, or 4
+#pragma unroll 1
+  for (int row = 0; row < rows;) {            // R steps each
     float xs[R][D];
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
       for (int t = 0; t < D; ++t) xs[r][t] = xn[r][t];
     const int row_now = row;
-    row = row + R < 8 ? row + R : 0;
-    set += row == 0 ? 1 : 0;
+    row += R;
     {   // past the end: a harmless re-read
-      const int ahead = set < SETS ? set : 0;
+      const int ahead = row < rows ? row : 0;
 #pragma unroll
-      for (int r = 0; r < R; ++r)
-        load_coords<D>(Wb + (size_t)(row + r) * in_features + (uint32_t)((ahead * 32 + n) * D), xn[r]);
+      for (int r = 0; r < R; ++r) load_coords<D>(Wb + (size_t)(ahead + r) * in_features, xn[r]);
     }
     uint32_t args[R], unsures[R];
     bool in_upper[R];                         // which of lanes L and L + 32 holds the result
-    if (!whole) {     // R steps' filters, without a branch between them
-      uint4 Bx[R][NM];
+    if (filter) {     // R steps' filters, without a branch between them
+      uint4 Bx[R];
       float X[R], m1[R], m2[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         float hx[D];
-        X[r] = 0.f;
 #pragma unroll
         for (int t = 0; t < D; ++t) {
           hx[t] = hs[t] * xs[r][t];
-          X[r] = X[r] + hx[t] * xs[r][t];
+          X[r] = t == 0 ? hx[t] * xs[r][t] : X[r] + hx[t] * xs[r][t];
         }
-#pragma unroll
-        for (int p = 0; p < NM; ++p) {
-          Bx[r][p] = B[p];
-          split_twice(own_coord<D>(hx, p, half), Bx[r][p].z, Bx[r][p].w);
+        if constexpr (D == 2) {
+          Bx[r].x = Bh.x;
+          Bx[r].y = Bh.y;
+          split_twice(own_coord<D>(hx, 0, half), Bx[r].z, Bx[r].w);
+        } else {
+          split_twice(own_coord<D>(hx, 0, half), Bx[r].x, Bx[r].y);
+          split_twice(own_coord<D>(hx, 1, half), Bx[r].z, Bx[r].w);
         }
         m1[r] = m2[r] = __builtin_inff();
       }
-      // The scores of the next tile are on the matrix cores while this one's minima are taken; the compiler
-      // would put them one behind the other to save registers.
-      auto score = [&](int i, f16v_t& sc) {
+      // One tile after the other, R rows each.
 #pragma unroll
-        for (int j = 0; j < 16; ++j) sc[j] = 0.f;
+      for (int i = 0; i < TILES; ++i) {
+        f16v_t sc[R], zero;
 #pragma unroll
-        for (int p = 0; p < NM; ++p)
-          sc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8v_t, A[i % TILES][p]),
-                                                      __builtin_bit_cast(h8v_t, Bx[i / TILES][p]), sc, 0, 0, 0);
-      };
-      f16v_t sc[2];
-      score(0, sc[0]);
+        for (int j = 0; j < 16; ++j) zero[j] = 0.f;
+        if constexpr (D == 4) {
+          const f16v_t base = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8v_t, feat[2 * i * 64 + lane]),
+                                                                     __builtin_bit_cast(h8v_t, Bh), zero, 0, 0, 0);
+          const h8v_t a = __builtin_bit_cast(h8v_t, feat[(2 * i + 1) * 64 + lane]);
 #pragma unroll
-      for (int i = 0; i < R * TILES; ++i) {
-        if (i + 1 < R * TILES) score(i + 1, sc[(i + 1) & 1]);
-        const f16v_t& v = sc[i & 1];
-        const int r = i / TILES;
+          for (int r = 0; r < R; ++r) sc[r] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, __builtin_bit_cast(h8v_t, Bx[r]), base, 0, 0, 0);
+        } else {
+          const h8v_t a = __builtin_bit_cast(h8v_t, feat[i * 64 + lane]);
 #pragma unroll
-        for (int k8 = 0; k8 < 2; ++k8) {
-          float e = min_nn(min_nn(v[8 * k8], v[8 * k8 + 1]), v[8 * k8 + 2]);
-          e = min_nn(min_nn(e, v[8 * k8 + 3]), v[8 * k8 + 4]);
-          e = min_nn(min_nn(e, v[8 * k8 + 5]), v[8 * k8 + 6]);
-          e = min_nn(e, v[8 * k8 + 7]);
-          e = __builtin_bit_cast(float, (__builtin_bit_cast(uint32_t, e) & ~kBlockMask) | (uint32_t)(4 * (i % TILES) + k8));
-          m2[r] = __builtin_amdgcn_fmed3f(e, m1[r], m2[r]);   // m1 <= m2: the middle one is the new second smallest
-          m1[r] = min_nn(m1[r], e);
+          for (int r = 0; r < R; ++r) sc[r] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, __builtin_bit_cast(h8v_t, Bx[r]), zero, 0, 0, 0);
         }
-        if (i + 1 < R * TILES) __builtin_amdgcn_sched_group_barrier(0x8, NM, 0);   // matrix instructions,
-        __builtin_amdgcn_sched_group_barrier(0x2, 14, 0);                          // then vector instructions
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          float e[2];
+#pragma unroll
+          for (int k8 = 0; k8 < 2; ++k8) {
+            const f16v_t& v = sc[r];
+            float m = min_nn(min_nn(v[8 * k8], v[8 * k8 + 1]), v[8 * k8 + 2]);
+            m = min_nn(min_nn(m, v[8 * k8 + 3]), v[8 * k8 + 4]);
+            m = min_nn(min_nn(m, v[8 * k8 + 5]), v[8 * k8 + 6]);
+            m = min_nn(m, v[8 * k8 + 7]);
+            e[k8] = __builtin_bit_cast(float, (__builtin_bit_cast(uint32_t, m) & ~kBlockMask) | (uint32_t)(4 * i + k8));
+          }
+          // m1 <= m2: of the four the second smallest is the middle one of m1 and the new ones, unless m2 is below it
+          m2[r] = min_nn(m2[r], __builtin_amdgcn_fmed3f(m1[r], e[0], e[1]));
+          m1[r] = min_nn(min_nn(m1[r], e[0]), e[1]);
+        }
       }
 #pragma unroll
       for (int r = 0; r < R; ++r) {
@@ -369,7 +458,7 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
         unsures[r] = ~((uint32_t)__ballot(second > limit) & (uint32_t)__ballot(X[r] <= max_norm));
         // the 8 centroids of the first block, four per half-wave
         const uint32_t blk = __builtin_bit_cast(uint32_t, first) & kBlockMask;
-        const float* cand = cbs + em_place<D>(8) * (int)blk + 4 * D * half;
+        const float* cand = fcb + em_place<D>(8) * (int)blk + 4 * D * half;
         float best = em_distance<D>(xs[r], h, cand);
         uint32_t arg = 8 * blk + 4 * half;
         const uint32_t m0 = arg;
@@ -383,6 +472,10 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
         args[r] = arg;
         in_upper[r] = bu < bl;         // the lower half-wave holds the lower indices
       }
+      if (repeats) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) args[r] = origin[args[r]];
+      }
       uint32_t any = 0;
 #pragma unroll
       for (int r = 0; r < R; ++r) any |= unsures[r];
@@ -390,8 +483,8 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
         int undecided = 0;
 #pragma unroll
         for (int r = 0; r < R; ++r) undecided += __builtin_popcount(unsures[r]);
-        if (undecided > kMostUndecided * R * (row_now == 0 ? 1 : 2)) {
-          filter = false;                     // the sets to come will be no better
+        if (undecided > kMostUndecided * R * (row_now % run == 0 ? 1 : 2)) {
+          filter = false;                     // the rows to come will be no better
           goto whole_codebook;
         }
       }
@@ -428,125 +521,58 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
           }
           if (n == src) arg = (uint32_t)found;
         }
-        uint8_t* const out = ab + (size_t)(row_now + r) * (in_features / D);
-        if (in_upper[r] == (half != 0)) out[(uint32_t)col] = (uint8_t)arg;
+        if (in_upper[r] == (half != 0)) ab[(size_t)(row_now + r) * (in_features / D)] = (uint8_t)arg;
       }
       continue;
     }
   whole_codebook:
-    const int now = row == 0 ? set - 1 : set;
-    set = now + 1;
-    row = 0;
-    const int ahead = set < SETS ? set : 0;
+    const int again = row_now - row_now % run;
+    row = again + run;
+    const int ahead = row < rows ? row : 0;
 #pragma unroll
     for (int r = 0; r < R; ++r)   // before the stores, as on the way past this: a wait for them is one for these too
-      load_coords<D>(Wb + (size_t)r * in_features + (uint32_t)((ahead * 32 + n) * D), xn[r]);
-    em_assign_whole<K, D>(cbs, Wb + (size_t)(4 * half) * in_features + (now * 32 + n) * D, in_features, h,
-                          ab + (size_t)(4 * half) * (in_features / D) + (now * 32 + n));
+      load_coords<D>(Wb + (size_t)(ahead + r) * in_features, xn[r]);
+    const size_t mine = (size_t)(again + (run / 2) * half);
+    if (D == 4 && run == 4)
+      em_assign_whole<K, D, 2>(cbs, Wb + mine * in_features, in_features, h, ab + mine * (in_features / D));
+    else
+      em_assign_whole<K, D, 4>(cbs, Wb + mine * in_features, in_features, h, ab + mine * (in_features / D));
   }
 }
 
 // Which codebooks take the filter; us at 4096 x 4096, loop over the centroids against filter (11008 x 4096 behind):
-//                                        d = 2, k = 256, 8 rows     d = 4, k = 256, 256 rows    d = 4, k = 64, 16 rows
-//   distinct centroids                   340, 109 (870, 283)        314, 84 (800, 220)          85, 40
+//                               d = 2, k = 64, 8 rows  d = 2, k = 256, 8 rows   d = 4, k = 256, 256 rows  d = 4, k = 64, 16 rows
+//   distinct centroids                    90, 50             340, 110 (870, 286)      314, 69 (800, 178)       85, 37
 //   vectors of the group, drawn with replacement (11, 1.5, 3 % of the centroids repeated, d = 2 with 8 rows most)
-//                                        342, 269 (875, 623)        314, 94 (796, 237)          85, 64
+//                                         89, 52             342, 117 (875, 325)      314, 74 (796, 185)       85, 39
 //   half of W and a quarter of the centroids zero
-//                                        332, 346                   308, 278 (786, 691)         82, 92
-//   every centroid twice, or W far from zero: no vector is decided
-//                                        340, 314                   310, 308 (794, 830)         85, 91
+//                                         86, 49             332, 110                 308, 72 (786, 186)       82, 37
+//   every centroid twice                  89, 57             340, 117 (-, 300)        310, 79 (794, 194)       85, 45
+//   W far from zero: no vector is decided 88, 110            338, 339 (-, 898)        309, 330 (794, 847)      85, 100
 //   zero, negative or very uneven weights in every set of 32 vectors: no filter
-//                                        338, 303                   309, 299 (794, 799)         85, 87
-// Equal centroids cost so much because all vectors nearest to them are undecided; an M-step leaves the zero vector in
-// the place of every empty cluster.  Not for d = 2, k = 64: 87, 82..110; d = 2, k = 32: 46, 62; d = 1, k = 64: 111, 170
-// (scalars lie too close for the filter).  Waves of 16 rows, which would split the centroids' features over twice the
-// vectors, were slower (144 for 124).
-template <int K, int D> constexpr bool em_filtered() { return (D == 2 && K == 256) || (D == 4 && K >= 64); }
-template <int K, int D> constexpr int em_threads() { return em_filtered<K, D>() ? 64 : 256; }
-template <int K, int D> constexpr int em_waves() { return em_filtered<K, D>() ? 2 : 1; }   // per SIMD: 256 registers each
+//                                         89, 91             338, 304                 309, 305 (794, 795)      85, 88
+// Not for d = 2, k = 32 and d = 1 (scalars lie too close for the filter).  Against the kernel that this replaces (a wave
+// to 8 rows, the features of all centroids in its registers, equal centroids undecided): d = 4, k = 256, 256 rows
+// 11008 x 4096 223 -> 178; d = 2, k = 256, 8 rows with centroids drawn from the vectors 267 -> 117, 512 x 512 81 -> 13.
+template <int K, int D> constexpr bool em_filtered() { return (D == 2 || D == 4) && K >= 64; }
+template <int K, int D> constexpr int em_waves() { return em_filtered<K, D>() ? (D == 4 && K == 256 ? 3 : 4) : 1; }   // per SIMD
 
-template <int K>
-__global__ __launch_bounds__((em_threads<K, 2>()), (em_waves<K, 2>())) void em_assign_kernel(const float* __restrict__ W,
-                                                        const float* __restrict__ hdiag,
-                                                        const float* __restrict__ cb,
-                                                        uint8_t* __restrict__ assign, int n_cb,
-                                                        long long n_groups, int in_features) {
+// The loop over the centroids, for ROWS rows (8, or 2 where a launch has few blocks) of one 8-row block and col-block per
+// wave; the codebook is that of the group the block lies in (NCB = 1), one codebook per row (NCB = 8: groups of one
+// row) or one per 4 rows (NCB = 2).  D values per centroid, 4 / D vectors per row and lane: lane L owns columns
+// 4L .. 4L+3, exactly as in the matrix-vector kernels.  Unfused binary32, sum over t in order.
+template <int K, int D, int NCB, int ROWS>
+__device__ __forceinline__ void em_assign_loop(const float* __restrict__ W, const float* __restrict__ hdiag,
+                                               const float* __restrict__ cb, uint8_t* __restrict__ assign, int n_cb,
+                                               int in_features, int group_rows, long long b, int part, float* cbs) {
 #pragma clang fp contract(off)
-  if constexpr (em_filtered<K, 2>()) {
-    em_assign_filtered<K, 2>(W, hdiag, cb, assign, n_cb, in_features, 8);
-  } else {
-  __shared__ __attribute__((aligned(16))) float2 cbs_all[4][K];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  float2* cbs = cbs_all[wave];
-  const long long g = (long long)blockIdx.x * 4 + wave;
-  if (g >= n_groups) return;   // whole waves leave; no workgroup barrier below
-  const long long rb = g / n_cb;
-  const int c = (int)(g - rb * n_cb);
-
-  const float2* cg = reinterpret_cast<const float2*>(cb) + g * K;
-#pragma unroll
-  for (int i = 0; i < (K + 63) / 64; ++i)
-    if (i * 64 + lane < K) cbs[i * 64 + lane] = cg[i * 64 + lane];
-  const float4 h = *reinterpret_cast<const float4*>(hdiag + (size_t)c * 256 + lane * 4);
-  float4 x[8];
-#pragma unroll
-  for (int r = 0; r < 8; ++r)
-    x[r] = *reinterpret_cast<const float4*>(W + (size_t)(rb * 8 + r) * in_features + (size_t)c * 256 + lane * 4);
-  wave_lds_sync();
-
-  float best[16];
-  uint32_t arg[16];
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    best[v] = __builtin_inff();
-    arg[v] = 0;
-  }
-  for (int m = 0; m < K; ++m) {
-    const float2 cm = cbs[m];   // the same address in every lane: one broadcast read
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const float ea0 = x[r].x - cm.x, ea1 = x[r].y - cm.y;
-      const float eb0 = x[r].z - cm.x, eb1 = x[r].w - cm.y;
-      const float da = h.x * (ea0 * ea0) + h.y * (ea1 * ea1);
-      const float db = h.z * (eb0 * eb0) + h.w * (eb1 * eb1);
-      if (da < best[2 * r]) { best[2 * r] = da; arg[2 * r] = m; }
-      if (db < best[2 * r + 1]) { best[2 * r + 1] = db; arg[2 * r + 1] = m; }
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < 8; ++r)
-    *reinterpret_cast<uint16_t*>(assign + (size_t)(rb * 8 + r) * (in_features / 2) + (size_t)c * 128 + lane * 2) =
-        (uint16_t)(arg[2 * r] | (arg[2 * r + 1] << 8));
-  }
-}
-
-// ---- any dimensionality and group height ---------------------------------------------------
-// E-step.  One wave per (8-row block, col-block); the codebook is that of the group the block
-// lies in (NCB = 1), one codebook per row (NCB = 8: groups of one row) or one per 4 rows (NCB = 2).
-// D values per centroid, 4 / D vectors per row and lane.  Same arithmetic as em_assign_kernel:
-// unfused binary32, sum over t in order.
-template <int K, int D, int NCB>
-__global__ __launch_bounds__((NCB == 1 ? em_threads<K, D>() : 256), (NCB == 1 ? em_waves<K, D>() : 1)) void em_assign_any_kernel(const float* __restrict__ W,
-                                                            const float* __restrict__ hdiag,
-                                                            const float* __restrict__ cb,
-                                                            uint8_t* __restrict__ assign, int n_cb,
-                                                            long long n_blocks, int in_features,
-                                                            int group_rows) {
-#pragma clang fp contract(off)
-  if constexpr (NCB == 1 && em_filtered<K, D>()) {
-    em_assign_filtered<K, D>(W, hdiag, cb, assign, n_cb, in_features, group_rows);
-  } else {
+  static_assert(ROWS == 8 || NCB == 1, "parts of a block share its codebook");
   constexpr int V = 4 / D;                 // vectors per row and lane
   constexpr int RPC = 8 / NCB;             // rows of the block that share a codebook
-  __shared__ __attribute__((aligned(16))) float cbs_all[4][NCB * K * D];
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  float* cbs = cbs_all[wave];
-  const long long b = (long long)blockIdx.x * 4 + wave;
-  if (b >= n_blocks) return;   // whole waves leave; no workgroup barrier below
   const long long rb = b / n_cb;
   const int c = (int)(b - rb * n_cb);
+  const long long row0 = rb * 8 + part * ROWS;
 
 #pragma unroll
   for (int q = 0; q < NCB; ++q) {
@@ -556,24 +582,25 @@ __global__ __launch_bounds__((NCB == 1 ? em_threads<K, D>() : 256), (NCB == 1 ? 
   }
   const float4 h4 = *reinterpret_cast<const float4*>(hdiag + (size_t)c * 256 + lane * 4);
   const float h[4] = {h4.x, h4.y, h4.z, h4.w};
-  float x[8][4];
+  float x[ROWS][4];
 #pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const float4 t = *reinterpret_cast<const float4*>(W + (size_t)(rb * 8 + r) * in_features + (size_t)c * 256 + lane * 4);
+  for (int r = 0; r < ROWS; ++r) {
+    const float4 t = *reinterpret_cast<const float4*>(W + (size_t)(row0 + r) * in_features + (size_t)c * 256 + lane * 4);
     x[r][0] = t.x; x[r][1] = t.y; x[r][2] = t.z; x[r][3] = t.w;
   }
   wave_lds_sync();
 
-  float best[8 * V];
-  uint32_t arg[8 * V];
+  float best[ROWS * V];
+  uint32_t arg[ROWS * V];
 #pragma unroll
-  for (int v = 0; v < 8 * V; ++v) {
+  for (int v = 0; v < ROWS * V; ++v) {
     best[v] = __builtin_inff();
     arg[v] = 0;
   }
+#pragma unroll 2
   for (int m = 0; m < K; ++m) {
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
+    for (int r = 0; r < ROWS; ++r) {
       const float* cm = cbs + (r / RPC) * K * D + m * D;   // the same address in every lane: broadcast reads
 #pragma unroll
       for (int v = 0; v < V; ++v) {
@@ -589,8 +616,8 @@ __global__ __launch_bounds__((NCB == 1 ? em_threads<K, D>() : 256), (NCB == 1 ? 
     }
   }
 #pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    uint8_t* a = assign + (size_t)(rb * 8 + r) * (in_features / D) + (size_t)c * (256 / D) + lane * V;
+  for (int r = 0; r < ROWS; ++r) {
+    uint8_t* a = assign + (size_t)(row0 + r) * (in_features / D) + (size_t)c * (256 / D) + lane * V;
     if constexpr (V == 4)
       *reinterpret_cast<uint32_t*>(a) = arg[4 * r] | (arg[4 * r + 1] << 8) | (arg[4 * r + 2] << 16) | (arg[4 * r + 3] << 24);
     else if constexpr (V == 2)
@@ -598,7 +625,44 @@ __global__ __launch_bounds__((NCB == 1 ? em_threads<K, D>() : 256), (NCB == 1 ? 
     else
       *a = (uint8_t)arg[r];
   }
+}
+
+// The E-step's kernels, workgroups of four waves.  strip_rows: filtered codebooks: the rows of a workgroup; the
+// others: 8 (a wave to a block) or 2 (a workgroup to a block).
+template <int K, int D, int NCB>
+__device__ __forceinline__ void em_assign(const float* __restrict__ W, const float* __restrict__ hdiag,
+                                          const float* __restrict__ cb, uint8_t* __restrict__ assign, int n_cb,
+                                          long long n_blocks, int in_features, int group_rows, int strip_rows) {
+  if constexpr (NCB == 1 && em_filtered<K, D>()) {
+    em_assign_filtered<K, D>(W, hdiag, cb, assign, n_cb, in_features, group_rows, strip_rows);
+  } else {
+    __shared__ __attribute__((aligned(16))) float cbs_all[4][NCB * K * D];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if constexpr (NCB == 1) {
+      if (strip_rows == 2) {
+        em_assign_loop<K, D, 1, 2>(W, hdiag, cb, assign, n_cb, in_features, group_rows, blockIdx.x, wave, cbs_all[wave]);
+        return;
+      }
+    }
+    const long long b = (long long)blockIdx.x * 4 + wave;
+    if (b >= n_blocks) return;   // whole waves leave; no workgroup barrier in the loop
+    em_assign_loop<K, D, NCB, 8>(W, hdiag, cb, assign, n_cb, in_features, group_rows, b, 0, cbs_all[wave]);
   }
+}
+
+template <int K>
+__global__ __launch_bounds__(256, (em_waves<K, 2>())) void em_assign_kernel(
+    const float* __restrict__ W, const float* __restrict__ hdiag, const float* __restrict__ cb, uint8_t* __restrict__ assign,
+    int n_cb, long long n_blocks, int in_features, int strip_rows) {
+  em_assign<K, 2, 1>(W, hdiag, cb, assign, n_cb, n_blocks, in_features, 8, strip_rows);
+}
+
+// any dimensionality and group height
+template <int K, int D, int NCB>
+__global__ __launch_bounds__(256, (NCB == 1 ? em_waves<K, D>() : 1)) void em_assign_any_kernel(
+    const float* __restrict__ W, const float* __restrict__ hdiag, const float* __restrict__ cb, uint8_t* __restrict__ assign,
+    int n_cb, long long n_blocks, int in_features, int group_rows, int strip_rows) {
+  em_assign<K, D, NCB>(W, hdiag, cb, assign, n_cb, n_blocks, in_features, group_rows, strip_rows);
 }
 
 // M-step.  An item is a group (NG = 1) or an 8-row block that holds NG = 8 / n_rows groups (groups of 1 or 4 rows);
@@ -619,7 +683,7 @@ __global__ __launch_bounds__((NCB == 1 ? em_threads<K, D>() : 256), (NCB == 1 ? 
 // all, and in brackets both with binary64 additions: d = 2, k = 64, 32 rows 67, 32 (75, 456); d = 2, k = 256, 8 rows 77,
 // 45 (72, 459), 128 rows 73, 39 (77, 501); d = 4, k = 256, 64 rows 69, 40 (81, 469), 256 rows 82, 59 (64, 270), where
 // the second half of the rows is read twice.  Weights further apart than 2^kSpread: 35 .. 64 for 28 .. 36 at 4096 x 4096.
-template <int K, int D, int NG, int GPW, int RB>
+template <int K, int D, int NG, int GPW, int RB, bool SHARED>
 struct EmTables {
   static constexpr int kEntries = NG * K;
   static constexpr int kCopies = kEntries >= 64 ? 1 : 64 / kEntries;
@@ -627,13 +691,13 @@ struct EmTables {
   // Counted: in tall groups with d = 4, k = 256 the weights' sums come from counts, 16 bits per centroid and vector position of a row for
   // the whole item (at most 256 rows): one 32-bit atomic in place of eight, and den[t] = sum over the positions of
   // count * h, exact products, at the end.
-  static constexpr bool kCounted = RB > 1 && K == 256 && D == 4;
+  static constexpr bool kCounted = !SHARED && RB > 1 && K == 256 && D == 4;
   static constexpr int kWords = 32;                         // dwords of counts per centroid: positions i and i + 32
-  static constexpr int kQuantities = kCounted ? D : 2 * D;
+  static constexpr int kQuantities = kCounted ? D : SHARED ? 2 : 2 * D;
   static constexpr int kTable = kQuantities * kStride;      // entries per item
-  static constexpr int kMaxWaves = GPW > 1 ? GPW : 8;
+  static constexpr int kMaxWaves = GPW > 1 ? GPW : SHARED ? 16 : 8;
   // an item has at most 2^kLog2N vectors; 51 bits are what the conversion below takes
-  static constexpr int kLog2N = (GPW > 1 ? 11 : RB > 1 ? 16 : 14) - (D == 4 ? 2 : D == 2 ? 1 : 0);
+  static constexpr int kLog2N = (GPW > 1 ? 11 : RB > 1 || SHARED ? 16 : 14) - (D == 4 ? 2 : D == 2 ? 1 : 0);
   static constexpr int kBits = 62 - kLog2N < 51 ? 62 - kLog2N : 51;
   static constexpr int kSpread = kBits - 36;
 };
@@ -675,12 +739,18 @@ __device__ __forceinline__ double wave_sum63(double v) {
   return v;
 }
 
-template <int K, int D, int NG, int GPW, int RB>
-__global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB>::kMaxWaves), (GPW > 1 ? 1 : 4)) void em_update_kernel(
+//   SHARED: few groups.  D workgroups take a group, a coordinate each, with up to 16 waves: what takes the time then is the
+// chain of a wave's vectors, one after the other (figures at em_shared; shares of the codebook instead of coordinates
+// leave every wave its chain: 24.6 us for 12.4 at 512 x 512, 256 rows, and 41 for 28 at 2048 x 2048).
+template <int K, int D, int NG, int GPW, int RB, bool SHARED>
+__global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWaves), (GPW > 1 ? 1 : 4)) void em_update_kernel(
     const float* __restrict__ W, const float* __restrict__ hdiag, const uint8_t* __restrict__ assign,
     float* __restrict__ cb_out, int n_cb, long long n_items, int in_features, int n_rows) {
-  using Tab = EmTables<K, D, NG, GPW, RB>;
+  static_assert(!SHARED || (GPW == 1 && NG == 1), "a workgroup has one group");
+  using Tab = EmTables<K, D, NG, GPW, RB, SHARED>;
+  constexpr int DT = SHARED ? 1 : D;                // coordinates of this workgroup
   constexpr int V = 4 / D;                          // vectors per row and lane
+  constexpr int N = V * DT;                         // values of a row and lane: DT of each vector
   constexpr int RPG = 8 / NG;                       // rows of an 8-row block that share a codebook
   constexpr int CW = Tab::kWords + 1;               // a gap spreads the centroids over the banks
   constexpr uint32_t kNone = 0x100;
@@ -688,7 +758,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB>::kMaxWaves), (GPW
   __shared__ uint32_t top_all[GPW * Tab::kTable];
   __shared__ uint32_t counts[Tab::kCounted ? K * CW : 1];
   __shared__ double h_all[Tab::kCounted ? 256 : 1];
-  __shared__ double hot_sums[Tab::kMaxWaves][NG][2 * D];
+  __shared__ double hot_sums[Tab::kMaxWaves][NG][2 * DT];
   __shared__ uint32_t hot_of[Tab::kMaxWaves][NG];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -699,7 +769,8 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB>::kMaxWaves), (GPW
   const int t_item = sub * 64 + lane, t_count = waves * 64;
   unsigned long long* sums = sum_all + slot * Tab::kTable;
   uint32_t* tops = top_all + slot * Tab::kTable;
-  const long long item = (long long)blockIdx.x * GPW + slot;
+  const long long item = SHARED ? (long long)(blockIdx.x / D) : (long long)blockIdx.x * GPW + slot;
+  const int t0 = SHARED ? (int)(blockIdx.x % D) : 0;   // the first of its coordinates
   if (GPW > 1 && item >= n_items) return;           // whole waves leave; no workgroup barrier with GPW > 1
   const long long ir = item / n_cb;                 // group row, or 8-row block where that holds several groups
   const int c = (int)(item - ir * n_cb);
@@ -709,17 +780,27 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB>::kMaxWaves), (GPW
     else __syncthreads();
   };
 
-  const float4 h4 = *reinterpret_cast<const float4*>(hdiag + (size_t)c * 256 + lane * 4);
-  const float* Wl = W + (size_t)row0 * in_features + (size_t)c * 256 + lane * 4;
+  float h[N];
+  auto load_values = [&](const float* p, float (&v)[N]) {
+    if constexpr (SHARED) {
+#pragma unroll
+      for (int i = 0; i < V; ++i) v[i] = p[i * D];
+    } else {
+      const float4 t = *reinterpret_cast<const float4*>(p);
+      v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+    }
+  };
+  load_values(hdiag + (size_t)c * 256 + lane * 4 + t0, h);
+  const float* Wl = W + (size_t)row0 * in_features + (size_t)c * 256 + lane * 4 + t0;
   const uint8_t* al = assign + (size_t)row0 * (in_features / D) + (size_t)c * (256 / D) + lane * V;
-  auto load = [&](int r, float4& xr, uint32_t& ar) {
-    xr = *reinterpret_cast<const float4*>(Wl + (size_t)r * in_features);
+  auto load = [&](int r, float (&xr)[N], uint32_t& ar) {
+    load_values(Wl + (size_t)r * in_features, xr);
     const uint8_t* ap = al + (size_t)r * (in_features / D);
     if constexpr (V == 4) ar = *reinterpret_cast<const uint32_t*>(ap);
     else if constexpr (V == 2) ar = *reinterpret_cast<const uint16_t*>(ap);
     else ar = *ap;
   };
-  float4 x[8 * RB];
+  float x[8 * RB][N];
   uint32_t a[8 * RB];
   auto load_part = [&](int p) {
 #pragma unroll
@@ -736,7 +817,6 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB>::kMaxWaves), (GPW
   }
   item_sync();
 
-  const float h[4] = {h4.x, h4.y, h4.z, h4.w};
   const int copy = Tab::kCopies > 1 ? lane % Tab::kCopies : 0;
   // the centroid of each group that the most lanes of a row share, among a few that are asked
   uint32_t hot[NG];
@@ -746,7 +826,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB>::kMaxWaves), (GPW
     int most = 11;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const uint32_t m = a[g * RPG + j % RPG] & 0xffu;
+      const uint32_t m = (a[g * RPG + j % RPG] & 0xffu);
       const uint32_t asked = (uint32_t)__builtin_amdgcn_readlane((int)m, 8 * j + 3);
       const int n = __builtin_popcountll(__ballot(m == asked));
       if (n > most && (K == 256 || asked < (uint32_t)K)) { most = n; hot[g] = asked; }
@@ -759,7 +839,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB>::kMaxWaves), (GPW
   {
     float big = 0.f, small = __builtin_inff();
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < N; ++t) {
       const float v = __builtin_fabsf(h[t]);
       big = max_nn(big, v);
       small = __builtin_fminf(small, v == 0.f ? __builtin_inff() : v);
@@ -771,10 +851,10 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB>::kMaxWaves), (GPW
     any_h = !finite || h_exp < 32 || __builtin_bit_cast(uint32_t, small) >> 23 < h_exp - Tab::kSpread;
   }
   constexpr int P = Tab::kBits;
-  auto finish = [&](int g, const double (&own)[2 * D]) {   // the wave's sums of the centroid kept in registers
+  auto finish = [&](int g, const double (&own)[2 * DT]) {   // the wave's sums of the centroid kept in registers
     if (hot[g] != kNone) {
 #pragma unroll
-      for (int q = 0; q < (Tab::kCounted ? D : 2 * D); ++q) {
+      for (int q = 0; q < (Tab::kCounted ? DT : 2 * DT); ++q) {
         const double sum = wave_sum63(own[q]);
         if (lane == 63) hot_sums[wave][g][q] = sum;
       }
@@ -791,24 +871,23 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB>::kMaxWaves), (GPW
 #pragma unroll
       for (int g = 0; g < NG; ++g) hot[g] = kNone;
     }
-    double own[2 * D] = {};
+    double own[2 * DT] = {};
     auto pass = [&](auto second) {
 #pragma unroll 1
       for (int r = 0; r < 8 * RB * parts; ++r) {
-        float4 xr4;
+        float xr[N];
         uint32_t ar;
-        load(RB > 1 ? r / (8 * RB) * waves * 8 * RB + r % (8 * RB) : r, xr4, ar);
-        const float xr[4] = {xr4.x, xr4.y, xr4.z, xr4.w};
+        load(RB > 1 ? r / (8 * RB) * waves * 8 * RB + r % (8 * RB) : r, xr, ar);
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-          const uint32_t m = (ar >> (8 * v)) & 0xffu;
-          if constexpr (!decltype(second)::value) count(m);
+          const uint32_t m = ((ar >> (8 * v)) & 0xffu);
           if (K < 256 && m >= (uint32_t)K) continue;
+          if constexpr (!decltype(second)::value) count(m);
           const bool kept = NG == 1 && m == hot[0];
           const int e = ((NG > 1 ? r / RPG : 0) * K + m) * Tab::kCopies + copy;
 #pragma unroll
           for (int q = 0; q < Tab::kQuantities; ++q) {
-            const double hv = h[v * D + q % D], term = q < D ? hv * (double)xr[v * D + q % D] : hv;
+            const double hv = h[v * DT + q % DT], term = q < DT ? hv * (double)xr[v * DT + q % DT] : hv;
             const int i = e + q * Tab::kStride;
             if constexpr (!decltype(second)::value) {
               if (!kept) atomicMax(tops + i, high_magnitude(term));
@@ -836,56 +915,60 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB>::kMaxWaves), (GPW
 #pragma unroll
       for (int r = 0; r < 8 * RB; ++r) {
         const int g = NG > 1 ? r / RPG : 0;
-        const float xr[4] = {x[r].x, x[r].y, x[r].z, x[r].w};
+        const float (&xr)[N] = x[r];
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-          const uint32_t m = (a[r] >> (8 * v)) & 0xffu;
+          const uint32_t m = ((a[r] >> (8 * v)) & 0xffu);
           count(m);
           if (m != hot[g] && (K == 256 || m < (uint32_t)K)) {
             uint32_t* e = tops + (g * K + m) * Tab::kCopies + copy;
 #pragma unroll
-            for (int t = 0; t < D; ++t) atomicMax(e + t * Tab::kStride, __builtin_bit_cast(uint32_t, xr[v * D + t]) & 0x7fffffffu);
+            for (int t = 0; t < DT; ++t) atomicMax(e + t * Tab::kStride, __builtin_bit_cast(uint32_t, xr[v * DT + t]) & 0x7fffffffu);
           }
         }
       }
     }
     item_sync();
-    unsigned long long h_fixed[4];                  // |h| < 2^(h_exp - 126)
+    unsigned long long h_fixed[N];                  // |h| < 2^(h_exp - 126)
 #pragma unroll
-    for (int t = 0; t < 4; ++t) h_fixed[t] = to_fixed((double)h[t], (P + 1149u - h_exp) << 20);
-    double own[2 * D] = {};
+    for (int t = 0; t < N; ++t) h_fixed[t] = to_fixed((double)h[t], (P + 1149u - h_exp) << 20);
+    double own[2 * DT] = {};
 #pragma unroll 1
     for (int p = parts - 1; p >= 0; --p) {          // the part at hand first
       if (p < parts - 1) load_part(p);
       // what this pass needs is computed again: kept from the first, it would not fit the registers
 #pragma unroll
       for (int r = 0; r < 8 * RB; ++r)
-        asm volatile("" : "+v"(x[r].x), "+v"(x[r].y), "+v"(x[r].z), "+v"(x[r].w), "+v"(a[r]));
+      {
+#pragma unroll
+        for (int t = 0; t < N; ++t) asm volatile("" : "+v"(x[r][t]));
+        asm volatile("" : "+v"(a[r]));
+      }
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
         constexpr int ROWS = NG > 1 ? RPG : 8 * RB;
 #pragma unroll
         for (int r = g * ROWS; r < (g + 1) * ROWS; ++r) {
-          const float xr[4] = {x[r].x, x[r].y, x[r].z, x[r].w};
+          const float (&xr)[N] = x[r];
 #pragma unroll
           for (int v = 0; v < V; ++v) {
-            const uint32_t m = (a[r] >> (8 * v)) & 0xffu;
+            const uint32_t m = ((a[r] >> (8 * v)) & 0xffu);
             if (m == hot[g]) {
 #pragma unroll
-              for (int t = 0; t < D; ++t) {
-                own[t] += (double)h[v * D + t] * (double)xr[v * D + t];
-                if constexpr (!Tab::kCounted) own[D + t] += (double)h[v * D + t];
+              for (int t = 0; t < DT; ++t) {
+                own[t] += (double)h[v * DT + t] * (double)xr[v * DT + t];
+                if constexpr (!Tab::kCounted) own[DT + t] += (double)h[v * DT + t];
               }
             } else if (K == 256 || m < (uint32_t)K) {
               const int e = (g * K + m) * Tab::kCopies + copy;
 #pragma unroll
-              for (int t = 0; t < D; ++t) {
+              for (int t = 0; t < DT; ++t) {
                 const int i = e + t * Tab::kStride;
                 const uint32_t top = tops[i];
-                const double hx = (double)h[v * D + t] * (double)xr[v * D + t];
+                const double hx = (double)h[v * DT + t] * (double)xr[v * DT + t];
                 if (top >= 0x7f800000u) add_nonfinite(sums + i, hx);
                 else atomicAdd(sums + i, to_fixed(hx, ((P + 1275u - h_exp) << 20) - ((top >> 3) & 0x0ff00000u)));
-                if constexpr (!Tab::kCounted) atomicAdd(sums + i + D * Tab::kStride, h_fixed[v * D + t]);
+                if constexpr (!Tab::kCounted) atomicAdd(sums + i + DT * Tab::kStride, h_fixed[v * DT + t]);
               }
             }
           }
@@ -893,7 +976,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB>::kMaxWaves), (GPW
         if constexpr (NG > 1) {                       // one part
           finish(g, own);
 #pragma unroll
-          for (int q = 0; q < 2 * D; ++q) own[q] = 0.;
+          for (int q = 0; q < 2 * DT; ++q) own[q] = 0.;
         }
       }
     }
@@ -901,7 +984,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB>::kMaxWaves), (GPW
   }
   item_sync();
   if constexpr (Tab::kCounted) {
-    for (int i = t_item; i < 2 * K; i += t_count) {           // two lanes per centroid
+    for (int i = t_item; i < 2 * K; i += t_count) {   // two lanes per centroid
       const int m = i >> 1, half = i & 1;
       const uint32_t* n = counts + m * CW + half * (Tab::kWords / 2);
       const double* hp = h_all + half * 4 * (Tab::kWords / 2);
@@ -937,12 +1020,12 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB>::kMaxWaves), (GPW
     item_sync();
   }
 
-  for (int i = t_item; i < NG * K * D; i += t_count) {
-    const int e = i / D, t = i % D, g = e / K;
+  for (int i = t_item; i < NG * K * DT; i += t_count) {
+    const int e = i / DT, t = i % DT, g = e / K;
     double num = 0., den = 0.;
 #pragma unroll
     for (int q = 0; q < Tab::kCopies; ++q) {
-      const int p = t * Tab::kStride + e * Tab::kCopies + q, p_h = p + D * Tab::kStride;
+      const int p = t * Tab::kStride + e * Tab::kCopies + q, p_h = p + DT * Tab::kStride;
       const uint32_t top = tops[p];
       if (any_h) {
         if (top != 0) num += top >= 0x7ff00000u ? from_nonfinite(sums[p]) : from_fixed(sums[p], (int)(top >> 20) + 1 - P);
@@ -958,13 +1041,13 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB>::kMaxWaves), (GPW
     for (int w = 0; w < waves; ++w) {
       if (hot_of[wave - sub + w][g] == (uint32_t)(e % K)) {
         num += hot_sums[wave - sub + w][g][t];
-        if constexpr (!Tab::kCounted) den += hot_sums[wave - sub + w][g][D + t];
+        if constexpr (!Tab::kCounted) den += hot_sums[wave - sub + w][g][DT + t];
       }
     }
     if constexpr (Tab::kCounted)
       den = __builtin_bit_cast(double, (uint64_t)counts[e * CW + 2 * t + 1] << 32 | counts[e * CW + 2 * t]);
     const long long gi = NG > 1 ? (ir * NG + g) * n_cb + c : item;
-    cb_out[(gi * K + e % K) * D + t] = den != 0. ? (float)num / (float)den : 0.f;
+    cb_out[(gi * K + e % K) * D + t0 + t] = den != 0. ? (float)num / (float)den : 0.f;
   }
 }
 
@@ -1075,32 +1158,66 @@ __global__ __launch_bounds__(64) void em_update_small_kernel(const float* __rest
     default: F(256); break;  \
   }
 
-// Workgroups of one block each (filtered) or of four.
-template <int K, int D> static unsigned em_grid(long long n_blocks) {
-  return (unsigned)(em_filtered<K, D>() ? n_blocks : (n_blocks + 3) / 4);
+// Rows of a strip.  Filtered: a workgroup to 8 rows in small launches and low groups, else to up to 32, which make the
+// centroids' features fewer times.  us with strips of 8, 32: 1536 x 1536 (1,152 blocks) d = 2, k = 64 12.7, 22.9, d = 2,
+// k = 256 23.8, 34.7, d = 4, k = 256 18.4, 24.9; 2048 x 2048 (2,048) 17.5, 24.8, 35.8, 39.9, 28.9, 27.7; 2048 x 4096 (4,096)
+// 31.9, 33.9, 68.7, 64.9, 52.0, 48.6; 4096 x 4096 57.8, 57.7, 122.9, 118.0, 97.2, 83.7.
+//   Loops: a wave to 8 rows, or to 2 where the blocks would leave SIMDs idle.  us with 8, 2: 512 x 512 (128 blocks) d = 1,
+// k = 64 26.6, 10.2, d = 2, k = 16 7.4, 3.2; 1536 x 1536 33.2, 22.5, 8.0, 5.9; 2048 x 2048 (2,048) 35.0, 32.4, 8.8, 8.3;
+// 2048 x 4096 61.8, 59.1, 16.0, 16.2; 4096 x 4096 117, 110, 30.8, 32.1 and d = 1, k = 8 22.7, 23.9.
+template <int K, int D, int NCB> static int em_strip_rows(const vq_desc& d, long long n_blocks) {
+  const long long cus = device_cus();
+  if (NCB == 1 && em_filtered<K, D>())
+    return d.group_rows <= kGroupRows || n_blocks < 16 * cus ? kGroupRows : d.group_rows < 32 ? d.group_rows : 32;
+  return NCB == 1 && n_blocks <= 8 * cus ? 2 : 8;
 }
+template <int K, int D, int NCB> static unsigned em_grid(long long n_blocks, int strip_rows) {
+  if (NCB == 1 && em_filtered<K, D>()) return (unsigned)(n_blocks / (strip_rows / kGroupRows));
+  return (unsigned)(strip_rows == 2 ? n_blocks : (n_blocks + 3) / 4);
+}
+constexpr long long kMostEmBlocks = 1ll << 23;   // of a launch: fewer than 2^32 threads
 
 hipError_t launch_em_assign(const vq_desc& d, const void* W, const void* hdiag, const void* cb, void* assign,
                             hipStream_t s) {
   const int k = d.k, out_features = d.out_features, in_features = d.in_features;
   const int n_cb = in_features / kGroupCols;
   const long long n_blocks = (long long)(out_features / kGroupRows) * n_cb;
-  const unsigned grid = (unsigned)((n_blocks + 3) / 4);
+  if (n_blocks > kMostEmBlocks) {       // in parts of whole groups
+    const int unit = d.group_rows > kGroupRows ? d.group_rows : kGroupRows;
+    const long long fit = kMostEmBlocks / n_cb * kGroupRows / unit * unit;
+    const int rows = fit < unit ? unit : (int)fit;   // a single row of groups: filtered ones take strips of up to 32 rows
+    for (int at = 0; rows < out_features && at < out_features; at += rows) {
+      vq_desc p = d;
+      p.out_features = rows < out_features - at ? rows : out_features - at;
+      const hipError_t e =
+          launch_em_assign(p, (const float*)W + (size_t)at * in_features, hdiag,
+                           (const float*)cb + (size_t)(at / d.group_rows) * n_cb * k * d.d,
+                           (uint8_t*)assign + (size_t)at * (in_features / d.d), s);
+      if (e != hipSuccess) return e;
+    }
+    if (rows < out_features) return hipSuccess;
+  }
   if (d.d == 2 && d.group_rows == kGroupRows && (k == 16 || k == 64 || k == 256)) {
-#define VQ_EM(K)                                                                                   \
-  hipLaunchKernelGGL(em_assign_kernel<K>, dim3((em_grid<K, 2>(n_blocks))), dim3((em_threads<K, 2>())), 0, s, (const float*)W, \
-                     (const float*)hdiag, (const float*)cb, (uint8_t*)assign, n_cb, n_blocks, in_features)
+#define VQ_EM(K)                                                                                                   \
+  do {                                                                                                             \
+    const int strip_rows = em_strip_rows<K, 2, 1>(d, n_blocks);                                                    \
+    hipLaunchKernelGGL(em_assign_kernel<K>, dim3((em_grid<K, 2, 1>(n_blocks, strip_rows))), dim3(256), 0, s,       \
+                       (const float*)W, (const float*)hdiag, (const float*)cb, (uint8_t*)assign, n_cb, n_blocks,   \
+                       in_features, strip_rows);                                                                   \
+  } while (0)
     if (k == 16) VQ_EM(16);
     else if (k == 64) VQ_EM(64);
     else VQ_EM(256);
 #undef VQ_EM
     return hipGetLastError();
   }
-#define VQ_EM_ANY(K, D, NCB)                                                                             \
-  hipLaunchKernelGGL((em_assign_any_kernel<K, D, NCB>), dim3((NCB == 1 ? em_grid<K, D>(n_blocks) : grid)), \
-                     dim3((NCB == 1 ? em_threads<K, D>() : 256)), 0, s, (const float*)W,                   \
-                     (const float*)hdiag, (const float*)cb, (uint8_t*)assign, n_cb, n_blocks, in_features, \
-                     d.group_rows)
+#define VQ_EM_ANY(K, D, NCB)                                                                                        \
+  do {                                                                                                             \
+    const int strip_rows = em_strip_rows<K, D, NCB>(d, n_blocks);                                                  \
+    hipLaunchKernelGGL((em_assign_any_kernel<K, D, NCB>), dim3((em_grid<K, D, NCB>(n_blocks, strip_rows))), dim3(256), 0, s, \
+                       (const float*)W, (const float*)hdiag, (const float*)cb, (uint8_t*)assign, n_cb, n_blocks,   \
+                       in_features, d.group_rows, strip_rows);                                                     \
+  } while (0)
   if (d.group_rows == 1) {   // a codebook per row: k * d <= 64 (checked by the caller)
     if (d.d == 1) {
 #define VQ_F(K) if constexpr (K <= 64) VQ_EM_ANY(K, 1, 8); else return hipErrorInvalidValue
@@ -1142,6 +1259,12 @@ hipError_t launch_em_assign(const vq_desc& d, const void* W, const void* hdiag, 
   return hipGetLastError();
 }
 
+// Whether D workgroups share a group of 16 rows or more in the M-step.  us with one, D: d = 4, k = 256, 256 rows 512 x 512
+// (4 groups) 28.0, 12.4, 2048 x 2048 (64) 28.3, 19.1, 2048 x 3072 (96) 28.5, 24.7; 64 rows 512 x 512 (16) 9.9, 5.7,
+// 1024 x 1536 (96) 10.2, 8.0, 1024 x 2048 (128) 10.3, 10.2; d = 2, k = 256, 128 rows 512 x 512 (8) 15.5, 12.5,
+// 2048 x 2048 (128) 15.7, 13.8; k = 64, 32 rows 1024 x 2048 (256) 8.6, 8.5.
+static bool em_shared(const vq_desc& d, long long n_items) { return n_items * d.d <= 2 * device_cus(); }
+
 template <int K, int D, int NG, int GPW, int RB>
 static void launch_update(const vq_desc& d, const void* W, const void* hdiag, const void* assign, void* cb_out,
                           hipStream_t s) {
@@ -1155,7 +1278,21 @@ static void launch_update(const vq_desc& d, const void* W, const void* hdiag, co
     }
   }
   const int waves = GPW > 1 ? GPW : RB > 1 ? 8 : d.group_rows / kGroupRows;
-  hipLaunchKernelGGL((em_update_kernel<K, D, NG, GPW, RB>), dim3((unsigned)((n_items + GPW - 1) / GPW)), dim3(64 * waves), 0, s,
+  if constexpr (GPW == 1 && NG == 1 && D > 1) {
+    if (em_shared(d, n_items)) {
+#define VQ_SHARED(RBS, WAVES)                                                                                              \
+  hipLaunchKernelGGL((em_update_kernel<K, D, 1, 1, RBS, true>), dim3((unsigned)(n_items * D)), dim3(64 * (WAVES)), 0, s,   \
+                     (const float*)W, (const float*)hdiag, (const uint8_t*)assign, (float*)cb_out, n_cb, n_items,          \
+                     d.in_features, d.group_rows)
+      if constexpr (RB > 1) {
+        if (d.group_rows == 256) { VQ_SHARED(2, 16); return; }
+      }
+      VQ_SHARED(1, d.group_rows / kGroupRows);
+#undef VQ_SHARED
+      return;
+    }
+  }
+  hipLaunchKernelGGL((em_update_kernel<K, D, NG, GPW, RB, false>), dim3((unsigned)((n_items + GPW - 1) / GPW)), dim3(64 * waves), 0, s,
                      (const float*)W, (const float*)hdiag, (const uint8_t*)assign, (float*)cb_out, n_cb, n_items,
                      d.in_features, d.group_rows);
 }

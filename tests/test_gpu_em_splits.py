@@ -1,0 +1,71 @@
+"""The quantiser's steps divide their work by the size of a launch: strips of 8 to 32 rows, waves of 8 or 2 rows, a group's
+coordinates to one workgroup or to several.  A launch over many rows against launches over a few rows each; and codebooks
+with any number of equal centroids against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_em import _gpu_em_any, _inputs_any, env  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+BITS = {8: 3, 16: 4, 32: 5, 64: 6, 256: 8}
+
+
+# (k, d, group rows): filtered with strips of 8, 16 and 32 rows, loops; groups that a wave, a workgroup or several take
+@pytest.mark.parametrize("shape", [(64, 2, 8), (64, 2, 32), (256, 2, 128), (64, 4, 16), (256, 4, 64), (256, 4, 256), (16, 1, 8),
+                                   (32, 2, 32), (16, 2, 256)], ids=str)
+def test_one_launch_and_many(env, shape):  # noqa: F811
+    torch, vq, _ = env
+    k, d, gr = shape
+    out_f, in_f, part = 5120, 2048, 512                       # 5120 blocks of 8 x 256; 512
+    g = torch.Generator("cuda").manual_seed(k + d + gr)
+    W = torch.randn((out_f, in_f), device="cuda", generator=g) * 0.02
+    h = 0.2 + 4.8 * torch.rand(in_f, device="cuda", generator=g)
+    cb = torch.randn((out_f // gr, in_f // 256, k, d), device="cuda", generator=g) * 0.02
+    cb[::2, :, k // 2:] = cb[::2, :, :k - k // 2]             # equal centroids in every other row of groups
+    cb[:, :, 1] = 0
+    cb[:, :, k - 1] = -0.0
+
+    def both(rows):
+        a = torch.full((out_f, in_f // d), 255, dtype=torch.uint8, device="cuda")
+        new = torch.full_like(cb, 777.0)
+        for r in range(0, out_f, rows):
+            desc = vq.make_desc(rows, in_f, k, BITS[k], gr, 256, d)
+            at = slice(r // gr, (r + rows) // gr)
+            vq.vq_em_assign(desc, W[r:r + rows], h, cb[at].contiguous(), a[r:r + rows])
+            out = torch.full_like(cb[at], 777.0).contiguous()
+            vq.vq_em_update(desc, W[r:r + rows], h, a[r:r + rows], out)
+            new[at] = out
+        torch.cuda.synchronize()
+        return a, new
+
+    (a, new), (a_parts, new_parts) = both(out_f), both(part)
+    assert torch.equal(a, a_parts)
+    # each sum is off by n * 2^-36 of its largest term at most (n vectors of a group), the quotient by three roundings
+    # to binary32 more; sums of both signs cancel, so the bound is taken on the magnitudes: all |x| <= 0.02 * 6
+    assert (new - new_parts).abs().max().item() <= 0.12 * (gr * 256 / d * 2.0 ** -36 * 25 + 2.0 ** -22)
+    assert not (new == 777.0).any()
+
+
+# the filter works on the distinct centroids, spread over the blocks of 8: fewer than blocks, as many, one more, all but one
+@pytest.mark.parametrize("distinct", ["blocks - 1", "blocks", "blocks + 1", "blocks + 7", "half", "all but one", "all"])
+@pytest.mark.parametrize("shape", [(2, 64, 8, 16, 512), (2, 64, 32, 64, 256), (2, 256, 8, 16, 256), (4, 64, 16, 32, 512),
+                                   (4, 256, 64, 64, 256)], ids=str)
+def test_equal_centroids(env, shape, distinct):  # noqa: F811
+    d, k, gr, out_f, in_f = shape
+    W, h, cb = _inputs_any(out_f, in_f, k, d, gr, 70 + k + d, from_data=False)
+    rng = np.random.default_rng(k + d)
+    n = {"half": k // 2, "all but one": k - 1, "all": k}.get(distinct)
+    if n is None:
+        n = k // 8 + int(distinct[6:].replace(" ", "") or 0)
+    for g in range(cb.shape[0]):
+        values = cb[g, :n].copy()
+        values[0] = 0
+        order = np.concatenate([np.arange(n), rng.integers(0, n, k - n)])
+        rng.shuffle(order)
+        cb[g] = values[order]
+        cb[g][(order == 0) & (rng.random(k) < 0.5)] = -0.0    # equal to the other zeros
+    f = oracle.VQFormat(out_f, in_f, k, 8, gr, 256, d)
+    a, _ = _gpu_em_any(env, (out_f, in_f, k, d, gr), W, h, cb)
+    np.testing.assert_array_equal(a, oracle.em_assign(f, W, h, cb))

@@ -151,3 +151,14 @@ def test_re_layout_of_the_6_bit_formats_keeps_to_the_size_of_a_launch(launches, 
     assert status == 0 and sum(l[1][0] for l in ls) == want
     assert all(l[1][0] * l[2] < 2 ** 32 for l in ls)
     assert status1 == 0 and len(ls1) == 1
+
+
+@pytest.mark.parametrize("shape", [(8, 2, 256), (16, 4, 64), (256, 4, 256)], ids=str)
+def test_e_step_keeps_to_the_size_of_a_launch(launches, shape):
+    """A launch takes fewer than 2^32 threads; larger matrices (fp32 weights up to the size of the memory) go in several."""
+    gr, d, k = shape
+    (status, ls), = launches([("assign", 2 ** 19 + 256, 65536, gr, d, k, vq.VQ_F16)])
+    assert status == 0
+    assert all(l[1][0] * l[2] < 2 ** 32 for l in ls)
+    strip = min(gr, 32)
+    assert sum(l[1][0] for l in ls) == (2 ** 19 + 256) // strip * 256
