@@ -10,12 +10,12 @@
 //     into registers one col-block earlier, all 16 lookups of a lane are issued
 //     before the first result is used;
 //   * X is batch-contiguous, while an MFMA operand wants 8 consecutive k per lane.
-//     gemm_kernel (NT = 128 / 256) copies X sub-tiles to LDS unchanged (16-byte loads, four
-//     sub-tiles ahead in registers, 16-byte LDS stores) and forms the operand with the
-//     transposing LDS read ds_read_b64_tr_b16; the col-block is consumed in 64- / 32-deep
-//     sub-steps through two X buffers (one barrier per sub-step), wave w owns a quarter of
+//     gemm_kernel has X sub-tiles loaded into LDS as they are (16 bytes a lane, no registers in between, two
+//     sub-tiles ahead) and forms the operand with the transposing LDS read ds_read_b64_tr_b16; the col-block is
+//     consumed in 2 to 8 sub-steps (one barrier each), wave w owns a quarter of
 //     the batch columns and 32*RBW rows (RBW x NT/128 accumulator tiles); with WM = 2 the
 //     workgroup has 8 waves and twice the rows, the second four waves taking the lower half;
+//   * ring_gemm_kernel (32 x 128 tiles) stages X through registers, four sub-tiles ahead;
 //   * gemm_tiny_kernel (16 x 16 tiles, a private X tile per wave) and gemm_small_kernel
 //     (32 x 32 tiles, bandwidth-bound batches) copy X the same way.
 #include <atomic>
@@ -436,15 +436,28 @@ __device__ __forceinline__ h8_t read_x_operand(const char* src) {
   return __builtin_bit_cast(h8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-template <int K, int RBW, int NT, int WM = 1>
-__global__ __launch_bounds__(256 * WM, WM == 1 ? 2 : 1) void gemm_kernel(const uint8_t* __restrict__ idx,
+// Tiles of Y to workgroups, which go to the 8 XCDs in turn: an XCD takes all column tiles of a tile row, one behind the
+// other, so its L2 has every column of X in use and the indices of a tile row in one XCD only.  Column tile = workgroup %
+// column tiles gave an XCD one column tile of eight, whose rows, a power of two apart, lie in a few of the L2's channels:
+// us before, after: 11008 x 4096, B = 2048 203, 200 (k = 256), 4096 x 11008 210, 199, 8352 x 1280, B = 1082 54.6, 51.9 (k = 64
+// with block scales).
+__device__ __forceinline__ void tile_of_workgroup(int n_tiles_n, int& mt, int& nt) {
+  const uint32_t b = blockIdx.x, tiles_m = gridDim.x / (uint32_t)n_tiles_n;
+  const uint32_t run = b / (8u * n_tiles_n), left = tiles_m - 8u * run, r = b - run * 8u * n_tiles_n;
+  const uint32_t rows = left < 8u ? left : 8u;   // of the last run
+  nt = (int)(r / rows);
+  mt = (int)(8u * run + r % rows);
+}
+
+template <int K>
+__global__ __launch_bounds__(256, 2) void ring_gemm_kernel(const uint8_t* __restrict__ idx,
                                                    const uint32_t* __restrict__ cb,
                                                    const uint16_t* __restrict__ X, int B, int ldx,
                                                    void* __restrict__ Y, int ldy, int y_f32,
                                                    int n_rb, int n_cb, int n_tiles_n, int rpc,
                                                    int rb0, int rb_end) {
   // the launch covers row-blocks [rb0, rb_end) of the matrix's n_rb; tile rows count from rb0
-  static_assert(NT == 128 || NT == 256 || (NT == 512 && WM == 2), "column tile");
+  constexpr int RBW = 1, NT = 128, WM = 1;
   constexpr int MT = 32 * RBW * WM;
   constexpr int KS = 8192 / NT;                  // k per X sub-tile: 64 or 32
   constexpr int NSUB = 256 / KS;                 // sub-steps per col-block: 4 or 8
@@ -458,8 +471,8 @@ __global__ __launch_bounds__(256 * WM, WM == 1 ? 2 : 1) void gemm_kernel(const u
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wc = wave & 3, wr = wave >> 2;       // column quarter, row half
-  const int mt = blockIdx.x / n_tiles_n;
-  const int nt = blockIdx.x - mt * n_tiles_n;
+  int mt, nt;
+  tile_of_workgroup(n_tiles_n, mt, nt);
 
   // X staging role: a sub-tile is copied in 4 passes of RPP rows; the thread owns 16 bytes
   // (8 batch columns from n_loc) of row x_row of every pass.  Columns at or beyond B are
@@ -589,6 +602,184 @@ __global__ __launch_bounds__(256 * WM, WM == 1 ? 2 : 1) void gemm_kernel(const u
   }
 }
 
+// One instruction: 64 lanes x 16 bytes of X (base + voff, voff per lane) into 1 KB of LDS from byte address lds on.  No
+// register takes the data; the wave's vmcnt counts it.  The compiler neither counts these loads (its own waits are then
+// stricter than it knows) nor uses m0 in these kernels.
+__device__ __forceinline__ void x_to_lds(const char* base, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(voff), "s"(base) : "memory");
+}
+
+// Until no more than N of the wave's loads are on their way (those of x_to_lds among them).
+template <int N> __device__ __forceinline__ void wait_loads() {
+  static_assert(N < 16, "four bits of the count");
+  asm volatile("" : : : "memory");
+  __builtin_amdgcn_s_waitcnt(0x0f70 | N);
+  asm volatile("" : : : "memory");
+}
+
+// Bound (11008 x 4096, B = 2048, k = 256: 200 us): the phases of a col-block follow one another.  Without the products
+// 132, without them and X 74 (decoding W, once per column tile), without them and the decoding 97 (X through L2).  With
+// X staged through registers in sub-tiles of half the size, one barrier per 8 products of a wave: 226; 2336 x 7168, B = 634
+// 58 -> 54; 4096 x 4096, B = 512, d = 4 with fp16 tables 52 -> 41.
+template <int K, int RBW, int NT, int WM = 1>
+__global__ __launch_bounds__(256 * WM, WM == 1 ? 2 : 1) void gemm_kernel(const uint8_t* __restrict__ idx,
+                                                   const uint32_t* __restrict__ cb,
+                                                   const uint16_t* __restrict__ X, int B, int ldx,
+                                                   void* __restrict__ Y, int ldy, int y_f32,
+                                                   int n_rb, int n_cb, int n_tiles_n, int rpc,
+                                                   int rb0, int rb_end) {
+  // the launch covers row-blocks [rb0, rb_end) of the matrix's n_rb; tile rows count from rb0
+  static_assert(NT == 128 || NT == 256 || (NT == 512 && WM == 2), "column tile");
+  constexpr int WAVES = 4 * WM;
+  constexpr int MT = 32 * RBW * WM;
+  constexpr int XB = WM == 2 ? 32768 : 16384;    // bytes of an X sub-tile
+  constexpr int KS = XB / 2 / NT;                // k per X sub-tile
+  constexpr int NSUB = 256 / KS;                 // sub-steps per col-block
+  static_assert(NSUB >= 2, "two sub-tiles are staged before the first sub-step");
+  constexpr int NB = NT / 128;                   // 32-column accumulator tiles per wave
+  __shared__ __attribute__((aligned(16))) char smem[3 * XB + MT * WS * 2];
+  char* const Xs_all = smem;                     // three buffers of [KS][NT] halfs
+  uint16_t* const Wt = reinterpret_cast<uint16_t*>(smem + 3 * XB);
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wc = wave & 3, wr = wave >> 2;       // column quarter, row half
+  int mt, nt;
+  tile_of_workgroup(n_tiles_n, mt, nt);
+
+  // X staging role: the wave copies PER pieces of 1 KB, RPI rows each.  The lane's 16 bytes lie behind one another in LDS; which
+  // 8 columns of the row they are follows from the swizzle (see above), which depends on row & 3.  Columns at or beyond
+  // B are loaded from column 0 instead: they only reach accumulator columns that are never written.
+  constexpr int RPI = 512 / NT, PER = XB / 1024 / WAVES;
+  constexpr int VAR = RPI >= 4 ? 1 : 4 / RPI;    // values of (first row of a piece) & 3
+  static_assert(PER % VAR == 0, "piece j of a wave starts at row j * RPI modulo 4");
+  uint32_t x_voff[VAR];
+#pragma unroll
+  for (int j = 0; j < VAR; ++j) {
+    const int r = lane / (NT / 8), at = lane % (NT / 8);
+    const int n_glob = nt * NT + (((at >> 1) ^ (2 * ((j * RPI + r) & 3))) << 4) + (at & 1) * 8;
+    x_voff[j] = (uint32_t)((r * ldx + (n_glob < B ? n_glob : 0)) * 2);
+  }
+  const uint32_t x_lds = lds_addr(reinterpret_cast<const uint32_t*>(Xs_all)) + wave * PER * 1024;
+  auto stage_x = [&](int t, int buf) {           // sub-tile t into buffer buf
+    const char* base = reinterpret_cast<const char*>(X) + ((size_t)t * KS + wave * PER * RPI) * ldx * 2;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) x_to_lds(base + (size_t)(j * RPI) * ldx * 2, x_voff[j % VAR], x_lds + buf * XB + j * 1024);
+  };
+  // operand role: lane i of a 16-lane block addresses row i / 4, fragment i % 4 of a 4 x 16 tile
+  int xr_off[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int kq = (lane & 15) >> 2;
+    const int chunk = ((wc * NB + b) * 32 + (lane & 16)) >> 4;
+    xr_off[b] = (8 * (lane >> 5) + kq) * NT * 2 + ((chunk ^ (2 * kq)) << 5) + (lane & 3) * 8;
+  }
+  const int n_subtiles = n_cb * NSUB;
+
+  f16v_t acc[RBW][NB];
+#pragma unroll
+  for (int a = 0; a < RBW; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+
+  // prologue: registers for col-block 0, X sub-tiles 0 and 1
+  GroupRegs<K> g[RBW];
+  long long rbs[RBW];
+  bool rb_ok[RBW];
+  // rows of groups, divided once; with two row-blocks a wave per col-block (48.2 us for 48.9, 11008 x 4096, B = 203)
+  int grows[RBW];
+  auto grow_of = [&](int a) { return RBW == 1 ? (long long)grows[a] : (rb_ok[a] ? rbs[a] : 0) / rpc; };
+#pragma unroll
+  for (int a = 0; a < RBW; ++a) {
+    rbs[a] = rb0 + (long long)mt * (4 * RBW * WM) + wave * RBW + a;
+    rb_ok[a] = rbs[a] < rb_end;
+    grows[a] = rb_ok[a] ? (int)rbs[a] / rpc : 0;
+    load_group<K>(g[a], idx, cb, rb_ok[a] ? rbs[a] : 0, 0, n_cb, lane, n_rb, grow_of(a), n_rb / rpc);
+  }
+  stage_x(0, 0);
+  stage_x(1, 1);                                 // NSUB > 1
+  int cur = 0;   // X buffer the next sub-step reads; sub-tile t + 1 lies or arrives in the next, the third is idle
+
+  for (int c = 0; c < n_cb; ++c) {
+    // every wave is past its MFMA reads of Wt (barrier at the end of the last sub-step); the
+    // tables live in the X buffer that is idle while a col-block is being decoded
+    uint32_t* lut = reinterpret_cast<uint32_t*>(Xs_all + (cur == 0 ? 2 : cur - 1) * XB) + wave * lut_dwords<K>();
+    static_assert(WAVES * lut_dwords<K>() * 4 <= XB, "the waves' tables must fit in one X buffer");
+#pragma unroll
+    for (int a = 0; a < RBW; ++a) {
+      const int m0 = (wave * RBW + a) * 8;
+      if (rb_ok[a]) {
+        decode_group<K>(g[a], lut, Wt, m0, lane);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+          *reinterpret_cast<uint2*>(Wt + wt_half_index(m0 + r, 4 * lane)) = make_uint2(0u, 0u);
+      }
+    }
+    wait_loads<0>();   // sub-tiles t and t + 1 of this col-block's first sub-step
+    __syncthreads();   // ... of all waves, and Wt, are complete
+
+#pragma unroll
+    for (int sub = 0; sub < NSUB; ++sub) {
+      const char* Xs = Xs_all + cur * XB;
+      // Sub-tile t + 2 goes into the buffer that was read last (after the last one harmless re-reads: nobody reads those
+      // copies).  Loads return in order, so the next col-block's indices, from memory, would hold up the sub-tiles that
+      // are loaded after them: they have the first two sub-steps, in the first of which nothing is waited for.
+      const int t = c * NSUB + sub;
+      if (sub == 0) {
+        // next col-block's registers (clamped on the last one: a harmless re-read)
+#pragma unroll
+        for (int a = 0; a < RBW; ++a)
+          load_group<K>(g[a], idx, cb, rb_ok[a] ? rbs[a] : 0, min(c + 1, n_cb - 1), n_cb, lane, n_rb, grow_of(a), n_rb / rpc);
+      }
+      stage_x(min(t + 2, n_subtiles - 1), cur == 0 ? 2 : cur - 1);
+      // wave w: batch columns [32*NB*w, 32*NB*(w+1)), all MT rows, the KS k of this sub-step
+#pragma unroll
+      for (int kk = 0; kk < KS / 16; ++kk) {
+        h8_t bv[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          bv[b] = read_x_operand<NT>(Xs + xr_off[b] + 16 * kk * NT * 2);
+#pragma unroll
+        for (int a = 0; a < RBW; ++a) {
+          const h8_t av = *reinterpret_cast<const h8_t*>(
+              Wt + wt_half_index(wr * 32 * RBW + 32 * a + (lane & 31), sub * KS + 16 * kk + 8 * (lane >> 5)));
+#pragma unroll
+          for (int b = 0; b < NB; ++b)
+            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, bv[b], acc[a][b], 0, 0, 0);
+        }
+      }
+      if (sub > 0) wait_loads<PER>();   // this wave's part of sub-tile t + 1
+      __syncthreads();   // reads of buffer cur (and, on the last sub-step, of Wt) done; sub-tile t + 1 complete
+      cur = cur == 2 ? 0 : cur + 1;
+    }
+  }
+
+  wait_loads<0>();   // the last re-reads: no load may arrive in LDS that is no longer this workgroup's
+
+  // ---- store: accumulator register i holds row 8*(i/4) + 4*(lane/32) + i%4, column lane%32
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int n = nt * NT + (wc * NB + b) * 32 + (lane & 31);
+    if (n < B) {
+#pragma unroll
+      for (int a = 0; a < RBW; ++a)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int row = rb0 * 8 + mt * MT + wr * 32 * RBW + 32 * a + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
+          if (row < rb_end * 8) {
+            const size_t o = (size_t)row * ldy + n;
+            if (y_f32) reinterpret_cast<float*>(Y)[o] = acc[a][b][i];
+            else reinterpret_cast<_Float16*>(Y)[o] = (_Float16)acc[a][b][i];
+          }
+        }
+    }
+  }
+}
+
 // ---- tiny batches (B <= 16 per workgroup column): latency- and bandwidth-bound --------
 // 16 rows (two row-blocks) x 16 batch columns per workgroup, v_mfma_f32_16x16x32_f16.  The
 // NW waves split K by col-block (wave w takes col-blocks w, w+NW, ...) and share nothing
@@ -600,12 +791,10 @@ __global__ __launch_bounds__(256 * WM, WM == 1 ? 2 : 1) void gemm_kernel(const u
 // into registers while the current one is processed.  The partial 16 x 16 tiles meet
 // in LDS at the end.  Many small workgroups (out/16 per 16 columns) keep every CU streaming.
 typedef float f4v_t __attribute__((ext_vector_type(4)));
-constexpr int kTinyXRows = 64;                 // rows of X a wave stages at a time
-constexpr int kTinyXPasses = kTinyXRows / 32;  // 32-row passes (1 KB each) per staging step
 
-// NW: waves per workgroup.  4; 8 where the workgroups do not outnumber the CUs (see launch_gemm).
+// NW: waves per workgroup.  4; 8 or 16 where the workgroups do not outnumber the CUs (see launch_gemm).
 template <int K, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void gemm_tiny_kernel(const uint8_t* __restrict__ idx,
+__global__ __launch_bounds__(64 * NW, NW == 16 ? 4 : 2) void gemm_tiny_kernel(const uint8_t* __restrict__ idx,
                                                            const uint32_t* __restrict__ cb,
                                                            const uint16_t* __restrict__ X, int B,
                                                            int ldx, void* __restrict__ Y, int ldy,
@@ -614,9 +803,11 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_tiny_kernel(const uint8_t* __
   // [k][16 columns], as in memory; a quarter of a col-block at a time, which keeps four waves under a
   // third of the LDS for every format but d = 4 (three workgroups per CU; fewer than 170
   // registers, so the registers allow three as well).  Eight waves take 83 KB and more, up to all 160 KB
-  // with d = 4: one workgroup per CU, which is all they are launched for.
-  __shared__ __attribute__((aligned(16))) uint16_t Xt_all[NW][kTinyXRows * 16];
-  __shared__ __attribute__((aligned(16))) uint32_t lut_all[NW][2 * lut_dwords<K>()];
+  // with d = 4: one workgroup per CU, which is all they are launched for.  Sixteen stage an eighth and have one table each.
+  constexpr int kTinyXPasses = NW == 16 ? 1 : 2;     // 32-row passes (1 KB each) per staging step
+  constexpr int kTables = NW == 16 ? 1 : 2;
+  __shared__ __attribute__((aligned(16))) uint16_t Xt_all[NW][kTinyXPasses * 32 * 16];
+  __shared__ __attribute__((aligned(16))) uint32_t lut_all[NW][kTables * lut_dwords<K>()];
   static_assert(sizeof(Wt_all) + sizeof(Xt_all) + sizeof(lut_all) <= 160 * 1024, "the LDS of a CU");
 
   const int tid = threadIdx.x;
@@ -651,26 +842,30 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_tiny_kernel(const uint8_t* __
   const int xr_lo = xr_base + xr_swap, xr_hi = xr_base + 128 - xr_swap;
   f4v_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
   GroupRegs<K> g[2][2];
-  u32x4_t xr[2][8];
+  u32x4_t xr[NW == 16 ? 1 : 2][8];            // sixteen waves have 128 registers each
 
   // every load is issued whether or not the col-block exists (clamped), so that the number
   // of loads in flight is static and the waits stay partial
-#define VQ_ISSUE(SLOT, C)                                                              \
+#define VQ_ISSUE_G(SLOT, C)                                                            \
   {                                                                                    \
     const int cc = min((C), n_cb - 1);                                                 \
     load_group<K>(g[SLOT][0], idx, cb, rb0, cc, n_cb, lane, n_rb, grow0, n_grows);     \
     load_group<K>(g[SLOT][1], idx, cb, rb1, cc, n_cb, lane, n_rb, grow1, n_grows);     \
+  }
+#define VQ_ISSUE_X(SLOT, C)                                                            \
+  {                                                                                    \
+    const int cc = min((C), n_cb - 1);                                                 \
     _Pragma("unroll") for (int j = 0; j < 8; ++j)                                      \
       xr[SLOT][j] = *reinterpret_cast<const u32x4_t*>(X + ((size_t)cc * 256 + 32 * j) * ldx + x_lane); \
   }
-#define VQ_PROCESS(SLOT)                                                               \
+#define VQ_PROCESS(SLOT, XS)                                                           \
   {                                                                                    \
     decode_group<K>(g[SLOT][0], lut, Wt, 0, lane);                                     \
-    decode_group<K>(g[SLOT][1], lut + lut_dwords<K>(), Wt, 8, lane);                                 \
+    decode_group<K>(g[SLOT][1], lut + (kTables - 1) * lut_dwords<K>(), Wt, 8, lane);   \
     _Pragma("unroll") for (int hf = 0; hf < 8 / kTinyXPasses; ++hf) {                  \
       _Pragma("unroll") for (int j = 0; j < kTinyXPasses; ++j)                         \
         *reinterpret_cast<u32x4_t*>(reinterpret_cast<char*>(Xt) + 1024 * j + xs_off) = \
-            x_ok ? xr[SLOT][kTinyXPasses * hf + j] : u32x4_t{0u, 0u, 0u, 0u};          \
+            x_ok ? xr[XS][kTinyXPasses * hf + j] : u32x4_t{0u, 0u, 0u, 0u};          \
       wave_lds_sync();                                                                 \
       _Pragma("unroll") for (int kk = 0; kk < kTinyXPasses; ++kk) {                    \
         const int k0 = 32 * (kTinyXPasses * hf + kk) + 8 * (lane >> 4);                \
@@ -683,14 +878,28 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_tiny_kernel(const uint8_t* __
     }                                                                                  \
   }
 
-  VQ_ISSUE(0, wave)
+  VQ_ISSUE_G(0, wave)
+  VQ_ISSUE_X(0, wave)
   for (int c = wave; c < n_cb; c += 2 * NW) {
-    VQ_ISSUE(1, c + NW)
-    VQ_PROCESS(0)
-    VQ_ISSUE(0, c + 2 * NW)
-    if (c + NW < n_cb) VQ_PROCESS(1)
+    VQ_ISSUE_G(1, c + NW)
+    if constexpr (NW == 16) {
+      VQ_PROCESS(0, 0)
+      if (c + NW < n_cb) {
+        VQ_ISSUE_X(0, c + NW)
+        VQ_ISSUE_G(0, c + 2 * NW)
+        VQ_PROCESS(1, 0)
+        VQ_ISSUE_X(0, c + 2 * NW)
+      }
+    } else {
+      VQ_ISSUE_X(1, c + NW)
+      VQ_PROCESS(0, 0)
+      VQ_ISSUE_G(0, c + 2 * NW)
+      VQ_ISSUE_X(0, c + 2 * NW)
+      if (c + NW < n_cb) VQ_PROCESS(1, 1)
+    }
   }
-#undef VQ_ISSUE
+#undef VQ_ISSUE_G
+#undef VQ_ISSUE_X
 #undef VQ_PROCESS
 
   // NW partial 16 x 16 tiles -> LDS -> sum -> Y   (lane l holds rows 4*(l/16)+i, column l%16)
@@ -715,17 +924,29 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_tiny_kernel(const uint8_t* __
   }
 }
 
+// Formats that take 16 waves from nine col-blocks on: those whose decoding fits 128 registers.  us with 8, 16: 4096 x 11008,
+// B = 16 k = 16 11.9, 10.6, k = 64 13.5, 12.9, k = 256 13.6, 13.1; 4096 x 4096 6.15, 5.66, 6.90, 6.38, 6.66, 6.40; 2048 x 6144,
+// B = 30 8.9, 7.9, 9.2, 9.0, 8.9, 8.7; 1024 x 2304 4.60, 4.40, 4.98, 4.83, 4.51, 4.53.  The others spill or gain nothing: k = 32 5.07,
+// 5.24 (1024 x 2304), k = 256 with int8 tables 6.74, 7.03 (4096 x 4096), block scales 16.7, 17.4 and 14.4, 17.0 (4096 x 11008).
+template <int K> constexpr bool kSixteen = K == 16 || K == 64 || K == 256 || K == kFmtK16I8 || K == kFmtD1K8;
+
 template <int K>
 hipError_t launch_tiny(const vq_desc& d, const void* idx_dev, const void* cb_dev, const void* X,
-                       int B, int ldx, void* Y, int ldy, int y_f32, hipStream_t s, bool eight_waves) {
+                       int B, int ldx, void* Y, int ldy, int y_f32, hipStream_t s, int waves) {
   const int n_rb = d.out_features / kGroupRows, n_cb = d.in_features / kGroupCols;
   const dim3 grid((unsigned)((n_rb + 1) / 2), (unsigned)((B + 15) / 16));
-  if (eight_waves)
-    hipLaunchKernelGGL((gemm_tiny_kernel<K, 8>), grid, dim3(512), 0, s, (const uint8_t*)idx_dev,
-                       (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y, ldy, y_f32, n_rb, n_cb, blocks_per_group(d));
-  else
-    hipLaunchKernelGGL((gemm_tiny_kernel<K, 4>), grid, dim3(256), 0, s, (const uint8_t*)idx_dev,
-                       (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y, ldy, y_f32, n_rb, n_cb, blocks_per_group(d));
+#define VQ_TINY(NW)                                                                                          \
+  hipLaunchKernelGGL((gemm_tiny_kernel<K, NW>), grid, dim3(64 * NW), 0, s, (const uint8_t*)idx_dev,          \
+                     (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y, ldy, y_f32, n_rb, n_cb, blocks_per_group(d))
+  if constexpr (kSixteen<K>) {
+    if (waves == 16) {
+      VQ_TINY(16);
+      return hipGetLastError();
+    }
+  }
+  if (waves >= 8) VQ_TINY(8);
+  else VQ_TINY(4);
+#undef VQ_TINY
   return hipGetLastError();
 }
 
@@ -893,14 +1114,19 @@ hipError_t launch_one(const vq_desc& d, const void* idx_dev, const void* cb_dev,
   const int n_rb = d.out_features / kGroupRows, n_cb = d.in_features / kGroupCols;
   if (rb_end < 0) rb_end = n_rb;
   const int tiles_m = (rb_end - rb0 + 4 * RBW * WM - 1) / (4 * RBW * WM), tiles_n = (B + NT - 1) / NT;
-  hipLaunchKernelGGL((gemm_kernel<K, RBW, NT, WM>), dim3((unsigned)(tiles_m * tiles_n)), dim3(256 * WM), 0, s,
-                     (const uint8_t*)idx_dev, (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y,
-                     ldy, y_f32, n_rb, n_cb, tiles_n, blocks_per_group(d), rb0, rb_end);
+  if constexpr (RBW == 1 && WM == 1)
+    hipLaunchKernelGGL((ring_gemm_kernel<K>), dim3((unsigned)(tiles_m * tiles_n)), dim3(256), 0, s,
+                       (const uint8_t*)idx_dev, (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y,
+                       ldy, y_f32, n_rb, n_cb, tiles_n, blocks_per_group(d), rb0, rb_end);
+  else
+    hipLaunchKernelGGL((gemm_kernel<K, RBW, NT, WM>), dim3((unsigned)(tiles_m * tiles_n)), dim3(256 * WM), 0, s,
+                       (const uint8_t*)idx_dev, (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y,
+                       ldy, y_f32, n_rb, n_cb, tiles_n, blocks_per_group(d), rb0, rb_end);
   return hipGetLastError();
 }
 
 // Large batches on the 128-row tiles: 128 x 512 tiles decode W once per 512 batch columns instead
-// of once per 256 and take 1.73 times as long as 128 x 256 tiles for twice the area, but a launch
+// of once per 256 and take 1.6 times as long as 128 x 256 tiles for twice the area, but a launch
 // pays for whole rounds of one workgroup per CU.  So the first m_a tile rows run with 512-column
 // tiles and the rest with 256-column tiles in a second launch, m_a chosen so that both launches
 // fill their rounds best (m_a = 0: 256-column tiles only).  Same units as launch_gemm's estimates:
@@ -920,11 +1146,11 @@ hipError_t launch_wide(const vq_desc& d, const void* idx_dev, const void* cb_dev
   int m_a = 0;
   const long long cus = device_cus();
   const double kscale = (double)d.in_features / 4096.0;
-  double best = 79.0 * kscale * (double)((rows128 * cols256 + cus - 1) / cus);
+  double best = 76.0 * kscale * (double)((rows128 * cols256 + cus - 1) / cus);
   for (long long m = 1; m <= rows128; ++m) {
     const long long rest = rows128 - m;
-    const double t = 137.0 * kscale * (double)((m * cols512 + cus - 1) / cus) +
-                     (rest > 0 ? 3.0 + 79.0 * kscale * (double)((rest * cols256 + cus - 1) / cus) : 0.0);
+    const double t = 122.0 * kscale * (double)((m * cols512 + cus - 1) / cus) +
+                     (rest > 0 ? 3.0 + 76.0 * kscale * (double)((rest * cols256 + cus - 1) / cus) : 0.0);
     if (t < best) {
       best = t;
       m_a = (int)m;
@@ -1003,14 +1229,16 @@ hipError_t launch_gemm(const vq_desc& d, const void* idx_dev, const void* cb_dev
   // with 8 waves 29.2), where a wave has a single col-block anyway, and for the formats that decode longest where
   // four waves take two each (k = 64 with block scales, 1024 x 2048 5.7, with 8 waves 6.1).  Then 32 x 32 tiles (gemm_small_kernel,
   // bandwidth-bound) while they are few enough to run in about one wave of workgroups, then
-  // gemm_kernel with 32 x 128 tiles while those fit the CUs once, and beyond that the cheapest
-  // of four tilings by a small cost model: 64 x 128 and 64 x 256 (4 waves, two workgroups per
-  // CU: time grows almost linearly with the tile count) and 128 x 128 and 128 x 256 (8 waves, one
-  // workgroup per CU: half the X traffic per product, but time moves in whole rounds of 256
-  // one tile per CU).  The constants are microseconds measured at in_features = 4096 on 4096- and
-  // 11008-row matrices, B = 512..4096, on 256 CUs.  A tile's time is its K loop, so every term
-  // scales with in_features and only the ratios matter here; the 4-wave tiles run two per CU, so
-  // their per-tile slope scales with 256 / CUs.
+  // ring_gemm_kernel (32 x 128 tiles) while those fit the CUs once, and beyond that the cheapest of four tilings of
+  // gemm_kernel by a small cost model: 64 x 128 and 64 x 256 (4 waves, two workgroups per CU: time grows with the tile
+  // count) and 64 x 256 and 128 x 256 (8 waves, one workgroup per CU: time moves in rounds of one tile per CU).  The
+  // constants are microseconds at in_features = 4096 on 256 CUs; a tile's time is its K loop, so every term scales with
+  // in_features and only the ratios matter here.  us with 64 x 128, 64 x 256, 64 x 256 of 8 waves, 128 x 256 tiles:
+  //   11008 x 4096, B = 203, k = 256 int8 59, 55, 48, 71; B = 400 91, 82, 90, 74; B = 2048, k = 256 308, 266, 291, 224
+  //   4096 x 4096, k = 16, B = 512 34, 47, 39, 62; B = 1024 55, 54, 50, 63; 11008 x 4096, B = 128 32, 48, 39, 62
+  //   11008 x 4096, k = 64, B = 256 52, 51, 46, 68; B = 512 87, 81, 95, 73; 3072 x 4096, k = 16, B = 700 46, 47, 38, 61
+  //   2336 x 7168, k = 16 int8, B = 634 55, 77, 70, 103; 2104 x 7680, k = 32, B = 1094 93, 92, 79, 119
+  // (the 128 x 128 tiles of 8 waves that the third replaces decode W twice as often: 55 for B = 203, 44 for 3072 x 4096).
   const int n_rb = d.out_features / kGroupRows;
   const long long tiles_tiny = (long long)((n_rb + 1) / 2) * ((B + 15) / 16);
   const long long tiles_small = (long long)((n_rb + 3) / 4) * ((B + 31) / 32);
@@ -1021,11 +1249,17 @@ hipError_t launch_gemm(const vq_desc& d, const void* idx_dev, const void* cb_dev
   const bool eight_waves = tiles_tiny <= cus && n_cb > 4;
   const bool small = B <= 32 || tiles_small <= 3 * cus;
   const bool one_round_32x128 = rows64 * cols128 <= cus / 2;
+  // us of whole rounds of one tile per CU and a last one that is part full, or of two 4-wave tiles per CU
+  const auto rounds = [&](long long tiles, double full, double first, double slope) {
+    const long long before = (tiles - 1) / cus;
+    return (double)before * full + first + slope * (double)(tiles - before * cus) / (double)cus;
+  };
   const double per_cu = 256.0 / (double)cus;
-  const double est[4] = {20.0 + 0.11 * per_cu * (double)(rows64 * cols128),              // 64 x 128
-                         35.0 + 0.165 * per_cu * (double)(rows64 * cols256),             // 64 x 256
-                         54.0 * (double)((rows128 * cols128 + cus - 1) / cus),           // 128 x 128
-                         79.0 * (double)((rows128 * cols256 + cus - 1) / cus)};          // 128 x 256
+  const long long n128 = rows64 * cols128, n256 = rows64 * cols256;
+  const double est[4] = {n128 <= cus ? 34.0 : n128 <= 2 * cus ? 54.0 : 5.0 + 0.112 * per_cu * (double)n128,   // 64 x 128
+                         n256 <= cus ? 44.0 + 0.035 * per_cu * (double)n256 : 15.0 + 0.19 * per_cu * (double)n256,   // 64 x 256
+                         rounds(n256, 48.0, 36.0, 12.0),                                 // 64 x 256, 8 waves
+                         rounds(rows128 * cols256, 76.0, 60.0, 16.0)};                   // 128 x 256, 8 waves
   int best = 0;
   for (int i = 1; i < 4; ++i)
     if (est[i] < est[best]) best = i;
@@ -1033,14 +1267,14 @@ hipError_t launch_gemm(const vq_desc& d, const void* idx_dev, const void* cb_dev
   {                                                                                               \
     if (tiny_pays<K>(tiles_tiny, tiles_small, d, B, cus))                                         \
       return launch_tiny<K>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s,                      \
-                            eight_waves && !((K == kFmtK64BN || K == kFmtD1K8BN) && (n_cb == 7 || n_cb == 8))); \
+                            !eight_waves || ((K == kFmtK64BN || K == kFmtD1K8BN) && (n_cb == 7 || n_cb == 8)) ? 4 : kSixteen<K> && n_cb > 8 ? 16 : 8); \
     if (small) return launch_small<K>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);           \
     if (one_round_32x128)                                                                         \
       return launch_one<K, 1, 128>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);              \
     if (best == 0) return launch_one<K, 2, 128>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s); \
     if (best == 1) return launch_one<K, 2, 256>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s); \
     if (best == 2)                                                                                \
-      return launch_one<K, 2, 128, 2>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);           \
+      return launch_one<K, 1, 256, 2>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);           \
     return launch_wide<K>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);                       \
   }
   const int fmt = format_tag(d);
