@@ -953,29 +953,35 @@ hipError_t launch_tiny(const vq_desc& d, const void* idx_dev, const void* cb_dev
 // ---- small batches (B <= 32): bandwidth-bound ---------------------------------
 // 32 rows x 32 batch columns per workgroup (many workgroups, so that every CU streams
 // weights); the whole col-block of X is staged at once and wave w multiplies its own
-// quarter of k; the four partial tiles meet in LDS at the end.  W tile and X tile are
+// quarter of k; the four partial tiles meet in LDS at the end (with two groups of four waves each group has half of the
+// col-blocks).  W tile and X tile are
 // double-buffered: decoding col-block c+1 overlaps the MFMAs of col-block c and one
 // barrier per col-block is enough.
-template <int K>
-__global__ __launch_bounds__(256, 2) void gemm_small_kernel(const uint8_t* __restrict__ idx,
+template <int K, int G>
+__global__ __launch_bounds__(256 * G, 2) void gemm_small_kernel(const uint8_t* __restrict__ idx,
                                                             const uint32_t* __restrict__ cb,
                                                             const uint16_t* __restrict__ X, int B,
                                                             int ldx, void* __restrict__ Y, int ldy,
                                                             int y_f32, int n_rb, int n_cb,
                                                             int n_tiles_n, int rpc) {
   constexpr int MT = 32, NT = 32;
-  __shared__ __attribute__((aligned(16))) uint16_t Wt_all[2][MT * WS];
+  __shared__ __attribute__((aligned(16))) uint16_t Wt_groups[G][2][MT * WS];
   // X tile [256 k][32 n] halfs as in memory; the 32-byte chunk c of row k sits at c ^ ((k >> 1) & 1),
   // which puts the four rows of a transposing read into four different bank groups
-  __shared__ __attribute__((aligned(16))) uint32_t Xs_all[2][4096];
-  __shared__ __attribute__((aligned(16))) uint32_t lut_all[4][lut_dwords<K>()];
+  __shared__ __attribute__((aligned(16))) uint32_t Xs_groups[G][2][4096];
+  __shared__ __attribute__((aligned(16))) uint32_t lut_all[4 * G][lut_dwords<K>()];
+  static_assert(sizeof(Wt_groups) + sizeof(Xs_groups) + sizeof(lut_all) <= 160 * 1024, "the LDS of a CU");
 
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = threadIdx.x & 63;
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int group = wave_all >> 2, wave = wave_all & 3;     // G groups of four waves
+  const int tid = threadIdx.x & 255;                        // in its group
+  auto& Wt_all = Wt_groups[group];
+  auto& Xs_all = Xs_groups[group];
+  const int c_first = n_cb * group / G, c_count = n_cb * (group + 1) / G - c_first;   // its col-blocks, G > 1: at least one
   const int mt = blockIdx.x / n_tiles_n;
   const int nt = blockIdx.x - mt * n_tiles_n;
-  uint32_t* lut = lut_all[wave];
+  uint32_t* lut = lut_all[wave_all];
 
   // X staging role: the col-block's tile is copied unchanged in 4 passes of 64 rows; the thread
   // owns 16 bytes (8 batch columns from n_loc) of row x_row of every pass.  A piece that lies
@@ -1014,7 +1020,7 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(const uint8_t* __res
   XRows xp[D];
 #pragma unroll
   for (int j = 0; j < D; ++j) {
-    const int cj = min(j, n_cb - 1);
+    const int cj = c_first + min(j, c_count - 1);
     load_group<K>(g[j], idx, cb, rb_ld, cj, n_cb, lane, n_rb, grow, n_grows);
     VQ_LOAD_X(j, cj)
   }
@@ -1035,7 +1041,7 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(const uint8_t* __res
       *reinterpret_cast<u32x4_t*>(reinterpret_cast<char*>(Xs_all[(j) & 1]) + 4096 * pass + xs_off) = \
           x_ok ? xp[j].r[pass] : u32x4_t{0u, 0u, 0u, 0u};                                       \
     if (REFILL) {                                                                               \
-      const int cn = min((c) + D, n_cb - 1);                                                    \
+      const int cn = c_first + min((c) + D, c_count - 1);                                       \
       load_group<K>(g[j], idx, cb, rb_ld, cn, n_cb, lane, n_rb, grow, n_grows);                 \
       VQ_LOAD_X(j, cn)                                                                          \
     }                                                                                           \
@@ -1043,7 +1049,7 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(const uint8_t* __res
   // multiply col-block c (staged in buffer j & 1) if it exists, then release the buffer
 #define VQ_MULTIPLY(j, c)                                                                       \
   {                                                                                             \
-    if ((c) < n_cb) {                                                                           \
+    if ((c) < c_count) {                                                                        \
       const uint16_t* Wt = Wt_all[(j) & 1];                                                     \
       const char* Xs = reinterpret_cast<const char*>(Xs_all[(j) & 1]);                          \
       _Pragma("unroll") for (int kk = 0; kk < 4; ++kk) {                                        \
@@ -1057,7 +1063,7 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(const uint8_t* __res
     __syncthreads();                                                                            \
   }
 
-  const int n_pad = (n_cb + D - 1) / D * D;
+  const int n_pad = ((n_cb + G - 1) / G + D - 1) / D * D;   // all groups take as many steps
   VQ_STAGE(0, 0, true)
   __syncthreads();
   int c0 = 0;
@@ -1076,17 +1082,19 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(const uint8_t* __res
 #undef VQ_LOAD_X
   static_assert(D == 4, "the unrolled ring above is written for four slots");
 
-  // four partial 32 x 32 tiles (one per wave) -> LDS -> sum -> Y
-  float* part = reinterpret_cast<float*>(Wt_all[0]);      // 4 x 32 x 32 floats = 16 KB
+  // 4 G partial 32 x 32 tiles (one per wave) -> LDS -> sum -> Y
+  float* part = reinterpret_cast<float*>(Wt_groups[0][0]);      // 4 G x 32 x 32 floats = 16 KB per group
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int m = 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-    part[(wave * MT + m) * 32 + (lane & 31)] = acc[i];
+    part[(wave_all * MT + m) * 32 + (lane & 31)] = acc[i];
   }
   __syncthreads();
-  for (int e = tid; e < MT * 32; e += 256) {
+  for (int e = threadIdx.x; e < MT * 32; e += 256 * G) {
     const int m = e >> 5, nl = e & 31;
-    const float sum = part[e] + part[MT * 32 + e] + part[2 * MT * 32 + e] + part[3 * MT * 32 + e];
+    float sum = part[e];
+#pragma unroll
+    for (int w = 1; w < 4 * G; ++w) sum += part[w * MT * 32 + e];
     const int row = mt * MT + m, n = nt * NT + nl;
     if (row < n_rb * 8 && n < B) {
       const size_t o = (size_t)row * ldy + n;
@@ -1101,9 +1109,18 @@ hipError_t launch_small(const vq_desc& d, const void* idx_dev, const void* cb_de
                         int B, int ldx, void* Y, int ldy, int y_f32, hipStream_t s) {
   const int n_rb = d.out_features / kGroupRows, n_cb = d.in_features / kGroupCols;
   const int tiles_m = (n_rb + 3) / 4, tiles_n = (B + 31) / 32;
-  hipLaunchKernelGGL((gemm_small_kernel<K>), dim3((unsigned)(tiles_m * tiles_n)), dim3(256), 0, s,
-                     (const uint8_t*)idx_dev, (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y,
-                     ldy, y_f32, n_rb, n_cb, tiles_n, blocks_per_group(d));
+  const dim3 grid((unsigned)(tiles_m * tiles_n));
+#define VQ_SMALL(G)                                                                                               \
+  hipLaunchKernelGGL((gemm_small_kernel<K, G>), grid, dim3(256 * G), 0, s, (const uint8_t*)idx_dev,               \
+                     (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y, ldy, y_f32, n_rb, n_cb, tiles_n, blocks_per_group(d))
+  // Two groups of waves where a CU has one workgroup, unless the steps, rounded up to four a group, would be a fifth more
+  // in all.  us with one, two: 1768 x 9216, B = 82, k = 16 27.7, 24.7; 2560 x 4096, B = 96, k = 64 16.1, 13.6; 1152 x 5376,
+  // B = 200, d = 4 21.6, 19.2; 8192 x 4096, B = 32, k = 256 int8 15.7, 13.8; 2048 x 4096, B = 96, k = 256 14.5, 14.2; nine
+  // col-blocks 2048 x 2304, B = 100, k = 32 12.5, 13.8; d = 4 with fp16 tables (80 KB of LDS a group) 24.0, 24.1.
+  const int steps1 = (n_cb + 3) / 4, steps2 = ((n_cb + 1) / 2 + 3) / 4;
+  if (K != kFmtD4F16 && tiles_m * tiles_n <= device_cus() && n_cb >= 8 && 10 * steps2 <= 6 * steps1) VQ_SMALL(2);
+  else VQ_SMALL(1);
+#undef VQ_SMALL
   return hipGetLastError();
 }
 
