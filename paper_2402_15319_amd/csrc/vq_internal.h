@@ -148,6 +148,10 @@ struct LoraDownBatchT {
   LoraDownProblem p[CAP];
 };
 using LoraDownBatch = LoraDownBatchT<kMaxProblemsPerLaunch>;
+// The narrow form: a grid row per product, row_begin holding the product's number of rows.
+struct LoraDownFew {
+  LoraDownProblem p[kFewProblems];
+};
 
 // The narrow form of a launch's argument (count <= kFewProblems).
 inline int log2_of(int v) { return v > 1 ? 31 - __builtin_clz((unsigned)v) : 0; }   // of a power of two; 0 for 0
@@ -166,9 +170,12 @@ inline GemvFewLora few_problems(const GemvBatchLora& b) {
   for (int i = 0; i < b.base.count && i < kFewProblems; ++i) f.l[i] = b.l[i];
   return f;
 }
-inline LoraDownBatchT<kFewProblems> few_problems(const LoraDownBatch& b) {
-  LoraDownBatchT<kFewProblems> f = {b.count, b.total_rows, {}};
-  for (int i = 0; i < b.count && i < kFewProblems; ++i) f.p[i] = b.p[i];
+inline LoraDownFew few_problems(const LoraDownBatch& b) {
+  LoraDownFew f = {};
+  for (int i = 0; i < b.count && i < kFewProblems; ++i) {
+    f.p[i] = b.p[i];
+    f.p[i].row_begin = (i + 1 < b.count ? b.p[i + 1].row_begin : b.total_rows) - b.p[i].row_begin;
+  }
   return f;
 }
 
