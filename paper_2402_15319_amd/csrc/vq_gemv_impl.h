@@ -367,7 +367,7 @@ template <int CAP> __device__ __forceinline__ GemvItem item_of(const GemvBatchT<
   const GemvProblem& q = b.p[pi];
   return {q.idx, q.cb, q.x, q.y, q.n_rb, q.n_cb, q.wg_begin, log2_dev(q.splits), log2_dev(q.rb_per_cb), b.y_f32};
 }
-__device__ __forceinline__ GemvItem item_of(const GemvFew& b, int pi) {
+template <int CAP> __device__ __forceinline__ GemvItem item_of(const GemvLines<CAP>& b, int pi) {
   const FewProblem& q = b.p[pi];
   const GemvItem it = {q.idx, q.cb, q.x, q.y, q.n_rb, q.n_cb, q.wg_begin, q.splits_log2, q.cb_log2, q.y_f32};
   // all of it at once: the compiler would fetch each field where it is used, one round trip after the other
@@ -461,11 +461,12 @@ __device__ __forceinline__ void store_rows(void* y, int y_f32, int rb, int lane,
 // the same three lane exchanges that end wave_reduce8.
 template <bool LORA, int CAP = kMaxProblemsPerLaunch> struct BatchOf { using type = GemvBatchT<CAP>; };
 template <int CAP> struct BatchOf<true, CAP> { using type = GemvBatchLoraT<CAP>; };
+template <> struct BatchOf<false, 1> { using type = GemvOne; };
 template <> struct BatchOf<false, kFewProblems> { using type = GemvFew; };
 template <> struct BatchOf<true, kFewProblems> { using type = GemvFewLora; };
 template <int CAP> __device__ __forceinline__ const GemvBatchT<CAP>& base_of(const GemvBatchT<CAP>& b) { return b; }
 template <int CAP> __device__ __forceinline__ const GemvBatchT<CAP>& base_of(const GemvBatchLoraT<CAP>& b) { return b.base; }
-__device__ __forceinline__ const GemvFew& base_of(const GemvFew& b) { return b; }
+template <int CAP> __device__ __forceinline__ const GemvLines<CAP>& base_of(const GemvLines<CAP>& b) { return b; }
 __device__ __forceinline__ const GemvFew& base_of(const GemvFewLora& b) { return b.base; }
 
 __device__ __forceinline__ uint4 lora_load_b(const LoraProblem& L, const void* fallback, int rb, int lane) {
@@ -510,7 +511,7 @@ __device__ __forceinline__ int find_problem(const GemvBatchT<CAP>& batch, int it
 
 __device__ __forceinline__ int find_problem(const GemvFew& b, int item) {
   static_assert(kFewProblems == 4, "");
-  return (item >= b.begin[1]) + (item >= b.begin[2]) + (item >= b.begin[3]);
+  return (item >= b.p[1].wg_begin) + (item >= b.p[2].wg_begin) + (item >= b.p[3].wg_begin);
 }
 
 // ---- persistent streaming kernel -------------------------------------------
@@ -1002,12 +1003,14 @@ __global__ __launch_bounds__(64 * WPW) void gemv_split_kernel(const typename Bat
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // few products: one row of the grid each; the workgroups that a product has fewer than the widest one leave
-  const int pi = CAP == kFewProblems ? (int)blockIdx.y : find_problem(batch, (int)blockIdx.x);
+  // one product: all of the grid; few: one row of it each, and the workgroups that a product has fewer than the widest leave
+  int pi = 0;
+  if constexpr (CAP == kFewProblems) pi = (int)blockIdx.y;
+  else if constexpr (CAP > kFewProblems) pi = find_problem(batch, (int)blockIdx.x);
   const GemvItem P = item_of(batch, pi);
   const int splits_log2 = P.splits_log2;
   const int rb_per_wg = WPW >> splits_log2;
-  const int wg_local = CAP == kFewProblems ? (int)blockIdx.x : (int)blockIdx.x - P.wg_begin;
+  const int wg_local = CAP <= kFewProblems ? (int)blockIdx.x : (int)blockIdx.x - P.wg_begin;
   const int rb = wg_local * rb_per_wg + (wave >> splits_log2);
   const int split = wave & ((1 << splits_log2) - 1);
   if (CAP == kFewProblems && wg_local * rb_per_wg >= P.n_rb) return;
@@ -1221,6 +1224,9 @@ hipError_t launch_gemv_impl(int fmt, const typename BatchOf<LORA>::type& batch, 
     return hipGetLastError();
   }
   const GemvBatch& b = base_of_host(batch);
+  if constexpr (!LORA) {
+    if (b.count == 1) return launch_split<false, 1>(fmt, problem_lines<1>(b), mode, dim3(grid_wgs), s, wpw);
+  }
   if (b.count > kFewProblems)
     return launch_split<LORA, kMaxProblemsPerLaunch>(fmt, batch, mode, dim3(grid_wgs), s, wpw);
   int widest = 0;               // workgroups of the product with most of them: wpw / splits row-blocks each

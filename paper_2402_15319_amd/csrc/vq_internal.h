@@ -77,7 +77,7 @@ struct GemvProblem {
 };
 
 // The kernel argument of a launch of many products (the host fills it for every launch; those of up to kFewProblems
-// products get the narrow one below, 288 instead of 14,352 bytes for the runtime to copy, about 1 us of a call's
+// products get a narrow one below, 256 or 64 instead of 14,352 bytes for the runtime to copy, about 1 us of a call's
 // host time: a decoder layer's launches hold one to three products).
 template <int CAP>
 struct GemvBatchT {
@@ -107,10 +107,17 @@ struct FewProblem {
   int32_t pad[2];
 };
 static_assert(sizeof(FewProblem) == 64, "one scalar load");
-struct GemvFew {
-  FewProblem p[kFewProblems];
-  int32_t begin[kFewProblems];   // wg_begin of every product; beyond the last one INT32_MAX
+// CAP: 1 or kFewProblems; beyond the last product wg_begin is INT32_MAX.  A single call is bound by the host, which copies
+// every byte of the argument: host us a call of one product, 4096 x 4096, k = 16, with 240, 272, 256 and 64 bytes
+// 2.65, 2.66, 2.66, 2.51 (256 x 256 2.65, 2.69, 2.65, 2.51); its kernel, launched behind one another 3.71 (with the search
+// of the table), 3.51, 3.52, 3.43.
+template <int CAP>
+struct GemvLines {
+  FewProblem p[CAP];
 };
+using GemvOne = GemvLines<1>;
+using GemvFew = GemvLines<kFewProblems>;
+static_assert(sizeof(GemvOne) == 64 && sizeof(GemvFew) == 256, "what the runtime copies");
 
 // Low-rank adapter of one problem (y = W x + B (A x)): what the GEMV epilogue needs.
 struct LoraProblem {
@@ -155,16 +162,17 @@ struct LoraDownFew {
 
 // The narrow form of a launch's argument (count <= kFewProblems).
 inline int log2_of(int v) { return v > 1 ? 31 - __builtin_clz((unsigned)v) : 0; }   // of a power of two; 0 for 0
-inline GemvFew few_problems(const GemvBatch& b) {
-  GemvFew f = {};
-  for (int i = 0; i < kFewProblems; ++i) f.begin[i] = 0x7fffffff;
-  for (int i = 0; i < b.count && i < kFewProblems; ++i) {
+template <int CAP>
+inline GemvLines<CAP> problem_lines(const GemvBatch& b) {
+  GemvLines<CAP> f = {};
+  for (int i = 0; i < CAP; ++i) {
     const GemvProblem& q = b.p[i];
-    f.p[i] = {q.idx, q.cb, q.x, q.y, q.n_rb, q.n_cb, q.wg_begin, log2_of(q.splits), log2_of(q.rb_per_cb), b.y_f32, {}};
-    f.begin[i] = q.wg_begin;
+    if (i < b.count) f.p[i] = {q.idx, q.cb, q.x, q.y, q.n_rb, q.n_cb, q.wg_begin, log2_of(q.splits), log2_of(q.rb_per_cb), b.y_f32, {}};
+    else f.p[i].wg_begin = 0x7fffffff;
   }
   return f;
 }
+inline GemvFew few_problems(const GemvBatch& b) { return problem_lines<kFewProblems>(b); }
 inline GemvFewLora few_problems(const GemvBatchLora& b) {
   GemvFewLora f = {few_problems(b.base), {}};
   for (int i = 0; i < b.base.count && i < kFewProblems; ++i) f.l[i] = b.l[i];

@@ -139,6 +139,19 @@ def test_wide_gemv_splits(launches):
     assert wrong == []
 
 
+@pytest.mark.parametrize("fmt", [K16, K64, (8, 2, 32, vq.VQ_I8), (1, 1, 4, vq.VQ_I8)], ids=str)
+def test_gemv_argument_goes_by_the_number_of_products(launches, fmt):
+    """A call of a few products is bound by the host, which copies the kernel's argument: one line of 64 bytes for a single
+    product, over a grid of one dimension; four lines for up to four, a grid row each; the whole table beyond."""
+    got = launches([("gemv", 1056, 2304, *fmt, 1, n) for n in (1, 2, 4, 5)] + [("gemv", [32, 1056], [512, 512], *fmt)])
+    for n, (status, ls) in zip((1, 2, 4, 5, 2), got):
+        assert status == 0 and len(ls) == 1
+        name, grid = ls[0][:2]
+        cap = 1 if n == 1 else 4 if n <= 4 else 256
+        assert "gemv_split_kernel" in name and f"Li{cap}EE" in name, name
+        assert grid[1:] == (n if cap == 4 else 1, 1)
+
+
 @pytest.mark.parametrize("fmt", [K64, K64_BN, (8, 2, 64, vq.VQ_I8_BN), (8, 1, 8, vq.VQ_I8), (8, 1, 8, vq.VQ_I8_BN)], ids=str)
 def test_re_layout_of_the_6_bit_formats_keeps_to_the_size_of_a_launch(launches, fmt):
     """A launch takes fewer than 2^32 threads; matrices that fit the memory (2^28 rows x 256 columns: 160 GB in all with
