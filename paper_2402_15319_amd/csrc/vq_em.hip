@@ -155,19 +155,15 @@ __device__ __forceinline__ void em_assign_whole(const float* cbs, const float* _
     best[r] = __builtin_inff();
     blk[r] = 0;
   }
-  float ahead[8][D];                          // the next 8 centroids; the same address in every lane
-#pragma unroll
-  for (int j = 0; j < 8; ++j) load_coords<D>(cbs + j * D, ahead[j]);
+  // The same address in every lane, but in a vector register: from a scalar one the compiler makes an address of its own
+  // for every coordinate (d = 4: 32 moves and 32 reads of 4 bytes per 8 centroids in place of 8 reads of 16).
+  uint32_t place = 0;
+  asm volatile("" : "+v"(place));
 #pragma unroll 1
-  for (uint32_t b = 0; b < K / 8; ++b) {
+  for (uint32_t b = 0; b < K / 8; ++b, place += em_place<D>(8)) {
     float cm[8][D], low[RR];
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-      for (int t = 0; t < D; ++t) cm[j][t] = ahead[j][t];
-    const float* next = cbs + em_place<D>(8) * (int)(b + 1 < K / 8 ? b + 1 : b);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) load_coords<D>(next + j * D, ahead[j]);
+    for (int j = 0; j < 8; ++j) load_coords<D>(cbs + place + j * D, cm[j]);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
 #pragma unroll

@@ -203,3 +203,56 @@ def test_m_step_adds_no_floating_point_in_lds(tmp_path):
     text = out.read_text()
     assert len(re.findall(r"\bds_add_u64\b", text)) > 100      # the tables' additions are in there
     assert re.findall(r"\b(?:ds|global|flat|buffer)_(?:pk_)?add(?:_rtn)?_f(?:16|32|64)\b|\bglobal_atomic_\w+|\bds_cmpst\w+", text) == []
+
+
+@pytest.fixture(scope="module")
+def device_asm(tmp_path_factory):
+    """f(source) -> {kernel: its lines}, compiled once."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if shutil.which(hipcc) is None:
+        pytest.skip("hipcc not available")
+    done = {}
+
+    def asm(source):
+        if source not in done:
+            out = tmp_path_factory.mktemp("asm") / (source + ".s")
+            flags = [f for f in vqbuild.HIPCC_FLAGS if f != "-fPIC"]
+            res = subprocess.run([hipcc, *flags, "-S", "--cuda-device-only", "-o", str(out), os.path.join(vqbuild.CSRC, source)],
+                                 capture_output=True, text=True)
+            assert res.returncode == 0, res.stderr[-2000:]
+            kernels = {}
+            for part in re.split(r"\n(?=_Z\S+:)", out.read_text()):
+                m = re.match(r"(_Z\S+):", part)
+                if m and "s_endpgm" in part:
+                    kernels[m[1]] = [l.split(";")[0].strip() for l in part[:part.rindex("s_endpgm")].splitlines()]
+            done[source] = kernels
+        return done[source]
+    return asm
+
+
+def loops(lines):
+    """The instructions of every backward branch's body."""
+    label = {l[:-1]: i for i, l in enumerate(lines) if l.endswith(":")}
+    for i, l in enumerate(lines):
+        m = re.match(r"s_c?branch\S* (\S+)", l)
+        if m and label.get(m[1], i) < i:
+            yield [t.split()[0] for t in lines[label[m[1]]:i] if t and not t.startswith(".") and not t.endswith(":")]
+
+
+def test_whole_codebook_is_read_a_centroid_at_a_time(device_asm):
+    """The E-step's loop over 8 centroids, the same for all lanes: with a scalar address the compiler reads each of their
+    coordinates by itself, from an address of its own (32 moves and 32 reads beside 240 instructions of arithmetic)."""
+    seen = 0
+    for name, lines in device_asm("vq_em.hip").items():
+        d4, d2 = re.search(r"em_assign_any_kernelILi(64|256)ELi4ELi1E", name), re.search(r"em_assign_(any_)?kernelILi(64|256)E(Li2ELi1E)?EE", name)
+        if not d4 and not d2:
+            continue
+        d = 4 if d4 else 2
+        inner = [l for l in loops(lines) if sum(t.startswith("v_sub_f32") for t in l) in (8 * d * 2, 8 * d * 4)
+                 and not any(t.startswith(("v_mfma", "v_readlane")) for t in l)]
+        assert inner, name
+        seen += 1
+        for l in inner:
+            assert not any(t.startswith("ds_read_b32") for t in l) and sum(t.startswith("ds_read") for t in l) <= 8, name
+            assert sum(t.startswith("v_mov_b32") for t in l) <= 8, name
+    assert seen == 2 + 2 + 2          # d = 4; d = 2 with groups of 8 rows, and with others
