@@ -211,9 +211,8 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
   constexpr int NM = D / 2;                   // coordinates per half-wave = matrix instructions of a tile's features
   constexpr uint32_t kBlockMask = 4 * TILES - 1;   // block number: tile, half-wave, upper or lower 8
   constexpr int R = 4;                        // steps filtered together
-  // Undecided vectors of a step from which the whole codebook is faster (judged by the first rows of a run of 8 or 4; later
-  // ones, whose run would be done twice, need twice as many).  A vector taken by itself costs 25, 17, 13 us per
-  // 4096 x 4096 and vector of a step (d = 2, d = 4 with k = 256, d = 4 with k = 64).
+  // Undecided vectors of a step from which the whole codebook is faster, for its rows and those to come.  A vector taken by
+  // itself costs 25, 17, 13 us per 4096 x 4096 and vector of a step (d = 2, d = 4 with k = 256, d = 4 with k = 64).
   constexpr int kMostUndecided = D == 2 ? (K == 256 ? 7 : 3) : K == 256 ? 13 : 3;
   __shared__ __attribute__((aligned(16))) float cbs[(K + K / 8) * D];
   __shared__ __attribute__((aligned(16))) float distinct[(K + K / 8) * D];
@@ -370,7 +369,19 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
     split_twice(own_coord<D>(hq, 0, half), Bh.x, Bh.y);
     if constexpr (D == 4) split_twice(own_coord<D>(hq, 1, half), Bh.z, Bh.w);
   }
-  const int run = rows < 8 ? rows : 8;        // rows that are taken again together: 8, or 4
+  // The filter decides hardly any of the vectors far from zero beside the distances between centroids: its margin is that
+  // share of their norm.  With K centroids drawn from a normal distribution, 95 % are undecided if the margin is the distance of
+  // two centroids times 2 / K (d = 2) or 0.5 / sqrt(K) (d = 4); each lane asks that of its first vector and two distinct
+  // centroids, and the wave follows the majority.  A rule of speed alone.
+  {
+    float a[D], norm = 0.f;
+    load_coords<D>(fcb + em_place<D>(8) * (n % NB), a);
+#pragma unroll
+    for (int t = 0; t < D; ++t) norm += h[t] * xn[0][t] * xn[0][t];
+    const float apart = em_distance<D>(a, h, fcb + em_place<D>(8) * ((n + 1) % NB));
+    const float share = D == 2 ? 2.f / K : K == 256 ? 0.5f / 16 : 0.5f / 8;
+    filter = filter && __builtin_popcountll(__ballot(EmMargin<D>::kX * norm > share * apart)) <= 32;
+  }
 #pragma unroll 1
   for (int row = 0; row < rows;) {            // R steps each
     float xs[R][D];
@@ -479,7 +490,7 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
         int undecided = 0;
 #pragma unroll
         for (int r = 0; r < R; ++r) undecided += __builtin_popcount(unsures[r]);
-        if (undecided > kMostUndecided * R * (row_now % run == 0 ? 1 : 2)) {
+        if (undecided > kMostUndecided * R) {
           filter = false;                     // the rows to come will be no better
           goto whole_codebook;
         }
@@ -522,17 +533,17 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
       continue;
     }
   whole_codebook:
-    const int again = row_now - row_now % run;
-    row = again + run;
+    const bool eight = rows - row_now >= 8;   // else 4
+    row = row_now + (eight ? 8 : 4);
     const int ahead = row < rows ? row : 0;
 #pragma unroll
     for (int r = 0; r < R; ++r)   // before the stores, as on the way past this: a wait for them is one for these too
       load_coords<D>(Wb + (size_t)(ahead + r) * in_features, xn[r]);
-    const size_t mine = (size_t)(again + (run / 2) * half);
-    if (D == 4 && run == 4)
-      em_assign_whole<K, D, 2>(cbs, Wb + mine * in_features, in_features, h, ab + mine * (in_features / D));
-    else
+    const size_t mine = (size_t)(row_now + (eight ? 4 : 2) * half);
+    if (eight)
       em_assign_whole<K, D, 4>(cbs, Wb + mine * in_features, in_features, h, ab + mine * (in_features / D));
+    else
+      em_assign_whole<K, D, 2>(cbs, Wb + mine * in_features, in_features, h, ab + mine * (in_features / D));
   }
 }
 

@@ -69,3 +69,58 @@ def test_equal_centroids(env, shape, distinct):  # noqa: F811
     f = oracle.VQFormat(out_f, in_f, k, 8, gr, 256, d)
     a, _ = _gpu_em_any(env, (out_f, in_f, k, d, gr), W, h, cb)
     np.testing.assert_array_equal(a, oracle.em_assign(f, W, h, cb))
+
+
+# rows and columns of the large launch: strips of 16 (d = 4: 4 to 12 blocks per CU, d = 2: 8 to 16) and of 32 rows
+@pytest.mark.parametrize("case", ["far in later runs", "near ties in later runs", "zero weights in one place", "nan and inf"])
+@pytest.mark.parametrize("shape", [(64, 2, 16, 2560), (64, 2, 32, 5120), (256, 2, 128, 2560), (256, 2, 32, 5120), (64, 4, 16, 2560), (64, 4, 64, 5120),
+                                   (256, 4, 64, 2560), (256, 4, 256, 5120)], ids=str)
+def test_strips_of_undecided_vectors(env, shape, case):  # noqa: F811
+    """Waves that give up the filter after some rows, or in some places only, in strips of every height: against launches of
+    few rows, which take strips of 8."""
+    torch, vq, _ = env
+    k, d, gr, out_f = shape
+    in_f, part = 2048, 512
+    g = torch.Generator("cuda").manual_seed(k + d + gr)
+    W = torch.randn((out_f, in_f), device="cuda", generator=g) * 0.02
+    h = 0.2 + 4.8 * torch.rand(in_f, device="cuda", generator=g)
+    cb = torch.randn((out_f // gr, in_f // 256, k, d), device="cuda", generator=g) * 0.02
+    row = torch.arange(out_f, device="cuda")
+    if case == "far in later runs":           # from a row of each 32 on that differs from strip to strip
+        far = row % 32 >= 4 * (row // 32 % 8)
+        W[far] += 5
+        cb[:, :, 1::2] += 5
+    elif case == "near ties in later runs":   # distinct centroids that the scores cannot tell apart
+        ulps = torch.argsort(torch.rand((*cb.shape[:2], k // 2), device="cuda", generator=g), dim=2)
+        cb[:, :, ::2] = 0.5
+        cb[:, :, ::2, 0] += ulps * 2.0 ** -23
+        W[row % 32 >= 4 * (row // 32 % 8)] = 0.5
+    elif case == "zero weights in one place":
+        h[32 * d:64 * d] = 0
+        h[1024::256] = 0
+    elif case == "nan and inf":
+        noise = torch.rand(W.shape, device="cuda", generator=g)
+        W[noise < 0.001] = float("nan")
+        W[noise > 0.999] = float("inf")
+
+    def assign(rows):
+        a = torch.full((out_f, in_f // d), 255, dtype=torch.uint8, device="cuda")
+        for r in range(0, out_f, rows):
+            vq.vq_em_assign(vq.make_desc(rows, in_f, k, BITS[k], gr, 256, d), W[r:r + rows], h,
+                            cb[r // gr:(r + rows) // gr].contiguous(), a[r:r + rows])
+        torch.cuda.synchronize()
+        return a
+
+    large = assign(out_f)
+    assert torch.equal(large, assign(part))
+    # and the defined arithmetic itself, on the first group
+    x, c, hv = W[:gr].view(gr, -1, 256 // d, 1, d), cb[0][:, None], h.view(1, -1, 256 // d, 1, d)
+    dist = None
+    for t in range(d):
+        e = x[..., t] - c[..., t]
+        term = hv[..., t] * (e * e)
+        dist = term if dist is None else dist + term
+    dist = torch.where(torch.isnan(dist), torch.full_like(dist, float("inf")), dist)
+    best = dist.min(dim=-1, keepdim=True).values
+    first = torch.where(torch.isinf(best[..., 0]), 0, (dist == best).int().argmax(dim=-1))
+    assert torch.equal(large[:gr], first.reshape(gr, -1).to(torch.uint8))
