@@ -1165,17 +1165,29 @@ __global__ __launch_bounds__(64) void em_update_small_kernel(const float* __rest
     default: F(256); break;  \
   }
 
-// Rows of a strip.  Filtered: a workgroup to 8 rows in small launches and low groups, else to up to 32, which make the
-// centroids' features fewer times.  us with strips of 8, 32: 1536 x 1536 (1,152 blocks) d = 2, k = 64 12.7, 22.9, d = 2,
-// k = 256 23.8, 34.7, d = 4, k = 256 18.4, 24.9; 2048 x 2048 (2,048) 17.5, 24.8, 35.8, 39.9, 28.9, 27.7; 2048 x 4096 (4,096)
-// 31.9, 33.9, 68.7, 64.9, 52.0, 48.6; 4096 x 4096 57.8, 57.7, 122.9, 118.0, 97.2, 83.7.
+// Rows of a strip.  Filtered: a workgroup to 8 rows in small launches and low groups, else to 16 or 32, which make the
+// centroids' features fewer times and, with d = 4, read a centroid for four vectors in place of two where they are undecided.
+// us with strips of 8, 16, 32, groups of 32 or 64 rows, and with weights of zero in every set of 32 vectors behind:
+//                       512 blocks                        1,024                             1,536
+//   d = 2, k = 64       7.2, 9.3, 14.8; 9.3, 13.7, 23.4   10.1, 10.7, 15.1; 15.4, 14.1, 23  12.9, 13.0, 17.5; 20.8, 20.6, 23.7
+//   d = 2, k = 256      12.5, 15.8, 26.5; 23, 36, 69      18.4, 18.6, 26.9; 40, 38, 69      24.4, 24.2, 32.1; 57, 66, 72
+//   d = 4, k = 64       6.0, 7.0, 10.4; 9.1, 12.6, 21     8.3, 8.4, 10.5; 14.9, 12.8, 21    10.6, 9.7, 12.3; 20.1, 20.9, 21.3
+//   d = 4, k = 256      8.9, 10.3, 16.0; 23, 36, 67       14.2, 12.8, 15.8; 47, 37, 67      17.9, 16.1, 19.6; 62, 66, 67
+//                       2,048                             3,072                             4,096
+//   d = 2, k = 64       15.6, 15.5, 17.6; 25.8, 24.6, 24  21.5, 21.0, 22.5; 37, 35, 38      27.6, 26.2, 27.5; 48, 46, 46
+//   d = 2, k = 256      30.8, 29.9, 32.3; 75, 73, 73      43.3, 42.1, 43.7; 113, 108, 124   57.3, 54.6, 56.3; 149, 143, 143
+//   d = 4, k = 64       12.9, 11.5, 12.5; 25.7, 23.3, 22  18.0, 16.0, 15.8; 37, 34, 37      23.3, 20.5, 19.5; 49, 44, 42
+//   d = 4, k = 256      21.5, 20.2, 20.2; 82, 73, 69      31.1, 28.5, 27.7; 122, 109, 124   40.7, 36.8, 36.2; 162, 144, 141
+// and 8,192 blocks 51.9, 48.1, 48.3; 108, 103, 103; 43.4, 37.9, 35.8; 76.9, 70.5, 66.8.
 //   Loops: a wave to 8 rows, or to 2 where the blocks would leave SIMDs idle.  us with 8, 2: 512 x 512 (128 blocks) d = 1,
 // k = 64 26.6, 10.2, d = 2, k = 16 7.4, 3.2; 1536 x 1536 33.2, 22.5, 8.0, 5.9; 2048 x 2048 (2,048) 35.0, 32.4, 8.8, 8.3;
 // 2048 x 4096 61.8, 59.1, 16.0, 16.2; 4096 x 4096 117, 110, 30.8, 32.1 and d = 1, k = 8 22.7, 23.9.
 template <int K, int D, int NCB> static int em_strip_rows(const vq_desc& d, long long n_blocks) {
   const long long cus = device_cus();
-  if (NCB == 1 && em_filtered<K, D>())
-    return d.group_rows <= kGroupRows || n_blocks < 16 * cus ? kGroupRows : d.group_rows < 32 ? d.group_rows : 32;
+  if (NCB == 1 && em_filtered<K, D>()) {
+    const int rows = n_blocks < (D == 4 ? 4 : 8) * cus ? kGroupRows : n_blocks < (D == 4 ? 12 : 16) * cus ? 16 : 32;
+    return d.group_rows <= kGroupRows ? kGroupRows : d.group_rows < rows ? d.group_rows : rows;
+  }
   return NCB == 1 && n_blocks <= 8 * cus ? 2 : 8;
 }
 template <int K, int D, int NCB> static unsigned em_grid(long long n_blocks, int strip_rows) {

@@ -175,3 +175,15 @@ def test_e_step_keeps_to_the_size_of_a_launch(launches, shape):
     assert all(l[1][0] * l[2] < 2 ** 32 for l in ls)
     strip = min(gr, 32)
     assert sum(l[1][0] for l in ls) == (2 ** 19 + 256) // strip * 256
+
+
+def test_e_step_strips(launches):
+    """Rows of a workgroup of the filtered E-step, by the number of blocks of 8 x 256 weights and the height of the groups
+    (256 CUs, and 128)."""
+    table = [(2, 64, 32, 2032, 8), (2, 256, 128, 2048, 16), (2, 64, 16, 8192, 16), (2, 64, 32, 4080, 16), (2, 256, 32, 4096, 32), (2, 64, 8, 4096, 8),
+             (4, 64, 16, 1008, 8), (4, 64, 16, 1024, 16), (4, 256, 256, 3040, 16), (4, 256, 64, 3072, 32), (4, 256, 8, 8192, 8), (4, 64, 16, 8192, 16)]
+    calls = [("assign", blocks * 8, 256, gr, d, k, vq.VQ_F16) for d, k, gr, blocks, _ in table]
+    calls += [("assign", blocks * 4, 256, gr, d, k, vq.VQ_F16, 1, 1, 128) for d, k, gr, blocks, _ in table if blocks * 4 % gr == 0]
+    want = [8 * b // rows for _, _, _, b, rows in table] + [4 * b // rows for _, _, gr, b, rows in table if b * 4 % gr == 0]
+    got = launches(calls)
+    assert [(st, len(ls), ls[0][1]) for st, ls in got] == [(0, 1, (n, 1, 1)) for n in want]
