@@ -564,6 +564,14 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
 template <int K, int D> constexpr bool em_filtered() { return (D == 2 || D == 4) && K >= 64; }
 template <int K, int D> constexpr int em_waves() { return em_filtered<K, D>() ? (D == 4 && K == 256 ? 3 : 4) : 1; }   // per SIMD
 
+// Centroids to an iteration of the loop below; with a codebook per row four waves per SIMD, and twice the loop where those have
+// the registers.  us with one, two, all, groups of one row: d = 1, k = 4 4096 x 4096 20.0, 22.8, 19.1, 512 x 512 5.4, 5.0, 4.4;
+// d = 1, k = 8 26.2, 27.3, 46.8, 8.2, 7.5, 9.2; d = 2, k = 16 33.4, 33.9, -, 11.9, 9.3, -; groups of 32 rows d = 1, k = 8
+// 2048 x 2048 -, 6.9, 6.0; d = 4, k = 4 -, 3.7, 3.6; groups of 4 rows, d = 2, k = 8 4096 x 4096 -, 17.8, 18.7.
+template <int K, int D, int NCB> constexpr int em_unroll() {
+  return NCB == 8 ? (K == 4 ? 4 : K == 8 && D == 1 ? 1 : 2) : NCB == 1 && K <= 8 ? K : 2;
+}
+
 // The loop over the centroids, for ROWS rows (8, or 2 where a launch has few blocks) of one 8-row block and col-block per
 // wave; the codebook is that of the group the block lies in (NCB = 1), one codebook per row (NCB = 8: groups of one
 // row) or one per 4 rows (NCB = 2).  D values per centroid, 4 / D vectors per row and lane: lane L owns columns
@@ -604,7 +612,7 @@ __device__ __forceinline__ void em_assign_loop(const float* __restrict__ W, cons
     best[v] = __builtin_inff();
     arg[v] = 0;
   }
-#pragma unroll 2
+#pragma unroll (em_unroll<K, D, NCB>())
   for (int m = 0; m < K; ++m) {
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
@@ -666,7 +674,7 @@ __global__ __launch_bounds__(256, (em_waves<K, 2>())) void em_assign_kernel(
 
 // any dimensionality and group height
 template <int K, int D, int NCB>
-__global__ __launch_bounds__(256, (NCB == 1 ? em_waves<K, D>() : 1)) void em_assign_any_kernel(
+__global__ __launch_bounds__(256, (NCB == 1 ? em_waves<K, D>() : NCB == 8 ? 4 : 1)) void em_assign_any_kernel(
     const float* __restrict__ W, const float* __restrict__ hdiag, const float* __restrict__ cb, uint8_t* __restrict__ assign,
     int n_cb, long long n_blocks, int in_features, int group_rows, int strip_rows) {
   em_assign<K, D, NCB>(W, hdiag, cb, assign, n_cb, n_blocks, in_features, group_rows, strip_rows);
@@ -1179,16 +1187,24 @@ __global__ __launch_bounds__(64) void em_update_small_kernel(const float* __rest
 //   d = 4, k = 64       12.9, 11.5, 12.5; 25.7, 23.3, 22  18.0, 16.0, 15.8; 37, 34, 37      23.3, 20.5, 19.5; 49, 44, 42
 //   d = 4, k = 256      21.5, 20.2, 20.2; 82, 73, 69      31.1, 28.5, 27.7; 122, 109, 124   40.7, 36.8, 36.2; 162, 144, 141
 // and 8,192 blocks 51.9, 48.1, 48.3; 108, 103, 103; 43.4, 37.9, 35.8; 76.9, 70.5, 66.8.
-//   Loops: a wave to 8 rows, or to 2 where the blocks would leave SIMDs idle.  us with 8, 2: 512 x 512 (128 blocks) d = 1,
-// k = 64 26.6, 10.2, d = 2, k = 16 7.4, 3.2; 1536 x 1536 33.2, 22.5, 8.0, 5.9; 2048 x 2048 (2,048) 35.0, 32.4, 8.8, 8.3;
-// 2048 x 4096 61.8, 59.1, 16.0, 16.2; 4096 x 4096 117, 110, 30.8, 32.1 and d = 1, k = 8 22.7, 23.9.
+//   Loops: a wave to 8 rows, or to 2 where the blocks would leave SIMDs idle and a codebook is long enough to be fetched
+// by four waves.  us with 8, 2:    128 blocks   512         1,024       1,536       1,792       2,048
+//   d = 1, k = 4                   3.6, 2.5     3.7, 2.8    3.9, 3.8    4.5, 4.7    4.6, 5.2    4.7, 5.7     1,280 4.4, 4.3
+//   d = 1, k = 8                   5.0, 2.9     5.1, 3.4    5.3, 4.7    6.0, 6.0    6.1, 6.5    6.3, 7.1
+//   d = 1, k = 16                  9.6, 3.8     10.0, 4.3   10.1, 6.7   10.7, 8.8   10.7, 9.8   10.9, 10.8
+//   d = 1, k = 64                  26.5, 9.0    27.2, 10.4  27.4, 17.7  33.5, 23.6  33.5, 26.6  33.7, 29.3   k = 32, 256 alike
+//   d = 2, k = 4                   3.3, 2.5     3.4, 2.8    3.6, 3.6    3.9, 4.2    4.0, 4.5    4.1, 4.9     d = 4 alike
+//   d = 2, k = 8                   4.4, 2.7     4.6, 3.0    4.8, 4.0    5.2, 4.9    5.2, 5.6    5.3, 6.1     d = 4 alike
+//   d = 2, k = 16                  6.9, 3.5     7.2, 3.9    7.3, 5.4    7.8, 7.0    7.8, 8.0    7.9, 8.4
+//   d = 2, k = 32                  11.6, 5.0    11.9, 5.5   12.1, 8.7   12.6, 11.9  12.7, 14.7  12.8, 15.0
+//   d = 4, k = 16                  6.4, 3.4     6.5, 3.7    6.7, 5.4    7.0, 6.9    7.1, 8.3    7.2, 8.7     k = 32 alike
 template <int K, int D, int NCB> static int em_strip_rows(const vq_desc& d, long long n_blocks) {
   const long long cus = device_cus();
   if (NCB == 1 && em_filtered<K, D>()) {
     const int rows = n_blocks < (D == 4 ? 4 : 8) * cus ? kGroupRows : n_blocks < (D == 4 ? 12 : 16) * cus ? 16 : 32;
     return d.group_rows <= kGroupRows ? kGroupRows : d.group_rows < rows ? d.group_rows : rows;
   }
-  return NCB == 1 && n_blocks <= 8 * cus ? 2 : 8;
+  return NCB == 1 && n_blocks <= (D == 1 && K >= 16 ? 8 : K == 4 ? 5 : 6) * cus ? 2 : 8;
 }
 template <int K, int D, int NCB> static unsigned em_grid(long long n_blocks, int strip_rows) {
   if (NCB == 1 && em_filtered<K, D>()) return (unsigned)(n_blocks / (strip_rows / kGroupRows));

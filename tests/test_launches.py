@@ -187,3 +187,19 @@ def test_e_step_strips(launches):
     want = [8 * b // rows for _, _, _, b, rows in table] + [4 * b // rows for _, _, gr, b, rows in table if b * 4 % gr == 0]
     got = launches(calls)
     assert [(st, len(ls), ls[0][1]) for st, ls in got] == [(0, 1, (n, 1, 1)) for n in want]
+
+
+def test_e_step_rows_of_a_wave(launches):
+    """Without the filter a wave takes 2 rows in launches of few blocks (a workgroup to a block), else 8."""
+    most = {(1, 4): 5, (1, 8): 6, (1, 16): 8, (1, 64): 8, (1, 256): 8, (2, 4): 5, (2, 8): 6, (2, 16): 6, (2, 32): 6, (4, 4): 5, (4, 16): 6, (4, 32): 6}
+    calls, want = [], []
+    for (d, k), per_cu in most.items():
+        for cus in (256, 128):
+            for blocks in (per_cu * cus, per_cu * cus + 4):
+                calls.append(("assign", blocks * 8, 256, 8, d, k, vq.VQ_F16, 1, 1, cus))
+                want.append(blocks if blocks == per_cu * cus else blocks // 4)
+    got = launches(calls)
+    assert [(st, len(ls), ls[0][1]) for st, ls in got] == [(0, 1, (n, 1, 1)) for n in want]
+    for gr, d, k in ((4, 2, 16), (1, 1, 4)):          # several codebooks to a block: always 8
+        (_, ls), = launches([("assign", 64, 256, gr, d, k, vq.VQ_F16)])
+        assert ls[0][1][0] == 2
