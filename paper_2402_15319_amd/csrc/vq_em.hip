@@ -1294,11 +1294,21 @@ hipError_t launch_em_assign(const vq_desc& d, const void* W, const void* hdiag, 
   return hipGetLastError();
 }
 
-// Whether D workgroups share a group of 16 rows or more in the M-step.  us with one, D: d = 4, k = 256, 256 rows 512 x 512
-// (4 groups) 28.0, 12.4, 2048 x 2048 (64) 28.3, 19.1, 2048 x 3072 (96) 28.5, 24.7; 64 rows 512 x 512 (16) 9.9, 5.7,
-// 1024 x 1536 (96) 10.2, 8.0, 1024 x 2048 (128) 10.3, 10.2; d = 2, k = 256, 128 rows 512 x 512 (8) 15.5, 12.5,
-// 2048 x 2048 (128) 15.7, 13.8; k = 64, 32 rows 1024 x 2048 (256) 8.6, 8.5.
-static bool em_shared(const vq_desc& d, long long n_items) { return n_items * d.d <= 2 * device_cus(); }
+// Whether D workgroups share a group of 16 rows or more in the M-step: up to two workgroups per CU, and up to one where
+// they have eight waves and more and both coordinates are needed for a line of W.  us with one, D, by groups:
+//                             8           64          96          128         192         256
+//   d = 4, k = 256, 256 rows  27.8, 12.5  28.3, 19.1  28.2, 24.7  29.1, 29.1
+//                   128 rows  17.7, 8.3   17.9, 10.7  18.1, 15.0  18.6, 17.0
+//                   64 rows   9.8, 5.7    10.0, 6.1   10.1, 7.8   10.1, 10.2              k = 16 and 64 alike
+//                   16 rows   9.9, 4.6    10.0, 4.8   10.0, 5.5   10.0, 5.6
+//   d = 2, k = 256, 256 rows  26.9, 21.1  27.2, 21.8  27.3, 22.4  28.1, 26.7  31.9, 44.8  35.2, 48.7
+//                   128 rows  15.4, 12.5  15.6, 12.8  15.7, 13.0  16.1, 14.0  18.1, 22.2  19.4, 22.9   k = 64 alike
+//                   64 rows   9.3, 7.9    9.4, 8.2    9.5, 8.4    9.7, 8.3    9.8, 11.1   11.2, 11.9
+//                   32 rows   8.4, 6.2    8.5, 6.3    8.5, 6.4    8.6, 6.4    8.7, 7.9    8.7, 8.0     k = 64 8.4, 8.4 from 192 on
+//                   16 rows   8.4, 5.7    8.6, 5.9    8.6, 5.9    8.6, 5.9    8.7, 6.8    8.7, 6.9
+static bool em_shared(const vq_desc& d, long long n_items) {
+  return n_items * d.d <= (d.d == 2 && d.group_rows >= 64 ? 1 : 2) * (long long)device_cus();
+}
 
 template <int K, int D, int NG, int GPW, int RB>
 static void launch_update(const vq_desc& d, const void* W, const void* hdiag, const void* assign, void* cb_out,

@@ -203,3 +203,17 @@ def test_e_step_rows_of_a_wave(launches):
     for gr, d, k in ((4, 2, 16), (1, 1, 4)):          # several codebooks to a block: always 8
         (_, ls), = launches([("assign", 64, 256, gr, d, k, vq.VQ_F16)])
         assert ls[0][1][0] == 2
+
+
+def test_m_step_workgroups_of_a_group(launches):
+    """A workgroup per coordinate where there are few groups, else one per group (256 CUs, and 128)."""
+    calls, want = [], []
+    for (d, k, gr), per_cu in {(2, 256, 64): 1, (2, 64, 128): 1, (2, 256, 256): 1, (2, 64, 32): 2, (2, 256, 16): 2, (4, 64, 16): 2, (4, 256, 64): 2,
+                               (4, 256, 256): 2}.items():
+        for cus in (256, 128):
+            most = per_cu * cus // d
+            for groups in (most, most + 1):
+                calls.append(("update", groups * gr, 256, gr, d, k, vq.VQ_F16, 1, 1, cus))
+                want.append(groups * (d if groups == most else 1))
+    got = launches(calls)
+    assert [(st, len(ls), ls[0][1]) for st, ls in got] == [(0, 1, (n, 1, 1)) for n in want]
