@@ -698,7 +698,8 @@ __global__ __launch_bounds__(256, (NCB == 1 ? em_waves<K, D>() : NCB == 8 ? 4 : 
 // all, and in brackets both with binary64 additions: d = 2, k = 64, 32 rows 67, 32 (75, 456); d = 2, k = 256, 8 rows 77,
 // 45 (72, 459), 128 rows 73, 39 (77, 501); d = 4, k = 256, 64 rows 69, 40 (81, 469), 256 rows 82, 59 (64, 270), where
 // the second half of the rows is read twice.  Weights further apart than 2^kSpread: 35 .. 64 for 28 .. 36 at 4096 x 4096.
-template <int K, int D, int NG, int GPW, int RB, bool SHARED>
+// SHARED: 0, or for the workgroups of a coordinate (see below) log2 of the weights of their groups at most.
+template <int K, int D, int NG, int GPW, int RB, int SHARED>
 struct EmTables {
   static constexpr int kEntries = NG * K;
   static constexpr int kCopies = kEntries >= 64 ? 1 : 64 / kEntries;
@@ -710,9 +711,9 @@ struct EmTables {
   static constexpr int kWords = 32;                         // dwords of counts per centroid: positions i and i + 32
   static constexpr int kQuantities = kCounted ? D : SHARED ? 2 : 2 * D;
   static constexpr int kTable = kQuantities * kStride;      // entries per item
-  static constexpr int kMaxWaves = GPW > 1 ? GPW : SHARED ? 16 : 8;
+  static constexpr int kMaxWaves = GPW > 1 ? GPW : SHARED > 14 ? 16 : 8;
   // an item has at most 2^kLog2N vectors; 51 bits are what the conversion below takes
-  static constexpr int kLog2N = (GPW > 1 ? 11 : RB > 1 || SHARED ? 16 : 14) - (D == 4 ? 2 : D == 2 ? 1 : 0);
+  static constexpr int kLog2N = (GPW > 1 ? 11 : SHARED ? SHARED : RB > 1 ? 16 : 14) - (D == 4 ? 2 : D == 2 ? 1 : 0);
   static constexpr int kBits = 62 - kLog2N < 51 ? 62 - kLog2N : 51;
   static constexpr int kSpread = kBits - 36;
 };
@@ -757,7 +758,7 @@ __device__ __forceinline__ double wave_sum63(double v) {
 //   SHARED: few groups.  D workgroups take a group, a coordinate each, with up to 16 waves: what takes the time then is the
 // chain of a wave's vectors, one after the other (figures at em_shared; shares of the codebook instead of coordinates
 // leave every wave its chain: 24.6 us for 12.4 at 512 x 512, 256 rows, and 41 for 28 at 2048 x 2048).
-template <int K, int D, int NG, int GPW, int RB, bool SHARED>
+template <int K, int D, int NG, int GPW, int RB, int SHARED>
 __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWaves), (GPW > 1 ? 1 : 4)) void em_update_kernel(
     const float* __restrict__ W, const float* __restrict__ hdiag, const uint8_t* __restrict__ assign,
     float* __restrict__ cb_out, int n_cb, long long n_items, int in_features, int n_rows) {
@@ -1325,19 +1326,21 @@ static void launch_update(const vq_desc& d, const void* W, const void* hdiag, co
   const int waves = GPW > 1 ? GPW : RB > 1 ? 8 : d.group_rows / kGroupRows;
   if constexpr (GPW == 1 && NG == 1 && D > 1) {
     if (em_shared(d, n_items)) {
-#define VQ_SHARED(RBS, WAVES)                                                                                              \
-  hipLaunchKernelGGL((em_update_kernel<K, D, 1, 1, RBS, true>), dim3((unsigned)(n_items * D)), dim3(64 * (WAVES)), 0, s,   \
+#define VQ_SHARED(RBS, WAVES, LOG2)                                                                                              \
+  hipLaunchKernelGGL((em_update_kernel<K, D, 1, 1, RBS, LOG2>), dim3((unsigned)(n_items * D)), dim3(64 * (WAVES)), 0, s,   \
                      (const float*)W, (const float*)hdiag, (const uint8_t*)assign, (float*)cb_out, n_cb, n_items,          \
                      d.in_features, d.group_rows)
       if constexpr (RB > 1) {
-        if (d.group_rows == 256) { VQ_SHARED(2, 16); return; }
+        if (d.group_rows == 256) VQ_SHARED(2, 16, 16);
+        else VQ_SHARED(1, 16, 15);
+      } else {
+        VQ_SHARED(1, d.group_rows / kGroupRows, 14);
       }
-      VQ_SHARED(1, d.group_rows / kGroupRows);
 #undef VQ_SHARED
       return;
     }
   }
-  hipLaunchKernelGGL((em_update_kernel<K, D, NG, GPW, RB, false>), dim3((unsigned)((n_items + GPW - 1) / GPW)), dim3(64 * waves), 0, s,
+  hipLaunchKernelGGL((em_update_kernel<K, D, NG, GPW, RB, 0>), dim3((unsigned)((n_items + GPW - 1) / GPW)), dim3(64 * waves), 0, s,
                      (const float*)W, (const float*)hdiag, (const uint8_t*)assign, (float*)cb_out, n_cb, n_items,
                      d.in_features, d.group_rows);
 }

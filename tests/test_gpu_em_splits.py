@@ -124,3 +124,24 @@ def test_strips_of_undecided_vectors(env, shape, case):  # noqa: F811
     best = dist.min(dim=-1, keepdim=True).values
     first = torch.where(torch.isinf(best[..., 0]), 0, (dist == best).int().argmax(dim=-1))
     assert torch.equal(large[:gr], first.reshape(gr, -1).to(torch.uint8))
+
+
+@pytest.mark.parametrize("shape", [(64, 2, 16), (256, 2, 64), (256, 2, 128), (64, 2, 256), (64, 4, 16), (256, 4, 64), (64, 4, 128), (256, 4, 256)], ids=str)
+def test_sums_of_shared_groups_keep_their_bits(env, shape):  # noqa: F811
+    """A group's sums are integers of 62 bits less the logarithm of its vectors, from the largest term down (at most 51), also
+    where its coordinates go to different workgroups: two values that cancel leave a third of the last of those bits."""
+    torch, vq, _ = env
+    k, d, gr = shape
+    bits = min(51, 62 - (max(14, int(np.log2(gr * 256))) - int(np.log2(d))))
+    tiny = 4 * 2.0 ** -bits               # terms below 2 (h) * 2 (x)
+    rng = np.random.default_rng(k + gr)
+    W = rng.normal(0, 1, (gr, 256)).astype(np.float32)
+    a = rng.integers(1, k, (gr, 256 // d)).astype(np.uint8)
+    where = rng.permutation(gr * 256 // d)[:3]
+    for at, v in zip(where, (1.0, -1.0, tiny)):
+        a.reshape(-1)[at] = 0
+        W.reshape(-1, d)[at] = v
+    new = torch.full((1, k, d), 777.0, device="cuda")
+    dev = [torch.from_numpy(t).cuda() for t in (W, np.ones(256, np.float32), a)]
+    vq.vq_em_update(vq.make_desc(gr, 256, k, BITS[k], gr, 256, d), *dev, new)
+    np.testing.assert_array_equal(new[0, 0].cpu().numpy(), np.full(d, np.float32(tiny) / np.float32(3)))
