@@ -1142,43 +1142,74 @@ hipError_t launch_one(const vq_desc& d, const void* idx_dev, const void* cb_dev,
   return hipGetLastError();
 }
 
-// Large batches on the 128-row tiles: 128 x 512 tiles decode W once per 512 batch columns instead
-// of once per 256 and take 1.6 times as long as 128 x 256 tiles for twice the area, but a launch
-// pays for whole rounds of one workgroup per CU.  So the first m_a tile rows run with 512-column
-// tiles and the rest with 256-column tiles in a second launch, m_a chosen so that both launches
-// fill their rounds best (m_a = 0: 256-column tiles only).  Same units as launch_gemm's estimates:
-// microseconds at in_features = 4096, scaled by kscale = in_features / 4096 (a tile's time is its
-// K loop); the 3 us of the second launch do not scale.
+// Large batches on the 128-row tiles: 128 x 512 tiles decode W once per 512 batch columns instead of once per 256 and take
+// 1.6 times as long as 128 x 256 tiles for twice the area, but a launch pays for whole rounds of one workgroup per CU.  So
+// the first m_a tile rows run with 512-column tiles and the rest with 256-column tiles in a second launch, m_a chosen so that
+// both launches fill their rounds best (0: 256-column tiles only).  The 512-column tile needs 128 accumulator registers per
+// wave, and what the block-normalised formats need to decode does not fit beside them: those keep 256 columns.
+template <int K> constexpr bool kBlockScales = K == kFmtK64BN || K == kFmtK16BN || K == kFmtD1K8BN || K == kFmtD4BN || K == kFmtK256I8BN;
+struct WideSplit {
+  int m_a;
+  double us;   // in the units of large_tiling
+};
+template <int K>
+WideSplit wide_split(const vq_desc& d, int B) {
+  const long long cus = device_cus(), rows128 = (d.out_features / kGroupRows + 15) / 16;
+  const long long cols256 = (B + 255) / 256, cols512 = (B + 511) / 512;
+  const auto rounds = [&](long long tiles) { return (tiles + cus - 1) / cus; };
+  if constexpr (kBlockScales<K>) return {0, 78.0 * (double)rounds(rows128 * cols256)};
+  WideSplit best = {0, 86.0 * (double)rounds(rows128 * cols256)};
+  const long long most = rounds(rows128 * cols512);
+  for (long long r5 = 1; r5 <= most; ++r5) {       // rounds of 512-column tiles, as many tile rows as fit them
+    const long long m = min(rows128, r5 * cus / cols512), r2 = rounds((rows128 - m) * cols256);
+    if (m == 0) continue;
+    const double us = 135.0 * (double)r5 + (r2 > 0 ? 86.0 * (double)r2 + 5.0 * 4096.0 / d.in_features : 0.0);
+    if (us < best.us)      // of those the fewest that leave the others no more rounds
+      best = {(int)max(rows128 - r2 * cus / cols256, (r5 - 1) * cus / cols512 + 1), us};
+  }
+  return best;
+}
+
 template <int K>
 hipError_t launch_wide(const vq_desc& d, const void* idx_dev, const void* cb_dev, const void* X, int B,
                        int ldx, void* Y, int ldy, int y_f32, hipStream_t s) {
-  // the 512-column tile needs 128 accumulator registers per wave: most formats fit the 256
-  // registers or spill up to four of them; the block-normalised ones would spill seven to ten and
-  // keep 256 columns
-  if constexpr (K == kFmtK64BN || K == kFmtK16BN || K == kFmtD1K8BN || K == kFmtD4BN || K == kFmtK256I8BN) {
-    return launch_one<K, 2, 256, 2>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);
-  } else {
-  const int n_rb = d.out_features / kGroupRows;
-  const long long rows128 = (n_rb + 15) / 16, cols256 = (B + 255) / 256, cols512 = (B + 511) / 512;
-  int m_a = 0;
-  const long long cus = device_cus();
-  const double kscale = (double)d.in_features / 4096.0;
-  double best = 76.0 * kscale * (double)((rows128 * cols256 + cus - 1) / cus);
-  for (long long m = 1; m <= rows128; ++m) {
-    const long long rest = rows128 - m;
-    const double t = 122.0 * kscale * (double)((m * cols512 + cus - 1) / cus) +
-                     (rest > 0 ? 3.0 + 76.0 * kscale * (double)((rest * cols256 + cus - 1) / cus) : 0.0);
-    if (t < best) {
-      best = t;
-      m_a = (int)m;
+  const int n_rb = d.out_features / kGroupRows, m_a = wide_split<K>(d, B).m_a;
+  if constexpr (!kBlockScales<K>) {
+    if (m_a > 0) {
+      const int rb_split = m_a * 16 < n_rb ? m_a * 16 : n_rb;
+      const hipError_t e = launch_one<K, 2, 512, 2>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s, 0, rb_split);
+      if (e != hipSuccess || rb_split == n_rb) return e;
+      return launch_one<K, 2, 256, 2>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s, rb_split, n_rb);
     }
   }
-  if (m_a == 0) return launch_one<K, 2, 256, 2>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);
-  const int rb_split = m_a * 16 < n_rb ? m_a * 16 : n_rb;
-  hipError_t e = launch_one<K, 2, 512, 2>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s, 0, rb_split);
-  if (e != hipSuccess || rb_split == n_rb) return e;
-  return launch_one<K, 2, 256, 2>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s, rb_split, n_rb);
-  }
+  return launch_one<K, 2, 256, 2>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);
+}
+
+// The tiling of gemm_kernel for products beyond one round of 32 x 128 tiles: 0 to 3 for 64 x 128 and 64 x 256 (4 waves, two
+// workgroups per CU), 64 x 256 and 128 x 256 (8 waves, one; with 128 x 512: wide_split).  All of them take their time in
+// rounds of one tile per CU.  Units: microseconds at in_features = 4096, of which only the ratios matter; a tile's time is its
+// K loop.  Fitted to the four times of 3,180 products of all formats (512 to 14,336 rows, 1,024 to 11,008 columns, B = 64 to
+// 2,500): the choice is 0.01 % (0.02 % with block scales, 0.5 % with d = 4 fp16 tables) above the fastest on average and 8 % at
+// most; 2.0 %, up to 45 %, while the first two were taken to grow with the number of tiles.  us of the four:
+//   11008 x 4096, B = 203, k = 256 int8 59, 55, 48, 71; B = 400 91, 82, 90, 74; B = 2048, k = 256 308, 266, 291, 224
+//   4096 x 4096, k = 16, B = 512 34, 47, 39, 62; B = 1024 55, 54, 50, 63; 11008 x 4096, B = 128 32, 48, 39, 62
+//   11424 x 8192, d = 1, k = 8, B = 350 (2.1 rounds of the first) 158, 144, 161, 125; 8192 x 5120, k = 32, B = 1513 214, 177, 181, 146
+//   4864 x 1536, d = 4 fp16, B = 2197 79, 62, 71, 55; 2104 x 7680, k = 32, B = 1094 93, 92, 79, 119
+// With d = 4 and fp16 tables the third takes 8 us longer whatever the columns: 13824 x 1024, B = 140 20, 19, 28, 24; x 11008 145,
+// 137, 117, 186.
+template <int K>
+int large_tiling(const vq_desc& d, int B) {
+  const long long n_rb = d.out_features / kGroupRows, rows64 = (n_rb + 7) / 8, cus = device_cus();
+  const double r128 = (double)((rows64 * ((B + 127) / 128) + cus - 1) / cus), r256 = (double)((rows64 * ((B + 255) / 256) + cus - 1) / cus);
+  constexpr bool BN = kBlockScales<K>;
+  double est[4] = {r128 <= 1 ? (BN ? 46.0 : 50.0) : 28.0 * r128 + (BN ? 7.0 : 14.0),
+                   r256 <= 1 ? (BN ? 61.0 : 70.0) : BN ? 44.0 * r256 - 3.0 : 46.0 * r256 + 4.0,
+                   r256 <= 1 ? (BN ? 53.0 : 60.0) : BN ? 48.0 * r256 - 1.0 : 49.0 * r256 + 6.0, wide_split<K>(d, B).us};
+  if (K == kFmtD4F16) est[2] += 12.0 * 4096.0 / d.in_features - 5.0;
+  int best = 0;
+  for (int i = 1; i < 4; ++i)
+    if (est[i] < est[best]) best = i;
+  return best;
 }
 
 // Whether the 16 x 16 tiles (tiles_tiny of them) beat the 32 x 32 ones (tiles_small).  They re-decode W once per
@@ -1246,40 +1277,15 @@ hipError_t launch_gemm(const vq_desc& d, const void* idx_dev, const void* cb_dev
   // with 8 waves 29.2), where a wave has a single col-block anyway, and for the formats that decode longest where
   // four waves take two each (k = 64 with block scales, 1024 x 2048 5.7, with 8 waves 6.1).  Then 32 x 32 tiles (gemm_small_kernel,
   // bandwidth-bound) while they are few enough to run in about one wave of workgroups, then
-  // ring_gemm_kernel (32 x 128 tiles) while those fit the CUs once, and beyond that the cheapest of four tilings of
-  // gemm_kernel by a small cost model: 64 x 128 and 64 x 256 (4 waves, two workgroups per CU: time grows with the tile
-  // count) and 64 x 256 and 128 x 256 (8 waves, one workgroup per CU: time moves in rounds of one tile per CU).  The
-  // constants are microseconds at in_features = 4096 on 256 CUs; a tile's time is its K loop, so every term scales with
-  // in_features and only the ratios matter here.  us with 64 x 128, 64 x 256, 64 x 256 of 8 waves, 128 x 256 tiles:
-  //   11008 x 4096, B = 203, k = 256 int8 59, 55, 48, 71; B = 400 91, 82, 90, 74; B = 2048, k = 256 308, 266, 291, 224
-  //   4096 x 4096, k = 16, B = 512 34, 47, 39, 62; B = 1024 55, 54, 50, 63; 11008 x 4096, B = 128 32, 48, 39, 62
-  //   11008 x 4096, k = 64, B = 256 52, 51, 46, 68; B = 512 87, 81, 95, 73; 3072 x 4096, k = 16, B = 700 46, 47, 38, 61
-  //   2336 x 7168, k = 16 int8, B = 634 55, 77, 70, 103; 2104 x 7680, k = 32, B = 1094 93, 92, 79, 119
-  // (the 128 x 128 tiles of 8 waves that the third replaces decode W twice as often: 55 for B = 203, 44 for 3072 x 4096).
+  // ring_gemm_kernel (32 x 128 tiles) while those fit the CUs once, and beyond that gemm_kernel (large_tiling).
   const int n_rb = d.out_features / kGroupRows;
   const long long tiles_tiny = (long long)((n_rb + 1) / 2) * ((B + 15) / 16);
   const long long tiles_small = (long long)((n_rb + 3) / 4) * ((B + 31) / 32);
-  const long long rows64 = (n_rb + 7) / 8, rows128 = (n_rb + 15) / 16;
-  const long long cols128 = (B + 127) / 128, cols256 = (B + 255) / 256;
   const long long cus = device_cus();
   const int n_cb = d.in_features / kGroupCols;
   const bool eight_waves = tiles_tiny <= cus && n_cb > 4;
   const bool small = B <= 32 || tiles_small <= 3 * cus;
-  const bool one_round_32x128 = rows64 * cols128 <= cus / 2;
-  // us of whole rounds of one tile per CU and a last one that is part full, or of two 4-wave tiles per CU
-  const auto rounds = [&](long long tiles, double full, double first, double slope) {
-    const long long before = (tiles - 1) / cus;
-    return (double)before * full + first + slope * (double)(tiles - before * cus) / (double)cus;
-  };
-  const double per_cu = 256.0 / (double)cus;
-  const long long n128 = rows64 * cols128, n256 = rows64 * cols256;
-  const double est[4] = {n128 <= cus ? 34.0 : n128 <= 2 * cus ? 54.0 : 5.0 + 0.112 * per_cu * (double)n128,   // 64 x 128
-                         n256 <= cus ? 44.0 + 0.035 * per_cu * (double)n256 : 15.0 + 0.19 * per_cu * (double)n256,   // 64 x 256
-                         rounds(n256, 48.0, 36.0, 12.0),                                 // 64 x 256, 8 waves
-                         rounds(rows128 * cols256, 76.0, 60.0, 16.0)};                   // 128 x 256, 8 waves
-  int best = 0;
-  for (int i = 1; i < 4; ++i)
-    if (est[i] < est[best]) best = i;
+  const bool one_round_32x128 = (long long)((n_rb + 7) / 8) * ((B + 127) / 128) <= cus / 2;
 #define VQ_GEMM_DISPATCH(K)                                                                       \
   {                                                                                               \
     if (tiny_pays<K>(tiles_tiny, tiles_small, d, B, cus))                                         \
@@ -1288,6 +1294,7 @@ hipError_t launch_gemm(const vq_desc& d, const void* idx_dev, const void* cb_dev
     if (small) return launch_small<K>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);           \
     if (one_round_32x128)                                                                         \
       return launch_one<K, 1, 128>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);              \
+    const int best = large_tiling<K>(d, B);                                                       \
     if (best == 0) return launch_one<K, 2, 128>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s); \
     if (best == 1) return launch_one<K, 2, 256>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s); \
     if (best == 2)                                                                                \

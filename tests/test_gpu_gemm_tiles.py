@@ -12,11 +12,10 @@ FORMATS = {
     "k256_bn": dict(k=256, index_bits=8, group_rows=64, int8_tables=True, block_norm=True),
     "d4_f16": dict(k=256, index_bits=8, group_rows=64, d=4),
 }
-# (rows, columns, B) on 256 CUs: 32 x 128 tiles; 64 x 128; 64 x 256 of 4 waves; 64 x 256 of 8; 128 x 256; 128 x 512 and 256;
-# 16 x 16 tiles of 16 waves; 32 x 32 tiles of two groups of waves, of one
+# (rows, columns, B); which kernel each takes on 256 CUs is at the test of that without a GPU (test_launches.py)
 SIZES = [(3904, 256, 200), (3904, 1280, 161), (8256, 256, 130), (8256, 768, 66), (25664, 512, 400), (8256, 512, 1090), (11072, 256, 203),
          (8384, 512, 256), (11072, 512, 410), (21568, 256, 384), (11072, 256, 2040), (11072, 768, 1281), (1088, 2304, 16), (64, 8448, 21),
-         (1088, 2048, 161), (1088, 3328, 170), (1088, 5120, 130), (1088, 2304, 161)]
+         (1088, 2048, 161), (1088, 3328, 170), (1088, 5120, 130), (1088, 2304, 161), (4032, 768, 250), (15424, 2048, 1090)]
 
 
 @pytest.mark.parametrize("size", SIZES, ids=str)

@@ -912,8 +912,8 @@ def test_int8_tables_gemm_tall(env, s, B):
 
 # The matrix-core kernels with 128- and 256-column tiles are chosen by tile count, so a short
 # matrix reaches them only with a wide batch: 1000 columns -> 32 x 128 tiles, 1300 -> 64 x 128,
-# 10100 -> 64 x 256, and the 8-wave tiles where whole rounds of 256 tiles fit best: 4600 -> 128 x 128,
-# 9200 -> 128 x 256 (ragged last column tile in each; 101 row-blocks leave a ragged row tile).
+# and the 8-wave tiles where whole rounds of 256 tiles fit best: 4600 -> 64 x 256, 9200 -> 128 x 256,
+# 10100 -> 128 x 512 (ragged last column tile in each; 101 row-blocks leave a ragged row tile).
 @pytest.mark.parametrize("B", [1000, 1300, 4600, 9200, 10100])
 @pytest.mark.parametrize("s", [_shape(800, 512, 16), _shape(808, 768, 256), _shape64(800, 512),
                                _shape16i8(808, 512), _shape_d1(808, 512)], ids=str)
@@ -1617,7 +1617,7 @@ def test_newer_kernels_replay_in_a_hip_graph(env):
     d1, _, _, i1, c1 = _setup(env, s1, 912)
     sg = _shape(808, 512, 16)
     dg, _, _, ig, cg = _setup(env, sg, 913)
-    Bg = 4600                                              # 128 x 128 tiles
+    Bg = 4600                                              # 64 x 256 tiles of 8 waves
     xs = {n: vqdev.to_device_bytes(workloads.make_x(n, 914)) for n in (1280, 768)}
     Xg = vqdev.to_device_bytes(workloads.make_X(512, Bg, 915))
     rng = np.random.default_rng(916)

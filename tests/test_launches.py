@@ -217,3 +217,46 @@ def test_m_step_workgroups_of_a_group(launches):
                 want.append(groups * (d if groups == most else 1))
     got = launches(calls)
     assert [(st, len(ls), ls[0][1]) for st, ls in got] == [(0, 1, (n, 1, 1)) for n in want]
+
+
+# The kernel of each size of the GPU test of the tiles with k = 256 and fp16 tables (256 CUs): 16 x 16 tiles of so many waves, 32 x 32
+# tiles of so many groups of waves, 32 x 128 tiles, then (32-row steps a wave, columns, wave rows) of the large tiles
+TILE_KERNELS = ["ring", "small 1", "1 256 2", "2 128 1", "2 512 2", "2 512 2", "1 256 2", "1 256 2", "2 256 2", "2 128 1", "2 256 2", "2 256 1",
+                "tiny 16", "tiny 16", "small 2", "small 2", "small 2", "small 1", "ring", "2 512 2 + 2 256 2"]
+
+
+def _kernel_of(name):
+    import re
+    kind, k, rest = re.search(r"(ring_gemm|gemm_tiny|gemm_small|gemm)_kernelILi(\d+)E((?:Li\d+E)*)", name).groups()
+    return " ".join({"ring_gemm": ["ring"], "gemm_tiny": ["tiny"], "gemm_small": ["small"], "gemm": []}[kind] + re.findall(r"Li(\d+)E", rest))
+
+
+def test_tiles_of_the_gpu_test(launches):
+    """What the sizes of test_gpu_gemm_tiles.py are there for."""
+    from test_gpu_gemm_tiles import SIZES
+    got = launches([("gemm", out, inp, *K256, B) for out, inp, B in SIZES])
+    assert [(st, " + ".join(_kernel_of(l[0]) for l in ls)) for st, ls in got] == [(0, t) for t in TILE_KERNELS]
+    assert set(sum((t.split(" + ") for t in TILE_KERNELS), [])) == {"ring", "small 1", "small 2", "tiny 16", "2 128 1", "2 256 1", "1 256 2", "2 256 2", "2 512 2"}
+    wide = [(out, inp, B) for (out, inp, B), t in zip(SIZES, TILE_KERNELS) if "512" in t.split()[1:2]]
+    for fmt in (K64_BN, K256_BN):       # block scales: no 512-column tiles; 16 x 16 tiles of 8 waves
+        for out, inp, B in wide + [(1088, 2304, 16)]:
+            (_, ls), = launches([("gemm", out, inp, *fmt, B)])
+            assert all(_kernel_of(l[0]).split()[:2] != ["2", "512"] and _kernel_of(l[0]) != "tiny 16" for l in ls)
+
+
+# (format, rows, columns, B, kernels): the large tiles on both sides of a round of workgroups; the times are at the rule
+LARGE = [
+    (K256, 4096, 4096, 512, "2 128 1"), (K256, 4160, 4096, 512, "1 256 2"), (K256, 8192, 4096, 256, "2 128 1"), (K256, 8256, 4096, 256, "1 256 2"),
+    (K256, 11008, 4096, 203, "1 256 2"), (K256, 11008, 4096, 400, "2 256 2"), ((16, 1, 8, vq.VQ_I8), 11424, 8192, 350, "2 256 2"),
+    ((8, 2, 32, vq.VQ_I8), 8192, 5120, 1513, "2 512 2"), (K256, 11008, 4096, 2048, "2 512 2 + 2 256 2"), (K64, 16384, 4096, 256, "1 256 2"),
+    (K64, 16416, 4096, 256, "2 256 2"), (K64_BN, 8192, 8192, 1350, "2 256 1"), (K64_BN, 4928, 7424, 787, "2 256 2"), (K64_BN, 8096, 1536, 1131, "2 256 1"),
+    (D4_F16, 13824, 1024, 140, "2 128 1"), (D4_F16, 13824, 2048, 140, "2 128 1"), (D4_F16, 13824, 11008, 140, "1 256 2"), (D4_F16, 4864, 1536, 2197, "2 512 2"),
+]
+
+
+def test_batched_product_takes_the_faster_large_tiles(launches):
+    got = launches([("gemm", out, inp, *fmt, B) for fmt, out, inp, B, _ in LARGE])
+    wrong = [(t, ls) for t, (st, ls) in zip(LARGE, got) if st != 0 or " + ".join(_kernel_of(l[0]) for l in ls) != t[4]]
+    assert wrong == []
+    (_, ls), = launches([("gemm", 4128, 4096, *K256, 256, 1, 128)])     # half the CUs: half the rows
+    assert _kernel_of(ls[0][0]) == "1 256 2"
