@@ -440,16 +440,22 @@ __device__ __forceinline__ h8_t read_x_operand(const char* src) {
 // other, so its L2 has every column of X in use and the indices of a tile row in one XCD only.  Column tile = workgroup %
 // column tiles gave an XCD one column tile of eight, whose rows, a power of two apart, lie in a few of the L2's channels:
 // us before, after: 11008 x 4096, B = 2048 203, 200 (k = 256), 4096 x 11008 210, 199, 8352 x 1280, B = 1082 54.6, 51.9 (k = 64
-// with block scales).
+// with block scales).  With more columns than rows X is the larger operand and each XCD would fetch all of it: there an XCD
+// takes all tile rows of a column tile.  us by rows, by columns: 1024 x 2048, d = 4 fp16, B = 2048 24.4, 21.5; 2368 x 2304, d = 1,
+// k = 8, B = 3358 72.5, 60.8; 1912 x 8960, k = 16, B = 4096 154, 140; 2048 x 11008, B = 2048 118, 128 (k = 16 int8), so not for as
+// many.  900 products: 1.4 % less on average, 3.4 % more at most.
+//   A kernel each: one that takes both orders loses up to 5 % with the first one (64 x 128 tiles, block scales).
+template <bool BY_COLUMNS>
 __device__ __forceinline__ void tile_of_workgroup(int n_tiles_n, int& mt, int& nt) {
   const uint32_t b = blockIdx.x, tiles_m = gridDim.x / (uint32_t)n_tiles_n;
-  const uint32_t run = b / (8u * n_tiles_n), left = tiles_m - 8u * run, r = b - run * 8u * n_tiles_n;
-  const uint32_t rows = left < 8u ? left : 8u;   // of the last run
-  nt = (int)(r / rows);
-  mt = (int)(8u * run + r % rows);
+  const uint32_t inner = BY_COLUMNS ? tiles_m : (uint32_t)n_tiles_n, outer = BY_COLUMNS ? (uint32_t)n_tiles_n : tiles_m;
+  const uint32_t run = b / (8u * inner), left = outer - 8u * run, r = b - run * 8u * inner;
+  const uint32_t lines = left < 8u ? left : 8u;   // of the last run
+  (BY_COLUMNS ? mt : nt) = (int)(r / lines);
+  (BY_COLUMNS ? nt : mt) = (int)(8u * run + r % lines);
 }
 
-template <int K>
+template <int K, bool BY_COLUMNS>
 __global__ __launch_bounds__(256, 2) void ring_gemm_kernel(const uint8_t* __restrict__ idx,
                                                    const uint32_t* __restrict__ cb,
                                                    const uint16_t* __restrict__ X, int B, int ldx,
@@ -472,7 +478,7 @@ __global__ __launch_bounds__(256, 2) void ring_gemm_kernel(const uint8_t* __rest
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wc = wave & 3, wr = wave >> 2;       // column quarter, row half
   int mt, nt;
-  tile_of_workgroup(n_tiles_n, mt, nt);
+  tile_of_workgroup<BY_COLUMNS>(n_tiles_n, mt, nt);
 
   // X staging role: a sub-tile is copied in 4 passes of RPP rows; the thread owns 16 bytes
   // (8 batch columns from n_loc) of row x_row of every pass.  Columns at or beyond B are
@@ -621,7 +627,7 @@ template <int N> __device__ __forceinline__ void wait_loads() {
 // 132, without them and X 74 (decoding W, once per column tile), without them and the decoding 97 (X through L2).  With
 // X staged through registers in sub-tiles of half the size, one barrier per 8 products of a wave: 226; 2336 x 7168, B = 634
 // 58 -> 54; 4096 x 4096, B = 512, d = 4 with fp16 tables 52 -> 41.
-template <int K, int RBW, int NT, int WM = 1>
+template <int K, int RBW, int NT, int WM, bool BY_COLUMNS>
 __global__ __launch_bounds__(256 * WM, WM == 1 ? 2 : 1) void gemm_kernel(const uint8_t* __restrict__ idx,
                                                    const uint32_t* __restrict__ cb,
                                                    const uint16_t* __restrict__ X, int B, int ldx,
@@ -646,7 +652,7 @@ __global__ __launch_bounds__(256 * WM, WM == 1 ? 2 : 1) void gemm_kernel(const u
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wc = wave & 3, wr = wave >> 2;       // column quarter, row half
   int mt, nt;
-  tile_of_workgroup(n_tiles_n, mt, nt);
+  tile_of_workgroup<BY_COLUMNS>(n_tiles_n, mt, nt);
 
   // X staging role: the wave copies PER pieces of 1 KB, RPI rows each.  The lane's 16 bytes lie behind one another in LDS; which
   // 8 columns of the row they are follows from the swizzle (see above), which depends on row & 3.  Columns at or beyond
@@ -1131,14 +1137,19 @@ hipError_t launch_one(const vq_desc& d, const void* idx_dev, const void* cb_dev,
   const int n_rb = d.out_features / kGroupRows, n_cb = d.in_features / kGroupCols;
   if (rb_end < 0) rb_end = n_rb;
   const int tiles_m = (rb_end - rb0 + 4 * RBW * WM - 1) / (4 * RBW * WM), tiles_n = (B + NT - 1) / NT;
-  if constexpr (RBW == 1 && WM == 1)
-    hipLaunchKernelGGL((ring_gemm_kernel<K>), dim3((unsigned)(tiles_m * tiles_n)), dim3(256), 0, s,
-                       (const uint8_t*)idx_dev, (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y,
-                       ldy, y_f32, n_rb, n_cb, tiles_n, blocks_per_group(d), rb0, rb_end);
-  else
-    hipLaunchKernelGGL((gemm_kernel<K, RBW, NT, WM>), dim3((unsigned)(tiles_m * tiles_n)), dim3(256 * WM), 0, s,
-                       (const uint8_t*)idx_dev, (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y,
-                       ldy, y_f32, n_rb, n_cb, tiles_n, blocks_per_group(d), rb0, rb_end);
+#define VQ_GEMM(...)                                                                                                \
+  hipLaunchKernelGGL((__VA_ARGS__), dim3((unsigned)(tiles_m * tiles_n)), dim3(256 * WM), 0, s, (const uint8_t*)idx_dev, \
+                     (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y, ldy, y_f32, n_rb, n_cb, tiles_n,        \
+                     blocks_per_group(d), rb0, rb_end)
+  const bool by_columns = B > d.out_features;
+  if constexpr (RBW == 1 && WM == 1) {
+    if (by_columns) VQ_GEMM(ring_gemm_kernel<K, true>);
+    else VQ_GEMM(ring_gemm_kernel<K, false>);
+  } else {
+    if (by_columns) VQ_GEMM(gemm_kernel<K, RBW, NT, WM, true>);
+    else VQ_GEMM(gemm_kernel<K, RBW, NT, WM, false>);
+  }
+#undef VQ_GEMM
   return hipGetLastError();
 }
 

@@ -15,7 +15,8 @@ FORMATS = {
 # (rows, columns, B); which kernel each takes on 256 CUs is at the test of that without a GPU (test_launches.py)
 SIZES = [(3904, 256, 200), (3904, 1280, 161), (8256, 256, 130), (8256, 768, 66), (25664, 512, 400), (8256, 512, 1090), (11072, 256, 203),
          (8384, 512, 256), (11072, 512, 410), (21568, 256, 384), (11072, 256, 2040), (11072, 768, 1281), (1088, 2304, 16), (64, 8448, 21),
-         (1088, 2048, 161), (1088, 3328, 170), (1088, 5120, 130), (1088, 2304, 161), (4032, 768, 250), (15424, 2048, 1090)]
+         (1088, 2048, 161), (1088, 3328, 170), (1088, 5120, 130), (1088, 2304, 161), (4032, 768, 250), (15424, 2048, 1090),
+         (576, 512, 1793), (576, 768, 4601), (2112, 2048, 10100)]     # more columns than rows
 
 
 @pytest.mark.parametrize("size", SIZES, ids=str)

@@ -222,7 +222,8 @@ def test_m_step_workgroups_of_a_group(launches):
 # The kernel of each size of the GPU test of the tiles with k = 256 and fp16 tables (256 CUs): 16 x 16 tiles of so many waves, 32 x 32
 # tiles of so many groups of waves, 32 x 128 tiles, then (32-row steps a wave, columns, wave rows) of the large tiles
 TILE_KERNELS = ["ring", "small 1", "1 256 2", "2 128 1", "2 512 2", "2 512 2", "1 256 2", "1 256 2", "2 256 2", "2 128 1", "2 256 2", "2 256 1",
-                "tiny 16", "tiny 16", "small 2", "small 2", "small 2", "small 1", "ring", "2 512 2 + 2 256 2"]
+                "tiny 16", "tiny 16", "small 2", "small 2", "small 2", "small 1", "ring", "2 512 2 + 2 256 2",
+                "2 128 1", "1 256 2", "2 512 2 + 2 256 2"]
 
 
 def _kernel_of(name):
@@ -260,3 +261,10 @@ def test_batched_product_takes_the_faster_large_tiles(launches):
     assert wrong == []
     (_, ls), = launches([("gemm", 4128, 4096, *K256, 256, 1, 128)])     # half the CUs: half the rows
     assert _kernel_of(ls[0][0]) == "1 256 2"
+
+
+def test_tiles_of_an_xcd(launches):
+    """With more columns than rows an XCD takes whole column tiles, else whole tile rows."""
+    sizes = [(1024, 512, 1024, 0), (1024, 512, 1025, 1), (576, 768, 4601, 1), (11072, 256, 203, 0), (800, 512, 1000, 1), (15424, 2048, 1090, 0)]
+    got = launches([("gemm", out, inp, *K256, B) for out, inp, B, _ in sizes])
+    assert [f"Lb{by}E" in ls[0][0] for (_, _, _, by), (_, ls) in zip(sizes, got)] == [True] * len(sizes)
