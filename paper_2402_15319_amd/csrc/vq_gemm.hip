@@ -930,11 +930,18 @@ __global__ __launch_bounds__(64 * NW, NW == 16 ? 4 : 2) void gemm_tiny_kernel(co
   }
 }
 
-// Formats that take 16 waves from nine col-blocks on: those whose decoding fits 128 registers.  us with 8, 16: 4096 x 11008,
-// B = 16 k = 16 11.9, 10.6, k = 64 13.5, 12.9, k = 256 13.6, 13.1; 4096 x 4096 6.15, 5.66, 6.90, 6.38, 6.66, 6.40; 2048 x 6144,
-// B = 30 8.9, 7.9, 9.2, 9.0, 8.9, 8.7; 1024 x 2304 4.60, 4.40, 4.98, 4.83, 4.51, 4.53.  The others spill or gain nothing: k = 32 5.07,
+// Formats that take 16 waves from nine col-blocks on: those whose decoding fits 128 registers.  us with 8, 16, calls in a graph:
+// 4096 x 11008, B = 16 k = 16 11.0, 9.9, k = 64 12.2, 11.6, k = 256 12.8, 12.5; 4096 x 4096 5.85, 5.42, 6.35, 5.87, 6.30, 6.00; 2048 x 6144,
+// B = 30 8.3, 7.6, 8.5, 8.4, 8.2, 8.0; 1024 x 2304 4.50, 4.30, 4.82, 4.71, 4.40, 4.38.  The others spill or gain nothing: k = 32 5.07,
 // 5.24 (1024 x 2304), k = 256 with int8 tables 6.74, 7.03 (4096 x 4096), block scales 16.7, 17.4 and 14.4, 17.0 (4096 x 11008).
+//   The 6-bit layouts where nearly every one of the sixteen has two col-blocks, so that loading the second one's X waits for
+// the first one's products: 3072 rows x 24 col-blocks 7.90, 7.62, x 28 8.51, 8.78, x 32 9.70, 10.13, x 33 9.89, 10.13, x 36 10.52, 10.29.
 template <int K> constexpr bool kSixteen = K == 16 || K == 64 || K == 256 || K == kFmtK16I8 || K == kFmtD1K8;
+template <int K> int tiny_waves(int n_cb, bool one_per_cu) {
+  if (!one_per_cu || n_cb <= 4) return 4;
+  if ((K == kFmtK64BN || K == kFmtD1K8BN) && (n_cb == 7 || n_cb == 8)) return 4;
+  return !kSixteen<K> || n_cb <= 8 || ((K == 64 || K == kFmtD1K8) && n_cb > 24 && n_cb < 35) ? 8 : 16;
+}
 
 template <int K>
 hipError_t launch_tiny(const vq_desc& d, const void* idx_dev, const void* cb_dev, const void* X,
@@ -1294,14 +1301,13 @@ hipError_t launch_gemm(const vq_desc& d, const void* idx_dev, const void* cb_dev
   const long long tiles_small = (long long)((n_rb + 3) / 4) * ((B + 31) / 32);
   const long long cus = device_cus();
   const int n_cb = d.in_features / kGroupCols;
-  const bool eight_waves = tiles_tiny <= cus && n_cb > 4;
   const bool small = B <= 32 || tiles_small <= 3 * cus;
   const bool one_round_32x128 = (long long)((n_rb + 7) / 8) * ((B + 127) / 128) <= cus / 2;
 #define VQ_GEMM_DISPATCH(K)                                                                       \
   {                                                                                               \
     if (tiny_pays<K>(tiles_tiny, tiles_small, d, B, cus))                                         \
       return launch_tiny<K>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s,                      \
-                            !eight_waves || ((K == kFmtK64BN || K == kFmtD1K8BN) && (n_cb == 7 || n_cb == 8)) ? 4 : kSixteen<K> && n_cb > 8 ? 16 : 8); \
+                            tiny_waves<K>(n_cb, tiles_tiny <= cus));                              \
     if (small) return launch_small<K>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);           \
     if (one_round_32x128)                                                                         \
       return launch_one<K, 1, 128>(d, idx_dev, cb_dev, X, B, ldx, Y, ldy, y_f32, s);              \

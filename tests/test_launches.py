@@ -268,3 +268,14 @@ def test_tiles_of_an_xcd(launches):
     sizes = [(1024, 512, 1024, 0), (1024, 512, 1025, 1), (576, 768, 4601, 1), (11072, 256, 203, 0), (800, 512, 1000, 1), (15424, 2048, 1090, 0)]
     got = launches([("gemm", out, inp, *K256, B) for out, inp, B, _ in sizes])
     assert [f"Lb{by}E" in ls[0][0] for (_, _, _, by), (_, ls) in zip(sizes, got)] == [True] * len(sizes)
+
+
+def test_waves_of_the_16_x_16_tiles(launches):
+    """16 from nine col-blocks on in the formats that have the registers, but not where the 6-bit layouts would have two
+    col-blocks to nearly every wave; 8 else, and 4 beyond a workgroup per CU or up to four col-blocks."""
+    d1_k8, k16_i8 = (32, 1, 8, vq.VQ_I8), (8, 2, 16, vq.VQ_I8)
+    table = [(K64, 9, 16), (K64, 8, 8), (K64, 24, 16), (K64, 25, 8), (K64, 34, 8), (K64, 35, 16), (K64, 43, 16), (K64, 4, 4), (d1_k8, 32, 8), (d1_k8, 36, 16),
+             (K256, 32, 16), (K16, 32, 16), (k16_i8, 28, 16), (K64_BN, 32, 8), (K64_BN, 8, 4), (K64_BN, 9, 8), (K256_BN, 16, 8), (D4, 16, 8)]
+    got = launches([("gemm", 2048, n_cb * 256, *fmt, 16) for fmt, n_cb, _ in table] + [("gemm", 4160, 2560, *K64, 16)])
+    want = [waves for _, _, waves in table] + [4]
+    assert [_kernel_of(ls[0][0]) for _, ls in got] == [f"tiny {w}" for w in want]
