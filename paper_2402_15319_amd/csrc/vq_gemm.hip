@@ -1126,12 +1126,14 @@ hipError_t launch_small(const vq_desc& d, const void* idx_dev, const void* cb_de
 #define VQ_SMALL(G)                                                                                               \
   hipLaunchKernelGGL((gemm_small_kernel<K, G>), grid, dim3(256 * G), 0, s, (const uint8_t*)idx_dev,               \
                      (const uint32_t*)cb_dev, (const uint16_t*)X, B, ldx, Y, ldy, y_f32, n_rb, n_cb, tiles_n, blocks_per_group(d))
-  // Two groups of waves where a CU has one workgroup, unless the steps, rounded up to four a group, would be a fifth more
-  // in all.  us with one, two: 1768 x 9216, B = 82, k = 16 27.7, 24.7; 2560 x 4096, B = 96, k = 64 16.1, 13.6; 1152 x 5376,
+  // Two groups of waves where a CU has one workgroup, unless the steps, rounded up to four a group, would be more than a fifth
+  // more in all; a tenth with k = 256 fp16 codebooks, where two groups gain least: two against one, 2048 rows,
+  // B = 100, 16, 18, 21, 28, 32, 36, 43 col-blocks 1.01, 1.10, 0.99, 1.06, 0.96, 1.02, 1.00; k = 64 0.90, 0.98, 0.85, 0.92, 0.86, 0.91, 0.88.
+  //  us with one, two: 1768 x 9216, B = 82, k = 16 27.7, 24.7; 2560 x 4096, B = 96, k = 64 16.1, 13.6; 1152 x 5376,
   // B = 200, d = 4 21.6, 19.2; 8192 x 4096, B = 32, k = 256 int8 15.7, 13.8; 2048 x 4096, B = 96, k = 256 14.5, 14.2; nine
   // col-blocks 2048 x 2304, B = 100, k = 32 12.5, 13.8; d = 4 with fp16 tables (80 KB of LDS a group) 24.0, 24.1.
   const int steps1 = (n_cb + 3) / 4, steps2 = ((n_cb + 1) / 2 + 3) / 4;
-  if (K != kFmtD4F16 && tiles_m * tiles_n <= device_cus() && n_cb >= 8 && 10 * steps2 <= 6 * steps1) VQ_SMALL(2);
+  if (K != kFmtD4F16 && tiles_m * tiles_n <= device_cus() && n_cb >= 8 && 20 * steps2 <= (K == 256 ? 11 : 12) * steps1) VQ_SMALL(2);
   else VQ_SMALL(1);
 #undef VQ_SMALL
   return hipGetLastError();

@@ -222,7 +222,7 @@ def test_m_step_workgroups_of_a_group(launches):
 # The kernel of each size of the GPU test of the tiles with k = 256 and fp16 tables (256 CUs): 16 x 16 tiles of so many waves, 32 x 32
 # tiles of so many groups of waves, 32 x 128 tiles, then (32-row steps a wave, columns, wave rows) of the large tiles
 TILE_KERNELS = ["ring", "small 1", "1 256 2", "2 128 1", "2 512 2", "2 512 2", "1 256 2", "1 256 2", "2 256 2", "2 128 1", "2 256 2", "2 256 1",
-                "tiny 16", "tiny 16", "small 2", "small 2", "small 2", "small 1", "ring", "2 512 2 + 2 256 2",
+                "tiny 16", "tiny 16", "small 2", "small 2", "small 1", "small 1", "ring", "2 512 2 + 2 256 2",
                 "2 128 1", "1 256 2", "2 512 2 + 2 256 2"]
 
 
@@ -279,3 +279,11 @@ def test_waves_of_the_16_x_16_tiles(launches):
     got = launches([("gemm", 2048, n_cb * 256, *fmt, 16) for fmt, n_cb, _ in table] + [("gemm", 4160, 2560, *K64, 16)])
     want = [waves for _, _, waves in table] + [4]
     assert [_kernel_of(ls[0][0]) for _, ls in got] == [f"tiny {w}" for w in want]
+
+
+def test_groups_of_waves_of_the_32_x_32_tiles(launches):
+    """Two where a CU has one workgroup and the steps rounded up to four a group are at most a fifth more (a tenth: k = 256)."""
+    table = [(K64, 8, 2), (K64, 9, 1), (K64, 12, 1), (K64, 13, 2), (K64, 17, 2), (K64, 28, 2), (K64, 7, 1), (K256, 8, 2), (K256, 9, 1), (K256, 16, 2),
+             (K256, 17, 1), (K256, 20, 1), (K256, 21, 2), (K256, 28, 1), (K256, 32, 2), (K256, 36, 1), (K256, 43, 2), (D4_F16, 16, 1)]
+    got = launches([("gemm", 2048, n_cb * 256, *fmt, 100) for fmt, n_cb, _ in table] + [("gemm", 2048, 4096, *K64, 130)])
+    assert [_kernel_of(ls[0][0]) for _, ls in got] == [f"small {g}" for _, _, g in table] + ["small 1"]
