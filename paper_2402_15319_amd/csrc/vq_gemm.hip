@@ -609,10 +609,10 @@ __global__ __launch_bounds__(256, 2) void ring_gemm_kernel(const uint8_t* __rest
 }
 
 // One instruction: 64 lanes x 16 bytes of X (base + voff, voff per lane) into 1 KB of LDS from byte address lds on.  No
-// register takes the data; the wave's vmcnt counts it.  The compiler neither counts these loads (its own waits are then
-// stricter than it knows) nor uses m0 in these kernels.
+// register takes the data; the wave's vmcnt counts it.  The compiler does not count these loads: its own waits are then
+// stricter than it knows.
 __device__ __forceinline__ void x_to_lds(const char* base, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(voff), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(voff), "s"(base) : "memory", "m0");
 }
 
 // Until no more than N of the wave's loads are on their way (those of x_to_lds among them).

@@ -256,3 +256,21 @@ def test_whole_codebook_is_read_a_centroid_at_a_time(device_asm):
             assert not any(t.startswith("ds_read_b32") for t in l) and sum(t.startswith("ds_read") for t in l) <= 8, name
             assert sum(t.startswith("v_mov_b32") for t in l) <= 8, name
     assert seen == 2 + 2 + 2          # d = 4; d = 2 with groups of 8 rows, and with others
+
+
+def test_only_the_loads_into_lds_use_m0(device_asm):
+    """A load into LDS takes its address from m0, which the asm statement that makes it sets first and tells the compiler about;
+    nothing else in the batched kernels reads or writes the register, and no statement is split."""
+    text = open(os.path.join(vqbuild.CSRC, "vq_gemm.hip")).read()
+    setters = re.findall(r'asm volatile\("s_mov_b32 m0,[^;]*;', text)
+    assert len(setters) == 1 and re.search(r':\s*"memory", "m0"\)', setters[0])
+    loads = 0
+    for name, lines in device_asm("vq_gemm.hip").items():
+        code = [l for l in lines if l and not l.startswith(".") and not l.endswith(":")]
+        for i, l in enumerate(code):
+            if re.search(r"\bm0\b", l):
+                assert re.fullmatch(r"s_mov_b32 m0, s\d+", l) and code[i + 1] == "s_nop 0" and code[i + 2].startswith("global_load_lds_dwordx4"), (name, code[i:i + 3])
+            if l.startswith("global_load_lds"):
+                loads += 1
+                assert code[i - 2].startswith("s_mov_b32 m0, "), (name, code[i - 2:i + 1])
+    assert loads > 1000
