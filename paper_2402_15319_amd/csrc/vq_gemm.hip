@@ -12,7 +12,7 @@
 //   * X is batch-contiguous, while an MFMA operand wants 8 consecutive k per lane.
 //     gemm_kernel has X sub-tiles loaded into LDS as they are (16 bytes a lane, no registers in between, two
 //     sub-tiles ahead) and forms the operand with the transposing LDS read ds_read_b64_tr_b16; the col-block is
-//     consumed in 2 to 8 sub-steps (one barrier each), wave w owns a quarter of
+//     consumed in 4 or 8 sub-steps (one barrier each), wave w owns a quarter of
 //     the batch columns and 32*RBW rows (RBW x NT/128 accumulator tiles); with WM = 2 the
 //     workgroup has 8 waves and twice the rows, the second four waves taking the lower half;
 //   * ring_gemm_kernel (32 x 128 tiles) stages X through registers, four sub-tiles ahead;
@@ -407,18 +407,18 @@ struct XRows {
 };
 
 // Rows row0 + j * RPP (j = 0..3) are wave-uniform; voff is the lane's part in bytes.
-template <int RPP, int PASSES = 4>
+template <int RPP>
 __device__ __forceinline__ void load_xrows(XRows& p, const uint16_t* X, long long row0, int ldx,
                                            uint32_t voff) {
   const char* base = reinterpret_cast<const char*>(X) + (size_t)row0 * ldx * 2;
 #pragma unroll
-  for (int j = 0; j < PASSES; ++j)
+  for (int j = 0; j < 4; ++j)
     p.r[j] = *reinterpret_cast<const u32x4_t*>(base + (size_t)j * RPP * ldx * 2 + voff);
 }
-template <int RPP, int NT, int PASSES = 4>
+template <int RPP, int NT>
 __device__ __forceinline__ void store_xrows(const XRows& p, char* dst) {
 #pragma unroll
-  for (int j = 0; j < PASSES; ++j) *reinterpret_cast<u32x4_t*>(dst + j * RPP * NT * 2) = p.r[j];
+  for (int j = 0; j < 4; ++j) *reinterpret_cast<u32x4_t*>(dst + j * RPP * NT * 2) = p.r[j];
 }
 // 8 consecutive k of the lane's column from two 4-row tiles at lo and hi.
 __device__ __forceinline__ h8_t read_x_operand2(const char* lo_src, const char* hi_src) {
@@ -455,6 +455,7 @@ __device__ __forceinline__ void tile_of_workgroup(int n_tiles_n, int& mt, int& n
   (BY_COLUMNS ? nt : mt) = (int)(8u * run + r % lines);
 }
 
+// 32 x 128 tiles: wave w decodes row-block w of the four and multiplies all of them with batch columns 32 w .. 32 w + 31.
 template <int K, bool BY_COLUMNS>
 __global__ __launch_bounds__(256, 2) void ring_gemm_kernel(const uint8_t* __restrict__ idx,
                                                    const uint32_t* __restrict__ cb,
@@ -463,12 +464,10 @@ __global__ __launch_bounds__(256, 2) void ring_gemm_kernel(const uint8_t* __rest
                                                    int n_rb, int n_cb, int n_tiles_n, int rpc,
                                                    int rb0, int rb_end) {
   // the launch covers row-blocks [rb0, rb_end) of the matrix's n_rb; tile rows count from rb0
-  constexpr int RBW = 1, NT = 128, WM = 1;
-  constexpr int MT = 32 * RBW * WM;
-  constexpr int KS = 8192 / NT;                  // k per X sub-tile: 64 or 32
-  constexpr int NSUB = 256 / KS;                 // sub-steps per col-block: 4 or 8
-  constexpr int NB = NT / 128;                   // 32-column accumulator tiles per wave
-  constexpr int D = NT == 512 ? 2 : 4;           // X pieces in flight per thread (sub-tiles ahead; registers are short at 512 columns)
+  constexpr int MT = 32, NT = 128;
+  constexpr int KS = 64;                         // k per X sub-tile
+  constexpr int NSUB = 256 / KS;                 // sub-steps per col-block
+  constexpr int D = 4;                           // X pieces in flight per thread (sub-tiles ahead)
   static_assert(NSUB % D == 0, "ring slot must be a compile-time constant");
   __shared__ __attribute__((aligned(16))) uint16_t Wt[MT * WS];
   __shared__ __attribute__((aligned(16))) uint32_t Xs_all[2][4096];     // [KS][NT] halfs each
@@ -476,15 +475,16 @@ __global__ __launch_bounds__(256, 2) void ring_gemm_kernel(const uint8_t* __rest
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wc = wave & 3, wr = wave >> 2;       // column quarter, row half
+  // 0 and the wave, which the compiler does not know: with constants it schedules the reads of W for another 3 to 4 %
+  // (4096 x 4096, B = 256 k = 64 24.5 -> 25.5 us, k = 32 24.6 -> 25.6)
+  const int wr = wave >> 2, wc = wave & 3;
   int mt, nt;
   tile_of_workgroup<BY_COLUMNS>(n_tiles_n, mt, nt);
 
   // X staging role: a sub-tile is copied in 4 passes of RPP rows; the thread owns 16 bytes
   // (8 batch columns from n_loc) of row x_row of every pass.  Columns at or beyond B are
   // loaded from column 0 instead: they only reach accumulator columns that are never written.
-  constexpr int RPP = 2048 * WM / NT;            // rows per pass
-  constexpr int PASSES = 4 / WM;
+  constexpr int RPP = 2048 / NT;                 // rows per pass
   const int x_row = tid / (NT / 8);
   const int n_loc = (tid % (NT / 8)) * 8;
   const int n_glob = nt * NT + n_loc;
@@ -493,47 +493,30 @@ __global__ __launch_bounds__(256, 2) void ring_gemm_kernel(const uint8_t* __rest
   uint32_t x_voff = (uint32_t)(((x_row - x_row_wave) * ldx + (n_glob < B ? n_glob : 0)) * 2);
   asm volatile("" : "+v"(x_voff));   // keep it one 32-bit register next to scalar row bases
   // operand role: lane i of a 16-lane block addresses row i / 4, fragment i % 4 of a 4 x 16 tile
-  int xr_off[NB];
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const int kq = (lane & 15) >> 2;
-    const int chunk = ((wc * NB + b) * 32 + (lane & 16)) >> 4;
-    xr_off[b] = (8 * (lane >> 5) + kq) * NT * 2 + ((chunk ^ (2 * kq)) << 5) + (lane & 3) * 8;
-  }
+  const int kq = (lane & 15) >> 2;
+  const int chunk = (wc * 32 + (lane & 16)) >> 4;
+  const int xr_off = (8 * (lane >> 5) + kq) * NT * 2 + ((chunk ^ (2 * kq)) << 5) + (lane & 3) * 8;
   const int n_subtiles = n_cb * NSUB;
 
-  f16v_t acc[RBW][NB];
+  f16v_t acc;
 #pragma unroll
-  for (int a = 0; a < RBW; ++a)
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 
   // prologue: registers for col-block 0, X sub-tile 0 into buffer 0, sub-tiles 1..D in flight
-  GroupRegs<K> g[RBW];
-  long long rbs[RBW];
-  bool rb_ok[RBW];
-  // Rows of groups.  Divided once for the 32 x 128 tile, where a col-block is short (4096 x 4096, B = 256 26.0 ->
-  // 24.4 us with 6-bit indices); the larger tiles hide the scalar division and are no faster without it
-  // (11008 x 4096, B = 203, k = 256: 48.2 us dividing per col-block, 48.9 once).
-  int grows[RBW];
-  auto grow_of = [&](int a) { return RBW == 1 ? (long long)grows[a] : (rb_ok[a] ? rbs[a] : 0) / rpc; };
-#pragma unroll
-  for (int a = 0; a < RBW; ++a) {
-    rbs[a] = rb0 + (long long)mt * (4 * RBW * WM) + wave * RBW + a;
-    rb_ok[a] = rbs[a] < rb_end;
-    grows[a] = rb_ok[a] ? (int)rbs[a] / rpc : 0;
-    load_group<K>(g[a], idx, cb, rb_ok[a] ? rbs[a] : 0, 0, n_cb, lane, n_rb, grow_of(a), n_rb / rpc);
-  }
+  GroupRegs<K> g;
+  const long long rb = rb0 + (long long)mt * 4 + wave;
+  const bool rb_ok = rb < rb_end;
+  // its row of groups, divided once: a col-block is short here (4096 x 4096, B = 256 26.0 -> 24.4 us with 6-bit indices)
+  const long long grow = rb_ok ? (int)rb / rpc : 0;
+  load_group<K>(g, idx, cb, rb_ok ? rb : 0, 0, n_cb, lane, n_rb, grow, n_rb / rpc);
   XRows ring[D];   // slot t % D holds sub-tile t + 1 when sub-step t starts
   {
     XRows first;
-    load_xrows<RPP, PASSES>(first, X, x_row_wave, ldx, x_voff);
+    load_xrows<RPP>(first, X, x_row_wave, ldx, x_voff);
 #pragma unroll
     for (int i = 0; i < D; ++i)
-      load_xrows<RPP, PASSES>(ring[i], X, (long long)min(i + 1, n_subtiles - 1) * KS + x_row_wave, ldx, x_voff);
-    store_xrows<RPP, NT, PASSES>(first, reinterpret_cast<char*>(Xs_all[0]) + xs_off);
+      load_xrows<RPP>(ring[i], X, (long long)min(i + 1, n_subtiles - 1) * KS + x_row_wave, ldx, x_voff);
+    store_xrows<RPP, NT>(first, reinterpret_cast<char*>(Xs_all[0]) + xs_off);
   }
   int cur = 0;   // X buffer the next MFMA step reads
 
@@ -541,20 +524,16 @@ __global__ __launch_bounds__(256, 2) void ring_gemm_kernel(const uint8_t* __rest
     // every wave is past its MFMA reads of Wt (barrier at the end of the last sub-step); the
     // tables live in the X buffer that is idle while a col-block is being decoded
     uint32_t* lut = Xs_all[1 - cur] + wave * lut_dwords<K>();
-    static_assert(4 * WM * lut_dwords<K>() <= 4096, "the waves' tables must fit in one X buffer");
+    static_assert(4 * lut_dwords<K>() <= 4096, "the waves' tables must fit in one X buffer");
+    if (rb_ok) {
+      decode_group<K>(g, lut, Wt, wave * 8, lane);
+    } else {
 #pragma unroll
-    for (int a = 0; a < RBW; ++a) {
-      const int m0 = (wave * RBW + a) * 8;
-      if (rb_ok[a]) {
-        decode_group<K>(g[a], lut, Wt, m0, lane);
-      } else {
-#pragma unroll
-        for (int r = 0; r < 8; ++r)
-          *reinterpret_cast<uint2*>(Wt + wt_half_index(m0 + r, 4 * lane)) = make_uint2(0u, 0u);
-      }
-      // next col-block's registers (clamped on the last one: a harmless re-read)
-      load_group<K>(g[a], idx, cb, rb_ok[a] ? rbs[a] : 0, min(c + 1, n_cb - 1), n_cb, lane, n_rb, grow_of(a), n_rb / rpc);
+      for (int r = 0; r < 8; ++r)
+        *reinterpret_cast<uint2*>(Wt + wt_half_index(wave * 8 + r, 4 * lane)) = make_uint2(0u, 0u);
     }
+    // next col-block's registers (clamped on the last one: a harmless re-read)
+    load_group<K>(g, idx, cb, rb_ok ? rb : 0, min(c + 1, n_cb - 1), n_cb, lane, n_rb, grow, n_rb / rpc);
     __syncthreads();   // Wt of this col-block and the X sub-tile in Xs[cur] are complete
 
 #pragma unroll
@@ -565,23 +544,14 @@ __global__ __launch_bounds__(256, 2) void ring_gemm_kernel(const uint8_t* __rest
       // loading sub-tile t + 1 + D into the slot it leaves
       const int t = c * NSUB + sub;
       XRows& slot = ring[sub % D];
-      store_xrows<RPP, NT, PASSES>(slot, reinterpret_cast<char*>(Xs_all[cur ^ 1]) + xs_off);
-      load_xrows<RPP, PASSES>(slot, X, (long long)min(t + 1 + D, n_subtiles - 1) * KS + x_row_wave, ldx, x_voff);
-      // wave w: batch columns [32*NB*w, 32*NB*(w+1)), all MT rows, the KS k of this sub-step
+      store_xrows<RPP, NT>(slot, reinterpret_cast<char*>(Xs_all[cur ^ 1]) + xs_off);
+      load_xrows<RPP>(slot, X, (long long)min(t + 1 + D, n_subtiles - 1) * KS + x_row_wave, ldx, x_voff);
+      // all 32 rows x the wave's 32 batch columns, the KS k of this sub-step
 #pragma unroll
       for (int kk = 0; kk < KS / 16; ++kk) {
-        h8_t bv[NB];
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-          bv[b] = read_x_operand<NT>(Xs + xr_off[b] + 16 * kk * NT * 2);
-#pragma unroll
-        for (int a = 0; a < RBW; ++a) {
-          const h8_t av = *reinterpret_cast<const h8_t*>(
-              Wt + wt_half_index(wr * 32 * RBW + 32 * a + (lane & 31), sub * KS + 16 * kk + 8 * (lane >> 5)));
-#pragma unroll
-          for (int b = 0; b < NB; ++b)
-            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, bv[b], acc[a][b], 0, 0, 0);
-        }
+        const h8_t bv = read_x_operand<NT>(Xs + xr_off + 16 * kk * NT * 2);
+        const h8_t av = *reinterpret_cast<const h8_t*>(Wt + wt_half_index(wr * 32 + (lane & 31), sub * KS + 16 * kk + 8 * (lane >> 5)));
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, bv, acc, 0, 0, 0);
       }
       __syncthreads();   // reads of Xs[cur] (and, on the last sub-step, of Wt) done; Xs[cur^1] complete
       cur ^= 1;
@@ -589,21 +559,16 @@ __global__ __launch_bounds__(256, 2) void ring_gemm_kernel(const uint8_t* __rest
   }
 
   // ---- store: accumulator register i holds row 8*(i/4) + 4*(lane/32) + i%4, column lane%32
+  const int n = nt * NT + wc * 32 + (lane & 31);
+  if (n < B) {
 #pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const int n = nt * NT + (wc * NB + b) * 32 + (lane & 31);
-    if (n < B) {
-#pragma unroll
-      for (int a = 0; a < RBW; ++a)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int row = rb0 * 8 + mt * MT + wr * 32 * RBW + 32 * a + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-          if (row < rb_end * 8) {
-            const size_t o = (size_t)row * ldy + n;
-            if (y_f32) reinterpret_cast<float*>(Y)[o] = acc[a][b][i];
-            else reinterpret_cast<_Float16*>(Y)[o] = (_Float16)acc[a][b][i];
-          }
-        }
+    for (int i = 0; i < 16; ++i) {
+      const int row = rb0 * 8 + mt * MT + wr * 32 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
+      if (row < rb_end * 8) {
+        const size_t o = (size_t)row * ldy + n;
+        if (y_f32) reinterpret_cast<float*>(Y)[o] = acc[i];
+        else reinterpret_cast<_Float16*>(Y)[o] = (_Float16)acc[i];
+      }
     }
   }
 }
