@@ -363,7 +363,7 @@ struct GemvItem {
   int n_rb, n_cb, wg_begin, splits_log2, cb_log2, y_f32;
 };
 __device__ __forceinline__ int log2_dev(int v) { return v > 1 ? 31 - __builtin_clz((uint32_t)v) : 0; }
-template <int CAP> __device__ __forceinline__ GemvItem item_of(const GemvBatchT<CAP>& b, int pi) {
+__device__ __forceinline__ GemvItem item_of(const GemvBatch& b, int pi) {
   const GemvProblem& q = b.p[pi];
   return {q.idx, q.cb, q.x, q.y, q.n_rb, q.n_cb, q.wg_begin, log2_dev(q.splits), log2_dev(q.rb_per_cb), b.y_f32};
 }
@@ -459,13 +459,13 @@ __device__ __forceinline__ void store_rows(void* y, int y_f32, int rb, int lane,
 // issued together with the loads of the row-block's last chunk) and t[8j .. 8j+7] (t = A x, fp32,
 // loaded once per problem); lanes with 8j >= rank hold zeros.  Eight fp32 multiply-adds, then
 // the same three lane exchanges that end wave_reduce8.
-template <bool LORA, int CAP = kMaxProblemsPerLaunch> struct BatchOf { using type = GemvBatchT<CAP>; };
-template <int CAP> struct BatchOf<true, CAP> { using type = GemvBatchLoraT<CAP>; };
+template <bool LORA, int CAP = kMaxProblemsPerLaunch> struct BatchOf { using type = GemvBatch; };
+template <> struct BatchOf<true, kMaxProblemsPerLaunch> { using type = GemvBatchLora; };
 template <> struct BatchOf<false, 1> { using type = GemvOne; };
 template <> struct BatchOf<false, kFewProblems> { using type = GemvFew; };
 template <> struct BatchOf<true, kFewProblems> { using type = GemvFewLora; };
-template <int CAP> __device__ __forceinline__ const GemvBatchT<CAP>& base_of(const GemvBatchT<CAP>& b) { return b; }
-template <int CAP> __device__ __forceinline__ const GemvBatchT<CAP>& base_of(const GemvBatchLoraT<CAP>& b) { return b.base; }
+__device__ __forceinline__ const GemvBatch& base_of(const GemvBatch& b) { return b; }
+__device__ __forceinline__ const GemvBatch& base_of(const GemvBatchLora& b) { return b.base; }
 template <int CAP> __device__ __forceinline__ const GemvLines<CAP>& base_of(const GemvLines<CAP>& b) { return b; }
 __device__ __forceinline__ const GemvFew& base_of(const GemvFewLora& b) { return b.base; }
 
@@ -499,8 +499,7 @@ __device__ __forceinline__ float lora_term(uint4 lb, const float (&tv)[8]) {
 }
 
 // Which problem does work item `item` belong to (wg_begin is ascending, p[0].wg_begin = 0).
-template <int CAP>
-__device__ __forceinline__ int find_problem(const GemvBatchT<CAP>& batch, int item) {
+__device__ __forceinline__ int find_problem(const GemvBatch& batch, int item) {
   int lo = 0, hi = batch.count;
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;

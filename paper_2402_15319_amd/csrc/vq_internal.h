@@ -79,16 +79,14 @@ struct GemvProblem {
 // The kernel argument of a launch of many products (the host fills it for every launch; those of up to kFewProblems
 // products get a narrow one below, 256 or 64 instead of 14,352 bytes for the runtime to copy, about 1 us of a call's
 // host time: a decoder layer's launches hold one to three products).
-template <int CAP>
-struct GemvBatchT {
+struct GemvBatch {
   int32_t count;
   int32_t y_f32;
   int32_t total_wgs;    // work items in the launch
   int32_t total_cost;   // groups in the launch
-  GemvProblem p[CAP];
+  GemvProblem p[kMaxProblemsPerLaunch];
 };
 constexpr int kFewProblems = 4;
-using GemvBatch = GemvBatchT<kMaxProblemsPerLaunch>;
 
 // The narrow argument.  What a wave needs of its product is one 64-byte line, fetched by one scalar load whose address
 // the workgroup number gives, and holds shift counts where the wide table holds divisors: nothing is loaded from memory
@@ -129,16 +127,15 @@ struct LoraProblem {
 constexpr int kMaxLoraRank = 64;
 constexpr int kLoraWorkspaceFloats = kMaxLoraRank;   // fp32 slots of workspace per problem
 
-template <int CAP>
-struct GemvBatchLoraT {
-  GemvBatchT<CAP> base;
-  LoraProblem l[CAP];
+struct GemvBatchLora {
+  GemvBatch base;
+  LoraProblem l[kMaxProblemsPerLaunch];
 };
-using GemvBatchLora = GemvBatchLoraT<kMaxProblemsPerLaunch>;
 struct GemvFewLora {
   GemvFew base;
   LoraProblem l[kFewProblems];
 };
+static_assert(sizeof(GemvFewLora) == 352, "what the runtime copies");
 
 // t = A x of every problem of a launch: one wave per row of A.
 struct LoraDownProblem {
@@ -148,13 +145,11 @@ struct LoraDownProblem {
   int32_t in_features;
   int32_t row_begin;    // rows of A of all earlier problems of the launch
 };
-template <int CAP>
-struct LoraDownBatchT {
+struct LoraDownBatch {
   int32_t count;
   int32_t total_rows;
-  LoraDownProblem p[CAP];
+  LoraDownProblem p[kMaxProblemsPerLaunch];
 };
-using LoraDownBatch = LoraDownBatchT<kMaxProblemsPerLaunch>;
 // The narrow form: a grid row per product, row_begin holding the product's number of rows.
 struct LoraDownFew {
   LoraDownProblem p[kFewProblems];
