@@ -549,18 +549,21 @@ __device__ __forceinline__ void em_assign_filtered(const float* __restrict__ W, 
 
 // Which codebooks take the filter; us at 4096 x 4096, loop over the centroids against filter (11008 x 4096 behind):
 //                               d = 2, k = 64, 8 rows  d = 2, k = 256, 8 rows   d = 4, k = 256, 256 rows  d = 4, k = 64, 16 rows
-//   distinct centroids                    90, 50             340, 110 (870, 286)      314, 69 (800, 178)       85, 37
+//   distinct centroids                    88, 50             340, 107 (870, 286)      314, 67 (800, 178)       85, 38
 //   vectors of the group, drawn with replacement (11, 1.5, 3 % of the centroids repeated, d = 2 with 8 rows most)
-//                                         89, 52             342, 117 (875, 325)      314, 74 (796, 185)       85, 39
+//                                         88, 52             342, 116 (875, 305)      314, 69 (796, 185)       85, 40
 //   half of W and a quarter of the centroids zero
 //                                         86, 49             332, 110                 308, 72 (786, 186)       82, 37
 //   every centroid twice                  89, 57             340, 117 (-, 300)        310, 79 (794, 194)       85, 45
-//   W far from zero: no vector is decided 88, 110            338, 339 (-, 898)        309, 330 (794, 847)      85, 100
+//   W far from zero: not tried            88, 89             338, 292                 309, 275                 85, 86
 //   zero, negative or very uneven weights in every set of 32 vectors: no filter
-//                                         89, 91             338, 304                 309, 305 (794, 795)      85, 88
-// Not for d = 2, k = 32 and d = 1 (scalars lie too close for the filter).  Against the kernel that this replaces (a wave
-// to 8 rows, the features of all centroids in its registers, equal centroids undecided): d = 4, k = 256, 256 rows
-// 11008 x 4096 223 -> 178; d = 2, k = 256, 8 rows with centroids drawn from the vectors 267 -> 117, 512 x 512 81 -> 13.
+//                                         88, 89             338, 289                 309, 279                 85, 86
+//   rows 4 to 7 of every 8 far from zero: found out by the filter
+//                                         86, 111              -, 333                   -, 352                   -, 106
+// Not for d = 2, k = 32 and d = 1 (scalars lie too close for the filter).  Against a wave to 8 rows alone, the features of all
+// centroids in its registers and equal centroids undecided: d = 4, k = 256, 256 rows 11008 x 4096 223 -> 178; d = 2, k = 256, 8 rows with
+// centroids drawn from the vectors 267 -> 116, 512 x 512 81 -> 10; d = 4 in groups of 8 rows, whose waves have four, 74 -> 82 and 24 -> 26
+// (2048 x 2048, far from zero, k = 256 and 64).
 template <int K, int D> constexpr bool em_filtered() { return (D == 2 || D == 4) && K >= 64; }
 template <int K, int D> constexpr int em_waves() { return em_filtered<K, D>() ? (D == 4 && K == 256 ? 3 : 4) : 1; }   // per SIMD
 
