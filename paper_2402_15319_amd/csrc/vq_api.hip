@@ -4,6 +4,7 @@
 // workgroups of the streaming kernel, the address of the static adapter scratch).
 #include <stddef.h>
 #include <string.h>
+#include <algorithm>
 #include <atomic>
 #include "vq_internal.h"
 
@@ -147,6 +148,18 @@ int static_scratch(float** out) {
   return VQ_OK;
 }
 
+// The order in which a launch of wide-group products hands out its work: the widest products first.  Workgroups start in
+// order and take as long as their product is wide, so a wide one at the end keeps a few CUs busy after the others.
+void widest_first(const vq_desc* descs, int n, uint16_t* order) {
+  bool sorted = true;
+  for (int i = 0; i < n; ++i) {
+    order[i] = (uint16_t)i;
+    sorted = sorted && (i == 0 || descs[i].in_features <= descs[i - 1].in_features);
+  }
+  if (!sorted)
+    std::stable_sort(order, order + n, [&](uint16_t a, uint16_t b) { return descs[a].in_features > descs[b].in_features; });
+}
+
 // The body of vq_gemv_multi and of its variants with a low-rank adapter (lora != NULL: t_ws is
 // device memory for kLoraWorkspaceFloats floats per problem, t = A x of problem i at slot i).
 int gemv_multi_impl(int count, const vq_desc* descs, const void* const* idx_dev,
@@ -209,31 +222,26 @@ int gemv_multi_impl(int count, const vq_desc* descs, const void* const* idx_dev,
       GemvBatchLora both;                       // 20 KB on the stack; only the used entries are filled
       GemvBatch& batch = both.base;
       memset(&batch, 0, offsetof(GemvBatch, p) + (size_t)n * sizeof(GemvProblem));
-      if (lora) {
-        for (int i = 0; i < n; ++i) {
-          LoraProblem& lp = both.l[i];
-          lp.B = (const uint16_t*)lora[first + i].B_f16;
-          lp.t = t_ws + (size_t)(first + i) * kLoraWorkspaceFloats;
-          lp.rank = lora[first + i].rank;
-          lp.pad = 0;
-        }
-      }
       batch.count = n;
       batch.y_f32 = (y_dtype == VQ_F32);
+      uint16_t order[kMaxProblemsPerLaunch];
+      widest_first(descs + first, n, order);
       long long wgs = 0;
       for (int i = 0; i < n; ++i) {
-        const vq_desc& d = descs[first + i];
+        const int at = first + order[i];
+        const vq_desc& d = descs[at];
         GemvProblem& p = batch.p[i];
-        p.idx = (const uint8_t*)idx_dev[first + i];
-        p.cb = (const uint32_t*)cb_dev[first + i];
-        p.x = (const uint16_t*)x_f16[first + i];
-        p.y = y[first + i];
+        p.idx = (const uint8_t*)idx_dev[at];
+        p.cb = (const uint32_t*)cb_dev[at];
+        p.x = (const uint16_t*)x_f16[at];
+        p.y = y[at];
         p.n_rb = d.out_features / kGroupRows;
         p.n_cb = d.in_features / kGroupCols;
         p.splits = 1;
         p.rb_per_cb = d.group_rows / kGroupRows;
         p.wg_begin = (int32_t)wgs;
         wgs += p.n_rb / 8;
+        if (lora) both.l[i] = {(const uint16_t*)lora[at].B_f16, t_ws + (size_t)at * kLoraWorkspaceFloats, lora[at].rank, 0};
       }
       if (wgs > 0x7fffffffll) return VQ_ERR_UNSUPPORTED;
       batch.total_wgs = (int32_t)wgs;

@@ -18,10 +18,27 @@
 // KS groups of 8 / KS waves split the col-block pairs between them, each with tables of its own; the partial
 // sums meet in LDS in a fixed order.  A 4096-row matrix is 64 items, a quarter of the CUs (rule and figures:
 // wide_splits below).
+//
+// What bounds it: the LDS, whose random 8-byte lookups of uniform indices take 7.4 clocks a wave (2.9 without
+// conflicts).  8 decoder layers in one launch (433 MB, d = 4): 119 -> 98 us, k = 256 int8 113 -> 91 us for 4 layers.
+// What that took: the widest products first (widest_first in vq_api.hip; CUs stood idle for a fifth of the launch, 108.9),
+// and two steps to a loop turn, whose loads are all unconditional and whose table buffers are constants: with a branch
+// around one load, or the next step's registers copied, the compiler waited for the new loads of a step before it used
+// the old ones (100), and half of the address instructions of the lookups go (98).  Not faster: a table of the 256 x 64
+// products c.x (conflict-free lookups of 3.0 clocks, but 3.2 more to write the table for 256 rows), 16 or 32 copies of
+// the table (5.0 + 1.6 and 3.1 + 3.2), 4-byte lookups of the int8 entries (7.0).
+#include <type_traits>
 #include "vq_gemv_impl.h"
 
 namespace vq {
 namespace {
+
+// The 64-row item of a workgroup of an unsplit launch.  Workgroups go to the eight XCDs in turn; the four items of a 256-row
+// group read the same tables, so each aligned 32 workgroups put four neighbouring items on one XCD, whose L2 then serves
+// three of the four reads.
+__device__ __forceinline__ int item_of_workgroup(int b, int total) {
+  return (b | 31) < total ? (b & ~31) | (b & 7) << 2 | ((b >> 3) & 3) : b;
+}
 
 template <int KS>
 struct D4Step {
@@ -38,7 +55,7 @@ struct D4Step {
 // normalization"): the group's 16 block-scale levels sit next to its table in LDS, and per row
 // the looked-up vector is multiplied by the scale of the lane's 32-weight block before the dot2.
 template <bool LORA, int MODE, int CAP, int KS>
-__global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LORA, CAP>::type arg) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MODE != 2 && (KS == 1 || (KS == 4 && MODE == 0)) ? 8 : 1))) void gemv_d4_kernel(const typename BatchOf<LORA, CAP>::type arg) {
   constexpr bool F16 = MODE == 1, BN = MODE == 2;
   const auto& batch = base_of(arg);
   constexpr int RBW = 8 / KS, THREADS = 512 / KS;   // row-blocks of a workgroup; threads that share tables
@@ -47,7 +64,7 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int item = (int)blockIdx.x / KS;
+  const int item = KS == 1 ? item_of_workgroup((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x / KS;
   const int pi = find_problem(batch, item);
   const GemvItem P = item_of(batch, pi);
   const int oct = item - P.wg_begin;                // which 64 rows
@@ -63,33 +80,30 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
   const uint16_t* levels = reinterpret_cast<const uint16_t*>(tab + wide_bn_level_offset((size_t)n_groups, 1024));
   const uint8_t* codes_lane = tab + wide_bn_code_offset((size_t)n_groups, 1024) + (size_t)rb * n_pairs * 64 + (lane >> 3) * 8;
   (void)levels; (void)codes_lane;
-  const uint8_t* idx_lane = P.idx + (size_t)rb * n_pairs * 1024 + lane * 16;
-  const uint16_t* x_lane = P.x + lane * 4;
-  const int st = KS == 1 ? tid : tid % THREADS;                     // table duty of this thread: entries st, st + THREADS, .. of the two
-  const int h1 = tid >> 8, e1 = tid & 255;          // KS = 1: its one entry
+  const uint8_t* idx_rb = P.idx + (size_t)rb * n_pairs * 1024;
+  const int st = wave % (THREADS / 64) * 64;        // table duty of this wave: entries st + lane, st + lane + THREADS, .. of the two
   const int p_begin = n_pairs * split / KS, p_end = n_pairs * (split + 1) / KS;
   const int steps = (n_pairs + KS - 1) / KS;        // of the longest split: all take as many barriers
 
-  auto load = [&](int p, D4Step<KS>& s) {
+  auto load = [&](int p, D4Step<KS>& s) {           // (tables first: they are needed first; all of an address but the lane's part is wave-uniform)
     const int c0 = 2 * p, c1 = 2 * p + 1;
-    const bool ok1 = c1 < n_cb;
-    s.w = *reinterpret_cast<const uint4*>(idx_lane + (size_t)p * 1024);
-    s.xa = *reinterpret_cast<const uint2*>(x_lane + (size_t)c0 * 256);
-    const uint2 xb = *reinterpret_cast<const uint2*>(x_lane + (size_t)(ok1 ? c1 : c0) * 256);
-    s.xb = ok1 ? xb : make_uint2(0u, 0u);
+    const int c1_ld = c1 < n_cb ? c1 : c0;          // an absent second col-block re-reads the first (not used)
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
-      const int h = KS == 1 ? h1 : (st + i * THREADS) >> 8, e = KS == 1 ? e1 : (st + i * THREADS) & 255;
-      const long long g = grow * n_cb + ((h == 0 || ok1) ? c0 + h : c0);  // an absent second col-block re-reads the first (not used)
+      const int h = (st + i * THREADS) >> 8, e0 = (st + i * THREADS) & 255;
+      const long long g = grow * n_cb + (h == 0 ? c0 : c1_ld);
       if constexpr (F16) {
-        s.q[i] = *reinterpret_cast<const uint2*>(tab + g * 2048 + e * 8);
+        s.q[i] = reinterpret_cast<const uint2*>(tab + g * 2048 + e0 * 8)[lane];
         s.sc[i] = 0;
       } else {
-        s.q[i] = make_uint2(*reinterpret_cast<const uint32_t*>(tab + g * 1024 + e * 4), 0u);
+        s.q[i] = make_uint2(reinterpret_cast<const uint32_t*>(tab + g * 1024 + e0 * 4)[lane], 0u);
         s.sc[i] = scales[g];
       }
-      if constexpr (BN) s.lv[i] = levels[g * 16 + (e & 15)];
+      if constexpr (BN) s.lv[i] = levels[g * 16 + (lane & 15)];
     }
+    s.w = reinterpret_cast<const uint4*>(idx_rb + (size_t)p * 1024)[lane];
+    s.xa = reinterpret_cast<const uint2*>(P.x + (size_t)c0 * 256)[lane];
+    s.xb = reinterpret_cast<const uint2*>(P.x + (size_t)c1_ld * 256)[lane];
     if constexpr (BN) s.cw = *reinterpret_cast<const uint2*>(codes_lane + (size_t)p * 64);
   };
 
@@ -104,25 +118,23 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
     lb = lora_load_b(arg.l[pi], P.x, rb, lane);
   }
 
-  D4Step<KS> cur, nxt;
+  D4Step<KS> even, odd;
   const int p_last = p_end > p_begin ? p_end - 1 : 0;
-  load(KS == 1 ? 0 : min(p_begin, p_last), cur);
-  for (int step = 0; step < steps; ++step) {
-    const int p = p_begin + step;
-    load(KS == 1 ? (p + 1 < n_pairs ? p + 1 : p) : min(p + 1, p_last), nxt);                  // one step ahead (a harmless re-read at the end)
-    const int buf = step & 1;
+  // One step: the next one's loads, this one's tables into buffer `buf`, a barrier, the lookups.
+  auto run_step = [&](auto buf, int p, const D4Step<KS>& cur, D4Step<KS>& nxt) {
+    load(min(p + 1, p_last), nxt);                  // one step ahead (a harmless re-read at the end)
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
-      const int h = KS == 1 ? h1 : (st + i * THREADS) >> 8, e = KS == 1 ? e1 : (st + i * THREADS) & 255;
+      const int h = (st + i * THREADS) >> 8, e = ((st + i * THREADS) & 255) + lane;
       const bool mine = h == 0 || 2 * p + 1 < n_cb; // the absent col-block of an odd matrix gets a zero table
-      tabs[buf][h][e] = !mine ? make_uint2(0u, 0u)
-                        : F16 ? cur.q[i] : d4_dequant_entry(cur.q[i].x, __builtin_bit_cast(_Float16, (uint16_t)cur.sc[i]));
+      tabs[buf][h][e] = zero_unless(mine, F16 ? cur.q[i] : d4_dequant_entry(cur.q[i].x, __builtin_bit_cast(_Float16, (uint16_t)cur.sc[i])));
       if constexpr (BN) {
         if (e < 16) levs[buf][h][e] = mine ? cur.lv[i] * 0x10001u : 0u;
       }
     }
     __syncthreads();   // tables of this step complete; the other buffer is free again (see header)
-    if (KS > 1 && p >= p_end) break;                // the longest splits' last step
+    if (KS > 1 && p >= p_end) return;               // the longest splits' last step
+    const uint2 xb = zero_unless(2 * p + 1 < n_cb, cur.xb);
     const uint2* T0 = tabs[buf][0];
     const uint2* T1 = tabs[buf][1];
 #pragma unroll
@@ -137,10 +149,17 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
       }
       acc[r] = dot2(t0.x, cur.xa.x, acc[r]);
       acc[r] = dot2(t0.y, cur.xa.y, acc[r]);
-      acc[r] = dot2(t1.x, cur.xb.x, acc[r]);
-      acc[r] = dot2(t1.y, cur.xb.y, acc[r]);
+      acc[r] = dot2(t1.x, xb.x, acc[r]);
+      acc[r] = dot2(t1.y, xb.y, acc[r]);
     }
-    cur = nxt;
+  };
+  load(min(p_begin, p_last), even);
+  const int p_stop = p_begin + steps;
+  for (int p = p_begin;;) {   // (two exits: at a merge the compiler would wait for all loads)
+    run_step(std::integral_constant<int, 0>(), p, even, odd);
+    if (++p >= p_stop) break;
+    run_step(std::integral_constant<int, 1>(), p, odd, even);
+    if (++p >= p_stop) break;
   }
 
   float v = wave_reduce8(acc, lane);   // every lane: the total of row (lane >> 3) & 7
@@ -181,7 +200,7 @@ struct K256Step {
 
 // BN: with blockwise normalisation; the plain C++ inner block replaces the hand-scheduled one.
 template <bool LORA, bool BN, int CAP, int KS>
-__global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf<LORA, CAP>::type arg) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(BN && !LORA && KS == 4 ? 6 : 1))) void gemv_k256i8_kernel(const typename BatchOf<LORA, CAP>::type arg) {
   const auto& batch = base_of(arg);
   constexpr int RBW = 8 / KS, THREADS = 512 / KS;   // row-blocks of a workgroup; threads that share tables
   __shared__ __attribute__((aligned(16))) uint32_t tabs_all[KS][2][2][256];   // [buffer][col-block of the pair][entry]
@@ -189,7 +208,7 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int item = (int)blockIdx.x / KS;
+  const int item = KS == 1 ? item_of_workgroup((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x / KS;
   const int pi = find_problem(batch, item);
   const GemvItem P = item_of(batch, pi);
   const int oct = item - P.wg_begin;                // which 64 rows
@@ -205,29 +224,26 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
   const uint16_t* levels = reinterpret_cast<const uint16_t*>(tab + wide_bn_level_offset((size_t)n_groups, 512));
   const uint8_t* codes_lane = tab + wide_bn_code_offset((size_t)n_groups, 512) + (size_t)rb * n_pairs * 64 + (lane >> 3) * 8;
   (void)levels; (void)codes_lane;
-  const uint8_t* idx_lane = P.idx + (size_t)rb * n_cb * 1024 + lane * 16;
-  const uint16_t* x_lane = P.x + lane * 4;
-  const int st = tid % THREADS;                     // table duty of this thread: entries st, st + THREADS, .. of the two
+  const uint8_t* idx_rb = P.idx + (size_t)rb * n_cb * 1024;
+  const int st = wave % (THREADS / 64) * 64;        // table duty of this wave: entries st + lane, st + lane + THREADS, .. of the two
   const int p_begin = n_pairs * split / KS, p_end = n_pairs * (split + 1) / KS;
   const int steps = (n_pairs + KS - 1) / KS;        // of the longest split: all take as many barriers
 
-  auto load = [&](int p, K256Step<KS>& s) {
+  auto load = [&](int p, K256Step<KS>& s) {         // (tables first: they are needed first; all of an address but the lane's part is wave-uniform)
     const int c0 = 2 * p, c1 = 2 * p + 1;
-    const bool ok1 = c1 < n_cb;
-    const int c1_ld = ok1 ? c1 : c0;                // an absent second col-block re-reads the first (not used)
-    s.w0 = *reinterpret_cast<const uint4*>(idx_lane + (size_t)c0 * 1024);
-    s.w1 = *reinterpret_cast<const uint4*>(idx_lane + (size_t)c1_ld * 1024);
-    s.xa = *reinterpret_cast<const uint2*>(x_lane + (size_t)c0 * 256);
-    const uint2 xb = *reinterpret_cast<const uint2*>(x_lane + (size_t)c1_ld * 256);
-    s.xb = ok1 ? xb : make_uint2(0u, 0u);
+    const int c1_ld = c1 < n_cb ? c1 : c0;          // an absent second col-block re-reads the first (not used)
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
-      const int h = (st + i * THREADS) >> 8, e = (st + i * THREADS) & 255;
+      const int h = (st + i * THREADS) >> 8, e0 = (st + i * THREADS) & 255;
       const long long g = grow * n_cb + (h == 0 ? c0 : c1_ld);
-      s.q[i] = *reinterpret_cast<const uint16_t*>(tab + g * 512 + e * 2);
+      s.q[i] = reinterpret_cast<const uint16_t*>(tab + g * 512 + e0 * 2)[lane];
       s.sc[i] = scales[g];
-      if constexpr (BN) s.lv[i] = levels[g * 16 + (e & 15)];
+      if constexpr (BN) s.lv[i] = levels[g * 16 + (lane & 15)];
     }
+    s.w0 = reinterpret_cast<const uint4*>(idx_rb + (size_t)c0 * 1024)[lane];
+    s.w1 = reinterpret_cast<const uint4*>(idx_rb + (size_t)c1_ld * 1024)[lane];
+    s.xa = reinterpret_cast<const uint2*>(P.x + (size_t)c0 * 256)[lane];
+    s.xb = reinterpret_cast<const uint2*>(P.x + (size_t)c1_ld * 256)[lane];
     if constexpr (BN) s.cw = *reinterpret_cast<const uint2*>(codes_lane + (size_t)p * 64);
   };
 
@@ -242,16 +258,13 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
     lb = lora_load_b(arg.l[pi], P.x, rb, lane);
   }
 
-  K256Step<KS> cur, nxt;
+  K256Step<KS> even, odd;
   const int p_last = p_end > p_begin ? p_end - 1 : 0;
-  load(min(p_begin, p_last), cur);
-  for (int step = 0; step < steps; ++step) {
-    const int p = p_begin + step;
-    load(min(p + 1, p_last), nxt);                  // one step ahead (a harmless re-read at the end)
-    const int buf = step & 1;
+  auto run_step = [&](auto buf, int p, const K256Step<KS>& cur, K256Step<KS>& nxt) {   // as in gemv_d4_kernel
+    load(min(p + 1, p_last), nxt);
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
-      const int h = (st + i * THREADS) >> 8, e = (st + i * THREADS) & 255;
+      const int h = (st + i * THREADS) >> 8, e = ((st + i * THREADS) & 255) + lane;
       const bool mine = h == 0 || 2 * p + 1 < n_cb; // the absent col-block of an odd matrix gets a zero table
       tabs[buf][h][e] = mine ? k64_dequant_pair(cur.q[i], __builtin_bit_cast(_Float16, (uint16_t)cur.sc[i])) : 0u;
       if constexpr (BN) {
@@ -259,17 +272,25 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
       }
     }
     __syncthreads();   // tables of this step complete; the other buffer is free again
-    if (KS > 1 && p >= p_end) break;                // the longest splits' last step
+    if (KS > 1 && p >= p_end) return;               // the longest splits' last step
+    const uint2 xb = zero_unless(2 * p + 1 < n_cb, cur.xb);
     if constexpr (BN) {
       k256_group_scaled(cur.w0.x, cur.w0.y, cur.w0.z, cur.w0.w, cur.cw.x, tabs[buf][0], levs[buf][0], cur.xa.x, cur.xa.y, acc);
-      k256_group_scaled(cur.w1.x, cur.w1.y, cur.w1.z, cur.w1.w, cur.cw.y, tabs[buf][1], levs[buf][1], cur.xb.x, cur.xb.y, acc);
+      k256_group_scaled(cur.w1.x, cur.w1.y, cur.w1.z, cur.w1.w, cur.cw.y, tabs[buf][1], levs[buf][1], xb.x, xb.y, acc);
     } else {
       const uint32_t base = lds_addr(&tabs[buf][0][0]);
       k256_group<0>(cur.w0.x, cur.w0.y, cur.w0.z, cur.w0.w, base, cur.xa.x, cur.xa.y, acc);
-      k256_group<1024>(cur.w1.x, cur.w1.y, cur.w1.z, cur.w1.w, base, cur.xb.x, cur.xb.y, acc);
+      k256_group<1024>(cur.w1.x, cur.w1.y, cur.w1.z, cur.w1.w, base, xb.x, xb.y, acc);
       acc_hazard_fence();
     }
-    cur = nxt;
+  };
+  load(min(p_begin, p_last), even);
+  const int p_stop = p_begin + steps;
+  for (int p = p_begin;;) {
+    run_step(std::integral_constant<int, 0>(), p, even, odd);
+    if (++p >= p_stop) break;
+    run_step(std::integral_constant<int, 1>(), p, odd, even);
+    if (++p >= p_stop) break;
   }
 
   float v = wave_reduce8(acc, lane);   // every lane: the total of row (lane >> 3) & 7
