@@ -200,7 +200,7 @@ struct K256Step {
 
 // BN: with blockwise normalisation; the plain C++ inner block replaces the hand-scheduled one.
 template <bool LORA, bool BN, int CAP, int KS>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(BN && !LORA && KS == 4 ? 6 : 1))) void gemv_k256i8_kernel(const typename BatchOf<LORA, CAP>::type arg) {
+__global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf<LORA, CAP>::type arg) {
   const auto& batch = base_of(arg);
   constexpr int RBW = 8 / KS, THREADS = 512 / KS;   // row-blocks of a workgroup; threads that share tables
   __shared__ __attribute__((aligned(16))) uint32_t tabs_all[KS][2][2][256];   // [buffer][col-block of the pair][entry]
