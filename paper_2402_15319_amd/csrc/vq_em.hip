@@ -699,8 +699,16 @@ __global__ __launch_bounds__(256, (NCB == 1 ? em_waves<K, D>() : NCB == 8 ? 4 : 
 //   Bound: the reads of W and the LDS (clocks a wave and CU: maximum 8, addition 13, gather 7; binary64 additions,
 // which depend on order, take 22 .. 31, binary32 ones 194).  us at 11008 x 4096, uniform assignments, one centroid for
 // all, and in brackets both with binary64 additions: d = 2, k = 64, 32 rows 67, 32 (75, 456); d = 2, k = 256, 8 rows 77,
-// 45 (72, 459), 128 rows 73, 39 (77, 501); d = 4, k = 256, 64 rows 69, 40 (81, 469), 256 rows 82, 59 (64, 270), where
-// the second half of the rows is read twice.  Weights further apart than 2^kSpread: 35 .. 64 for 28 .. 36 at 4096 x 4096.
+// 45 (72, 459), 128 rows 73, 39 (77, 501); d = 4, k = 256, 64 rows 69, 40 (81, 469).  Weights further apart than 2^kSpread:
+// 35 .. 64 for 28 .. 36 at 4096 x 4096.
+//   Counted tables (d = 4, k = 256, 128 rows and more) take a quick pass: one scale for the whole group, from the largest |x|
+// of its first 32 rows (with twice that and more found later, once more with that of all rows), instead of a maximum and a
+// look at it for every vector and entry (52 + 8 clocks of LDS a wave's vectors for 120), and each row is read once, four
+// rows a wave ahead, in 80 registers for three workgroups per CU instead of two.  A sum that is not 2^28 times its members'
+// roundings (it cancels, or they are small beside the group's largest; a centroid or so of 256) is formed again as
+// before, from its members alone: the assignment is read again, and of W those.  Infinities, NaN and weights further apart: entry by
+// entry.  us at 11008 x 4096, before, after: 256 rows 77 .. 82, 57 .. 61 (49 where nothing is formed again), 128 rows 80, 61; 4096 x
+// 4096, 256 rows 37.5, 34.7, every centroid twice 37.0, 38.3, rows 4 to 7 of 8 far from zero 46, 36, half of W zero 39, 39.
 // SHARED: 0, or for the workgroups of a coordinate (see below) log2 of the weights of their groups at most.
 template <int K, int D, int NG, int GPW, int RB, int SHARED>
 struct EmTables {
@@ -762,7 +770,7 @@ __device__ __forceinline__ double wave_sum63(double v) {
 // chain of a wave's vectors, one after the other (figures at em_shared; shares of the codebook instead of coordinates
 // leave every wave its chain: 24.6 us for 12.4 at 512 x 512, 256 rows, and 41 for 28 at 2048 x 2048).
 template <int K, int D, int NG, int GPW, int RB, int SHARED>
-__global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWaves), (GPW > 1 ? 1 : 4)) void em_update_kernel(
+__global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWaves), (GPW > 1 ? 1 : EmTables<K, D, NG, GPW, RB, SHARED>::kCounted ? 6 : 4)) void em_update_kernel(
     const float* __restrict__ W, const float* __restrict__ hdiag, const uint8_t* __restrict__ assign,
     float* __restrict__ cb_out, int n_cb, long long n_items, int in_features, int n_rows) {
   static_assert(!SHARED || (GPW == 1 && NG == 1), "a workgroup has one group");
@@ -771,6 +779,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
   constexpr int V = 4 / D;                          // vectors per row and lane
   constexpr int N = V * DT;                         // values of a row and lane: DT of each vector
   constexpr int RPG = 8 / NG;                       // rows of an 8-row block that share a codebook
+  constexpr int RW = Tab::kCounted ? 1 : RB;        // 8-row blocks that a wave holds at a time
   constexpr int CW = Tab::kWords + 1;               // a gap spreads the centroids over the banks
   constexpr uint32_t kNone = 0x100;
   __shared__ __attribute__((aligned(16))) unsigned long long sum_all[GPW * Tab::kTable];
@@ -779,10 +788,11 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
   __shared__ double h_all[Tab::kCounted ? 256 : 1];
   __shared__ double hot_sums[Tab::kMaxWaves][NG][2 * DT];
   __shared__ uint32_t hot_of[Tab::kMaxWaves][NG];
+  __shared__ uint32_t wave_top[Tab::kCounted ? Tab::kMaxWaves : 1], weak[Tab::kCounted ? K / 32 + 1 : 1];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int waves = GPW > 1 ? 1 : (int)blockDim.x / 64;   // of this item
-  const int parts = RB > 1 ? n_rows / (8 * RB * waves) : 1;   // what a wave takes one after the other, 8 * RB rows each
+  const int parts = RB > 1 ? n_rows / (8 * RW * waves) : 1;   // what a wave takes one after the other, 8 * RW rows each
   const int sub = GPW > 1 ? 0 : wave;               // this wave's place among them
   const int slot = GPW > 1 ? wave : 0;
   const int t_item = sub * 64 + lane, t_count = waves * 64;
@@ -793,7 +803,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
   if (GPW > 1 && item >= n_items) return;           // whole waves leave; no workgroup barrier with GPW > 1
   const long long ir = item / n_cb;                 // group row, or 8-row block where that holds several groups
   const int c = (int)(item - ir * n_cb);
-  const long long row0 = ir * (NG > 1 ? 8 : n_rows) + sub * 8 * RB;
+  const long long row0 = ir * (NG > 1 ? 8 : n_rows) + sub * 8 * RW;
   auto item_sync = [] {
     if constexpr (GPW > 1) wave_lds_sync();
     else __syncthreads();
@@ -819,21 +829,44 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
     else if constexpr (V == 2) ar = *reinterpret_cast<const uint16_t*>(ap);
     else ar = *ap;
   };
-  float x[8 * RB][N];
-  uint32_t a[8 * RB];
+  float x[8 * RW][N];
+  uint32_t a[8 * RW];
   auto load_part = [&](int p) {
 #pragma unroll
-    for (int r = 0; r < 8 * RB; ++r) load(p * waves * 8 * RB + r, x[r], a[r]);
+    for (int r = 0; r < 8 * RW; ++r) load(p * waves * 8 * RW + r, x[r], a[r]);
   };
-  load_part(0);
-  for (int i = t_item; i < Tab::kTable; i += t_count) {
-    sums[i] = 0ull;
-    tops[i] = 0u;
-  }
+  // Counted: the quick pass streams parts of QR rows a wave
+  constexpr int QR = Tab::kCounted ? 4 : 1;
+  float xq[2][QR][4];
+  uint32_t mq[2][QR];
+  auto load_quick = [&](int p, float (&xr)[QR][4], uint32_t (&mr)[QR]) {
+    if constexpr (Tab::kCounted) {
+#pragma unroll
+      for (int r = 0; r < QR; ++r) {
+        const int row = (p >> 1) * 64 + 2 * r + (p & 1);
+        const float4 t = *reinterpret_cast<const float4*>(Wl + (size_t)row * in_features);
+        xr[r][0] = t.x; xr[r][1] = t.y; xr[r][2] = t.z; xr[r][3] = t.w;
+        mr[r] = al[(size_t)row * (in_features / D)];
+      }
+    }
+  };
+  auto clear = [&] {
+    for (int i = t_item; i < Tab::kTable; i += t_count) {
+      sums[i] = 0ull;
+      tops[i] = 0u;
+    }
+    if constexpr (Tab::kCounted) {
+      for (int i = t_item; i < K * CW; i += t_count) counts[i] = 0u;
+      if (t_item <= K / 32) weak[t_item] = 0u;
+    }
+  };
   if constexpr (Tab::kCounted) {
-    for (int i = t_item; i < K * CW; i += t_count) counts[i] = 0u;
+    load_quick(0, xq[0], mq[0]);
     for (int i = t_item; i < 256; i += t_count) h_all[i] = hdiag[(size_t)c * 256 + i];
+  } else {
+    load_part(0);
   }
+  clear();
   item_sync();
 
   const int copy = Tab::kCopies > 1 ? lane % Tab::kCopies : 0;
@@ -845,7 +878,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
     int most = 11;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const uint32_t m = (a[g * RPG + j % RPG] & 0xffu);
+      const uint32_t m = ((Tab::kCounted ? mq[0][j % QR] : a[g * RPG + j % RPG]) & 0xffu);
       const uint32_t asked = (uint32_t)__builtin_amdgcn_readlane((int)m, 8 * j + 3);
       const int n = __builtin_popcountll(__ballot(m == asked));
       if (n > most && (K == 256 || asked < (uint32_t)K)) { most = n; hot[g] = asked; }
@@ -870,6 +903,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
     any_h = !finite || h_exp < 32 || __builtin_bit_cast(uint32_t, small) >> 23 < h_exp - Tab::kSpread;
   }
   constexpr int P = Tab::kBits;
+  constexpr int PQ = 49;                            // of the quick pass: an entry holds 2^13 vectors, more are summed again
   auto finish = [&](int g, const double (&own)[2 * DT]) {   // the wave's sums of the centroid kept in registers
     if (hot[g] != kNone) {
 #pragma unroll
@@ -883,7 +917,101 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
   auto count = [&](uint32_t m) {
     if constexpr (Tab::kCounted) atomicAdd(counts + m * CW + (lane & 31), 1u << (16 * (lane >> 5)));
   };
-  if (any_h) {
+  // The quick pass (counted tables): all entries scaled by the largest |x| of the first 32 rows, twice which the
+  // others may reach (checked).  Rows are read once, four a wave ahead of those that are added, and an entry takes no maximum and no look at it.
+  bool quick = Tab::kCounted && !any_h;
+  uint32_t x_exp = 0;                               // |x| < 2^(x_exp - 126)
+  double own_quick[2 * DT] = {};
+  if constexpr (Tab::kCounted) {
+    auto largest = [&](const float (&xr)[QR][4]) {   // NaN if there is one
+      float top = 0.f;
+#pragma unroll
+      for (int r = 0; r < QR; ++r)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) top = max_nn(top, __builtin_fabsf(xr[r][v]));
+      return top;
+    };
+    auto add = [&](const float (&xr)[QR][4], const uint32_t (&mr)[QR]) {
+      const uint32_t scale = (PQ + 1275u - h_exp - x_exp) << 20;
+#pragma unroll
+      for (int r = 0; r < QR; ++r) {
+        const uint32_t m = mr[r];
+        count(m);
+        if (m == hot[0]) {
+#pragma unroll
+          for (int t = 0; t < D; ++t) own_quick[t] += (double)h[t] * (double)xr[r][t];
+        } else {
+#pragma unroll
+          for (int t = 0; t < D; ++t) atomicAdd(sums + m * Tab::kCopies + t * Tab::kStride, to_fixed((double)h[t] * (double)xr[r][t], scale));
+        }
+      }
+    };
+    // the largest of the waves' values, to all of them
+    auto of_all = [&](float top) {
+      top = __any(!(top < __builtin_inff())) ? __builtin_inff() : -wave_min(-top);
+      if (lane == 0) wave_top[wave] = __builtin_bit_cast(uint32_t, top);
+      __syncthreads();
+      uint32_t all = 0;
+      for (int w = 0; w < waves; ++w) all = max(all, wave_top[w]);
+      return all;
+    };
+    const int n_parts = n_rows / 32;                // an even number
+    uint32_t all = 0;
+    if (quick) {
+      all = of_all(largest(xq[0]));
+      quick = all < 0x7f000000u;
+    }
+    if (quick) {
+      x_exp = (all >> 23) + 1;
+      const float limit = __builtin_bit_cast(float, min(x_exp + 1u, 254u) << 23);
+      bool over = false;
+#pragma unroll 1
+      for (int p = 0; p < n_parts; p += 2) {
+        load_quick(p + 1, xq[1], mq[1]);
+        over = over || __any(!(largest(xq[0]) < limit));
+        add(xq[0], mq[0]);
+        if (p + 2 < n_parts) load_quick(p + 2, xq[0], mq[0]);
+        over = over || __any(!(largest(xq[1]) < limit));
+        add(xq[1], mq[1]);
+        if (over) weak[K / 32] = 1u;
+        over = *(volatile uint32_t*)(weak + K / 32) != 0u;   // in any wave
+        if (over) break;
+      }
+      finish(0, own_quick);
+      __syncthreads();
+      if (weak[K / 32] != 0u) {                     // once more, with the largest of all rows
+        float top = 0.f;
+#pragma unroll 1
+        for (int p = 0; p < n_parts; p += 2) {
+          load_quick(p, xq[0], mq[0]);
+          load_quick(p + 1, xq[1], mq[1]);
+          top = max_nn(top, max_nn(largest(xq[0]), largest(xq[1])));
+        }
+        all = of_all(top);
+        clear();
+        quick = all < 0x7f000000u;
+        x_exp = all >> 23;
+#pragma unroll
+        for (int t = 0; t < D; ++t) own_quick[t] = 0.;
+        load_quick(0, xq[0], mq[0]);
+        __syncthreads();
+        if (quick) {
+#pragma unroll 1
+          for (int p = 0; p < n_parts; p += 2) {
+            load_quick(p + 1, xq[1], mq[1]);
+            add(xq[0], mq[0]);
+            if (p + 2 < n_parts) load_quick(p + 2, xq[0], mq[0]);
+            add(xq[1], mq[1]);
+          }
+          finish(0, own_quick);
+          __syncthreads();
+        }
+      }
+    }
+  }
+  const bool by_entry = any_h || (Tab::kCounted && !quick);
+  auto accumulate = [&] {
+  if (by_entry) {
     // Entries scaled by their largest |h x| and |h|, as high words of binary64 (|term| < 2^(field - 1022)).  Rare: rows are read
     // again one by one.
     if constexpr (NG > 1) {
@@ -893,10 +1021,10 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
     double own[2 * DT] = {};
     auto pass = [&](auto second) {
 #pragma unroll 1
-      for (int r = 0; r < 8 * RB * parts; ++r) {
+      for (int r = 0; r < 8 * RW * parts; ++r) {
         float xr[N];
         uint32_t ar;
-        load(RB > 1 ? r / (8 * RB) * waves * 8 * RB + r % (8 * RB) : r, xr, ar);
+        load(RB > 1 ? r / (8 * RW) * waves * 8 * RW + r % (8 * RW) : r, xr, ar);
 #pragma unroll
         for (int v = 0; v < V; ++v) {
           const uint32_t m = ((ar >> (8 * v)) & 0xffu);
@@ -926,13 +1054,13 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
     pass(std::true_type{});
 #pragma unroll
     for (int g = 0; g < NG; ++g) finish(g, own);
-  } else {
+  } else if constexpr (!Tab::kCounted) {
     // Entries scaled by their largest |x|, as binary32 (|x| < 2^(field - 126)), and all by the largest weight.
 #pragma unroll 1
     for (int p = 0; p < parts; ++p) {
       if (p > 0) load_part(p);
 #pragma unroll
-      for (int r = 0; r < 8 * RB; ++r) {
+      for (int r = 0; r < 8 * RW; ++r) {
         const int g = NG > 1 ? r / RPG : 0;
         const float (&xr)[N] = x[r];
 #pragma unroll
@@ -957,7 +1085,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
       if (p < parts - 1) load_part(p);
       // what this pass needs is computed again: kept from the first, it would not fit the registers
 #pragma unroll
-      for (int r = 0; r < 8 * RB; ++r)
+      for (int r = 0; r < 8 * RW; ++r)
       {
 #pragma unroll
         for (int t = 0; t < N; ++t) asm volatile("" : "+v"(x[r][t]));
@@ -965,7 +1093,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
       }
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
-        constexpr int ROWS = NG > 1 ? RPG : 8 * RB;
+        constexpr int ROWS = NG > 1 ? RPG : 8 * RW;
 #pragma unroll
         for (int r = g * ROWS; r < (g + 1) * ROWS; ++r) {
           const float (&xr)[N] = x[r];
@@ -1002,15 +1130,18 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
     if constexpr (NG == 1) finish(0, own);
   }
   item_sync();
-  if constexpr (Tab::kCounted) {
+  };
+  auto weights_from_counts = [&] {
     for (int i = t_item; i < 2 * K; i += t_count) {   // two lanes per centroid
       const int m = i >> 1, half = i & 1;
       const uint32_t* n = counts + m * CW + half * (Tab::kWords / 2);
       const double* hp = h_all + half * 4 * (Tab::kWords / 2);
       double den[D] = {};
+      uint32_t members = 0;
 #pragma unroll 4
       for (int w = 0; w < Tab::kWords / 2; ++w) {
         const double lo = n[w] & 0xffffu, hi = n[w] >> 16;
+        members += (n[w] & 0xffffu) + (n[w] >> 16);
 #pragma unroll
         for (int t = 0; t < D; ++t) den[t] += lo * hp[4 * w + t] + hi * hp[4 * w + 128 + t];
       }
@@ -1026,6 +1157,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
       }
 #pragma unroll
       for (int t = 0; t < D; ++t) den[t] += __shfl_xor(den[t], 1, 64);
+      members += __shfl_xor(members, 1, 64);
       if (half == 0) {                              // in the place of the centroid's counts, which both lanes have read
         uint32_t* out = counts + m * CW;
 #pragma unroll
@@ -1034,11 +1166,12 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
           out[2 * t] = (uint32_t)u;
           out[2 * t + 1] = (uint32_t)(u >> 32);
         }
+        out[2 * D] = members;
       }
     }
     item_sync();
-  }
-
+  };
+  auto write_centroids = [&] {
   for (int i = t_item; i < NG * K * DT; i += t_count) {
     const int e = i / DT, t = i % DT, g = e / K;
     double num = 0., den = 0.;
@@ -1046,27 +1179,95 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
     for (int q = 0; q < Tab::kCopies; ++q) {
       const int p = t * Tab::kStride + e * Tab::kCopies + q, p_h = p + DT * Tab::kStride;
       const uint32_t top = tops[p];
-      if (any_h) {
+      if (by_entry) {
         if (top != 0) num += top >= 0x7ff00000u ? from_nonfinite(sums[p]) : from_fixed(sums[p], (int)(top >> 20) + 1 - P);
         if constexpr (!Tab::kCounted) {
           const uint32_t top_h = tops[p_h];
           if (top_h != 0) den += top_h >= 0x7ff00000u ? from_nonfinite(sums[p_h]) : from_fixed(sums[p_h], (int)(top_h >> 20) + 1 - P);
         }
+      } else if (Tab::kCounted && quick) {
+        num += from_fixed(sums[p], (int)x_exp + (int)h_exp + 771 - PQ);
       } else {
         num += top >= 0x7f800000u ? from_nonfinite(sums[p]) : from_fixed(sums[p], (int)(top >> 23) + (int)h_exp + 771 - P);
         if constexpr (!Tab::kCounted) den += from_fixed(sums[p_h], (int)h_exp + 897 - P);
       }
     }
+    int hot_in = 0;
     for (int w = 0; w < waves; ++w) {
       if (hot_of[wave - sub + w][g] == (uint32_t)(e % K)) {
+        ++hot_in;
         num += hot_sums[wave - sub + w][g][t];
         if constexpr (!Tab::kCounted) den += hot_sums[wave - sub + w][g][DT + t];
       }
     }
-    if constexpr (Tab::kCounted)
+    if constexpr (Tab::kCounted) {
       den = __builtin_bit_cast(double, (uint64_t)counts[e * CW + 2 * t + 1] << 32 | counts[e * CW + 2 * t]);
+      // the members' roundings, half a unit each, against 2^-28 of their sum
+      const double unit = __builtin_bit_cast(double, (uint64_t)((int)x_exp + (int)h_exp + 771 - PQ) << 52);
+      const uint32_t members = counts[e * CW + 2 * D];
+      if (quick && hot_in < waves && !(__builtin_fabs(num) >= 0x1p27 * unit * (double)members && members <= 8192u)) atomicOr(weak + (e >> 5), 1u << (e & 31));
+    }
     const long long gi = NG > 1 ? (ir * NG + g) * n_cb + c : item;
     cb_out[(gi * K + e % K) * D + t0 + t] = den != 0. ? (float)num / (float)den : 0.f;
+  }
+  };
+  if (!quick) accumulate();
+  if constexpr (Tab::kCounted) weights_from_counts();
+  write_centroids();
+  if constexpr (Tab::kCounted) {
+    if (!quick) return;
+    __syncthreads();
+    uint32_t some = 0;
+    for (int w = 0; w < K / 32; ++w) some |= weak[w];
+    if (some == 0) return;
+    // Centroids whose sums cancel, or whose members are far smaller than the largest, are summed once more at the scale of
+    // their own members.
+    auto is_weak = [&](uint32_t m) { return (weak[m >> 5] >> (m & 31) & 1u) != 0; };
+    uint32_t mr[4][8];
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+      if (p < n_rows / 64) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) mr[p][r] = al[(size_t)(p * 64 + r) * (in_features / D)];
+      }
+    auto members = [&](auto f) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+        if (p < n_rows / 64) {
+          float4 v[8];
+#pragma unroll
+          for (int r = 0; r < 8; ++r)
+            if (is_weak(mr[p][r])) v[r] = *reinterpret_cast<const float4*>(Wl + (size_t)(p * 64 + r) * in_features);
+#pragma unroll
+          for (int r = 0; r < 8; ++r)
+            if (is_weak(mr[p][r])) {
+              const float xr[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
+#pragma unroll
+              for (int t = 0; t < D; ++t) f(mr[p][r] + t * Tab::kStride, t, xr[t]);
+            }
+        }
+    };
+    for (int i = t_item; i < K * D; i += t_count) {
+      if (is_weak(i % K)) {
+        sums[i] = 0ull;
+        tops[i] = 0u;
+      }
+    }
+    __syncthreads();
+    members([&](uint32_t e, int, float xv) { atomicMax(tops + e, __builtin_bit_cast(uint32_t, xv) & 0x7fffffffu); });
+    __syncthreads();
+    members([&](uint32_t e, int t, float xv) {
+      atomicAdd(sums + e, to_fixed((double)h[t] * (double)xv, ((P + 1275u - h_exp) << 20) - ((tops[e] >> 3) & 0x0ff00000u)));
+    });
+    __syncthreads();
+    for (int i = t_item; i < K * D; i += t_count) {
+      const int m = i / D, t = i % D, e = m + t * Tab::kStride;
+      if (is_weak(m)) {
+        const double den = __builtin_bit_cast(double, (uint64_t)counts[m * CW + 2 * t + 1] << 32 | counts[m * CW + 2 * t]);
+        const double num = from_fixed(sums[e], (int)(tops[e] >> 23) + (int)h_exp + 771 - P);
+        cb_out[(item * K + m) * D + t] = den != 0. ? (float)num / (float)den : 0.f;
+      }
+    }
   }
 }
 

@@ -1,0 +1,81 @@
+"""The M-step of many tall groups (d = 4, k = 256, 128 or 256 rows, more than half a group per CU): one scale for a group,
+taken from its first rows, centroids summed again where that leaves their sums too few bits, and the general path for
+infinities.  Against 64-bit sums, on every run and in every order of the rows the same."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+KINDS = ["normal", "later rows larger", "odd rows larger", "one value larger", "small and cancelling", "zeros", "uneven weights",
+         "infinities"]
+
+
+def _inputs(rows, kind):
+    rng = np.random.default_rng(rows + KINDS.index(kind))
+    gr, gc = 26, 5                                  # 130 groups
+    W = (rng.standard_normal((gr, rows, gc * 256)) * 0.02).astype(np.float32)
+    h = rng.uniform(0.2, 5.0, gc * 256).astype(np.float32)
+    a = rng.integers(0, 256, (gr, rows, gc * 64)).astype(np.uint8)
+    if kind == "later rows larger":                 # by more than the first ones' scale allows
+        W[::2, 8:] *= 300
+    elif kind == "odd rows larger":
+        W[1::2, 1::2] *= 2.0 ** 20
+    elif kind == "one value larger":
+        W[:, -1, 255::256] = -3e3
+    elif kind == "small and cancelling":
+        at = np.repeat(a, 4, axis=2)
+        W[(at >= 5) & (at < 9)] *= np.float32(2.0 ** -60)     # four centroids far below the rest, subnormal ones too
+        W[at == 5] *= np.float32(2.0 ** -70)
+        W[:, 1] = -W[:, 0]                                    # pairs that cancel, each in the same centroid
+        a[:, 1] = a[:, 0]
+        W[:, 2:][np.repeat(a[:, 2:], 4, axis=2) == 9] = 0     # ... and nothing else in it
+    elif kind == "zeros":
+        W[::2] = 0
+        W[1::2][np.repeat(a[1::2], 4, axis=2) < 200] = 0
+    elif kind == "uneven weights":
+        h[::7] *= np.float32(2.0 ** -20)
+        h[3::256] = 0
+    elif kind == "infinities":
+        W[0, -1, 5], W[1, 3, 300], W[2, rows // 2, 7], W[3, 0, 0] = np.inf, -np.inf, np.nan, 1e37   # (h x below 2^128: the numerator is rounded to binary32)
+    return W.reshape(gr * rows, gc * 256), h, a.reshape(gr * rows, gc * 64)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("rows", [128, 256])
+def test_against_64_bit_sums_in_any_order(rows, kind):
+    import torch
+    import paper_2402_15319_amd as vq
+    W, h, a = _inputs(rows, kind)
+    gr, gc = W.shape[0] // rows, W.shape[1] // 256
+    desc = vq.make_desc(W.shape[0], W.shape[1], 256, 8, rows, 256, 4)
+    order = np.random.default_rng(1).permutation(rows)
+
+    def update(W, a):
+        new = torch.full((gr, gc, 256, 4), 777.0, dtype=torch.float32, device="cuda:0")
+        vq.vq_em_update(desc, torch.from_numpy(W).cuda(), torch.from_numpy(h).cuda(), torch.from_numpy(a).cuda(), new)
+        return new.cpu().numpy()
+
+    got = update(W, a)
+    np.testing.assert_array_equal(update(W, a), got)
+    if kind != "zeros":          # (half of the lanes in one centroid: its sums are kept by lane, in binary64)
+        shuffled = [m.reshape(gr, rows, -1)[:, order].reshape(m.shape) for m in (W, a)]
+        np.testing.assert_array_equal(update(*shuffled), got)
+    with np.errstate(invalid="ignore"):
+        for g in range(gr):
+            for c in range(gc):
+                x = W[g * rows:(g + 1) * rows, c * 256:(c + 1) * 256].astype(np.float64).reshape(-1, 4)
+                hv = np.broadcast_to(h[c * 256:(c + 1) * 256].astype(np.float64), (rows, 256)).reshape(-1, 4)
+                m = a[g * rows:(g + 1) * rows, c * 64:(c + 1) * 64].reshape(-1)
+                n = np.bincount(m, minlength=256)
+                for t in range(4):
+                    num = np.bincount(m, hv[:, t] * x[:, t], 256)
+                    den = np.bincount(m, hv[:, t], 256)
+                    want = np.where(den != 0, num / np.where(den != 0, den, 1), 0)
+                    top = np.zeros(256)
+                    np.maximum.at(top, m, np.abs(hv[:, t] * x[:, t]))
+                    # numerator, denominator and quotient rounded once each, the numerator's sum good to 2^-28 of itself or,
+                    # with even weights, to n * 2^-36 of its largest term (n * 2^-34 with the roundings of these sums)
+                    with np.errstate(over="ignore"):
+                        bound = 3.2 * 2.0 ** -24 * np.abs(want) + n * 2.0 ** -34 * top / np.where(den != 0, den, 1) + 2.0 ** -149
+                    ok = (np.abs(got[g, c, :, t] - want) <= bound) | (np.isnan(want) & np.isnan(got[g, c, :, t])) | (want == got[g, c, :, t])
+                    assert ok.all(), (g, c, t, np.flatnonzero(~ok)[:4], got[g, c, ~ok, t][:4], want[~ok][:4])
