@@ -148,8 +148,9 @@ int static_scratch(float** out) {
   return VQ_OK;
 }
 
-// The order in which a launch of wide-group products hands out its work: the widest products first.  Workgroups start in
-// order and take as long as their product is wide, so a wide one at the end keeps a few CUs busy after the others.
+// The order in which a launch of wide-group products hands out its work: the widest products first, equal ones as they
+// come.  Workgroups start in order and take as long as their product is wide, so a wide one at the end keeps a few CUs busy
+// after the others.  (Sorted in place with the index to break ties: a stable sort would take a buffer from the heap.)
 void widest_first(const vq_desc* descs, int n, uint16_t* order) {
   bool sorted = true;
   for (int i = 0; i < n; ++i) {
@@ -157,7 +158,9 @@ void widest_first(const vq_desc* descs, int n, uint16_t* order) {
     sorted = sorted && (i == 0 || descs[i].in_features <= descs[i - 1].in_features);
   }
   if (!sorted)
-    std::stable_sort(order, order + n, [&](uint16_t a, uint16_t b) { return descs[a].in_features > descs[b].in_features; });
+    std::sort(order, order + n, [&](uint16_t a, uint16_t b) {
+      return descs[a].in_features != descs[b].in_features ? descs[a].in_features > descs[b].in_features : a < b;
+    });
 }
 
 // The body of vq_gemv_multi and of its variants with a low-rank adapter (lora != NULL: t_ws is

@@ -1,10 +1,11 @@
 // Stand-in for the HIP runtime calls that libvq makes, for tests of what the library launches (no GPU needed):
 // this program is linked against libvq.so and its own definitions of those calls come first in the lookup, so
 // nothing reaches the real runtime.  Reads one call a line from stdin,
-//   op out in group_rows d k bits dtype B count cus        (op: assign, update, gemm, pack, gemv)
+//   op out in group_rows d k bits dtype B count cus        (op: assign, update, gemm, pack, gemv, lora: with static scratch)
 // with several "out in" pairs as out1+out2+.. in1+in2+.. for gemv, and prints the status, then every launch:
 //   status ; kernel gx gy gz threads a b ..  ; ..
-// a, b, ..: for the kernels named below the integer arguments that the tests look at.
+// a, b, ..: for the kernels named below the integer arguments that the tests look at.  At the end, on stderr: how many
+// times the library has taken memory from the heap.
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
@@ -23,6 +24,8 @@ std::map<const void*, std::string>& names() {   // filled while libvq's initiali
   return n;
 }
 int g_cus = 256;
+bool g_in_library = false;
+long long g_allocations = 0;
 std::ostringstream g_out;
 dim3 g_grid, g_block;
 size_t g_shared;
@@ -34,6 +37,11 @@ const Ints kInts[] = {{"gemm_tiny_kernel", 8, 3}, {"gemm_small_kernel", 8, 4}, {
 }  // namespace
 
 extern "C" {
+void* __libc_malloc(size_t);
+void* malloc(size_t n) {   // operator new comes here too
+  g_allocations += g_in_library;
+  return __libc_malloc(n);
+}
 void** __hipRegisterFatBinary(const void*) { static void* handle; return &handle; }
 void __hipUnregisterFatBinary(void**) {}
 void __hipRegisterFunction(void**, const void* host, char*, const char* device, unsigned, void*, void*, void*, void*, int*) {
@@ -49,11 +57,13 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, hi
   return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t, hipStream_t) {
+  g_in_library = false;
   const std::string& name = names()[f];
   g_out << " ; " << name << " " << grid.x << " " << grid.y << " " << grid.z << " " << block.x * block.y * block.z;
   for (const Ints& k : kInts)
     if (name.find(k.kernel) != std::string::npos)
       for (int i = 0; i < k.count; ++i) g_out << " " << *static_cast<int32_t*>(args[k.first + i]);
+  g_in_library = true;
   return hipSuccess;
 }
 hipError_t hipGetLastError() { return hipSuccess; }
@@ -87,20 +97,26 @@ int main() {
       for (int c = 0; c < count; ++c) ds.push_back(d);
     }
     g_out.str("");
+    g_in_library = op != "gemv" && op != "lora";
     const int ld = (B + 7) / 8 * 8;
     if (op == "assign") status = vq_em_assign(&ds[0], ptr(0), ptr(1), ptr(2), ptr(3), nullptr);
     else if (op == "update") status = vq_em_update(&ds[0], ptr(0), ptr(1), ptr(2), ptr(3), nullptr);
     else if (op == "pack") status = vq_pack_layout(&ds[0], ptr(0), ptr(1), ptr(2), ptr(3), nullptr);
     else if (op == "gemm") status = vq_gemm_batched(&ds[0], ptr(0), ptr(1), ptr(2), B, ld, ptr(3), ld, VQ_F16, nullptr);
-    else if (op == "gemv") {
+    else if (op == "gemv" || op == "lora") {
       const std::vector<const void*> p(ds.size(), ptr(0)), x(ds.size(), ptr(1));
       const std::vector<void*> y(ds.size(), ptr(2));
-      status = vq_gemv_multi((int)ds.size(), ds.data(), p.data(), p.data(), x.data(), y.data(), VQ_F16, nullptr);
+      const std::vector<vq_lora_desc> adapters(ds.size(), {ptr(3), ptr(4), 16, 0});
+      g_in_library = true;
+      if (op == "gemv") status = vq_gemv_multi((int)ds.size(), ds.data(), p.data(), p.data(), x.data(), y.data(), VQ_F16, nullptr);
+      else status = vq_gemv_lora_multi_static((int)ds.size(), ds.data(), p.data(), p.data(), x.data(), adapters.data(), y.data(), VQ_F16, nullptr);
     } else {
       std::fprintf(stderr, "unknown op %s\n", op.c_str());
       return 1;
     }
+    g_in_library = false;
     std::cout << status << g_out.str() << "\n";
   }
+  std::cerr << "allocations " << g_allocations << "\n";
   return 0;
 }

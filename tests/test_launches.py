@@ -44,6 +44,7 @@ def launches(tmp_path_factory):
                 parsed.append((name, (int(gx), int(gy), int(gz)), int(threads), [int(i) for i in ints]))
             out.append((int(status), parsed))
         assert len(out) == len(calls)
+        run.allocations = int(res.stderr.split()[-1])   # of the library in these calls
         return out
     return run
 
@@ -137,6 +138,17 @@ def test_wide_gemv_splits(launches):
     wrong = [(w, ls[0][1][0]) for w, (st, ls) in zip(WIDE, got)
              if st != 0 or len(ls) != 1 or ls[0][1][0] != sum(w[1]) // 64 * w[4] or f"Li{w[4]}E" not in ls[0][0]]
     assert wrong == []
+
+
+def test_no_call_allocates(launches):
+    """Many products, of widths in any order (the tall-group formats start the widest first), with and without adapters."""
+    widths = [256, 2304, 768, 2304, 512, 1280, 4096] * 30
+    fmts = [K16, K64, K64_BN, K256, D4, D4_F16, D4_BN, K256_I8, K256_BN]
+    calls = [(op, [1024] * len(w), w, *fmt) for fmt in fmts for op in ("gemv", "lora") for w in (widths, sorted(widths), sorted(widths)[::-1])]
+    calls += [(op, 4096, 2304, *fmt, 40) for fmt in fmts for op in ("gemm", "pack")]
+    calls += [(op, 4096, 2304, gr, d, k, vq.VQ_F16) for gr, d, k in ((8, 2, 16), (64, 4, 256), (256, 4, 256), (8, 1, 8)) for op in ("assign", "update")]
+    assert all(st == 0 and ls for st, ls in launches(calls))
+    assert launches.allocations == 0
 
 
 @pytest.mark.parametrize("fmt", [K16, K64, (8, 2, 32, vq.VQ_I8), (1, 1, 4, vq.VQ_I8)], ids=str)
