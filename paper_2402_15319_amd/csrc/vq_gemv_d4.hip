@@ -40,14 +40,29 @@ __device__ __forceinline__ int item_of_workgroup(int b, int total) {
   return (b | 31) < total ? (b & ~31) | (b & 7) << 2 | ((b >> 3) & 3) : b;
 }
 
+// Table duty.  The waves that share tables write 512 entries, KS per thread: entry e0 + lane of table h (of the pair's first or
+// second col-block).  From KS = 4 on the first half of them is of table 0 and the rest of table 1, and a scale and a
+// level are held per table, not per entry: with KS = 4 k = 256 with block scales has 78 registers for 81, which makes room
+// for a third workgroup per CU (us, 4096, 11008 and 3 x 4096 rows of 4096 columns: 6.43, 12.43, 12.67 -> 6.45, 11.92, 12.04), and
+// d = 4 with an adapter 62, where a limit of 64 made it spill (7.90, 11.92, 12.11 -> 7.15, 10.88, 10.77).
+template <int KS>
+struct Duty {
+  static constexpr int THREADS = 512 / KS;                          // threads that share tables
+  static constexpr int TABLES = KS == 1 ? 1 : 2;                    // of a thread's entries
+  static constexpr int PER_TABLE = KS / TABLES;
+  // st: the first entry of the wave
+  static __device__ __forceinline__ int h(int st, int i) { return PER_TABLE == 1 ? (st + i * THREADS) >> 8 : i / PER_TABLE; }
+  static __device__ __forceinline__ int e0(int st, int i) { return (st + i * THREADS) & 255; }
+};
+
 template <int KS>
 struct D4Step {
   uint4 w;        // the lane's 8 + 8 index bytes of the pair
   uint2 xa, xb;   // its activations in the two col-blocks
-  uint2 q[KS];      // this thread's table entries: 4 int8 in .x, or 4 fp16
-  uint32_t sc[KS];  // int8 tables: the fp16 scales of their tables
+  uint2 q[KS];                   // this thread's table entries: 4 int8 in .x, or 4 fp16
+  uint32_t sc[Duty<KS>::TABLES]; // int8 tables: the fp16 scales of their tables
   uint2 cw;       // blockwise normalisation: the lane's block codes in the two col-blocks (row r in bits [4r, 4r+4))
-  uint32_t lv[KS];  // ... and level (entry & 15) of their tables (fp16)
+  uint32_t lv[Duty<KS>::TABLES]; // ... and level (lane & 15) of their tables (fp16)
 };
 
 // MODE 1 (F16): the tables are fp16 (2 KB per group, copied to LDS as they are) instead of int8
@@ -55,10 +70,10 @@ struct D4Step {
 // normalization"): the group's 16 block-scale levels sit next to its table in LDS, and per row
 // the looked-up vector is multiplied by the scale of the lane's 32-weight block before the dot2.
 template <bool LORA, int MODE, int CAP, int KS>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MODE != 2 && (KS == 1 || (KS == 4 && MODE == 0)) ? 8 : 1))) void gemv_d4_kernel(const typename BatchOf<LORA, CAP>::type arg) {
+__global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LORA, CAP>::type arg) {
   constexpr bool F16 = MODE == 1, BN = MODE == 2;
   const auto& batch = base_of(arg);
-  constexpr int RBW = 8 / KS, THREADS = 512 / KS;   // row-blocks of a workgroup; threads that share tables
+  constexpr int RBW = 8 / KS;                       // row-blocks of a workgroup
   __shared__ __attribute__((aligned(16))) uint2 tabs_all[KS][2][2][256];   // [buffer][col-block of the pair][entry]
   __shared__ uint32_t levs_all[KS][2][2][16];                               // BN: the tables' levels, the value in both halves
   const int tid = threadIdx.x;
@@ -81,7 +96,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MODE != 2 &
   const uint8_t* codes_lane = tab + wide_bn_code_offset((size_t)n_groups, 1024) + (size_t)rb * n_pairs * 64 + (lane >> 3) * 8;
   (void)levels; (void)codes_lane;
   const uint8_t* idx_rb = P.idx + (size_t)rb * n_pairs * 1024;
-  const int st = wave % (THREADS / 64) * 64;        // table duty of this wave: entries st + lane, st + lane + THREADS, .. of the two
+  using duty = Duty<KS>;
+  const int st = wave % (duty::THREADS / 64) * 64;  // table duty of this wave: entries st + lane, st + lane + THREADS, .. of the two
   const int p_begin = n_pairs * split / KS, p_end = n_pairs * (split + 1) / KS;
   const int steps = (n_pairs + KS - 1) / KS;        // of the longest split: all take as many barriers
 
@@ -90,16 +106,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MODE != 2 &
     const int c1_ld = c1 < n_cb ? c1 : c0;          // an absent second col-block re-reads the first (not used)
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
-      const int h = (st + i * THREADS) >> 8, e0 = (st + i * THREADS) & 255;
-      const long long g = grow * n_cb + (h == 0 ? c0 : c1_ld);
-      if constexpr (F16) {
-        s.q[i] = reinterpret_cast<const uint2*>(tab + g * 2048 + e0 * 8)[lane];
-        s.sc[i] = 0;
-      } else {
-        s.q[i] = make_uint2(reinterpret_cast<const uint32_t*>(tab + g * 1024 + e0 * 4)[lane], 0u);
-        s.sc[i] = scales[g];
+      const long long g = grow * n_cb + (duty::h(st, i) == 0 ? c0 : c1_ld);
+      if constexpr (F16) s.q[i] = reinterpret_cast<const uint2*>(tab + g * 2048 + duty::e0(st, i) * 8)[lane];
+      else s.q[i] = make_uint2(reinterpret_cast<const uint32_t*>(tab + g * 1024 + duty::e0(st, i) * 4)[lane], 0u);
+      if (i % duty::PER_TABLE == 0) {
+        s.sc[i / duty::PER_TABLE] = F16 ? 0 : scales[g];
+        if constexpr (BN) s.lv[i / duty::PER_TABLE] = levels[g * 16 + (lane & 15)];
       }
-      if constexpr (BN) s.lv[i] = levels[g * 16 + (lane & 15)];
     }
     s.w = reinterpret_cast<const uint4*>(idx_rb + (size_t)p * 1024)[lane];
     s.xa = reinterpret_cast<const uint2*>(P.x + (size_t)c0 * 256)[lane];
@@ -125,11 +138,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MODE != 2 &
     load(min(p + 1, p_last), nxt);                  // one step ahead (a harmless re-read at the end)
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
-      const int h = (st + i * THREADS) >> 8, e = ((st + i * THREADS) & 255) + lane;
+      const int h = duty::h(st, i), e = duty::e0(st, i) + lane;
       const bool mine = h == 0 || 2 * p + 1 < n_cb; // the absent col-block of an odd matrix gets a zero table
-      tabs[buf][h][e] = zero_unless(mine, F16 ? cur.q[i] : d4_dequant_entry(cur.q[i].x, __builtin_bit_cast(_Float16, (uint16_t)cur.sc[i])));
+      tabs[buf][h][e] = zero_unless(mine, F16 ? cur.q[i] : d4_dequant_entry(cur.q[i].x, __builtin_bit_cast(_Float16, (uint16_t)cur.sc[i / duty::PER_TABLE])));
       if constexpr (BN) {
-        if (e < 16) levs[buf][h][e] = mine ? cur.lv[i] * 0x10001u : 0u;
+        if (i % duty::PER_TABLE == 0 && e < 16) levs[buf][h][e] = mine ? cur.lv[i / duty::PER_TABLE] * 0x10001u : 0u;
       }
     }
     __syncthreads();   // tables of this step complete; the other buffer is free again (see header)
@@ -193,16 +206,16 @@ struct K256Step {
   uint4 w0, w1;   // the lane's 16 index bytes in the two col-blocks of the pair
   uint2 xa, xb;   // its activations there
   uint32_t q[KS];   // this thread's table entries (2 int8)
-  uint32_t sc[KS];  // the fp16 scales of their tables
+  uint32_t sc[Duty<KS>::TABLES];   // the fp16 scales of their tables
   uint2 cw;       // blockwise normalisation: the lane's block codes in the two col-blocks
-  uint32_t lv[KS];  // ... and level (entry & 15) of their tables (fp16)
+  uint32_t lv[Duty<KS>::TABLES];   // ... and level (lane & 15) of their tables (fp16)
 };
 
 // BN: with blockwise normalisation; the plain C++ inner block replaces the hand-scheduled one.
 template <bool LORA, bool BN, int CAP, int KS>
 __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf<LORA, CAP>::type arg) {
   const auto& batch = base_of(arg);
-  constexpr int RBW = 8 / KS, THREADS = 512 / KS;   // row-blocks of a workgroup; threads that share tables
+  constexpr int RBW = 8 / KS;                       // row-blocks of a workgroup
   __shared__ __attribute__((aligned(16))) uint32_t tabs_all[KS][2][2][256];   // [buffer][col-block of the pair][entry]
   __shared__ uint32_t levs_all[KS][2][2][16];                                  // BN: the tables' levels, the value in both halves
   const int tid = threadIdx.x;
@@ -225,7 +238,8 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
   const uint8_t* codes_lane = tab + wide_bn_code_offset((size_t)n_groups, 512) + (size_t)rb * n_pairs * 64 + (lane >> 3) * 8;
   (void)levels; (void)codes_lane;
   const uint8_t* idx_rb = P.idx + (size_t)rb * n_cb * 1024;
-  const int st = wave % (THREADS / 64) * 64;        // table duty of this wave: entries st + lane, st + lane + THREADS, .. of the two
+  using duty = Duty<KS>;
+  const int st = wave % (duty::THREADS / 64) * 64;  // table duty of this wave: entries st + lane, st + lane + THREADS, .. of the two
   const int p_begin = n_pairs * split / KS, p_end = n_pairs * (split + 1) / KS;
   const int steps = (n_pairs + KS - 1) / KS;        // of the longest split: all take as many barriers
 
@@ -234,11 +248,12 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
     const int c1_ld = c1 < n_cb ? c1 : c0;          // an absent second col-block re-reads the first (not used)
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
-      const int h = (st + i * THREADS) >> 8, e0 = (st + i * THREADS) & 255;
-      const long long g = grow * n_cb + (h == 0 ? c0 : c1_ld);
-      s.q[i] = reinterpret_cast<const uint16_t*>(tab + g * 512 + e0 * 2)[lane];
-      s.sc[i] = scales[g];
-      if constexpr (BN) s.lv[i] = levels[g * 16 + (lane & 15)];
+      const long long g = grow * n_cb + (duty::h(st, i) == 0 ? c0 : c1_ld);
+      s.q[i] = reinterpret_cast<const uint16_t*>(tab + g * 512 + duty::e0(st, i) * 2)[lane];
+      if (i % duty::PER_TABLE == 0) {
+        s.sc[i / duty::PER_TABLE] = scales[g];
+        if constexpr (BN) s.lv[i / duty::PER_TABLE] = levels[g * 16 + (lane & 15)];
+      }
     }
     s.w0 = reinterpret_cast<const uint4*>(idx_rb + (size_t)c0 * 1024)[lane];
     s.w1 = reinterpret_cast<const uint4*>(idx_rb + (size_t)c1_ld * 1024)[lane];
@@ -264,11 +279,11 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
     load(min(p + 1, p_last), nxt);
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
-      const int h = (st + i * THREADS) >> 8, e = ((st + i * THREADS) & 255) + lane;
+      const int h = duty::h(st, i), e = duty::e0(st, i) + lane;
       const bool mine = h == 0 || 2 * p + 1 < n_cb; // the absent col-block of an odd matrix gets a zero table
-      tabs[buf][h][e] = mine ? k64_dequant_pair(cur.q[i], __builtin_bit_cast(_Float16, (uint16_t)cur.sc[i])) : 0u;
+      tabs[buf][h][e] = mine ? k64_dequant_pair(cur.q[i], __builtin_bit_cast(_Float16, (uint16_t)cur.sc[i / duty::PER_TABLE])) : 0u;
       if constexpr (BN) {
-        if (e < 16) levs[buf][h][e] = mine ? cur.lv[i] * 0x10001u : 0u;
+        if (i % duty::PER_TABLE == 0 && e < 16) levs[buf][h][e] = mine ? cur.lv[i / duty::PER_TABLE] * 0x10001u : 0u;
       }
     }
     __syncthreads();   // tables of this step complete; the other buffer is free again
