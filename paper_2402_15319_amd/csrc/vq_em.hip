@@ -701,26 +701,13 @@ __global__ __launch_bounds__(256, (NCB == 1 ? em_waves<K, D>() : NCB == 8 ? 4 : 
 // all, and in brackets both with binary64 additions: d = 2, k = 64, 32 rows 67, 32 (75, 456); d = 2, k = 256, 8 rows 77,
 // 45 (72, 459), 128 rows 73, 39 (77, 501); d = 4, k = 256, 64 rows 69, 40 (81, 469).  Weights further apart than 2^kSpread:
 // 35 .. 64 for 28 .. 36 at 4096 x 4096.
-//   Counted tables (d = 4, k = 256, 128 rows and more) take a quick pass: one scale for the whole group, from the largest |x|
-// of its first 32 rows (with twice that and more found later, once more with that of all rows), instead of a maximum and a
-// look at it for every vector and entry (52 + 8 clocks of LDS a wave's vectors for 120), and each row is read once, four
-// rows a wave ahead, in 80 registers for three workgroups per CU instead of two.  A sum that is not 2^28 times its members'
-// roundings (it cancels, or they are small beside the group's largest; a centroid or so of 256) is formed again as
-// before, from its members alone: the assignment is read again, and of W those.  Infinities, NaN and weights further apart: entry by
-// entry.  us at 11008 x 4096, before, after: 256 rows 77 .. 82, 57 .. 61 (49 where nothing is formed again), 128 rows 80, 61; 4096 x
-// 4096, 256 rows 37.5, 34.7, every centroid twice 37.0, 38.3, rows 4 to 7 of 8 far from zero 46, 36, half of W zero 39, 39.
 // SHARED: 0, or for the workgroups of a coordinate (see below) log2 of the weights of their groups at most.
 template <int K, int D, int NG, int GPW, int RB, int SHARED>
 struct EmTables {
   static constexpr int kEntries = NG * K;
   static constexpr int kCopies = kEntries >= 64 ? 1 : 64 / kEntries;
   static constexpr int kStride = kEntries * kCopies;        // entries per quantity
-  // Counted: in tall groups with d = 4, k = 256 the weights' sums come from counts, 16 bits per centroid and vector position of a row for
-  // the whole item (at most 256 rows): one 32-bit atomic in place of eight, and den[t] = sum over the positions of
-  // count * h, exact products, at the end.
-  static constexpr bool kCounted = !SHARED && RB > 1 && K == 256 && D == 4;
-  static constexpr int kWords = 32;                         // dwords of counts per centroid: positions i and i + 32
-  static constexpr int kQuantities = kCounted ? D : SHARED ? 2 : 2 * D;
+  static constexpr int kQuantities = SHARED ? 2 : 2 * D;
   static constexpr int kTable = kQuantities * kStride;      // entries per item
   static constexpr int kMaxWaves = GPW > 1 ? GPW : SHARED > 14 ? 16 : 8;
   // an item has at most 2^kLog2N vectors; 51 bits are what the conversion below takes
@@ -739,6 +726,10 @@ __device__ __forceinline__ unsigned long long to_fixed(double v, uint32_t scale_
 }
 __device__ __forceinline__ double from_fixed(unsigned long long sum, int scale) {
   return (double)(long long)sum * __builtin_bit_cast(double, (uint64_t)scale << 52);
+}
+// h * x + 1.5 * 2^52, rounded once, as above (h holds the scale).
+__device__ __forceinline__ unsigned long long fixed_product(double h, double x) {
+  return __builtin_bit_cast(uint64_t, __builtin_fma(h, x, 0x1.8p52)) - 0x4338000000000000ull;
 }
 // An entry that has met infinities or NaN holds what it has met: 1 +inf, 2 -inf, 4 NaN.
 __device__ __forceinline__ void add_nonfinite(unsigned long long* sum, double v) {
@@ -770,7 +761,7 @@ __device__ __forceinline__ double wave_sum63(double v) {
 // chain of a wave's vectors, one after the other (figures at em_shared; shares of the codebook instead of coordinates
 // leave every wave its chain: 24.6 us for 12.4 at 512 x 512, 256 rows, and 41 for 28 at 2048 x 2048).
 template <int K, int D, int NG, int GPW, int RB, int SHARED>
-__global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWaves), (GPW > 1 ? 1 : EmTables<K, D, NG, GPW, RB, SHARED>::kCounted ? 6 : 4)) void em_update_kernel(
+__global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWaves), (GPW > 1 ? 1 : 4)) void em_update_kernel(
     const float* __restrict__ W, const float* __restrict__ hdiag, const uint8_t* __restrict__ assign,
     float* __restrict__ cb_out, int n_cb, long long n_items, int in_features, int n_rows) {
   static_assert(!SHARED || (GPW == 1 && NG == 1), "a workgroup has one group");
@@ -779,20 +770,15 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
   constexpr int V = 4 / D;                          // vectors per row and lane
   constexpr int N = V * DT;                         // values of a row and lane: DT of each vector
   constexpr int RPG = 8 / NG;                       // rows of an 8-row block that share a codebook
-  constexpr int RW = Tab::kCounted ? 1 : RB;        // 8-row blocks that a wave holds at a time
-  constexpr int CW = Tab::kWords + 1;               // a gap spreads the centroids over the banks
   constexpr uint32_t kNone = 0x100;
   __shared__ __attribute__((aligned(16))) unsigned long long sum_all[GPW * Tab::kTable];
   __shared__ uint32_t top_all[GPW * Tab::kTable];
-  __shared__ uint32_t counts[Tab::kCounted ? K * CW : 1];
-  __shared__ double h_all[Tab::kCounted ? 256 : 1];
   __shared__ double hot_sums[Tab::kMaxWaves][NG][2 * DT];
   __shared__ uint32_t hot_of[Tab::kMaxWaves][NG];
-  __shared__ uint32_t wave_top[Tab::kCounted ? Tab::kMaxWaves : 1], weak[Tab::kCounted ? K / 32 + 1 : 1];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int waves = GPW > 1 ? 1 : (int)blockDim.x / 64;   // of this item
-  const int parts = RB > 1 ? n_rows / (8 * RW * waves) : 1;   // what a wave takes one after the other, 8 * RW rows each
+  const int parts = RB > 1 ? n_rows / (8 * RB * waves) : 1;   // what a wave takes one after the other, 8 * RB rows each
   const int sub = GPW > 1 ? 0 : wave;               // this wave's place among them
   const int slot = GPW > 1 ? wave : 0;
   const int t_item = sub * 64 + lane, t_count = waves * 64;
@@ -803,7 +789,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
   if (GPW > 1 && item >= n_items) return;           // whole waves leave; no workgroup barrier with GPW > 1
   const long long ir = item / n_cb;                 // group row, or 8-row block where that holds several groups
   const int c = (int)(item - ir * n_cb);
-  const long long row0 = ir * (NG > 1 ? 8 : n_rows) + sub * 8 * RW;
+  const long long row0 = ir * (NG > 1 ? 8 : n_rows) + sub * 8 * RB;
   auto item_sync = [] {
     if constexpr (GPW > 1) wave_lds_sync();
     else __syncthreads();
@@ -829,44 +815,17 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
     else if constexpr (V == 2) ar = *reinterpret_cast<const uint16_t*>(ap);
     else ar = *ap;
   };
-  float x[8 * RW][N];
-  uint32_t a[8 * RW];
+  float x[8 * RB][N];
+  uint32_t a[8 * RB];
   auto load_part = [&](int p) {
 #pragma unroll
-    for (int r = 0; r < 8 * RW; ++r) load(p * waves * 8 * RW + r, x[r], a[r]);
+    for (int r = 0; r < 8 * RB; ++r) load(p * waves * 8 * RB + r, x[r], a[r]);
   };
-  // Counted: the quick pass streams parts of QR rows a wave
-  constexpr int QR = Tab::kCounted ? 4 : 1;
-  float xq[2][QR][4];
-  uint32_t mq[2][QR];
-  auto load_quick = [&](int p, float (&xr)[QR][4], uint32_t (&mr)[QR]) {
-    if constexpr (Tab::kCounted) {
-#pragma unroll
-      for (int r = 0; r < QR; ++r) {
-        const int row = (p >> 1) * 64 + 2 * r + (p & 1);
-        const float4 t = *reinterpret_cast<const float4*>(Wl + (size_t)row * in_features);
-        xr[r][0] = t.x; xr[r][1] = t.y; xr[r][2] = t.z; xr[r][3] = t.w;
-        mr[r] = al[(size_t)row * (in_features / D)];
-      }
-    }
-  };
-  auto clear = [&] {
-    for (int i = t_item; i < Tab::kTable; i += t_count) {
-      sums[i] = 0ull;
-      tops[i] = 0u;
-    }
-    if constexpr (Tab::kCounted) {
-      for (int i = t_item; i < K * CW; i += t_count) counts[i] = 0u;
-      if (t_item <= K / 32) weak[t_item] = 0u;
-    }
-  };
-  if constexpr (Tab::kCounted) {
-    load_quick(0, xq[0], mq[0]);
-    for (int i = t_item; i < 256; i += t_count) h_all[i] = hdiag[(size_t)c * 256 + i];
-  } else {
-    load_part(0);
+  load_part(0);
+  for (int i = t_item; i < Tab::kTable; i += t_count) {
+    sums[i] = 0ull;
+    tops[i] = 0u;
   }
-  clear();
   item_sync();
 
   const int copy = Tab::kCopies > 1 ? lane % Tab::kCopies : 0;
@@ -878,7 +837,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
     int most = 11;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const uint32_t m = ((Tab::kCounted ? mq[0][j % QR] : a[g * RPG + j % RPG]) & 0xffu);
+      const uint32_t m = (a[g * RPG + j % RPG] & 0xffu);
       const uint32_t asked = (uint32_t)__builtin_amdgcn_readlane((int)m, 8 * j + 3);
       const int n = __builtin_popcountll(__ballot(m == asked));
       if (n > most && (K == 256 || asked < (uint32_t)K)) { most = n; hot[g] = asked; }
@@ -903,115 +862,17 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
     any_h = !finite || h_exp < 32 || __builtin_bit_cast(uint32_t, small) >> 23 < h_exp - Tab::kSpread;
   }
   constexpr int P = Tab::kBits;
-  constexpr int PQ = 49;                            // of the quick pass: an entry holds 2^13 vectors, more are summed again
   auto finish = [&](int g, const double (&own)[2 * DT]) {   // the wave's sums of the centroid kept in registers
     if (hot[g] != kNone) {
 #pragma unroll
-      for (int q = 0; q < (Tab::kCounted ? DT : 2 * DT); ++q) {
+      for (int q = 0; q < 2 * DT; ++q) {
         const double sum = wave_sum63(own[q]);
         if (lane == 63) hot_sums[wave][g][q] = sum;
       }
     }
     if (lane == 63) hot_of[wave][g] = hot[g];
   };
-  auto count = [&](uint32_t m) {
-    if constexpr (Tab::kCounted) atomicAdd(counts + m * CW + (lane & 31), 1u << (16 * (lane >> 5)));
-  };
-  // The quick pass (counted tables): all entries scaled by the largest |x| of the first 32 rows, twice which the
-  // others may reach (checked).  Rows are read once, four a wave ahead of those that are added, and an entry takes no maximum and no look at it.
-  bool quick = Tab::kCounted && !any_h;
-  uint32_t x_exp = 0;                               // |x| < 2^(x_exp - 126)
-  double own_quick[2 * DT] = {};
-  if constexpr (Tab::kCounted) {
-    auto largest = [&](const float (&xr)[QR][4]) {   // NaN if there is one
-      float top = 0.f;
-#pragma unroll
-      for (int r = 0; r < QR; ++r)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) top = max_nn(top, __builtin_fabsf(xr[r][v]));
-      return top;
-    };
-    auto add = [&](const float (&xr)[QR][4], const uint32_t (&mr)[QR]) {
-      const uint32_t scale = (PQ + 1275u - h_exp - x_exp) << 20;
-#pragma unroll
-      for (int r = 0; r < QR; ++r) {
-        const uint32_t m = mr[r];
-        count(m);
-        if (m == hot[0]) {
-#pragma unroll
-          for (int t = 0; t < D; ++t) own_quick[t] += (double)h[t] * (double)xr[r][t];
-        } else {
-#pragma unroll
-          for (int t = 0; t < D; ++t) atomicAdd(sums + m * Tab::kCopies + t * Tab::kStride, to_fixed((double)h[t] * (double)xr[r][t], scale));
-        }
-      }
-    };
-    // the largest of the waves' values, to all of them
-    auto of_all = [&](float top) {
-      top = __any(!(top < __builtin_inff())) ? __builtin_inff() : -wave_min(-top);
-      if (lane == 0) wave_top[wave] = __builtin_bit_cast(uint32_t, top);
-      __syncthreads();
-      uint32_t all = 0;
-      for (int w = 0; w < waves; ++w) all = max(all, wave_top[w]);
-      return all;
-    };
-    const int n_parts = n_rows / 32;                // an even number
-    uint32_t all = 0;
-    if (quick) {
-      all = of_all(largest(xq[0]));
-      quick = all < 0x7f000000u;
-    }
-    if (quick) {
-      x_exp = (all >> 23) + 1;
-      const float limit = __builtin_bit_cast(float, min(x_exp + 1u, 254u) << 23);
-      bool over = false;
-#pragma unroll 1
-      for (int p = 0; p < n_parts; p += 2) {
-        load_quick(p + 1, xq[1], mq[1]);
-        over = over || __any(!(largest(xq[0]) < limit));
-        add(xq[0], mq[0]);
-        if (p + 2 < n_parts) load_quick(p + 2, xq[0], mq[0]);
-        over = over || __any(!(largest(xq[1]) < limit));
-        add(xq[1], mq[1]);
-        if (over) weak[K / 32] = 1u;
-        over = *(volatile uint32_t*)(weak + K / 32) != 0u;   // in any wave
-        if (over) break;
-      }
-      finish(0, own_quick);
-      __syncthreads();
-      if (weak[K / 32] != 0u) {                     // once more, with the largest of all rows
-        float top = 0.f;
-#pragma unroll 1
-        for (int p = 0; p < n_parts; p += 2) {
-          load_quick(p, xq[0], mq[0]);
-          load_quick(p + 1, xq[1], mq[1]);
-          top = max_nn(top, max_nn(largest(xq[0]), largest(xq[1])));
-        }
-        all = of_all(top);
-        clear();
-        quick = all < 0x7f000000u;
-        x_exp = all >> 23;
-#pragma unroll
-        for (int t = 0; t < D; ++t) own_quick[t] = 0.;
-        load_quick(0, xq[0], mq[0]);
-        __syncthreads();
-        if (quick) {
-#pragma unroll 1
-          for (int p = 0; p < n_parts; p += 2) {
-            load_quick(p + 1, xq[1], mq[1]);
-            add(xq[0], mq[0]);
-            if (p + 2 < n_parts) load_quick(p + 2, xq[0], mq[0]);
-            add(xq[1], mq[1]);
-          }
-          finish(0, own_quick);
-          __syncthreads();
-        }
-      }
-    }
-  }
-  const bool by_entry = any_h || (Tab::kCounted && !quick);
-  auto accumulate = [&] {
-  if (by_entry) {
+  if (any_h) {
     // Entries scaled by their largest |h x| and |h|, as high words of binary64 (|term| < 2^(field - 1022)).  Rare: rows are read
     // again one by one.
     if constexpr (NG > 1) {
@@ -1021,15 +882,14 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
     double own[2 * DT] = {};
     auto pass = [&](auto second) {
 #pragma unroll 1
-      for (int r = 0; r < 8 * RW * parts; ++r) {
+      for (int r = 0; r < 8 * RB * parts; ++r) {
         float xr[N];
         uint32_t ar;
-        load(RB > 1 ? r / (8 * RW) * waves * 8 * RW + r % (8 * RW) : r, xr, ar);
+        load(RB > 1 ? r / (8 * RB) * waves * 8 * RB + r % (8 * RB) : r, xr, ar);
 #pragma unroll
         for (int v = 0; v < V; ++v) {
           const uint32_t m = ((ar >> (8 * v)) & 0xffu);
           if (K < 256 && m >= (uint32_t)K) continue;
-          if constexpr (!decltype(second)::value) count(m);
           const bool kept = NG == 1 && m == hot[0];
           const int e = ((NG > 1 ? r / RPG : 0) * K + m) * Tab::kCopies + copy;
 #pragma unroll
@@ -1054,19 +914,18 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
     pass(std::true_type{});
 #pragma unroll
     for (int g = 0; g < NG; ++g) finish(g, own);
-  } else if constexpr (!Tab::kCounted) {
+  } else {
     // Entries scaled by their largest |x|, as binary32 (|x| < 2^(field - 126)), and all by the largest weight.
 #pragma unroll 1
     for (int p = 0; p < parts; ++p) {
       if (p > 0) load_part(p);
 #pragma unroll
-      for (int r = 0; r < 8 * RW; ++r) {
+      for (int r = 0; r < 8 * RB; ++r) {
         const int g = NG > 1 ? r / RPG : 0;
         const float (&xr)[N] = x[r];
 #pragma unroll
         for (int v = 0; v < V; ++v) {
           const uint32_t m = ((a[r] >> (8 * v)) & 0xffu);
-          count(m);
           if (m != hot[g] && (K == 256 || m < (uint32_t)K)) {
             uint32_t* e = tops + (g * K + m) * Tab::kCopies + copy;
 #pragma unroll
@@ -1085,7 +944,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
       if (p < parts - 1) load_part(p);
       // what this pass needs is computed again: kept from the first, it would not fit the registers
 #pragma unroll
-      for (int r = 0; r < 8 * RW; ++r)
+      for (int r = 0; r < 8 * RB; ++r)
       {
 #pragma unroll
         for (int t = 0; t < N; ++t) asm volatile("" : "+v"(x[r][t]));
@@ -1093,7 +952,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
       }
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
-        constexpr int ROWS = NG > 1 ? RPG : 8 * RW;
+        constexpr int ROWS = NG > 1 ? RPG : 8 * RB;
 #pragma unroll
         for (int r = g * ROWS; r < (g + 1) * ROWS; ++r) {
           const float (&xr)[N] = x[r];
@@ -1104,7 +963,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
 #pragma unroll
               for (int t = 0; t < DT; ++t) {
                 own[t] += (double)h[v * DT + t] * (double)xr[v * DT + t];
-                if constexpr (!Tab::kCounted) own[DT + t] += (double)h[v * DT + t];
+                own[DT + t] += (double)h[v * DT + t];
               }
             } else if (K == 256 || m < (uint32_t)K) {
               const int e = (g * K + m) * Tab::kCopies + copy;
@@ -1115,7 +974,7 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
                 const double hx = (double)h[v * DT + t] * (double)xr[v * DT + t];
                 if (top >= 0x7f800000u) add_nonfinite(sums + i, hx);
                 else atomicAdd(sums + i, to_fixed(hx, ((P + 1275u - h_exp) << 20) - ((top >> 3) & 0x0ff00000u)));
-                if constexpr (!Tab::kCounted) atomicAdd(sums + i + DT * Tab::kStride, h_fixed[v * DT + t]);
+                atomicAdd(sums + i + DT * Tab::kStride, h_fixed[v * DT + t]);
               }
             }
           }
@@ -1130,48 +989,6 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
     if constexpr (NG == 1) finish(0, own);
   }
   item_sync();
-  };
-  auto weights_from_counts = [&] {
-    for (int i = t_item; i < 2 * K; i += t_count) {   // two lanes per centroid
-      const int m = i >> 1, half = i & 1;
-      const uint32_t* n = counts + m * CW + half * (Tab::kWords / 2);
-      const double* hp = h_all + half * 4 * (Tab::kWords / 2);
-      double den[D] = {};
-      uint32_t members = 0;
-#pragma unroll 4
-      for (int w = 0; w < Tab::kWords / 2; ++w) {
-        const double lo = n[w] & 0xffffu, hi = n[w] >> 16;
-        members += (n[w] & 0xffffu) + (n[w] >> 16);
-#pragma unroll
-        for (int t = 0; t < D; ++t) den[t] += lo * hp[4 * w + t] + hi * hp[4 * w + 128 + t];
-      }
-#pragma unroll
-      for (int t = 0; t < D; ++t) {
-        if (den[t] != den[t]) {                     // 0 * infinity or NaN: such a weight counts only where it is used
-          den[t] = 0.;
-          for (int w = 0; w < Tab::kWords / 2; ++w) {
-            if (n[w] & 0xffffu) den[t] += (double)(n[w] & 0xffffu) * hp[4 * w + t];
-            if (n[w] >> 16) den[t] += (double)(n[w] >> 16) * hp[4 * w + 128 + t];
-          }
-        }
-      }
-#pragma unroll
-      for (int t = 0; t < D; ++t) den[t] += __shfl_xor(den[t], 1, 64);
-      members += __shfl_xor(members, 1, 64);
-      if (half == 0) {                              // in the place of the centroid's counts, which both lanes have read
-        uint32_t* out = counts + m * CW;
-#pragma unroll
-        for (int t = 0; t < D; ++t) {
-          const uint64_t u = __builtin_bit_cast(uint64_t, den[t]);
-          out[2 * t] = (uint32_t)u;
-          out[2 * t + 1] = (uint32_t)(u >> 32);
-        }
-        out[2 * D] = members;
-      }
-    }
-    item_sync();
-  };
-  auto write_centroids = [&] {
   for (int i = t_item; i < NG * K * DT; i += t_count) {
     const int e = i / DT, t = i % DT, g = e / K;
     double num = 0., den = 0.;
@@ -1179,95 +996,377 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
     for (int q = 0; q < Tab::kCopies; ++q) {
       const int p = t * Tab::kStride + e * Tab::kCopies + q, p_h = p + DT * Tab::kStride;
       const uint32_t top = tops[p];
-      if (by_entry) {
+      if (any_h) {
         if (top != 0) num += top >= 0x7ff00000u ? from_nonfinite(sums[p]) : from_fixed(sums[p], (int)(top >> 20) + 1 - P);
-        if constexpr (!Tab::kCounted) {
-          const uint32_t top_h = tops[p_h];
-          if (top_h != 0) den += top_h >= 0x7ff00000u ? from_nonfinite(sums[p_h]) : from_fixed(sums[p_h], (int)(top_h >> 20) + 1 - P);
-        }
-      } else if (Tab::kCounted && quick) {
-        num += from_fixed(sums[p], (int)x_exp + (int)h_exp + 771 - PQ);
+        const uint32_t top_h = tops[p_h];
+        if (top_h != 0) den += top_h >= 0x7ff00000u ? from_nonfinite(sums[p_h]) : from_fixed(sums[p_h], (int)(top_h >> 20) + 1 - P);
       } else {
         num += top >= 0x7f800000u ? from_nonfinite(sums[p]) : from_fixed(sums[p], (int)(top >> 23) + (int)h_exp + 771 - P);
-        if constexpr (!Tab::kCounted) den += from_fixed(sums[p_h], (int)h_exp + 897 - P);
+        den += from_fixed(sums[p_h], (int)h_exp + 897 - P);
       }
     }
-    int hot_in = 0;
     for (int w = 0; w < waves; ++w) {
       if (hot_of[wave - sub + w][g] == (uint32_t)(e % K)) {
-        ++hot_in;
         num += hot_sums[wave - sub + w][g][t];
-        if constexpr (!Tab::kCounted) den += hot_sums[wave - sub + w][g][DT + t];
+        den += hot_sums[wave - sub + w][g][DT + t];
       }
-    }
-    if constexpr (Tab::kCounted) {
-      den = __builtin_bit_cast(double, (uint64_t)counts[e * CW + 2 * t + 1] << 32 | counts[e * CW + 2 * t]);
-      // the members' roundings, half a unit each, against 2^-28 of their sum
-      const double unit = __builtin_bit_cast(double, (uint64_t)((int)x_exp + (int)h_exp + 771 - PQ) << 52);
-      const uint32_t members = counts[e * CW + 2 * D];
-      if (quick && hot_in < waves && !(__builtin_fabs(num) >= 0x1p27 * unit * (double)members && members <= 8192u)) atomicOr(weak + (e >> 5), 1u << (e & 31));
     }
     const long long gi = NG > 1 ? (ir * NG + g) * n_cb + c : item;
     cb_out[(gi * K + e % K) * D + t0 + t] = den != 0. ? (float)num / (float)den : 0.f;
   }
+}
+
+// M-step of tall groups (128 or 256 rows) with d = 4, k = 256, a workgroup of eight waves to a group.  As em_update_kernel, but:
+//   Counts: the weights' sums come from counts, 16 bits per centroid and vector position of a row for the whole group: one
+// 32-bit atomic in place of eight, and den[t] = sum over the positions of count * h, exact products, at the end.
+//   One scale for the whole group, from the largest |x| of the rows that are read first, every other one of the first 64
+// (with twice that and more found later, once more with that of all rows), instead of a maximum and a look at it for every vector and
+// entry (52 + 8 clocks of LDS a wave's vectors for 120), and each row is read once, four rows a wave ahead, in 78 registers
+// without spills for three workgroups per CU.  A sum that is not 2^28 times its members' roundings (it cancels, or they
+// are small beside the group's largest) is formed again from its members alone, at their own scale: the assignment is read again, and of W
+// those.  Infinities, NaN and weights further apart: entry by entry.  us at 11008 x 4096, two passes of em_update_kernel before, this kernel:
+// uniform assignments 256 rows 81, 56, 128 rows 80, 56; of the E-step 81, 51, 80, 51.  A kernel of its own, since the code of
+// em_update_kernel changed for every other instance where it had both (72 to 73 registers with d = 1, k = 64).
+__global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
+    const float* __restrict__ W, const float* __restrict__ hdiag, const uint8_t* __restrict__ assign,
+    float* __restrict__ cb_out, int n_cb, int in_features, int n_rows) {
+  constexpr int K = 256, D = 4, WAVES = 8;
+  constexpr int kWords = 32;                        // dwords of counts per centroid: positions i and i + 32
+  constexpr int CW = kWords + 1;                    // a gap spreads the centroids over the banks
+  constexpr int QR = 4;                             // rows that a wave reads ahead
+  constexpr int P = EmTables<K, D, 1, 1, 2, 0>::kBits, kSpread = EmTables<K, D, 1, 1, 2, 0>::kSpread;
+  constexpr int PQ = 49;                            // of the quick pass: an entry holds 2^13 vectors, more are summed again
+  constexpr uint32_t kNone = 0x100;
+  __shared__ __attribute__((aligned(16))) unsigned long long sums[D * K];
+  __shared__ uint32_t tops[D * K];
+  __shared__ uint32_t counts[K * CW];
+  __shared__ double h_all[256];
+  __shared__ double hot_sums[WAVES][D];
+  __shared__ uint32_t hot_of[WAVES], wave_top[WAVES], weak[K / 32], over;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int item = blockIdx.x;
+  const int ir = item / n_cb;
+  const int c = item - ir * n_cb;
+  const long long row0 = (long long)ir * n_rows + wave * 8;   // of each 64 rows a wave has eight
+  const float* Ww = W + (size_t)row0 * in_features + (size_t)c * 256;   // the wave's (all of an address but the lane's part is uniform)
+  const uint8_t* aw = assign + (size_t)row0 * (in_features / D) + (size_t)c * 64;
+  // What is made of the lane is not to be kept: an address of 64 bits per row, for one, would not fit the registers.
+  auto not_kept = [](uint32_t v) {
+    asm volatile("" : "+v"(v));
+    return v;
   };
-  if (!quick) accumulate();
-  if constexpr (Tab::kCounted) weights_from_counts();
-  write_centroids();
-  if constexpr (Tab::kCounted) {
-    if (!quick) return;
+  auto weights = [&](int row) {
+    return *reinterpret_cast<const float4*>(reinterpret_cast<const uint8_t*>(Ww + (size_t)row * in_features) + not_kept(lane * 16));
+  };
+  auto centroid = [&](int row) { return (uint32_t)*(aw + (size_t)row * (in_features / D) + not_kept(lane)); };
+  const float4 h4 = reinterpret_cast<const float4*>(hdiag + (size_t)c * 256)[lane];
+  float xq[2][QR][4];
+  uint32_t mq[2][QR];
+  auto load = [&](int p, float (&xr)[QR][4], uint32_t (&mr)[QR]) {   // every other one of the wave's rows in 64
+#pragma unroll
+    for (int r = 0; r < QR; ++r) {
+      const int row = (p >> 1) * 64 + 2 * r + (p & 1);
+      const float4 t = weights(row);
+      xr[r][0] = t.x; xr[r][1] = t.y; xr[r][2] = t.z; xr[r][3] = t.w;
+      mr[r] = centroid(row);
+    }
+  };
+  auto clear = [&] {
+    const int t = not_kept(tid);
+    for (int i = t; i < D * K; i += 512) sums[i] = 0ull;
+    for (int i = t; i < K * CW; i += 512) counts[i] = 0u;
+    if (tid == 0) over = 0u;
+  };
+  auto clear_tops = [&] {
+    for (int i = not_kept(tid); i < D * K; i += 512) tops[i] = 0u;
+  };
+  load(0, xq[0], mq[0]);
+  const float h[4] = {h4.x, h4.y, h4.z, h4.w};
+  if (tid < 256) h_all[tid] = hdiag[(size_t)c * 256 + tid];
+  if (tid < K / 32) weak[tid] = 0u;
+  clear();
+
+  // the centroid that the most lanes of a row share, among a few that are asked
+  uint32_t hot = kNone;
+  int most = 11;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const uint32_t m = mq[0][j % QR];
+    const uint32_t asked = (uint32_t)__builtin_amdgcn_readlane((int)m, 8 * j + 3);
+    const int n = __builtin_popcountll(__ballot(m == asked));
+    if (n > most) { most = n; hot = asked; }
+  }
+  if (lane == 0) hot_of[wave] = hot;
+
+  // are the weights of the col-block finite and near each other (every wave sees the same ones)
+  uint32_t h_exp;                                   // exponent field of the largest
+  bool any_h;
+  {
+    float big = 0.f, small = __builtin_inff();
+#pragma unroll
+    for (int t = 0; t < D; ++t) {
+      const float v = __builtin_fabsf(h[t]);
+      big = max_nn(big, v);
+      small = __builtin_fminf(small, v == 0.f ? __builtin_inff() : v);
+    }
+    const bool finite = !__any(!(big < __builtin_inff()));
+    big = -wave_min(finite ? -big : 0.f);
+    small = wave_min(finite ? small : 0.f);
+    h_exp = __builtin_bit_cast(uint32_t, big) >> 23;
+    any_h = !finite || h_exp < 32 || __builtin_bit_cast(uint32_t, small) >> 23 < h_exp - kSpread;
+  }
+  auto largest = [&](const float (&xr)[QR][4]) {    // NaN if there is one
+    float top = 0.f;
+#pragma unroll
+    for (int r = 0; r < QR; ++r)
+#pragma unroll
+      for (int t = 0; t < D; ++t) top = max_nn(top, __builtin_fabsf(xr[r][t]));
+    return top;
+  };
+  // the largest of the waves' values, to all of them, infinity for NaN
+  auto of_all = [&](float top) {
+    top = __any(!(top < __builtin_inff())) ? __builtin_inff() : -wave_min(-top);
+    if (lane == 0) wave_top[wave] = __builtin_bit_cast(uint32_t, top);
     __syncthreads();
-    uint32_t some = 0;
-    for (int w = 0; w < K / 32; ++w) some |= weak[w];
-    if (some == 0) return;
-    // Centroids whose sums cancel, or whose members are far smaller than the largest, are summed once more at the scale of
-    // their own members.
-    auto is_weak = [&](uint32_t m) { return (weak[m >> 5] >> (m & 31) & 1u) != 0; };
-    uint32_t mr[4][8];
+    uint32_t all = 0;
 #pragma unroll
-    for (int p = 0; p < 4; ++p)
-      if (p < n_rows / 64) {
+    for (int w = 0; w < WAVES; ++w) all = max(all, wave_top[w]);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
+  };
+  auto count = [&](uint32_t m) { atomicAdd(counts + m * CW + (lane & 31), 1u << (16 * (lane >> 5))); };
+  auto finish = [&](const double (&own)[D], double scale) {   // the wave's sums of the centroid kept in registers
+    if (hot != kNone) {
 #pragma unroll
-        for (int r = 0; r < 8; ++r) mr[p][r] = al[(size_t)(p * 64 + r) * (in_features / D)];
+      for (int t = 0; t < D; ++t) {
+        const double sum = wave_sum63(own[t]);
+        if (lane == 63) hot_sums[wave][t] = sum * scale;
       }
-    auto members = [&](auto f) {
+    }
+  };
+
+  __syncthreads();
+  uint32_t all = of_all(largest(xq[0]));
+  bool quick = !any_h && all < 0x7f000000u;
+  uint32_t x_exp = (all >> 23) + 1;             // |x| < 2^(x_exp - 126)
+  float limit = __builtin_bit_cast(float, min(x_exp + 1u, 254u) << 23);
+  while (quick) {                                   // once, or twice
+    double hs[D], own[D] = {};
+    const double scale = __builtin_bit_cast(double, (uint64_t)(PQ + 1275u - h_exp - x_exp) << 52);
 #pragma unroll
-      for (int p = 0; p < 4; ++p)
-        if (p < n_rows / 64) {
-          float4 v[8];
+    for (int t = 0; t < D; ++t) hs[t] = h_all[4 * lane + t] * scale;
+    auto add = [&](const float (&xr)[QR][4], const uint32_t (&mr)[QR]) {
 #pragma unroll
-          for (int r = 0; r < 8; ++r)
-            if (is_weak(mr[p][r])) v[r] = *reinterpret_cast<const float4*>(Wl + (size_t)(p * 64 + r) * in_features);
+      for (int r = 0; r < QR; ++r) {
+        const uint32_t m = mr[r];
+        count(m);
+        if (m == hot) {
 #pragma unroll
-          for (int r = 0; r < 8; ++r)
-            if (is_weak(mr[p][r])) {
-              const float xr[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
+          for (int t = 0; t < D; ++t) own[t] += hs[t] * (double)xr[r][t];
+        } else {
 #pragma unroll
-              for (int t = 0; t < D; ++t) f(mr[p][r] + t * Tab::kStride, t, xr[t]);
-            }
+          for (int t = 0; t < D; ++t) atomicAdd(sums + t * K + m, fixed_product(hs[t], (double)xr[r][t]));
         }
+      }
     };
-    for (int i = t_item; i < K * D; i += t_count) {
-      if (is_weak(i % K)) {
-        sums[i] = 0ull;
-        tops[i] = 0u;
+    const int n_parts = n_rows / 32;                // an even number
+    bool past = false;
+#pragma unroll 1
+    for (int p = 0; p < n_parts; p += 2) {
+      load(p + 1, xq[1], mq[1]);
+      past = past || __any(!(largest(xq[0]) < limit));
+      add(xq[0], mq[0]);
+      if (p + 2 < n_parts) load(p + 2, xq[0], mq[0]);
+      past = past || __any(!(largest(xq[1]) < limit));
+      add(xq[1], mq[1]);
+      if (past) over = 1u;
+      past = __hip_atomic_load(&over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0u;   // in any wave
+      if (past) break;
+    }
+    finish(own, __builtin_bit_cast(double, (uint64_t)(771u - PQ + h_exp + x_exp) << 52));
+    __syncthreads();
+    if (over == 0u) break;
+    float top = 0.f;                                // once more, with the largest of all rows
+#pragma unroll 1
+    for (int p = 0; p < n_parts; p += 2) {
+      load(p, xq[0], mq[0]);
+      load(p + 1, xq[1], mq[1]);
+      top = max_nn(top, max_nn(largest(xq[0]), largest(xq[1])));
+    }
+    all = of_all(top);
+    clear();
+    quick = all < 0x7f000000u;
+    x_exp = all >> 23;
+    limit = __builtin_inff();
+    load(0, xq[0], mq[0]);
+    __syncthreads();
+  }
+  if (!quick) {
+    // Entries scaled by their largest |h x|, as high words of binary64 (|term| < 2^(field - 1022)).  Rare: rows are read
+    // again one by one.
+    clear();
+    clear_tops();
+    __syncthreads();
+    double own[D] = {};
+    auto pass = [&](auto second) {
+#pragma unroll 1
+      for (int r = 0; r < n_rows / WAVES; ++r) {
+        const int row = (r >> 3) * 64 + (r & 7);
+        const float4 x4 = weights(row);
+        const float xr[4] = {x4.x, x4.y, x4.z, x4.w};
+        const uint32_t m = centroid(row);
+        if constexpr (!decltype(second)::value) count(m);
+#pragma unroll
+        for (int t = 0; t < D; ++t) {
+          const double term = h_all[4 * lane + t] * (double)xr[t];
+          const int e = t * K + m;
+          if constexpr (!decltype(second)::value) {
+            if (m != hot) atomicMax(tops + e, high_magnitude(term));
+          } else if (m == hot) {
+            own[t] += term;
+          } else {
+            const uint32_t top = tops[e];
+            if (top >= 0x7ff00000u) add_nonfinite(sums + e, term);
+            else atomicAdd(sums + e, to_fixed(term, ((P + 2045u) << 20) - (top & 0x7ff00000u)));
+          }
+        }
+      }
+    };
+    pass(std::false_type{});
+    __syncthreads();
+    pass(std::true_type{});
+    finish(own, 1.);
+    __syncthreads();
+  }
+
+  // Two lanes per centroid: the weights' sums of half the positions each, then two coordinates each.
+  const int m = not_kept(tid) >> 1, half = tid & 1;
+  double den[2];
+  uint32_t members = 0;
+  {
+    const uint32_t* n = counts + m * CW + half * (kWords / 2);
+    const double* hp = h_all + half * 4 * (kWords / 2);
+    double part[D] = {};
+#pragma unroll 4
+    for (int w = 0; w < kWords / 2; ++w) {
+      const double lo = n[w] & 0xffffu, hi = n[w] >> 16;
+      members += (n[w] & 0xffffu) + (n[w] >> 16);
+#pragma unroll
+      for (int t = 0; t < D; ++t) part[t] += lo * hp[4 * w + t] + hi * hp[4 * w + 128 + t];
+    }
+#pragma unroll
+    for (int t = 0; t < D; ++t) {
+      if (part[t] != part[t]) {                     // 0 * infinity or NaN: such a weight counts only where it is used
+        part[t] = 0.;
+        for (int w = 0; w < kWords / 2; ++w) {
+          if (n[w] & 0xffffu) part[t] += (double)(n[w] & 0xffffu) * hp[4 * w + t];
+          if (n[w] >> 16) part[t] += (double)(n[w] >> 16) * hp[4 * w + 128 + t];
+        }
+      }
+      part[t] += __shfl_xor(part[t], 1, 64);
+    }
+    members += __shfl_xor(members, 1, 64);
+    den[0] = half ? part[2] : part[0];
+    den[1] = half ? part[3] : part[1];
+  }
+  // num: of its two coordinates, the sums in the tables
+  auto write = [&](const double (&num)[2]) {
+    double total[2] = {num[0], num[1]};
+    int kept = 0;                                   // waves that have their part of it in registers
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+      if (hot_of[w] == (uint32_t)m) {
+        ++kept;
+        total[0] += hot_sums[w][2 * half];
+        total[1] += hot_sums[w][2 * half + 1];
       }
     }
-    __syncthreads();
-    members([&](uint32_t e, int, float xv) { atomicMax(tops + e, __builtin_bit_cast(uint32_t, xv) & 0x7fffffffu); });
-    __syncthreads();
-    members([&](uint32_t e, int t, float xv) {
-      atomicAdd(sums + e, to_fixed((double)h[t] * (double)xv, ((P + 1275u - h_exp) << 20) - ((tops[e] >> 3) & 0x0ff00000u)));
-    });
-    __syncthreads();
-    for (int i = t_item; i < K * D; i += t_count) {
-      const int m = i / D, t = i % D, e = m + t * Tab::kStride;
-      if (is_weak(m)) {
-        const double den = __builtin_bit_cast(double, (uint64_t)counts[m * CW + 2 * t + 1] << 32 | counts[m * CW + 2 * t]);
-        const double num = from_fixed(sums[e], (int)(tops[e] >> 23) + (int)h_exp + 771 - P);
-        cb_out[(item * K + m) * D + t] = den != 0. ? (float)num / (float)den : 0.f;
+    float2 out;
+    out.x = den[0] != 0. ? (float)total[0] / (float)den[0] : 0.f;
+    out.y = den[1] != 0. ? (float)total[1] / (float)den[1] : 0.f;
+    *reinterpret_cast<float2*>(cb_out + ((long long)item * K + m) * D + 2 * half) = out;
+    return kept;
+  };
+  const int e0 = 2 * half * K + m;                  // of its first coordinate; the second follows K entries later
+  double num[2];
+  bool exact = members <= 8192u;                    // 2^28 times its members' roundings, half a unit each
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int e = e0 + j * K;
+    if (quick) {
+      num[j] = from_fixed(sums[e], (int)x_exp + (int)h_exp + 771 - PQ);
+      const unsigned long long size = (long long)sums[e] < 0 ? 0ull - sums[e] : sums[e];
+      exact = exact && size >= (unsigned long long)members << 27;
+    } else {
+      const uint32_t top = tops[e];
+      num[j] = top == 0 ? 0. : top >= 0x7ff00000u ? from_nonfinite(sums[e]) : from_fixed(sums[e], (int)(top >> 20) + 1 - P);
+    }
+  }
+  const int kept = write(num);
+  if (!quick) return;
+  if (kept < WAVES && !exact) atomicOr(weak + (m >> 5), 1u << (m & 31));
+  __syncthreads();
+  uint32_t some = 0;
+#pragma unroll
+  for (int w = 0; w < K / 32; ++w) some |= weak[w];
+  if (some == 0) return;
+
+  // The sums that are not are formed again, at the scale of their own members.
+  auto is_weak = [&](uint32_t v) { return (weak[v >> 5] >> (v & 31) & 1u) != 0; };
+  if (is_weak(m)) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      sums[e0 + j * K] = 0ull;
+      tops[e0 + j * K] = 0u;
+    }
+  }
+  uint32_t rows = 0;                                // the wave's rows with a vector of theirs in this lane
+#pragma unroll 1
+  for (int p = 0; p < n_rows / 64; ++p) {
+    uint32_t v[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) v[r] = centroid(p * 64 + r);
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      if (v[r] != hot && is_weak(v[r])) rows |= 1u << (8 * p + r);
+  }
+  auto again = [&](auto f) {
+#pragma unroll 1
+    for (int p = 0; p < n_rows / 64; ++p) {
+      const uint32_t here = rows >> (8 * p);
+      if (!__any((here & 0xffu) != 0)) continue;
+      float4 x[8];
+      uint32_t v[8];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        if (here >> r & 1u) {
+          x[r] = weights(p * 64 + r);
+          v[r] = centroid(p * 64 + r);
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        if (here >> r & 1u) {
+          f(v[r], 0, x[r].x);
+          f(v[r] + K, 1, x[r].y);
+          f(v[r] + 2 * K, 2, x[r].z);
+          f(v[r] + 3 * K, 3, x[r].w);
+        }
       }
     }
+  };
+  __syncthreads();
+  again([&](uint32_t e, int, float xv) { atomicMax(tops + e, __builtin_bit_cast(uint32_t, xv) & 0x7fffffffu); });
+  __syncthreads();
+  again([&](uint32_t e, int t, float xv) {
+    atomicAdd(sums + e, to_fixed(h_all[4 * lane + t] * (double)xv, ((P + 1275u - h_exp) << 20) - ((tops[e] >> 3) & 0x0ff00000u)));
+  });
+  __syncthreads();
+  if (is_weak(m)) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) num[j] = from_fixed(sums[e0 + j * K], (int)(tops[e0 + j * K] >> 23) + (int)h_exp + 771 - P);
+    write(num);
   }
 }
 
@@ -1544,9 +1643,14 @@ static void launch_update(const vq_desc& d, const void* W, const void* hdiag, co
       return;
     }
   }
-  hipLaunchKernelGGL((em_update_kernel<K, D, NG, GPW, RB, 0>), dim3((unsigned)((n_items + GPW - 1) / GPW)), dim3(64 * waves), 0, s,
-                     (const float*)W, (const float*)hdiag, (const uint8_t*)assign, (float*)cb_out, n_cb, n_items,
-                     d.in_features, d.group_rows);
+  if constexpr (K == 256 && D == 4 && RB > 1) {
+    hipLaunchKernelGGL(em_update_counted_kernel, dim3((unsigned)n_items), dim3(512), 0, s, (const float*)W, (const float*)hdiag,
+                       (const uint8_t*)assign, (float*)cb_out, n_cb, d.in_features, d.group_rows);
+  } else {
+    hipLaunchKernelGGL((em_update_kernel<K, D, NG, GPW, RB, 0>), dim3((unsigned)((n_items + GPW - 1) / GPW)), dim3(64 * waves), 0, s,
+                       (const float*)W, (const float*)hdiag, (const uint8_t*)assign, (float*)cb_out, n_cb, n_items,
+                       d.in_features, d.group_rows);
+  }
 }
 
 // Up to 8 rows a group to a wave and four waves to a workgroup; beyond that a workgroup to a group, a wave to 8 rows up to
