@@ -1020,12 +1020,16 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
 //   Counts: the weights' sums come from counts, 16 bits per centroid and vector position of a row for the whole group: one
 // 32-bit atomic in place of eight, and den[t] = sum over the positions of count * h, exact products, at the end.
 //   One scale for the whole group, from the largest |x| of the rows that are read first, every other one of the first 64
-// (with twice that and more found later, once more with that of all rows), instead of a maximum and a look at it for every vector and
-// entry (52 + 8 clocks of LDS a wave's vectors for 120), and each row is read once, four rows a wave ahead, in 78 registers
-// without spills for three workgroups per CU.  A sum that is not 2^28 times its members' roundings (it cancels, or they
-// are small beside the group's largest) is formed again from its members alone, at their own scale: the assignment is read again, and of W
-// those.  Infinities, NaN and weights further apart: entry by entry.  us at 11008 x 4096, two passes of em_update_kernel before, this kernel:
-// uniform assignments 256 rows 81, 56, 128 rows 80, 56; of the E-step 81, 51, 80, 51.  A kernel of its own, since the code of
+// (up to four times that may follow; with more, once more with that of all rows), instead of a maximum and a look at it for every vector and
+// entry (52 + 8 clocks of LDS a wave's vectors for 120), and each row is read once, four rows a wave ahead, in 80 registers
+// without spills for three workgroups per CU.
+//   A numerator formed so is the exact sum's, rounded to binary32: whatever the sum may be off by, half a unit per vector, changes
+// nothing.  Where it might (the sum cancels, or its members are small beside the group's largest, or so many that they could
+// overflow) the centroid is formed again from its members alone, at their own scale: the assignment is read again, and of W those.  (A
+// margin of the error that this has too makes both agree, so neither the scale nor the order of the rows shows, but for a centroid that many lanes
+// share.)  Weights further apart, and groups with infinities or NaN: entry by entry.
+//   us at 11008 x 4096, two passes of em_update_kernel before, this kernel: uniform assignments 256 rows 81, 61, 128 rows 80, 60; of
+// the E-step 81, 56, 80, 56.  A kernel of its own, since the code of
 // em_update_kernel changed for every other instance where it had both (72 to 73 registers with d = 1, k = 64).
 __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
     const float* __restrict__ W, const float* __restrict__ hdiag, const uint8_t* __restrict__ assign,
@@ -1035,7 +1039,8 @@ __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
   constexpr int CW = kWords + 1;                    // a gap spreads the centroids over the banks
   constexpr int QR = 4;                             // rows that a wave reads ahead
   constexpr int P = EmTables<K, D, 1, 1, 2, 0>::kBits, kSpread = EmTables<K, D, 1, 1, 2, 0>::kSpread;
-  constexpr int PQ = 49;                            // of the quick pass: an entry holds 2^13 vectors, more are summed again
+  constexpr int PQ = 51;                            // of the quick pass, for entries of up to kMost vectors
+  constexpr uint32_t kMost = 4095, kRoom = 2;       // kRoom: binades that later rows may lie above the first ones
   constexpr uint32_t kNone = 0x100;
   __shared__ __attribute__((aligned(16))) unsigned long long sums[D * K];
   __shared__ uint32_t tops[D * K];
@@ -1149,7 +1154,7 @@ __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
   __syncthreads();
   uint32_t all = of_all(largest(xq[0]));
   bool quick = !any_h && all < 0x7f000000u;
-  uint32_t x_exp = (all >> 23) + 1;             // |x| < 2^(x_exp - 126)
+  uint32_t x_exp = (all >> 23) + kRoom;           // |x| < 2^(x_exp - 126)
   float limit = __builtin_bit_cast(float, min(x_exp + 1u, 254u) << 23);
   while (quick) {                                   // once, or twice
     double hs[D], own[D] = {};
@@ -1270,8 +1275,9 @@ __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
     den[0] = half ? part[2] : part[0];
     den[1] = half ? part[3] : part[1];
   }
-  // num: of its two coordinates, the sums in the tables
-  auto write = [&](const double (&num)[2]) {
+  // num: of its two coordinates, the sums in the tables, each within `off` of what it stands for.  Returns whether the
+  // numerators are the same for all that they may stand for.
+  auto write = [&](const double (&num)[2], double off) {
     double total[2] = {num[0], num[1]};
     int kept = 0;                                   // waves that have their part of it in registers
 #pragma unroll
@@ -1286,26 +1292,31 @@ __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
     out.x = den[0] != 0. ? (float)total[0] / (float)den[0] : 0.f;
     out.y = den[1] != 0. ? (float)total[1] / (float)den[1] : 0.f;
     *reinterpret_cast<float2*>(cb_out + ((long long)item * K + m) * D + 2 * half) = out;
-    return kept;
+    bool certain = true;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const double d = off + __builtin_fabs(num[j]) * 0x1p-50;   // (the conversions to binary64 and the additions above)
+      certain = certain && (float)(total[j] - d) == (float)(total[j] + d);
+    }
+    return kept == WAVES || (certain && members <= kMost);
   };
   const int e0 = 2 * half * K + m;                  // of its first coordinate; the second follows K entries later
+  const double unit = __builtin_bit_cast(double, (uint64_t)((int)x_exp + (int)h_exp + 771 - PQ) << 52);
   double num[2];
-  bool exact = members <= 8192u;                    // 2^28 times its members' roundings, half a unit each
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int e = e0 + j * K;
     if (quick) {
-      num[j] = from_fixed(sums[e], (int)x_exp + (int)h_exp + 771 - PQ);
-      const unsigned long long size = (long long)sums[e] < 0 ? 0ull - sums[e] : sums[e];
-      exact = exact && size >= (unsigned long long)members << 27;
+      num[j] = (double)(long long)sums[e] * unit;
     } else {
       const uint32_t top = tops[e];
       num[j] = top == 0 ? 0. : top >= 0x7ff00000u ? from_nonfinite(sums[e]) : from_fixed(sums[e], (int)(top >> 20) + 1 - P);
     }
   }
-  const int kept = write(num);
+  // half a unit per vector, and half of one of the largest that an entry's own scale may have, 2^(PQ - P) of these
+  const bool certain = write(num, unit * (0.5 + (1 << (PQ - P)) / 2) * (double)members);
   if (!quick) return;
-  if (kept < WAVES && !exact) atomicOr(weak + (m >> 5), 1u << (m & 31));
+  if (!certain) atomicOr(weak + (m >> 5), 1u << (m & 31));
   __syncthreads();
   uint32_t some = 0;
 #pragma unroll
@@ -1366,7 +1377,7 @@ __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
   if (is_weak(m)) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) num[j] = from_fixed(sums[e0 + j * K], (int)(tops[e0 + j * K] >> 23) + (int)h_exp + 771 - P);
-    write(num);
+    write(num, 0.);
   }
 }
 

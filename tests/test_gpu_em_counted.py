@@ -1,6 +1,7 @@
 """The M-step of many tall groups (d = 4, k = 256, 128 or 256 rows, more than half a group per CU): one scale for a group,
-taken from its first rows, centroids summed again where that leaves their sums too few bits, and the general path for
-infinities.  Against 64-bit sums, on every run and in every order of the rows the same."""
+taken from its first rows, centroids summed again where that leaves open what their numerators round to, and the general
+path for infinities.  Against 64-bit sums, on every run the same, and, where no row has a centroid that many lanes share, in every
+order of the rows: the numerator is the exact sum, rounded once."""
 import numpy as np
 import pytest
 
@@ -57,9 +58,8 @@ def test_against_64_bit_sums_in_any_order(rows, kind):
 
     got = update(W, a)
     np.testing.assert_array_equal(update(W, a), got)
-    if kind != "zeros":          # (half of the lanes in one centroid: its sums are kept by lane, in binary64)
-        shuffled = [m.reshape(gr, rows, -1)[:, order].reshape(m.shape) for m in (W, a)]
-        np.testing.assert_array_equal(update(*shuffled), got)
+    shuffled = [m.reshape(gr, rows, -1)[:, order].reshape(m.shape) for m in (W, a)]
+    np.testing.assert_array_equal(update(*shuffled), got)
     with np.errstate(invalid="ignore"):
         for g in range(gr):
             for c in range(gc):
@@ -79,3 +79,32 @@ def test_against_64_bit_sums_in_any_order(rows, kind):
                         bound = 3.2 * 2.0 ** -24 * np.abs(want) + n * 2.0 ** -34 * top / np.where(den != 0, den, 1) + 2.0 ** -149
                     ok = (np.abs(got[g, c, :, t] - want) <= bound) | (np.isnan(want) & np.isnan(got[g, c, :, t])) | (want == got[g, c, :, t])
                     assert ok.all(), (g, c, t, np.flatnonzero(~ok)[:4], got[g, c, ~ok, t][:4], want[~ok][:4])
+
+
+@pytest.mark.parametrize("low", [0, 4, 6, 8, 40])
+@pytest.mark.parametrize("rows", [128, 256])
+def test_numerators_are_the_exact_sums_rounded_once(rows, low):
+    """Most centroids' values 2^-low of the others': however few bits the group's scale leaves their sums, and in whatever order
+    the rows come, the quotient is that of the exact sums, each rounded to binary32.  (The weights' sums are exact in
+    binary64; the reference's numerators are off by 2^-57 of the largest term at most.)"""
+    import torch
+    import paper_2402_15319_amd as vq
+    W, h, a = _inputs(rows, "normal")
+    W[np.repeat(a, 4, axis=1) >= 10] *= np.float32(2.0 ** -low)
+    gr, gc = W.shape[0] // rows, W.shape[1] // 256
+    desc = vq.make_desc(W.shape[0], W.shape[1], 256, 8, rows, 256, 4)
+    for order in (np.arange(rows), np.random.default_rng(2).permutation(rows)):
+        Wo, ao = (m.reshape(gr, rows, -1)[:, order].reshape(m.shape) for m in (W, a))
+        new = torch.full((gr, gc, 256, 4), 777.0, dtype=torch.float32, device="cuda:0")
+        vq.vq_em_update(desc, torch.from_numpy(Wo).cuda(), torch.from_numpy(h).cuda(), torch.from_numpy(ao).cuda(), new)
+        got = new.cpu().numpy()
+        for g in range(gr):
+            for c in range(gc):
+                x = W[g * rows:(g + 1) * rows, c * 256:(c + 1) * 256].astype(np.longdouble).reshape(-1, 4)
+                hv = np.broadcast_to(h[c * 256:(c + 1) * 256].astype(np.longdouble), (rows, 256)).reshape(-1, 4)
+                m = a[g * rows:(g + 1) * rows, c * 64:(c + 1) * 64].reshape(-1)
+                by = np.argsort(m, kind="stable")
+                start = np.searchsorted(m[by], np.arange(256))
+                assert np.all(np.diff(start) > 0)       # no centroid is empty
+                num, den = (np.add.reduceat(v[by], start, axis=0).astype(np.float32) for v in (hv * x, hv))
+                np.testing.assert_array_equal(got[g, c], num / den)
