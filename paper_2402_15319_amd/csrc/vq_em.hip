@@ -1020,16 +1020,21 @@ __global__ __launch_bounds__((64 * EmTables<K, D, NG, GPW, RB, SHARED>::kMaxWave
 //   Counts: the weights' sums come from counts, 16 bits per centroid and vector position of a row for the whole group: one
 // 32-bit atomic in place of eight, and den[t] = sum over the positions of count * h, exact products, at the end.
 //   One scale for the whole group, from the largest |x| of the rows that are read first, every other one of the first 64
-// (up to four times that may follow; with more, once more with that of all rows), instead of a maximum and a look at it for every vector and
+// (up to four times that may follow, see below), instead of a maximum and a look at it for every vector and
 // entry (52 + 8 clocks of LDS a wave's vectors for 120), and each row is read once, four rows a wave ahead, in 80 registers
 // without spills for three workgroups per CU.
 //   A numerator formed so is the exact sum's, rounded to binary32: whatever the sum may be off by, half a unit per vector, changes
 // nothing.  Where it might (the sum cancels, or its members are small beside the group's largest, or so many that they could
-// overflow) the centroid is formed again from its members alone, at their own scale: the assignment is read again, and of W those.  (A
-// margin of the error that this has too makes both agree, so neither the scale nor the order of the rows shows, but for a centroid that many lanes
-// share.)  Weights further apart, and groups with infinities or NaN: entry by entry.
-//   us at 11008 x 4096, two passes of em_update_kernel before, this kernel: uniform assignments 256 rows 81, 61, 128 rows 80, 60; of
-// the E-step 81, 56, 80, 56.  A kernel of its own, since the code of
+// overflow) the centroid is formed again from its members alone, at their own scale: the assignment is read again, and of W those, the next
+// eight of a lane's at a time (one chain of memory round trips; row by row in chunks it took 13 us of a group).  A margin of the error
+// that this has too makes both agree, so neither the scale nor the order of the rows shows, but for a centroid that many lanes
+// share.  A vector beyond the scale, an infinity or a NaN has its centroid formed again; where more than 16 lanes of a wave meet
+// such ones in four rows, the group is taken once more with the scale of all its rows.  Weights further apart: entry by entry.
+//   us, two passes of em_update_kernel before, this kernel, at 11008 x 4096, 256 rows; 128 rows; 4096 x 4096, 256 rows; 128 rows:
+// uniform assignments 81, 51; 81, 54; 34, 25; 36, 27; of the E-step 81, 50; 81, 51; 34, 24; 36, 26; a few values 30 times as
+// large 81, 55; 80, 63; 37, 28; 36, 28; half of W zero, of the E-step 86, 62; 85, 71; 37, 36; 37, 32; odd rows 400 times the even
+// ones (twice taken) 81, 75; 80, 84; 36, 34; 35, 41; all sums zero (all formed again) 81, 117; 80, 118; 37, 57; 35, 49.
+//   A kernel of its own, since the code of
 // em_update_kernel changed for every other instance where it had both (72 to 73 registers with d = 1, k = 64).
 __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
     const float* __restrict__ W, const float* __restrict__ hdiag, const uint8_t* __restrict__ assign,
@@ -1048,9 +1053,8 @@ __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
   __shared__ double h_all[256];
   __shared__ double hot_sums[WAVES][D];
   __shared__ uint32_t hot_of[WAVES], wave_top[WAVES], weak[K / 32], over;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int item = blockIdx.x;
   const int ir = item / n_cb;
   const int c = item - ir * n_cb;
@@ -1062,6 +1066,7 @@ __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
     asm volatile("" : "+v"(v));
     return v;
   };
+  auto thread = [&] { return (int)not_kept(lane) + wave * 64; };
   auto weights = [&](int row) {
     return *reinterpret_cast<const float4*>(reinterpret_cast<const uint8_t*>(Ww + (size_t)row * in_features) + not_kept(lane * 16));
   };
@@ -1079,18 +1084,18 @@ __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
     }
   };
   auto clear = [&] {
-    const int t = not_kept(tid);
+    const int t = thread();
+    if (t < K / 32) weak[t] = 0u;
     for (int i = t; i < D * K; i += 512) sums[i] = 0ull;
     for (int i = t; i < K * CW; i += 512) counts[i] = 0u;
-    if (tid == 0) over = 0u;
+    if (t == 0) over = 0u;
   };
   auto clear_tops = [&] {
-    for (int i = not_kept(tid); i < D * K; i += 512) tops[i] = 0u;
+    for (int i = thread(); i < D * K; i += 512) tops[i] = 0u;
   };
   load(0, xq[0], mq[0]);
   const float h[4] = {h4.x, h4.y, h4.z, h4.w};
-  if (tid < 256) h_all[tid] = hdiag[(size_t)c * 256 + tid];
-  if (tid < K / 32) weak[tid] = 0u;
+  if (wave < 4) h_all[wave * 64 + lane] = hdiag[(size_t)c * 256 + wave * 64 + lane];
   clear();
 
   // the centroid that the most lanes of a row share, among a few that are asked
@@ -1130,15 +1135,15 @@ __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
       for (int t = 0; t < D; ++t) top = max_nn(top, __builtin_fabsf(xr[r][t]));
     return top;
   };
-  // the largest of the waves' values, to all of them, infinity for NaN
-  auto of_all = [&](float top) {
-    top = __any(!(top < __builtin_inff())) ? __builtin_inff() : -wave_min(-top);
+  // The exponent field of the largest of the workgroup's lanes', of those that are below 2^127.
+  auto exponent_of_all = [&](float top) {
+    top = -wave_min(top < 0x1p127f ? -top : 0.f);
     if (lane == 0) wave_top[wave] = __builtin_bit_cast(uint32_t, top);
     __syncthreads();
     uint32_t all = 0;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) all = max(all, wave_top[w]);
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)(all >> 23));
   };
   auto count = [&](uint32_t m) { atomicAdd(counts + m * CW + (lane & 31), 1u << (16 * (lane >> 5))); };
   auto finish = [&](const double (&own)[D], double scale) {   // the wave's sums of the centroid kept in registers
@@ -1152,16 +1157,30 @@ __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
   };
 
   __syncthreads();
-  uint32_t all = of_all(largest(xq[0]));
-  bool quick = !any_h && all < 0x7f000000u;
-  uint32_t x_exp = (all >> 23) + kRoom;           // |x| < 2^(x_exp - 126)
-  float limit = __builtin_bit_cast(float, min(x_exp + 1u, 254u) << 23);
-  while (quick) {                                   // once, or twice
+  uint32_t x_exp = exponent_of_all(largest(xq[0])) + kRoom;   // |x| < 2^(x_exp - 126)
+  bool again = false;
+  while (!any_h) {                                  // once, or twice
+    float limit = __builtin_bit_cast(float, min(x_exp + 1u, 254u) << 23), seen = 0.f;
     double hs[D], own[D] = {};
     const double scale = __builtin_bit_cast(double, (uint64_t)(PQ + 1275u - h_exp - x_exp) << 52);
 #pragma unroll
     for (int t = 0; t < D; ++t) hs[t] = h_all[4 * lane + t] * scale;
-    auto add = [&](const float (&xr)[QR][4], const uint32_t (&mr)[QR]) {
+    auto add = [&](float (&xr)[QR][4], const uint32_t (&mr)[QR]) {
+      const float top = largest(xr);
+      seen = max_nn(seen, top);
+      if (__any(!(top < limit))) {                  // rare: such a vector's centroid is formed again
+        if (!again && __builtin_popcountll(__ballot(!(top < limit))) > 16) over = 1u;   // ... all of them, if they are many
+#pragma unroll
+        for (int r = 0; r < QR; ++r) {
+          const float v = max_nn(max_nn(__builtin_fabsf(xr[r][0]), __builtin_fabsf(xr[r][1])),
+                                 max_nn(__builtin_fabsf(xr[r][2]), __builtin_fabsf(xr[r][3])));
+          if (!(v < limit) && mr[r] != hot) {
+            atomicOr(weak + (mr[r] >> 5), 1u << (mr[r] & 31));
+#pragma unroll
+            for (int t = 0; t < D; ++t) xr[r][t] = 0.f;
+          }
+        }
+      }
 #pragma unroll
       for (int r = 0; r < QR; ++r) {
         const uint32_t m = mr[r];
@@ -1176,38 +1195,31 @@ __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
       }
     };
     const int n_parts = n_rows / 32;                // an even number
-    bool past = false;
+    int p = 0;
 #pragma unroll 1
-    for (int p = 0; p < n_parts; p += 2) {
+    for (; p < n_parts; p += 2) {
       load(p + 1, xq[1], mq[1]);
-      past = past || __any(!(largest(xq[0]) < limit));
       add(xq[0], mq[0]);
       if (p + 2 < n_parts) load(p + 2, xq[0], mq[0]);
-      past = past || __any(!(largest(xq[1]) < limit));
       add(xq[1], mq[1]);
-      if (past) over = 1u;
-      past = __hip_atomic_load(&over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0u;   // in any wave
-      if (past) break;
+      if (__hip_atomic_load(&over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0u) break;   // in any wave
     }
     finish(own, __builtin_bit_cast(double, (uint64_t)(771u - PQ + h_exp + x_exp) << 52));
     __syncthreads();
     if (over == 0u) break;
-    float top = 0.f;                                // once more, with the largest of all rows
+    again = true;                                   // once more, with the largest of all rows
 #pragma unroll 1
-    for (int p = 0; p < n_parts; p += 2) {
+    for (p += 2; p < n_parts; p += 2) {
       load(p, xq[0], mq[0]);
       load(p + 1, xq[1], mq[1]);
-      top = max_nn(top, max_nn(largest(xq[0]), largest(xq[1])));
+      seen = max_nn(seen, max_nn(largest(xq[0]), largest(xq[1])));
     }
-    all = of_all(top);
+    x_exp = exponent_of_all(seen);
     clear();
-    quick = all < 0x7f000000u;
-    x_exp = all >> 23;
-    limit = __builtin_inff();
     load(0, xq[0], mq[0]);
     __syncthreads();
   }
-  if (!quick) {
+  if (any_h) {
     // Entries scaled by their largest |h x|, as high words of binary64 (|term| < 2^(field - 1022)).  Rare: rows are read
     // again one by one.
     clear();
@@ -1246,7 +1258,7 @@ __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
   }
 
   // Two lanes per centroid: the weights' sums of half the positions each, then two coordinates each.
-  const int m = not_kept(tid) >> 1, half = tid & 1;
+  const int i_thread = thread(), m = i_thread >> 1, half = i_thread & 1;
   double den[2];
   uint32_t members = 0;
   {
@@ -1306,16 +1318,15 @@ __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int e = e0 + j * K;
-    if (quick) {
+    if (!any_h) {
       num[j] = (double)(long long)sums[e] * unit;
     } else {
       const uint32_t top = tops[e];
       num[j] = top == 0 ? 0. : top >= 0x7ff00000u ? from_nonfinite(sums[e]) : from_fixed(sums[e], (int)(top >> 20) + 1 - P);
     }
   }
-  // half a unit per vector, and half of one of the largest that an entry's own scale may have, 2^(PQ - P) of these
-  const bool certain = write(num, unit * (0.5 + (1 << (PQ - P)) / 2) * (double)members);
-  if (!quick) return;
+  const bool certain = write(num, unit * (double)members);   // half a unit per vector, twice
+  if (any_h) return;
   if (!certain) atomicOr(weak + (m >> 5), 1u << (m & 31));
   __syncthreads();
   uint32_t some = 0;
@@ -1323,7 +1334,8 @@ __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
   for (int w = 0; w < K / 32; ++w) some |= weak[w];
   if (some == 0) return;
 
-  // The sums that are not are formed again, at the scale of their own members.
+  // Those that are not are formed again, at the scale of their own members.
+  const uint32_t bits = members <= kMost ? PQ : P;
   auto is_weak = [&](uint32_t v) { return (weak[v >> 5] >> (v & 31) & 1u) != 0; };
   if (is_weak(m)) {
 #pragma unroll
@@ -1331,52 +1343,72 @@ __global__ __launch_bounds__(512, 6) void em_update_counted_kernel(
       sums[e0 + j * K] = 0ull;
       tops[e0 + j * K] = 0u;
     }
+    counts[m * CW + kWords] = bits;
   }
   uint32_t rows = 0;                                // the wave's rows with a vector of theirs in this lane
-#pragma unroll 1
-  for (int p = 0; p < n_rows / 64; ++p) {
-    uint32_t v[8];
+  {
+    uint32_t v[32];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) v[r] = centroid(p * 64 + r);
+    for (int r = 0; r < 32; ++r)
+      if (r < n_rows / WAVES) v[r] = centroid((r >> 3) * 64 + (r & 7));
 #pragma unroll
-    for (int r = 0; r < 8; ++r)
-      if (v[r] != hot && is_weak(v[r])) rows |= 1u << (8 * p + r);
+    for (int r = 0; r < 32; ++r)
+      if (r < n_rows / WAVES && v[r] != hot && is_weak(v[r])) rows |= 1u << r;
   }
-  auto again = [&](auto f) {
-#pragma unroll 1
-    for (int p = 0; p < n_rows / 64; ++p) {
-      const uint32_t here = rows >> (8 * p);
-      if (!__any((here & 0xffu) != 0)) continue;
-      float4 x[8];
-      uint32_t v[8];
+  // The next eight of a lane's, all at a time.
+  float4 x[8];
+  uint32_t v[8];
+  auto fetch = [&](uint32_t left) {
 #pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        if (here >> r & 1u) {
-          x[r] = weights(p * 64 + r);
-          v[r] = centroid(p * 64 + r);
-        }
+    for (int b = 0; b < 8; ++b) {
+      v[b] = kNone;
+      if (left != 0) {
+        const int r = __builtin_ctz(left), row = (r >> 3) * 64 + (r & 7);
+        x[b] = *reinterpret_cast<const float4*>(Ww + (size_t)row * in_features + 4 * lane);
+        v[b] = aw[(size_t)row * (in_features / D) + lane];
+        left &= left - 1;
       }
+    }
+    return left;
+  };
+  auto all_of = [&](auto f) {
 #pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        if (here >> r & 1u) {
-          f(v[r], 0, x[r].x);
-          f(v[r] + K, 1, x[r].y);
-          f(v[r] + 2 * K, 2, x[r].z);
-          f(v[r] + 3 * K, 3, x[r].w);
-        }
+    for (int b = 0; b < 8; ++b) {
+      if (v[b] != kNone) {
+        f(v[b], 0, x[b].x);
+        f(v[b], 1, x[b].y);
+        f(v[b], 2, x[b].z);
+        f(v[b], 3, x[b].w);
       }
     }
   };
   __syncthreads();
-  again([&](uint32_t e, int, float xv) { atomicMax(tops + e, __builtin_bit_cast(uint32_t, xv) & 0x7fffffffu); });
+  uint32_t todo = rows, left;
+  while (true) {
+    left = fetch(todo);
+    all_of([&](uint32_t v, int t, float xv) { atomicMax(tops + t * K + v, __builtin_bit_cast(uint32_t, xv) & 0x7fffffffu); });
+    if (!__any(left != 0)) break;
+    todo = left;
+  }
+  todo = rows & ~todo;                              // (the last ones are at hand)
   __syncthreads();
-  again([&](uint32_t e, int t, float xv) {
-    atomicAdd(sums + e, to_fixed(h_all[4 * lane + t] * (double)xv, ((P + 1275u - h_exp) << 20) - ((tops[e] >> 3) & 0x0ff00000u)));
-  });
+  while (true) {
+    all_of([&](uint32_t v, int t, float xv) {
+      const uint32_t top = tops[t * K + v];
+      const double hx = h_all[4 * lane + t] * (double)xv;
+      if (top >= 0x7f800000u) add_nonfinite(sums + t * K + v, hx);
+      else atomicAdd(sums + t * K + v, to_fixed(hx, ((counts[v * CW + kWords] + 1275u - h_exp) << 20) - ((top >> 3) & 0x0ff00000u)));
+    });
+    if (!__any(todo != 0)) break;
+    todo = fetch(todo);
+  }
   __syncthreads();
   if (is_weak(m)) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) num[j] = from_fixed(sums[e0 + j * K], (int)(tops[e0 + j * K] >> 23) + (int)h_exp + 771 - P);
+    for (int j = 0; j < 2; ++j) {
+      const uint32_t top = tops[e0 + j * K];
+      num[j] = top >= 0x7f800000u ? from_nonfinite(sums[e0 + j * K]) : from_fixed(sums[e0 + j * K], (int)(top >> 23) + (int)h_exp + 771 - (int)bits);
+    }
     write(num, 0.);
   }
 }

@@ -108,3 +108,67 @@ def test_numerators_are_the_exact_sums_rounded_once(rows, low):
                 assert np.all(np.diff(start) > 0)       # no centroid is empty
                 num, den = (np.add.reduceat(v[by], start, axis=0).astype(np.float32) for v in (hv * x, hv))
                 np.testing.assert_array_equal(got[g, c], num / den)
+
+
+def _update_and_compare(W, h, a, rows):
+    """One call and a second one, which gives the same, against 64-bit sums: numerator, denominator and quotient rounded once
+    each, and sums of n terms that are off by n * 2^-34 of the largest (n * 2^-52 in the kernel, more in the reference)."""
+    import torch
+    import paper_2402_15319_amd as vq
+    gr, gc = W.shape[0] // rows, W.shape[1] // 256
+    desc = vq.make_desc(W.shape[0], W.shape[1], 256, 8, rows, 256, 4)
+    args = [torch.from_numpy(v).cuda() for v in (W, h, a)]
+    runs = []
+    for _ in range(2):
+        new = torch.full((gr, gc, 256, 4), 777.0, dtype=torch.float32, device="cuda:0")
+        vq.vq_em_update(desc, *args, new)
+        runs.append(new.cpu().numpy())
+    got = runs[0]
+    np.testing.assert_array_equal(runs[1], got)
+    with np.errstate(invalid="ignore", over="ignore", divide="ignore"):
+        for g in range(gr):
+            for c in range(gc):
+                x = W[g * rows:(g + 1) * rows, c * 256:(c + 1) * 256].astype(np.float64).reshape(-1, 4)
+                hv = np.broadcast_to(h[c * 256:(c + 1) * 256].astype(np.float64), (rows, 256)).reshape(-1, 4)
+                m = a[g * rows:(g + 1) * rows, c * 64:(c + 1) * 64].reshape(-1)
+                n = np.bincount(m, minlength=256)
+                for t in range(4):
+                    num, den = np.bincount(m, hv[:, t] * x[:, t], 256), np.bincount(m, hv[:, t], 256)
+                    want = np.where(den != 0, num.astype(np.float32) / den.astype(np.float32), np.float32(0))
+                    top = np.zeros(256)
+                    np.maximum.at(top, m, np.abs(hv[:, t] * x[:, t]))
+                    bound = 3.2 * 2.0 ** -24 * np.abs(want) + n * 2.0 ** -34 * top / np.where(den != 0, den, 1) + 2.0 ** -149
+                    ok = (np.abs(got[g, c, :, t] - want) <= bound) | (np.isnan(want) & np.isnan(got[g, c, :, t])) | (want == got[g, c, :, t])
+                    assert ok.all(), (g, c, t, np.flatnonzero(~ok)[:4], got[g, c, ~ok, t][:4], want[~ok][:4])
+    return got
+
+
+@pytest.mark.parametrize("kind", ["few", "few, first rows too", "lanes at the line", "group", "group and infinities", "beyond 2^127"])
+@pytest.mark.parametrize("rows", [128, 256])
+def test_values_beyond_the_scale(rows, kind):
+    """Values that the scale from the first rows leaves no room for: a few, whose centroids are formed again; so many (17 lanes
+    of a wave) that the group is taken once more; some that no scale takes."""
+    W, h, a = _inputs(rows, "normal")
+    group = W.reshape(-1, rows, W.shape[1])
+    if kind == "few":
+        group[:, rows // 2::7, 5::301] *= 60
+        group[::3, rows - 1, 9] = 1e30
+    elif kind == "few, first rows too":              # infinities in the sample: the others give the scale
+        group[::2, 0, 7], group[::2, 2, 300], group[1::2, 4, 1000] = np.inf, np.nan, 1e30
+        group[:, 1, 5::301] *= 60
+    elif kind == "lanes at the line":
+        group[::2, 9, :4 * 16:4] = 5                 # 16 lanes of one wave: formed again; 17: the group once more
+        group[1::2, 9, :4 * 17:4] = 5
+    elif kind == "group":
+        group[:, rows // 2:] *= 50
+    elif kind == "group and infinities":
+        group[:, rows // 2:] *= 50
+        group[::2, rows // 2 + 3, 5], group[::3, 3, 9], group[::5, rows - 1, 700] = np.inf, -np.inf, np.nan
+    elif kind == "beyond 2^127":
+        h[:] = np.minimum(h, 0.5)
+        group[:, 2, 4], group[::2, 64, 300] = 2e38, -3e38
+    got = _update_and_compare(W, h, a, rows)
+    # where the scale comes from the same rows or not: the same in another order
+    order = np.random.default_rng(3).permutation(rows)
+    W2, a2 = (v.reshape(-1, rows, v.shape[1])[:, order].reshape(v.shape) for v in (W, a))
+    np.testing.assert_array_equal(_update_and_compare(W2, h, a2, rows), got)
