@@ -172,3 +172,39 @@ def test_values_beyond_the_scale(rows, kind):
     order = np.random.default_rng(3).permutation(rows)
     W2, a2 = (v.reshape(-1, rows, v.shape[1])[:, order].reshape(v.shape) for v in (W, a))
     np.testing.assert_array_equal(_update_and_compare(W2, h, a2, rows), got)
+
+
+@pytest.mark.parametrize("kind", ["one centroid", "half of the lanes", "half of the lanes, cancelling", "kept by some waves",
+                                  "kept by some waves, cancelling", "more than an entry holds", "infinite weights", "no weights"])
+@pytest.mark.parametrize("rows", [128, 256])
+def test_skewed_assignments_and_weights(rows, kind):
+    """Centroids that many lanes of a row share, whose sums a wave keeps in registers: all waves, or those whose first rows
+    have it; entries with more vectors than their bits take; weights that are infinite, NaN or zero."""
+    W, h, a = _inputs(rows, "normal")
+    group, ga = W.reshape(-1, rows, W.shape[1]), a.reshape(-1, rows, a.shape[1])
+    first = np.arange(rows) % 64 < 32                # rows of waves 0 to 3
+    if kind == "one centroid":
+        a[:] = 200
+    elif kind.startswith("half of the lanes"):
+        a[:, 1::2] = 3
+        if "cancelling" in kind:
+            group[:, 1::2] = -group[:, ::2]
+            ga[:, 1::2] = ga[:, ::2]
+    elif kind.startswith("kept by some waves"):      # and in the table by the others
+        ga[:, first, ::3] = 77
+        ga[:, ~first, 5::9] = 77
+        if "cancelling" in kind:
+            group[:, 1::2] = -group[:, ::2]
+            ga[:, 1::2] = ga[:, ::2]
+    elif kind == "more than an entry holds":         # not in the rows that the waves look at first: 3 / 4 of the group's vectors
+        group[:] = np.abs(group) / 64 + np.float32(0.49)
+        group[:, 64:] *= 4                           # as far as the scale reaches, all of one sign
+        ga[:, 64:] = 9
+        h[:] = 1.96875
+    elif kind == "infinite weights":
+        h[4:8], h[132:136], h[300], h[700] = np.inf, np.nan, np.inf, -np.inf
+        W[:, 700] = 1
+    elif kind == "no weights":
+        h[:300] = 0
+        h[512:520] = 0
+    _update_and_compare(W, h, a, rows)
