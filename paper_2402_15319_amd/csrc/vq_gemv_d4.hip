@@ -33,9 +33,14 @@
 namespace vq {
 namespace {
 
-// The 64-row item of a workgroup of an unsplit launch.  Workgroups go to the eight XCDs in turn; the four items of a 256-row
-// group read the same tables, so each aligned 32 workgroups put four neighbouring items on one XCD, whose L2 then serves
-// three of the four reads.
+// The 64-row item of a workgroup.  Workgroups go to the eight XCDs in turn; the four items of a 256-row group read the same
+// tables, so each aligned 32 workgroups put four neighbouring items on one XCD, whose L2 then serves three of the four reads.
+// 4 layers of 4096 / 11008 in one launch, d = 4, in the order of the workgroups and in this one: what the L2s fetch, by
+// counter, 145 -> 109 MiB with fp16 tables and 121 -> 103 with int8 (of 2 KB and 1 KB a group), us 50.2 -> 45.3 and 48.8 -> 48.6; 32000 x
+// 4096 11.8 -> 10.6 and 11.7 -> 10.4, with block scales 15.7 -> 14.9; 16 products of 11008 x 4096 45.2 -> 41.7 and 43.3 -> 43.4.  Where
+// fewer rows share a table it only spreads the reads over memory differently: 64 rows, 512 items of 2048 columns 5.8 -> 6.4
+// (fp16 tables 5.8 -> 7.0), 1024 of 8192 30.8 -> 35.2, 128 rows 5.8 -> 6.3; so it does for k = 256, d = 2, whose tables are 512 bytes (205
+// -> 196 MiB): 256 rows, 32000 x 4096 17.5 -> 19.2, 16 of 4096 x 4096 31.0 -> 32.4.
 __device__ __forceinline__ int item_of_workgroup(int b, int total) {
   return (b | 31) < total ? (b & ~31) | (b & 7) << 2 | ((b >> 3) & 3) : b;
 }
@@ -69,7 +74,7 @@ struct D4Step {
 // with a scale.  MODE 2 (BN): int8 tables with blockwise normalisation (appendix "Blockwise data
 // normalization"): the group's 16 block-scale levels sit next to its table in LDS, and per row
 // the looked-up vector is multiplied by the scale of the lane's 32-weight block before the dot2.
-template <bool LORA, int MODE, int CAP, int KS>
+template <bool LORA, int MODE, int CAP, int KS, bool XCD>
 __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LORA, CAP>::type arg) {
   constexpr bool F16 = MODE == 1, BN = MODE == 2;
   const auto& batch = base_of(arg);
@@ -79,7 +84,7 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int item = KS == 1 ? item_of_workgroup((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x / KS;
+  const int item = XCD ? item_of_workgroup((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x / KS;
   const int pi = find_problem(batch, item);
   const GemvItem P = item_of(batch, pi);
   const int oct = item - P.wg_begin;                // which 64 rows
@@ -212,7 +217,7 @@ struct K256Step {
 };
 
 // BN: with blockwise normalisation; the plain C++ inner block replaces the hand-scheduled one.
-template <bool LORA, bool BN, int CAP, int KS>
+template <bool LORA, bool BN, int CAP, int KS, bool = false>
 __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf<LORA, CAP>::type arg) {
   const auto& batch = base_of(arg);
   constexpr int RBW = 8 / KS;                       // row-blocks of a workgroup
@@ -221,7 +226,7 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int item = KS == 1 ? item_of_workgroup((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x / KS;
+  const int item = (int)blockIdx.x / KS;
   const int pi = find_problem(batch, item);
   const GemvItem P = item_of(batch, pi);
   const int oct = item - P.wg_begin;                // which 64 rows
@@ -361,46 +366,60 @@ static int wide_splits(const GemvBatch& b, int fmt) {
   return pairs >= 4 && !(f16 && pairs >= 8 && pairs < 16) ? 2 : 1;
 }
 
-// (kernel, template arguments before CAP)
-#define VQ_LAUNCH_WIDE(KERNEL, ...)                                                                              \
+// Whether neighbouring items go to one XCD (figures at item_of_workgroup): where all groups have 256 rows, but not up to two
+// items of 2048 columns per CU (512: 5.8 -> 6.3 us, fp16 tables 5.8 -> 6.2; 640 of 2304 9.8 -> 9.2, 512 of 4096 10.7 -> 10.0).
+static bool neighbours_by_xcd(const GemvBatch& b) {
+  int widest = 0;
+  for (int i = 0; i < b.count; ++i) {
+    if (b.p[i].rb_per_cb != 32) return false;
+    widest = max(widest, b.p[i].n_cb);
+  }
+  return widest > 8 || b.total_wgs > 2 * (long long)device_cus();
+}
+
+// (kernel, whether it has a variant for neighbours_by_xcd, template arguments before CAP)
+#define VQ_LAUNCH_WIDE(KERNEL, XCD, ...)                                                                         \
   do {                                                                                                           \
     const int ks = wide_splits(base_of_host(batch), fmt);                                                        \
     const dim3 grid((unsigned)(total_wgs * ks));                                                                 \
-    if (base_of_host(batch).count > kFewProblems)                                                                \
-      hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kMaxProblemsPerLaunch, 1>), grid, dim3(512), 0, s, batch);         \
-    else if (ks == 8) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFewProblems, 8>), grid, dim3(512), 0, s, few_problems(batch)); \
-    else if (ks == 4) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFewProblems, 4>), grid, dim3(512), 0, s, few_problems(batch)); \
-    else if (ks == 2) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFewProblems, 2>), grid, dim3(512), 0, s, few_problems(batch)); \
-    else hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFewProblems, 1>), grid, dim3(512), 0, s, few_problems(batch)); \
+    const bool xcd = XCD && neighbours_by_xcd(base_of_host(batch));                                              \
+    if (base_of_host(batch).count > kFewProblems) {                                                              \
+      if (xcd) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kMaxProblemsPerLaunch, 1, XCD>), grid, dim3(512), 0, s, batch); \
+      else hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kMaxProblemsPerLaunch, 1, false>), grid, dim3(512), 0, s, batch); \
+    } else if (ks == 8) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFewProblems, 8, false>), grid, dim3(512), 0, s, few_problems(batch)); \
+    else if (ks == 4) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFewProblems, 4, false>), grid, dim3(512), 0, s, few_problems(batch)); \
+    else if (ks == 2) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFewProblems, 2, false>), grid, dim3(512), 0, s, few_problems(batch)); \
+    else if (xcd) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFewProblems, 1, XCD>), grid, dim3(512), 0, s, few_problems(batch)); \
+    else hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFewProblems, 1, false>), grid, dim3(512), 0, s, few_problems(batch)); \
   } while (0)
 
 hipError_t launch_gemv_k256i8(const GemvBatch& batch, int total_wgs, hipStream_t s, int fmt) {
-  if (fmt == kFmtK256I8BN) VQ_LAUNCH_WIDE(gemv_k256i8_kernel, false, true);
-  else if (fmt == kFmtK256I8) VQ_LAUNCH_WIDE(gemv_k256i8_kernel, false, false);
+  if (fmt == kFmtK256I8BN) VQ_LAUNCH_WIDE(gemv_k256i8_kernel, false, false, true);
+  else if (fmt == kFmtK256I8) VQ_LAUNCH_WIDE(gemv_k256i8_kernel, false, false, false);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 hipError_t launch_gemv_d4(const GemvBatch& batch, int total_wgs, hipStream_t s, int fmt) {
-  if (fmt == kFmtD4F16) VQ_LAUNCH_WIDE(gemv_d4_kernel, false, 1);
-  else if (fmt == kFmtD4BN) VQ_LAUNCH_WIDE(gemv_d4_kernel, false, 2);
-  else if (fmt == kFmtD4) VQ_LAUNCH_WIDE(gemv_d4_kernel, false, 0);
+  if (fmt == kFmtD4F16) VQ_LAUNCH_WIDE(gemv_d4_kernel, true, false, 1);
+  else if (fmt == kFmtD4BN) VQ_LAUNCH_WIDE(gemv_d4_kernel, true, false, 2);
+  else if (fmt == kFmtD4) VQ_LAUNCH_WIDE(gemv_d4_kernel, true, false, 0);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 // The same kernels with the low-rank adapter term added to every row before it is stored.
 hipError_t launch_gemv_k256i8_lora(const GemvBatchLora& batch, int total_wgs, hipStream_t s, int fmt) {
-  if (fmt == kFmtK256I8BN) VQ_LAUNCH_WIDE(gemv_k256i8_kernel, true, true);
-  else if (fmt == kFmtK256I8) VQ_LAUNCH_WIDE(gemv_k256i8_kernel, true, false);
+  if (fmt == kFmtK256I8BN) VQ_LAUNCH_WIDE(gemv_k256i8_kernel, false, true, true);
+  else if (fmt == kFmtK256I8) VQ_LAUNCH_WIDE(gemv_k256i8_kernel, false, true, false);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 hipError_t launch_gemv_d4_lora(const GemvBatchLora& batch, int total_wgs, hipStream_t s, int fmt) {
-  if (fmt == kFmtD4F16) VQ_LAUNCH_WIDE(gemv_d4_kernel, true, 1);
-  else if (fmt == kFmtD4BN) VQ_LAUNCH_WIDE(gemv_d4_kernel, true, 2);
-  else if (fmt == kFmtD4) VQ_LAUNCH_WIDE(gemv_d4_kernel, true, 0);
+  if (fmt == kFmtD4F16) VQ_LAUNCH_WIDE(gemv_d4_kernel, true, true, 1);
+  else if (fmt == kFmtD4BN) VQ_LAUNCH_WIDE(gemv_d4_kernel, true, true, 2);
+  else if (fmt == kFmtD4) VQ_LAUNCH_WIDE(gemv_d4_kernel, true, true, 0);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

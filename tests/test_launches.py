@@ -140,6 +140,21 @@ def test_wide_gemv_splits(launches):
     assert wrong == []
 
 
+def test_neighbouring_items_on_one_xcd(launches):
+    """The order of workgroups that lets 64-row items share their tables in an L2: unsplit launches of d = 4 whose groups have 256
+    rows, but for short launches of up to 2048 columns (times at the rule); no variant of any other kernel."""
+    def d4(rows, dtype=vq.VQ_I8):
+        return (rows, 4, 256, dtype)
+    cases = [(d4(256), [32768], [2304], True), (d4(256), [32768], [2048], False), (d4(256), [33024], [2048], True),
+             (d4(128), [32768], [4096], False), (d4(64), [32768], [4096], False), (d4(256), [4096], [4096], False),   # (the last is split)
+             (d4(256), [1024] * 5, [4096] * 5, True), (d4(128), [1024] * 5, [4096] * 5, False), (d4(256), [1024] * 5, [1024] * 5, False),
+             (d4(256, vq.VQ_F16), [32000], [4096], True), (d4(256, vq.VQ_I8_BN), [32000], [4096], True),
+             ((256, 2, 256, vq.VQ_I8), [32000], [4096], False), ((256, 2, 256, vq.VQ_I8_BN), [11008] * 5, [4096] * 5, False)]
+    for op in ("gemv", "lora"):
+        got = launches([(op, outs, ins, *fmt) for fmt, outs, ins, _ in cases])
+        assert [(st, ls[-1][0].split("EEEv")[0].endswith("Lb1")) for st, ls in got] == [(0, want) for *_, want in cases]
+
+
 def test_no_call_allocates(launches):
     """Many products, of widths in any order (the tall-group formats start the widest first), with and without adapters."""
     widths = [256, 2304, 768, 2304, 512, 1280, 4096] * 30

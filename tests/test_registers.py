@@ -47,7 +47,7 @@ def test_wide_group_products(resources):
     192 items on 256 CUs.  With block scales and an adapter: two."""
     kernels = {n: r for n, r in resources.items() if "gemv_d4_kernel" in n or "gemv_k256i8_kernel" in n}
     assert {n: r for n, r in kernels.items() if r[1] != 0} == {}
-    four = {n: r[0] for n, r in kernels.items() if re.search(r"Li4ELi4EE", n)}
+    four = {n: r[0] for n, r in kernels.items() if re.search(r"Li4ELi4ELb0EE", n)}
     assert len(four) == 2 * 2 + 2 * 3
     both = re.compile(r"gemv_k256i8_kernelILb1ELb1E")
     assert {n: r for n, r in four.items() if r > (96 if both.search(n) else 80)} == {}
