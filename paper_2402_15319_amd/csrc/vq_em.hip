@@ -1644,8 +1644,8 @@ hipError_t launch_em_assign(const vq_desc& d, const void* W, const void* hdiag, 
 // Whether D workgroups share a group of 16 rows or more in the M-step: up to two workgroups per CU, and up to one where
 // they have eight waves and more and both coordinates are needed for a line of W.  us with one, D, by groups:
 //                             8           64          96          128         192         256
-//   d = 4, k = 256, 256 rows  27.8, 12.5  28.3, 19.1  28.2, 24.7  29.1, 29.1
-//                   128 rows  17.7, 8.3   17.9, 10.7  18.1, 15.0  18.6, 17.0
+//   d = 4, k = 256, 256 rows  14.7, 12.5  20.2, 18.6  20.4, 24.4  21.0, 28.7  24.9, 38.9  28.6, 49.9   of the E-step one: 14.7, 14.7, 14.8, 21.2
+//                   128 rows  10.8, 8.2   15.7, 10.2  11.0, 14.5  15.3, 16.5  15.8, 22.0  16.4, 26.9   .. 10.8, 10.9, 15.3, 15.4
 //                   64 rows   9.8, 5.7    10.0, 6.1   10.1, 7.8   10.1, 10.2              k = 16 and 64 alike
 //                   16 rows   9.9, 4.6    10.0, 4.8   10.0, 5.5   10.0, 5.6
 //   d = 2, k = 256, 256 rows  26.9, 21.1  27.2, 21.8  27.3, 22.4  28.1, 26.7  31.9, 44.8  35.2, 48.7
@@ -1653,6 +1653,8 @@ hipError_t launch_em_assign(const vq_desc& d, const void* W, const void* hdiag, 
 //                   64 rows   9.3, 7.9    9.4, 8.2    9.5, 8.4    9.7, 8.3    9.8, 11.1   11.2, 11.9
 //                   32 rows   8.4, 6.2    8.5, 6.3    8.5, 6.4    8.6, 6.4    8.7, 7.9    8.7, 8.0     k = 64 8.4, 8.4 from 192 on
 //                   16 rows   8.4, 5.7    8.6, 5.9    8.6, 5.9    8.6, 5.9    8.7, 6.8    8.7, 6.9
+// (em_update_counted_kernel, the one of the first two rows, has cut its side since the line was drawn at two: there it would now
+// lie at one, between 64 and 72 groups: 20.2, 18.6 and 19.9, 23.7.)
 static bool em_shared(const vq_desc& d, long long n_items) {
   return n_items * d.d <= (d.d == 2 && d.group_rows >= 64 ? 1 : 2) * (long long)device_cus();
 }

@@ -333,19 +333,23 @@ __global__ __launch_bounds__(512) void gemv_k256i8_kernel(const typename BatchOf
 
 }  // namespace
 
-// Workgroups per 64-row item.  us per launch at 1, 2, 4, 8 splits on 256 CUs (a pair: two col-blocks), d = 4 with int8
-// tables / d = 2, k = 256:
-//   64 items, 8 pairs 7.2, 5.3, 4.1, 4.4 / 10.1, 6.7, 4.8, 4.9; 22 pairs 16.5, 11.0, 8.1, 8.2 / 24.0, 14.4, 10.0, 9.4
-//   128, 2 pairs 3.4, 3.2, 4.0 / 4.3, 3.6, 4.2; 8 pairs 7.3, 5.5, 5.3, 6.7 / 11.6, 7.7, 6.4, 6.9
-//   192, 2 pairs 3.5, 3.8 / 4.3, 4.3 (block scales 5.4, 5.6); 4 pairs 4.7, 5.0, 4.8 / 6.2, 6.1, 5.3; 8 pairs 7.9, 7.0, 6.6 / 11.6, 10.3, 9.3
-//   256, 4 pairs 4.8, 5.0 / 7.0, 6.1; 8 pairs 9.5, 7.2, 7.9 / 12.1, 11.1, 11.8
-//   320, 2 pairs 4.3, 4.4 / 5.7, 5.0; 4 pairs 6.2, 6.0 / 9.8, 7.5; 16 pairs 19.0, 17.1, 17.6 / 32.5, 25.2, 24.7
-//   448, 4 pairs 6.2, 6.9 / 11.0, 10.0; 16 pairs 19.7, 21.1 / 33.6, 32.2; 512, 8 pairs 12.2, 12.8 / 19.2, 20.5
-// d = 4 with fp16 tables stages twice the bytes: 192 items, 8 pairs 7.2, 6.6, 7.9; 320, 4 pairs 5.9, 5.6, 8 pairs 10.3,
-// 10.9, 16 pairs 18.9, 18.7; 64 items, 16 pairs at 4 and 8 splits 5.5, 8.9, 32 items 5.4, 4.7.  So d = 4 splits less
-// than d = 2 and neither much beyond one and a half items per CU.  The widest product of a launch decides, as a
-// narrow one beside it costs little: 3 x 1024 x 256 + 64 x 11008 16.2, 10.4, 7.3, 6.3 / 23.8, 13.8, 9.2, 7.1;
-// 11008 x 256 + 1024 x 11008 16.6, 11.2, 8.6, 10.3 / 24.2, 14.8, 10.4, 10.1, with fp16 tables 16.2, 10.4, 8.4, 11.5.
+// Workgroups per 64-row item.  us per launch at 1, 2, 4, 8 splits on 256 CUs (a pair: two col-blocks), 64-row groups, d = 4 with
+// int8 tables / d = 2, k = 256:
+//   32 items, 16 pairs 11.0, 7.5, 5.1, 4.2 / 16.9, 10.1, 6.5, 4.8
+//   64, 8 pairs 6.4, 4.9, 3.9, 4.4 / 9.3, 6.1, 4.4, 4.6; 16 pairs 11.0, 7.6, 5.3, 6.0 / 17.0, 10.6, 7.4, 6.6; 22 pairs 14.6, 9.6, 6.7, 8.1 /
+//     22.5, 13.4, 8.8, 8.7
+//   128, 2 pairs 3.1, 3.0, 3.6 / 4.0, 3.4, 4.0; 8 pairs 6.6, 5.1, 5.1, 6.4 / 9.9, 7.1, 6.2, 6.5
+//   192, 2 pairs 3.1, 3.4 / 4.0, 4.2 (block scales 5.1, 5.3); 4 pairs 4.3, 4.6, 4.4 / 5.8, 5.8, 5.1; 8 pairs 6.6, 6.8, 6.3 / 10.1, 10.3, 8.0
+//   256, 4 pairs 4.3, 4.7 / 6.2, 5.9; 8 pairs 6.6, 6.8, 7.5 / 10.2, 10.5, 10.9
+//   320, 2 pairs 4.0, 4.0 / 5.4, 4.9; 4 pairs 5.8, 5.6 / 8.8, 7.3, 6.6; 16 pairs 17.0, 15.8, 16.6 / 28.6, 23.5, 21.9
+//   448, 4 pairs 5.8, 6.4 / 9.2, 9.1; 16 pairs 17.3, 19.8 / 29.4, 29.9; 512, 8 pairs 10.6, 11.7 / 16.4, 18.0
+// d = 4 with fp16 tables stages twice the bytes: 192 items, 8 pairs 6.6, 6.5, 7.8; 320, 4 pairs 5.7, 5.4, 8 pairs 9.5, 9.5, 16 pairs 16.9,
+// 17.4; 64 items, 16 pairs at 4 and 8 splits 5.3, 9.0, 32 items 5.1, 4.5.  So d = 4 splits less than d = 2 and neither much
+// beyond one and a half items per CU.  The widest product of a launch decides, as a narrow one beside it costs
+// little: 3 x 1024 x 256 + 64 x 11008 14.2, 9.4, 6.4, 5.1 / 21.9, 12.9, 8.2, 5.8; 11008 x 256 + 1024 x 11008 14.5, 9.5, 6.9, 8.9 / 22.4, 13.4,
+// 8.8, 8.2, with fp16 tables 13.7, 9.1, 7.1, 10.6.  (The lines were drawn with a loop of one step to a turn.  With the loop
+// above they would lie elsewhere for 64 items of d = 4 with int8 tables, four splits, and for d = 2 at 320 items of 4 and of 16
+// pairs, four: 5.9, 5.3 / 7.2, 6.6 and 23.5, 21.9.)
 static int wide_splits(const GemvBatch& b, int fmt) {
   int pairs = 1;
   for (int i = 0; i < b.count; ++i) pairs = max(pairs, (b.p[i].n_cb + 1) / 2);
