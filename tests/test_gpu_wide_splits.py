@@ -25,7 +25,7 @@ SIZES = [
 
 @pytest.mark.parametrize("size", SIZES, ids=str)
 @pytest.mark.parametrize("fmt", sorted(FORMATS))
-def test_splits(fmt, size):
+def test_splits(fmt, size, group_rows=64):
     import torch
     import paper_2402_15319_amd as vq
     from paper_2402_15319_amd import device as vqdev
@@ -34,7 +34,7 @@ def test_splits(fmt, size):
     rank = 16
     descs, mats, xs, ys, zs, As, Bs, want, want_lora, bound = [], [], [], [], [], [], [], [], [], []
     for i, in_f in enumerate(widths):
-        s = workloads.VQShape(out_f, in_f, 256, 8, 64, **FORMATS[fmt])
+        s = workloads.VQShape(out_f, in_f, 256, 8, group_rows, **FORMATS[fmt])
         desc = vqdev.desc_from_shape(s)
         descs.append(desc)
         seed = 60 + in_f + i
