@@ -107,11 +107,11 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
   const int steps = (n_pairs + KS - 1) / KS;        // of the longest split: all take as many barriers
 
   auto load = [&](int p, D4Step<KS>& s) {           // (tables first: they are needed first; all of an address but the lane's part is wave-uniform)
-    const int c0 = 2 * p, c1 = 2 * p + 1;
-    const int c1_ld = c1 < n_cb ? c1 : c0;          // an absent second col-block re-reads the first (not used)
+    const int c0 = 2 * p, c1_ld = KS == 1 ? min(c0 + 1, n_cb - 1) : c0 + 1 < n_cb ? c0 + 1 : c0;   // an absent second col-block re-reads the first (not used)
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
-      const long long g = grow * n_cb + (duty::h(st, i) == 0 ? c0 : c1_ld);
+      const int h = duty::h(st, i);
+      const long long g = grow * n_cb + (KS == 1 ? min(c0 + h, n_cb - 1) : h == 0 ? c0 : c1_ld);   // (KS = 1: h is not a constant)
       if constexpr (F16) s.q[i] = reinterpret_cast<const uint2*>(tab + g * 2048 + duty::e0(st, i) * 8)[lane];
       else s.q[i] = make_uint2(reinterpret_cast<const uint32_t*>(tab + g * 1024 + duty::e0(st, i) * 4)[lane], 0u);
       if (i % duty::PER_TABLE == 0) {
@@ -139,8 +139,8 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
   D4Step<KS> even, odd;
   const int p_last = p_end > p_begin ? p_end - 1 : 0;
   // One step: the next one's loads, this one's tables into buffer `buf`, a barrier, the lookups.
-  auto run_step = [&](auto buf, int p, const D4Step<KS>& cur, D4Step<KS>& nxt) {
-    load(min(p + 1, p_last), nxt);                  // one step ahead (a harmless re-read at the end)
+  auto run_step = [&](auto buf, auto ahead, int p, const D4Step<KS>& cur, D4Step<KS>& nxt) {
+    if constexpr (ahead) load(min(p + 1, p_last), nxt);   // (a harmless re-read at the end)
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
       const int h = duty::h(st, i), e = duty::e0(st, i) + lane;
@@ -171,12 +171,17 @@ __global__ __launch_bounds__(512) void gemv_d4_kernel(const typename BatchOf<LOR
       acc[r] = dot2(t1.y, xb.y, acc[r]);
     }
   };
+  // A single step looks no further: one or two col-blocks (in two workgroups: up to four), which waited at the end for what nothing
+  // uses.  1408 x 256, fp16 tables 2.61 -> 2.49 us, 16 of 2688 x 256 3.95 -> 3.57, int8 4352 x 256 2.70 -> 2.57.  Not in the kernels
+  // whose registers it would take beyond what lets four workgroups share a CU.
+  constexpr bool kAlone = !BN && (KS == 1 || (KS == 2 && !LORA));
   load(min(p_begin, p_last), even);
   const int p_stop = p_begin + steps;
-  for (int p = p_begin;;) {   // (two exits: at a merge the compiler would wait for all loads)
-    run_step(std::integral_constant<int, 0>(), p, even, odd);
+  if (kAlone && steps == 1) run_step(std::integral_constant<int, 0>(), std::false_type(), p_begin, even, odd);
+  else for (int p = p_begin;;) {   // (two exits: at a merge the compiler would wait for all loads)
+    run_step(std::integral_constant<int, 0>(), std::true_type(), p, even, odd);
     if (++p >= p_stop) break;
-    run_step(std::integral_constant<int, 1>(), p, odd, even);
+    run_step(std::integral_constant<int, 1>(), std::true_type(), p, odd, even);
     if (++p >= p_stop) break;
   }
 
